@@ -193,16 +193,50 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
 // adds), each load's lane offset inside the slab is loop invariant, and the wave index is a compile-time
 // constant of the loop copy a wave runs, so the LDS address of a load is scalar too (no lane read-back).
 // ---------------------------------------------------------------------------------------------
+// LM head: the float32 logits (if wanted) and the best (value, column) of row m among the wave's columns n0 + 32 tn + 8 j
+// + 4 h + i, taken straight from the accumulators of the row.  NaN never wins; the lowest column wins among equals.
+template <int TN>
+__device__ __forceinline__ void head_row(const HeadOut &o, const f32x16 (&acc)[TN], int m, bool m_ok, int n0, int N, int h, int cand) {
+    float best = -__builtin_huge_valf();
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int n = n0 + 32 * tn + 8 * j + 4 * h;
+            if (n >= N) continue;
+            if (o.logits && m_ok)
+                *(f32x4 *)(o.logits + (size_t)m * N + n) = f32x4{acc[tn][4 * j], acc[tn][4 * j + 1], acc[tn][4 * j + 2], acc[tn][4 * j + 3]};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) best = fmaxf(best, acc[tn][4 * j + i]);
+        }
+    int arg = 0x7fffffff;
+#pragma unroll
+    for (int tn = TN - 1; tn >= 0; --tn)
+#pragma unroll
+        for (int e = 15; e >= 0; --e) {
+            const int n = n0 + 32 * tn + 8 * (e >> 2) + 4 * h + (e & 3);
+            if (n < N && acc[tn][e] == best) arg = n;
+        }
+    const float vo = __shfl_xor(best, 32, 64);
+    const int ao = __shfl_xor(arg, 32, 64);
+    if (vo > best || (vo == best && ao < arg)) { best = vo; arg = ao; }
+    if (h == 0 && m_ok) {
+        o.cand_val[(size_t)m * o.n_cand + cand] = best;
+        o.cand_idx[(size_t)m * o.n_cand + cand] = arg;
+    }
+}
+
 // One output tile: rows [bm, bm + BM), column tile nb (of width BN; BN/2 output columns for SwiGLU).
-// PARTIAL: the tile covers K tiles [kt0, kt0 + nk_part) only and stores its raw float32 sums to
+// HEAD: the epilogue is head_row above.  PARTIAL: the tile covers K tiles [kt0, kt0 + nk_part) only and stores its raw float32 sums to
 // part[z][m][n] (row stride N), for an epilogue pass that adds the slices in order.
 // LDS stages of the 256x256 tile's ring (32 KB each): a K tile is requested three tiles ahead.  A fifth stage (the
 // whole 160 KB of a compute unit) measured the same, alone and beside a bandwidth-bound kernel on the other
 // partition: what that neighbour costs is not memory latency the ring could cover.
 #define RS_NS_FULL 4
-template <int BM, int BN, int EPI, int NS, int NW, bool PARTIAL = false>
+template <int BM, int BN, int EPI, int NS, int NW, bool PARTIAL = false, bool HEAD = false>
 __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem,
-                                                 const int kt0 = 0, const int nk_part = 0, float *part = nullptr, const int z = 0) {
+                                                 const int kt0 = 0, const int nk_part = 0, float *part = nullptr, const int z = 0,
+                                                 const HeadOut *ho = nullptr) {
     constexpr int BK = 32;
     constexpr int WGN = NW / 2;                      // waves: 2 along M x NW/2 along N
     constexpr int WM = BM / 2, WN = BN / WGN;
@@ -355,6 +389,17 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 
+    if (HEAD) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            const int m = bm + wm * WM + 32 * tm + c32;
+            f32x16 row[TN];
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) row[tn] = acc[tn][tm];
+            head_row<TN>(*ho, row, m, m < M, nb * BN + wn * WN, N, h, nb * WGN + wn);
+        }
+        return;
+    }
     if (PARTIAL) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
@@ -512,14 +557,14 @@ static void launch_direct_splitk(hipStream_t st, const GemmArgs &a, int S) {
         hipLaunchKernelGGL(skinny_epilogue_kernel<EPI_STORE>, dim3(eblocks), dim3(256), 0, st, a, a.partials, S, a.N);
 }
 
-// Main pass of the large-tile kernel only, whole K in one slice: part[m][n] (row stride N) holds the float32
-// sums.  False (nothing launched) when the shape is not one the kernel takes.
-bool launch_gemm_direct_partials(hipStream_t st, const GemmArgs &a, float *part) {
-    if (!(a.K % 32 == 0 && a.K >= 32 && a.Wp && a.M >= 1 && a.N >= 1024 && a.N % 4 == 0)) return false;
-    const int m_tiles = (a.M + 127) / 128, n_tiles = (a.N + 255) / 256;
-    constexpr int lds = 5 * (128 + 256) * 32 * 2;
-    hipLaunchKernelGGL(gemm_direct_splitk_kernel, dim3(m_tiles * n_tiles), dim3(256), lds, st, a, m_tiles, n_tiles, a.K / 32, part);
-    return true;
+// LM head of more than 64 rows: whole K per tile, all row tiles of a column tile next to each other on one XCD.
+template <int BM, int NS>
+__global__ __launch_bounds__(256) void gemm_head_kernel(GemmArgs a, HeadOut o, int m_tiles, int n_tiles) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    const int total = m_tiles * n_tiles, per_xcd = (total + 7) >> 3;
+    const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (t >= total) return;
+    gemm_direct_tile<BM, 256, EPI_STORE, NS, 4, false, true>(a, (t % m_tiles) * BM, t / m_tiles, smem, 0, 0, nullptr, 0, &o);
 }
 
 template <int EPI>
@@ -870,9 +915,9 @@ static inline int shared_splits(int N, int K, int epi) {
     return S;
 }
 
-template <int EPI, int CH>
+template <int EPI, int CH, bool HEAD = false>
 __global__ __launch_bounds__(256, 2) void gemm_skinny_shared_kernel(GemmArgs a, float *__restrict__ part, int kb_per_wg,
-                                                                     int Kb, int Nv) {
+                                                                     int Kb, int Nv, HeadOut ho) {
     constexpr int PD = 8;                      // ring depth; divides CH, so ring slots are static in the unrolled chunk
     static_assert(CH % PD == 0 && CH * 2 == 32, "4 waves x 8 pieces fill one slab");
     extern __shared__ __attribute__((aligned(1024))) bf16_t slab[];   // [2][CH][2 token tiles][64 lanes][8]
@@ -947,6 +992,15 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_shared_kernel(GemmArgs a, 
         // every wave has read slab c and written its pieces of slab c+1; the weight loads stay in flight
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
+    if (HEAD) {
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) {
+            const f32x16 row[2] = {acc[0][tm], acc[1][tm]};
+            const int m = 32 * tm + c32;
+            head_row<2>(ho, row, m, m < M, blockIdx.x * 256 + wave * 64, a.N, h, blockIdx.x * 4 + wave);
+        }
+        return;
+    }
     // each wave owns its rows: partial tile straight from the accumulators
 #pragma unroll
     for (int tn = 0; tn < 2; ++tn)
@@ -1000,12 +1054,12 @@ __global__ __launch_bounds__(256) void skinny_epilogue_kernel(GemmArgs a, const 
 
 template <int EPI>
 static void launch_skinny_epi(hipStream_t st, const GemmArgs &a, float *partials) {
-    if (skinny_shared_applies(a)) {
+    if (EPI != EPI_STORE && skinny_shared_applies(a)) {
         constexpr int CH = RS_SHARED_CH, lds = 2 * CH * 2048;
         const int Nv = shared_virtual_n(a.N, a.epi), S = shared_splits(a.N, a.K, a.epi);
         const int kbpw = skinny_kblocks(a.K) / S;
         hipLaunchKernelGGL((gemm_skinny_shared_kernel<EPI, CH>), dim3(Nv / 256, S), dim3(256), lds, st, a, partials, kbpw,
-                           skinny_kblocks(a.K), Nv);
+                           skinny_kblocks(a.K), Nv, HeadOut{});
         hipLaunchKernelGGL(skinny_epilogue_kernel<EPI>, dim3((a.M * (a.N / 4) + 255) / 256), dim3(256), 0, st, a, partials, S, Nv);
         return;
     }
@@ -1025,20 +1079,17 @@ static void launch_skinny_epi(hipStream_t st, const GemmArgs &a, float *partials
     hipLaunchKernelGGL(skinny_epilogue_kernel<EPI>, dim3(eblocks), dim3(256), 0, st, a, partials, S, Nv);
 }
 
-// Whether the partial-sum pass of a plain projection (M <= 64 rows) can take the shared-activation streaming kernel.
-bool gemm_skinny_partials_shared(int N, int K) {
-    return K % 16 == 0 && skinny_kblocks(K) % (4 * RS_SHARED_CH) == 0 && N >= 4096;
-}
+static inline bool head_streams(int N, int K) { return K % 16 == 0 && skinny_kblocks(K) % (4 * RS_SHARED_CH) == 0 && N >= 4096; }
 
 void launch_gemm_skinny_partials(hipStream_t st, const GemmArgs &a, float *partials, int *S_out, int *Nv_out) {
-    if (gemm_skinny_partials_shared(a.N, a.K)) {
+    if (head_streams(a.N, a.K)) {
         constexpr int CH = RS_SHARED_CH;
         const int Nv = shared_virtual_n(a.N, EPI_STORE), S = shared_splits(a.N, a.K, EPI_STORE);
         *S_out = S;
         *Nv_out = Nv;
         if (a.M <= 0 || a.N <= 0) return;
         hipLaunchKernelGGL((gemm_skinny_shared_kernel<EPI_STORE, CH>), dim3(Nv / 256, S), dim3(256), 2 * CH * 2048, st, a, partials,
-                           skinny_kblocks(a.K) / S, skinny_kblocks(a.K), Nv);
+                           skinny_kblocks(a.K) / S, skinny_kblocks(a.K), Nv, HeadOut{});
         return;
     }
     constexpr int RT = RS_SKINNY_RT, PD = 10;
@@ -1048,6 +1099,29 @@ void launch_gemm_skinny_partials(hipStream_t st, const GemmArgs &a, float *parti
     if (a.M <= 0 || a.N <= 0) return;
     hipLaunchKernelGGL((gemm_skinny_kernel<EPI_STORE, RT, PD>), dim3(Nv / (32 * RT), S), dim3(256), RT * 32768, st, a, partials,
                        skinny_kb_per_wg(a.K, S), skinny_kblocks(a.K), Nv);
+}
+
+// LM head with the greedy choice begun in the epilogue.  Up to 64 rows the weight-streaming kernel, one workgroup per 256
+// columns over the whole K (a vocabulary too narrow to fill the chip that way takes K slices and launch_head_argmax);
+// above that the large-tile kernel, 128- or 256-row tiles.
+// The product used to leave its float32 sums in a scratch matrix that one workgroup per row read back, chose from and
+// copied to the caller's logits: at 256 rows of a 128256-wide head 106 us of argmax behind 323 us of product (131 MB
+// written, read and written again, and 1002 tiles of 128x256 where 501 of 256x256 are two rounds); now 280 + 5 us.
+int head_candidates(int M, int N, int K) {
+    if (M < 1 || N % 4) return 0;
+    if (M <= 64 && head_streams(N, K)) return shared_splits(N, K, EPI_STORE) == 1 ? shared_virtual_n(N, EPI_STORE) / 64 : 0;
+    return K % 32 == 0 && K >= 32 && N >= 1024 ? (N + 255) / 256 * 2 : 0;
+}
+void launch_gemm_head(hipStream_t st, const GemmArgs &a, const HeadOut &o) {
+    if (a.M <= 64 && head_streams(a.N, a.K)) {
+        hipLaunchKernelGGL((gemm_skinny_shared_kernel<EPI_STORE, RS_SHARED_CH, true>), dim3(shared_virtual_n(a.N, EPI_STORE) / 256), dim3(256),
+                           2 * RS_SHARED_CH * 2048, st, a, (float *)nullptr, skinny_kblocks(a.K), skinny_kblocks(a.K), 0, o);
+        return;
+    }
+    const int n_tiles = (a.N + 255) / 256, m_tiles = a.M <= 128 ? 1 : (a.M + 255) / 256;
+    const dim3 grid((m_tiles * n_tiles + 7) / 8 * 8);
+    if (a.M <= 128) hipLaunchKernelGGL((gemm_head_kernel<128, 5>), grid, dim3(256), 5 * 384 * 64, st, a, o, m_tiles, n_tiles);
+    else hipLaunchKernelGGL((gemm_head_kernel<256, RS_NS_FULL>), grid, dim3(256), RS_NS_FULL * 32768, st, a, o, m_tiles, n_tiles);
 }
 
 void launch_gemm_skinny(hipStream_t st, const GemmArgs &a, float *partials) {
@@ -1080,6 +1154,9 @@ void gemm_kernels_init() {
     set((const void *)gemm_skinny_kernel<EPI_SWIGLU, RT, PD>, RT * 32768);
     set((const void *)gemm_skinny_shared_kernel<EPI_SWIGLU, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
     set((const void *)gemm_skinny_shared_kernel<EPI_STORE, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
+    set((const void *)gemm_skinny_shared_kernel<EPI_STORE, RS_SHARED_CH, true>, 2 * RS_SHARED_CH * 2048);
+    set((const void *)gemm_head_kernel<128, 5>, 122880);
+    set((const void *)gemm_head_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
     set((const void *)gemm_skinny_shared_kernel<EPI_RESIDUAL, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
     set((const void *)gemm_direct_splitk_kernel, 5 * (128 + 256) * 32 * 2);
     set((const void *)gemm_grouped_kernel<EPI_STORE>, RS_NS_FULL * 32768);

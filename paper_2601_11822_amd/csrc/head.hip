@@ -47,9 +47,30 @@ void launch_gather_last_rows(hipStream_t st, const bf16_t *x, bf16_t *out, int d
 // comparison is taken on the float32 sums; NaN never wins).  Optionally writes the float32 logits
 // and scatters the token to tok_by_slot[row_slot[m]].
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void head_argmax_kernel(HeadArgmaxArgs a) {
+// The workgroup's best (value, column) pair, lowest column among equals, to up to two places.
+static __device__ void head_choose(float best, int arg, int32_t *to_a, int32_t *to_b) {
     __shared__ float s_val[256];
     __shared__ int s_arg[256];
+    const int tid = threadIdx.x;
+    s_val[tid] = best;
+    s_arg[tid] = arg;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (tid < o) {
+            const float v = s_val[tid + o];
+            const int g = s_arg[tid + o];
+            if (v > s_val[tid] || (v == s_val[tid] && g < s_arg[tid])) { s_val[tid] = v; s_arg[tid] = g; }
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        const int tok = s_arg[0] == 0x7fffffff ? 0 : s_arg[0];   // a row of NaNs: token 0
+        if (to_a) *to_a = tok;
+        if (to_b) *to_b = tok;
+    }
+}
+
+__global__ __launch_bounds__(256) void head_argmax_kernel(HeadArgmaxArgs a) {
     const int m = blockIdx.x, tid = threadIdx.x;
     float best = -INFINITY;
     int arg = 0x7fffffff;
@@ -70,25 +91,28 @@ __global__ __launch_bounds__(256) void head_argmax_kernel(HeadArgmaxArgs a) {
         if (a.logits) a.logits[(size_t)m * a.N + n] = v;
         take(v, n);
     }
-    s_val[tid] = best;
-    s_arg[tid] = arg;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (tid < o) {
-            const float v = s_val[tid + o];
-            const int g = s_arg[tid + o];
-            if (v > s_val[tid] || (v == s_val[tid] && g < s_arg[tid])) { s_val[tid] = v; s_arg[tid] = g; }
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        const int tok = s_arg[0] == 0x7fffffff ? 0 : s_arg[0];   // a row of NaNs: token 0
-        if (a.tokens) a.tokens[m] = tok;
-        if (a.tok_by_slot) a.tok_by_slot[a.row_slot ? a.row_slot[m] : m] = tok;
-    }
+    head_choose(best, arg, a.tokens ? a.tokens + m : nullptr, a.tok_by_slot ? a.tok_by_slot + (a.row_slot ? a.row_slot[m] : m) : nullptr);
 }
 
 void launch_head_argmax(hipStream_t st, const HeadArgmaxArgs &a) {
     if (a.M <= 0) return;
     hipLaunchKernelGGL(head_argmax_kernel, dim3(a.M), dim3(256), 0, st, a);
+}
+
+// One workgroup per row over the row's candidates (a few thousand at most, one per wave tile of the head's product).
+__global__ __launch_bounds__(256) void head_pick_kernel(HeadPickArgs a) {
+    const int m = blockIdx.x;
+    float best = -INFINITY;
+    int arg = 0x7fffffff;
+    for (int c = threadIdx.x; c < a.n_cand; c += 256) {
+        const float v = a.cand_val[(size_t)m * a.n_cand + c];
+        const int g = a.cand_idx[(size_t)m * a.n_cand + c];
+        if (v > best || (v == best && g < arg)) { best = v; arg = g; }
+    }
+    head_choose(best, arg, a.tokens ? a.tokens + m : nullptr, a.tok_by_slot ? a.tok_by_slot + (a.row_slot ? a.row_slot[m] : m) : nullptr);
+}
+
+void launch_head_pick(hipStream_t st, const HeadPickArgs &a) {
+    if (a.M <= 0) return;
+    hipLaunchKernelGGL(head_pick_kernel, dim3(a.M), dim3(256), 0, st, a);
 }

@@ -92,9 +92,17 @@ void launch_gemm_skinny(hipStream_t st, const GemmArgs &a, float *partials);
 // Main pass only (a.epi must be EPI_STORE): leaves part[s][m][n], s < *S_out K-slices, row stride
 // *Nv_out floats; the product's element (m, n) is the sum of its slices in slice order.
 void launch_gemm_skinny_partials(hipStream_t st, const GemmArgs &a, float *partials, int *S_out, int *Nv_out);
-// True where that pass streams the weights with the shared-activation kernel (about HBM rate for M <= 64 rows).
-bool gemm_skinny_partials_shared(int N, int K);
-bool launch_gemm_direct_partials(hipStream_t st, const GemmArgs &a, float *part);
+// LM head (a.epi EPI_STORE) with the greedy choice begun in the epilogue: every wave writes the float32 logits of its
+// tile, if wanted, and the best (value, column) of each row among its columns to cand_val / cand_idx [M][n_cand].
+struct HeadOut {
+    float *logits;       // [M][N] or nullptr
+    float *cand_val;     // [M][n_cand]
+    int32_t *cand_idx;
+    int n_cand;
+};
+// Candidates per row of the pass for M rows, or 0 where the shape is not one the pass takes.
+int head_candidates(int M, int N, int K);
+void launch_gemm_head(hipStream_t st, const GemmArgs &a, const HeadOut &o);
 size_t packed_weight_elems(int N, int K);
 void launch_pack_weights(hipStream_t st, const bf16_t *W, bf16_t *Wp, int N, int K);
 
@@ -199,6 +207,16 @@ struct HeadArgmaxArgs {
     int S, M, N, Nv;
 };
 void launch_head_argmax(hipStream_t st, const HeadArgmaxArgs &a);
+// The same choice over the candidates that launch_gemm_head left.
+struct HeadPickArgs {
+    const float *cand_val;
+    const int32_t *cand_idx;
+    int32_t *tokens;
+    const int32_t *row_slot;
+    int32_t *tok_by_slot;
+    int M, n_cand;
+};
+void launch_head_pick(hipStream_t st, const HeadPickArgs &a);
 
 // Counts workgroups per physical CU: hist[(xcc << 8) | (se << 5) | (sh << 4) | cu] += 1.
 void launch_cu_probe(hipStream_t st, int32_t *hist, int n_workgroups);

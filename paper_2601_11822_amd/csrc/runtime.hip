@@ -825,18 +825,14 @@ int32_t decode_layer(rs_ctx *c, Workspace &w, int32_t layer, const void *x_in, v
     return RS_OK;
 }
 
-// Final RMSNorm + LM head + greedy choice for n rows of x, in groups of at most 64 rows (the
-// weight-streaming GEMM's limit).  The chosen tokens go to `tokens` (row order) and/or to
-// tok_by_slot[row_slot[row]].
+// Final RMSNorm + LM head + greedy choice for n rows of x, in groups of c->head_group[side] rows (one pass over the
+// weights each).  The chosen tokens go to `tokens` (row order) and/or to tok_by_slot[row_slot[row]].
 int32_t head_greedy(rs_ctx *c, int side, const bf16_t *x, int n, float *logits, int32_t *tokens,
                     const int32_t *row_slot, int32_t *tok_by_slot) {
     const rs_model_desc &m = c->m;
     Workspace &w = c->ws[side];
     hipStream_t st = c->side[side].stream;
     const int d = m.d_model, V = c->head.vocab;
-    // one pass over the weights per group of rows: the large-tile kernel (up to RS_HEAD_GROUP rows; with K only
-    // d_model deep and a very wide N it also beats the weight-streaming kernel at a few rows: 243 against 249 us
-    // at one row, 259 against 299 us at 64 rows for a 128256 x 4096 head), else the weight-streaming kernel (64 rows)
     const int group = c->head_group[side];
     for (int g0 = 0; g0 < n; g0 += group) {
         const int mg = std::min(group, n - g0);
@@ -844,16 +840,21 @@ int32_t head_greedy(rs_ctx *c, int side, const bf16_t *x, int n, float *logits, 
         launch_rmsnorm(st, x + (size_t)g0 * d, (const bf16_t *)c->head.final_norm, w.h, mg, d, m.rms_eps);
         GemmArgs g{w.h, (const bf16_t *)c->head.lm_head, nullptr, c->packed_lm, nullptr, nullptr, nullptr, mg, V, d, EPI_STORE,
                    0, c->side[side].cus};
-        int S = 1, Nv = V;
-        if (mg <= 64 && gemm_skinny_partials_shared(V, d)) {   // a function of the shapes alone
-            launch_gemm_skinny_partials(st, g, c->head_part[side], &S, &Nv);
-        } else if (!launch_gemm_direct_partials(st, g, c->head_part[side])) {
+        float *lg = logits ? logits + (size_t)g0 * V : nullptr;
+        int32_t *tk = tokens ? tokens + g0 : nullptr;
+        const int32_t *rsl = row_slot ? row_slot + g0 : nullptr;
+        const int nc = head_candidates(mg, V, d);   // a function of the shapes alone
+        if (nc > 0) {
+            float *cv = c->head_part[side];
+            int32_t *ci = (int32_t *)(cv + (size_t)mg * nc);
+            launch_gemm_head(st, g, HeadOut{lg, cv, ci, nc});
+            launch_head_pick(st, HeadPickArgs{cv, ci, tk, rsl, tok_by_slot, mg, nc});
+        } else {
             if (mg > 64) return fail(RS_ERR_STATE, "head group of %d rows without the large-tile kernel", mg);
+            int S = 1, Nv = V;
             launch_gemm_skinny_partials(st, g, c->head_part[side], &S, &Nv);
+            launch_head_argmax(st, HeadArgmaxArgs{c->head_part[side], lg, tk, rsl, tok_by_slot, S, mg, V, Nv});
         }
-        HeadArgmaxArgs ha{c->head_part[side], logits ? logits + (size_t)g0 * V : nullptr, tokens ? tokens + g0 : nullptr,
-                          row_slot ? row_slot + g0 : nullptr, tok_by_slot, S, mg, V, Nv};
-        launch_head_argmax(st, ha);
     }
     HIP_TRY(hipGetLastError());
     return RS_OK;
@@ -1222,7 +1223,9 @@ int32_t rs_set_head(rs_ctx *c, const rs_head_weights *w) {
                 // more than 64 rows per call and a shape the large-tile kernel takes: groups of up to 256 rows
                 const bool big = c->ws[s].rows > 64 && d % 32 == 0 && w->vocab >= 1024 && w->vocab % 4 == 0;
                 c->head_group[s] = big ? std::min(c->ws[s].rows, RS_HEAD_GROUP) : 64;
-                const size_t elems = std::max(skinny_partial_elems(64, w->vocab, d, EPI_STORE), (size_t)c->head_group[s] * w->vocab);
+                // K-sliced sums where the choice is a pass of its own, else (value, column) candidates of each row
+                size_t elems = 2 * (size_t)c->head_group[s] * std::max(head_candidates(64, w->vocab, d), head_candidates(c->head_group[s], w->vocab, d));
+                if (!head_candidates(64, w->vocab, d)) elems = std::max(elems, skinny_partial_elems(64, w->vocab, d, EPI_STORE));
                 HIP_TRY(hipMalloc((void **)&c->head_part[s], elems * sizeof(float)));
             }
         }
