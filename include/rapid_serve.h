@@ -201,7 +201,7 @@ int32_t rs_decode_layer(rs_ctx *ctx, int32_t layer, const void *x_in, void *x_ou
  * with it).  The first call with a given (layer, pointers, max_blk, B, max_ctx_bucket, current
  * decode stream) records rs_decode_layer's kernel sequence on the decode stream and instantiates
  * it (set-up work: allocates); every call launches the instantiated graph on that stream, one
- * runtime call instead of fourteen.  Pointers are part of the graph: the CONTENTS of x_in,
+ * runtime call instead of one per kernel.  Pointers are part of the graph: the CONTENTS of x_in,
  * ctx_lens and block_tables are read at replay, so a serving loop keeps them in place and updates
  * them between steps.  max_ctx_bucket plays the role of max_ctx but is baked into the launch
  * shape: a multiple of 512 (or the context limit of rs_init) that bounds ctx_lens[i]+1 for as

@@ -8,10 +8,11 @@
 //   * RMSNorm needs a whole row before it can scale an element, which would cost a kernel of its own in
 //     front of the QKV and the gate/up projection.  But the row's scale is one scalar: with
 //     s = 1/sqrt(mean(x^2) + eps),  RMSNorm(x; g) W^T = s * ((x . g) W^T).  The streaming kernel therefore
-//     reads the hidden state x row-major as it is, multiplies by the gain while it stages the rows in LDS,
-//     and adds up the squares of the part of each row it sees; the per-slice sums of squares go out
-//     beside the partial products, and the consumer of the partial products (the rotary/KV epilogue, the
-//     SwiGLU epilogue) forms s and applies it.  No normalised copy of x is ever written.
+//     (QKV) reads the hidden state x row-major as it is, multiplies by the gain while it stages the rows in
+//     LDS, and adds up the squares of the part of each row it sees; the per-slice sums of squares go out
+//     beside the partial products, and their consumer (the rotary/KV epilogue) forms s and applies it.  The
+//     gate/up projection's input has a producer, the output projection's epilogue: that writes x1 . g2 and the
+//     sums of squares itself, so the widest stream of the layer copies its activations and converts nothing.
 //   * The 4 waves of a workgroup take different weight rows over the SAME K slice, so the slice's
 //     activation rows are fetched once per workgroup into LDS (double buffered, 16 k-blocks at a time)
 //     and every wave's vector memory path carries weights only: each wave keeps PD one-kilobyte weight
@@ -31,17 +32,31 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // ten more vector instructions per element of a 256x256 epilogue, for digits far below the bf16 the result is rounded to
 __device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 
-#define DS_CH 16   // k-blocks per activation chunk: two 32 KB slabs in LDS
+// The RMSNorm scale of row m from the sums of squares of its parts, added in order.
+__device__ __forceinline__ float row_scale(const float *ssq_part, int S_ssq, int m, int d, float eps) {
+    float t = 0.f;
+    for (int s = 0; s < S_ssq; ++s) t += ssq_part[s * RS_SSQ_ROWS + m];
+    return 1.0f / sqrtf(t / (float)d + eps);
+}
 
-// ACT 0: activations fragment-packed (two 32-row tiles per k-block), as the attention merge and the SwiGLU
-//        epilogue write them.
+#define DS_CH 16   // k-blocks per activation chunk: two slabs of MT x 16 KB in LDS
+
+// ACT 0: activations fragment-packed (packed_mt(M) row tiles per k-block), as their producers write them.
 // ACT 1: activations row-major [M][K]; multiplied by gain[K] while staged; sums of squares written out.
+// RT   : 32-row weight tiles per wave.  MT: 32-row activation tiles, ceil(M / 32): rows past M are neither fetched
+//        (their lanes repeat row M - 1) nor multiplied beyond the last tile that holds a row.
 // PAIR : RT == 2 and the wave's two tiles are row tile f of Wp (gate) and of Wp2 (up); else RT tiles of Wp.
 // PSPLIT: RT == 1 and the pair is spread over waves: waves 0-1 take gate tiles 2x, 2x+1 of Wp, waves 2-3 the matching
 //         up tiles of Wp2 (half as many features per workgroup as PAIR, the same sums and the same output columns).
-template <int ACT, int RT, bool PAIR, int PD, bool PSPLIT = false>
-__global__ __launch_bounds__(256, 2) void dstream_kernel(DGemmArgs a, int kb_per_wg, int Nv) {
-    constexpr int CH = DS_CH;
+// A pair covers the whole K (one slice): its accumulators are the finished sums, so the row scale, SwiGLU and the packed
+// output are the epilogue of this kernel and no partial products are written.
+// Llama-3-8B gate/up on 256 CUs: at 64 rows 51.6 + 5.7 us with the gain and the squares formed in this stream (about 50
+// vector instructions per staged kilobyte, more cycles than its matrix instructions) and SwiGLU in a kernel of its own,
+// 47 us now; at one row 37.4 + 4.8 -> 38.3 us (6.2 TB/s).  A second row tile that holds no row is not staged or
+// multiplied (QKV at one row 13.0 -> 10.9 us).
+template <int ACT, int RT, bool PAIR, bool PSPLIT, int MT>
+__global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs a, int kb_per_wg, int Nv, DFuseArgs fz) {
+    constexpr int CH = DS_CH, PD = 8;
     // An activation piece is stored 8 steps after its load was issued, right behind a weight fragment that is
     // consumed PD steps after ITS issue: with PD == 8 the two are due together and the in-order wait counts cost
     // nothing; a deeper ring would make every piece wait for weights that are not needed yet (measured: 2x slower).
@@ -52,7 +67,10 @@ __global__ __launch_bounds__(256, 2) void dstream_kernel(DGemmArgs a, int kb_per
     static_assert(CH % PD == 0, "ring slots are static inside an unrolled chunk");
     static_assert(!PAIR || RT == 2, "a pair is a gate tile and an up tile");
     static_assert(!PSPLIT || (RT == 1 && !PAIR), "a split pair is one tile per wave");
-    extern __shared__ __attribute__((aligned(1024))) bf16_t slab[];   // [2][CH][2 row tiles][64 lanes][8]
+    constexpr bool FUSED = PAIR || PSPLIT;
+    static_assert(!FUSED || ACT == 0, "a pair reads what the output projection's epilogue wrote");
+    constexpr int NPC = 4 * MT;   // activation pieces (1 KB) a wave brings per chunk
+    extern __shared__ __attribute__((aligned(1024))) bf16_t slab[];   // [2][CH][MT row tiles][64 lanes][8]
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int c32 = lane & 31, h = lane >> 5;
     const int M = a.M, K = a.K;
@@ -60,7 +78,7 @@ __global__ __launch_bounds__(256, 2) void dstream_kernel(DGemmArgs a, int kb_per
     const int kb_end = kb_begin + kb_per_wg - 1;     // loads past the slice re-read its last k-block
     const int nchunks = kb_per_wg / CH;
     const int Nt = ((a.N + 63) / 64) * 2;
-    const size_t wstride = (size_t)Nt * 512;
+    const size_t wstride = (size_t)Nt * 512, xstride = (size_t)packed_mt(M) * 512;
     const bf16_t *w[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
@@ -72,28 +90,33 @@ __global__ __launch_bounds__(256, 2) void dstream_kernel(DGemmArgs a, int kb_per
             w[t] = a.Wp + (size_t)min((4 * (int)blockIdx.x + wave) * RT + t, Nt - 1) * 512 + lane * 8;
     }
 
-    f32x16 acc[RT][2];
+    f32x16 acc[RT][MT];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < MT; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    // ---- activation pieces: a chunk's slab is 32 pieces of 1 KB; wave w brings 8 of them per chunk
-    // ACT 0: piece q = 8 wave + j is (k-block q/2, row tile q%2) of the packed matrix: one contiguous kilobyte.
+    // ---- activation pieces: a chunk's slab is 16 MT pieces of 1 KB; wave w brings 4 MT of them per chunk
+    // ACT 0: piece q = 4 MT w + j is (k-block q/MT, row tile q%MT) of the packed matrix.
     // ACT 1: piece j of wave w is rows 8j..8j+7 x the chunk's 16-byte columns 8w..8w+7 (lane l: row 8j + l%8,
     //        column 8w + l/8): eight 128-byte runs of eight rows, stored to the fragment order
-    //        ((k-block*2 + row tile)*64 + half*32 + row%32).
-    float ssq[8];
+    //        ((k-block*MT + row tile)*64 + half*32 + row%32).
+    float ssq[NPC];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ssq[j] = 0.f;
+    for (int j = 0; j < NPC; ++j) ssq[j] = 0.f;
     const int k8 = 8 * wave + (lane >> 3);            // ACT 1: this lane's 16-byte column inside a chunk
+    int xoff[MT];                                     // ACT 0: this lane's chunk of row tile t within a k-block
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int r = min(32 * t + c32, M - 1);
+        xoff[t] = (r >> 5) * 512 + (h * 32 + (r & 31)) * 8;
+    }
     auto x_addr = [&](int chunk, int j) -> const bf16_t * {
         if (ACT == 0) {
-            const int q = 8 * wave + j;
-            const size_t kb = (size_t)min(kb_begin + chunk * CH + (q >> 1), kb_end);
-            return a.A_packed + kb * 1024 + (q & 1) * 512 + lane * 8;
+            const size_t kb = (size_t)min(kb_begin + chunk * CH + 4 * wave + j / MT, kb_end);
+            return a.A_packed + kb * xstride + xoff[j % MT];
         } else {
             const int m = min(8 * j + (lane & 7), M - 1);
             const int ch = min(chunk, nchunks - 1);
@@ -104,32 +127,43 @@ __global__ __launch_bounds__(256, 2) void dstream_kernel(DGemmArgs a, int kb_per
         const int ch = min(chunk, nchunks - 1);
         return a.gain + (size_t)(kb_begin + ch * CH) * 16 + k8 * 8;
     };
-    auto x_store = [&](bf16_t *dst_slab, int j, bf16x8 xv, bf16x8 gv, bool count) {
+    const bool counts = ACT == 1 && blockIdx.x == 0;
+    auto x_store = [&](bf16_t *dst_slab, int j, bf16x8 xv, const float (&gf)[8], bool count) {
         if (ACT == 0) {
-            *(bf16x8 *)&dst_slab[(8 * wave + j) * 512 + lane * 8] = xv;
+            *(bf16x8 *)&dst_slab[(NPC * wave + j) * 512 + lane * 8] = xv;
         } else {
             const int m = 8 * j + (lane & 7);
             bf16x8 hv;
-            float s = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float f = m < M ? (float)xv[e] : 0.f;
-                s += f * f;
-                hv[e] = (bf16_t)(f * (float)gv[e]);
+            for (int e = 0; e < 8; ++e) hv[e] = (bf16_t)((float)xv[e] * gf[e]);
+            if (counts && count) {
+                float s = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s += (float)xv[e] * (float)xv[e];
+                ssq[j] += s;
             }
-            if (count) ssq[j] += s;
-            *(bf16x8 *)&dst_slab[(((k8 >> 1) * 2 + (m >> 5)) * 64 + (k8 & 1) * 32 + (m & 31)) * 8] = hv;
+            *(bf16x8 *)&dst_slab[(((k8 >> 1) * MT + (m >> 5)) * 64 + (k8 & 1) * 32 + (m & 31)) * 8] = hv;
         }
     };
-    {   // chunk 0's slab, up front
-        bf16x8 t[8], g = zero_bf16x8();
-        if (ACT == 1) g = ld_bf16x8(g_addr(0));
+    float sc[MT];   // FUSED: RMSNorm scales of this lane's rows
+    if (FUSED) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] = ld_bf16x8(x_addr(0, j));
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x_store(slab, j, t[j], g, true);
+        for (int tm = 0; tm < MT; ++tm) sc[tm] = row_scale(fz.ssq_part, fz.S_ssq, 32 * tm + c32, K, fz.eps);
     }
-    bf16x8 rw[PD][RT], rxs[8], rg = zero_bf16x8();
+    float gf[8];
+    auto gains = [&](bf16x8 g) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) gf[e] = (float)g[e];
+    };
+    {   // chunk 0's slab, up front
+        bf16x8 t[NPC];
+        if (ACT == 1) gains(ld_bf16x8(g_addr(0)));
+#pragma unroll
+        for (int j = 0; j < NPC; ++j) t[j] = ld_bf16x8(x_addr(0, j));
+#pragma unroll
+        for (int j = 0; j < NPC; ++j) x_store(slab, j, t[j], gf, true);
+    }
+    bf16x8 rw[PD][RT], rxs[NPC], rg = zero_bf16x8();
     auto load_w = [&](int p, int step) {
         const size_t kb = (size_t)min(kb_begin + step, kb_end);
 #pragma unroll
@@ -140,41 +174,95 @@ __global__ __launch_bounds__(256, 2) void dstream_kernel(DGemmArgs a, int kb_per
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     for (int c = 0; c < nchunks; ++c) {
-        const bf16_t *cur = slab + (c & 1) * (CH * 1024) + lane * 8;
-        bf16_t *nxt = slab + ((c + 1) & 1) * (CH * 1024);
+        const bf16_t *cur = slab + (c & 1) * (CH * MT * 512) + lane * 8;
+        bf16_t *nxt = slab + ((c + 1) & 1) * (CH * MT * 512);
         const bool more = c + 1 < nchunks;
+        bf16x8 xf[2][MT];   // activation fragments, read one step ahead of their MFMAs
+#pragma unroll
+        for (int tm = 0; tm < MT; ++tm) xf[0][tm] = *(const bf16x8 *)&cur[tm * 512];
 #pragma unroll
         for (int s = 0; s < CH; ++s) {
             const int p = s % PD;
-            const bf16x8 x0 = *(const bf16x8 *)&cur[(2 * s) * 512], x1 = *(const bf16x8 *)&cur[(2 * s + 1) * 512];
+            if (s + 1 < CH)
 #pragma unroll
-            for (int t = 0; t < RT; ++t) {
-                acc[t][0] = mfma32(rw[p][t], x0, acc[t][0]);
-                acc[t][1] = mfma32(rw[p][t], x1, acc[t][1]);
-            }
-            // the piece of the next slab that was fetched eight steps ago
-            if (s >= 8) x_store(nxt, s - 8, rxs[s - 8], rg, more);
+                for (int tm = 0; tm < MT; ++tm) xf[(s + 1) & 1][tm] = *(const bf16x8 *)&cur[((s + 1) * MT + tm) * 512];
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int tm = 0; tm < MT; ++tm) acc[t][tm] = mfma32(rw[p][t], xf[s & 1][tm], acc[t][tm]);
+            // the pieces of the next slab that were fetched eight steps ago
+            if (ACT == 1 && s == 8) gains(rg);
+#pragma unroll
+            for (int j = 0; j < NPC; ++j)
+                if (j * 8 / NPC == s - 8) x_store(nxt, j, rxs[j], gf, more);
             load_w(p, c * CH + s + PD);
-            if (s < 8) {
-                if (ACT == 1 && s == 0) rg = ld_bf16x8(g_addr(c + 1));
-                rxs[s] = ld_bf16x8(x_addr(c + 1, s));
-            }
+            if (ACT == 1 && s == 0) rg = ld_bf16x8(g_addr(c + 1));
+#pragma unroll
+            for (int j = 0; j < NPC; ++j)
+                if (j * 8 / NPC == s) rxs[j] = ld_bf16x8(x_addr(c + 1, j));
             __builtin_amdgcn_sched_barrier(0);
         }
         // every wave has read slab c and written its pieces of slab c+1; the weight loads stay in flight
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
+    if (FUSED) {
+        const int Mt_out = packed_mt(M);
+        auto emit = [&](const f32x16 &g, const f32x16 &u, int tm, int ftile) {
+            const int m = 32 * tm + c32;
+            if (m >= M) return;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int n = 32 * ftile + 8 * j + 4 * h;
+                if (n >= a.N) continue;
+                bf16x4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(silu_f(g[4 * j + i] * sc[tm]) * (u[4 * j + i] * sc[tm]));
+                *(bf16x4 *)(fz.out + packed_offset(m, n, Mt_out) + (n & 7)) = v;
+            }
+        };
+        if (PAIR) {
+#pragma unroll
+            for (int tm = 0; tm < MT; ++tm) emit(acc[0][tm], acc[RT - 1][tm], tm, 4 * (int)blockIdx.x + wave);
+        } else {
+            // gate and up of a feature tile sit in waves w and w + 2, which trade halves through LDS: w finishes the
+            // first H row tiles, w + 2 the rest
+            constexpr int H = (MT + 1) / 2;
+            f32x4 *xch = (f32x4 *)slab;   // free since the last barrier: [wave][H][4][64 lanes]
+            const bool up = wave >= 2;
+#pragma unroll
+            for (int q = 0; q < H; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    f32x4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = up ? acc[0][q][4 * j + i] : acc[0][min(H + q, MT - 1)][4 * j + i];
+                    xch[((wave * H + q) * 4 + j) * 64 + lane] = v;
+                }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < H; ++q) {
+                f32x16 other;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const f32x4 v = xch[(((wave ^ 2) * H + q) * 4 + j) * 64 + lane];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) other[4 * j + i] = v[i];
+                }
+                const int ftile = 2 * (int)blockIdx.x + (wave & 1);
+                if (!up) emit(acc[0][q], other, q, ftile);
+                else if (H + q < MT) emit(other, acc[0][min(H + q, MT - 1)], min(H + q, MT - 1), ftile);
+            }
+        }
+        return;
+    }
     // each wave owns its rows: partial tile straight from the accumulators
 #pragma unroll
     for (int tn = 0; tn < RT; ++tn)
 #pragma unroll
-        for (int tm = 0; tm < 2; ++tm) {
+        for (int tm = 0; tm < MT; ++tm) {
             const int m = 32 * tm + c32;
             if (m >= M) continue;
-            // virtual columns: 64 per feature tile of a pair (32 gate, then 32 up), else the weight rows themselves
-            const int col = PSPLIT ? (2 * (int)blockIdx.x + (wave & 1)) * 64 + 32 * (wave >> 1)
-                                   : (int)blockIdx.x * (128 * RT) + wave * (32 * RT) + 32 * tn;
-            float *dst = a.part + ((size_t)blockIdx.y * M + m) * Nv + col;
+            float *dst = a.part + ((size_t)blockIdx.y * M + m) * Nv + (int)blockIdx.x * (128 * RT) + wave * (32 * RT) + 32 * tn;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 f32x4 v = {acc[tn][tm][4 * j], acc[tn][tm][4 * j + 1], acc[tn][tm][4 * j + 2], acc[tn][tm][4 * j + 3]};
@@ -185,15 +273,16 @@ __global__ __launch_bounds__(256, 2) void dstream_kernel(DGemmArgs a, int kb_per
         // sums of squares of the slice: lanes with the same l%8 hold the same row, then the 4 waves in wave order
         float *red = (float *)slab;   // free since the last barrier
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NPC; ++j) {
             float v = ssq[j];
             v += __shfl_xor(v, 8, 64);
             v += __shfl_xor(v, 16, 64);
             v += __shfl_xor(v, 32, 64);
-            if (lane < 8) red[wave * 64 + 8 * j + lane] = v;
+            if (lane < 8) red[wave * (32 * MT) + 8 * j + lane] = v;
         }
         __syncthreads();
-        if (tid < 64) a.ssq_part[blockIdx.y * 64 + tid] = ((red[tid] + red[64 + tid]) + red[128 + tid]) + red[192 + tid];
+        if (tid < 32 * MT)
+            a.ssq_part[blockIdx.y * RS_SSQ_ROWS + tid] = ((red[tid] + red[32 * MT + tid]) + red[64 * MT + tid]) + red[96 * MT + tid];
     }
 }
 
@@ -210,22 +299,24 @@ DGemmPlan dgemm_plan(int N, int K, bool pair) {
     p.Nv = p.cols * 256;
     const int Kb = K / 16;
     // K slices: as many as keep the launch within about one workgroup per compute unit of a half-chip partition
-    // (128) with at least 32 k-blocks (two chunks) per slice, in whole chunks.  (A wide gate/up pair was split
-    // once more before, for the whole chip's sake: 2 % slower on a 128-CU partition; the whole chip now gets its
-    // workgroups from the half-height forms of the launcher instead, which leave the sums as they are.)  Measured on the Llama-3-8B shapes: on a partition the stream is bound by what one compute unit can
-    // pull, so one large workgroup per unit beats two half-sized ones (the activation rows are staged once
-    // instead of twice); on the whole chip more, smaller workgroups win a little -- this is the better compromise.
+    // (128) with at least 32 k-blocks (two chunks) per slice, in whole chunks.  Measured on the Llama-3-8B shapes: on
+    // a partition the stream is bound by what one compute unit can pull, so one large workgroup per unit beats two
+    // half-sized ones (the activation rows are staged once instead of twice); on the whole chip more, smaller
+    // workgroups win a little -- this is the better compromise.
+    // A gate/up pair is never cut: a slice of it would have to leave partial sums for a kernel of its own to finish,
+    // and the pair is wide enough to fill the chip (two slices: 2 % slower on 128 CUs even before its epilogue moved
+    // into the stream).
     const int cap = 128;
     int S = 1;
-    for (int s = 2; s <= 64; ++s)
+    for (int s = 2; s <= 64 && !pair; ++s)
         if (Kb % (s * DS_CH) == 0 && Kb / s >= 2 * DS_CH && p.cols * s <= cap) S = s;
     p.S = S;
     p.kb_per_wg = Kb / S;
     return p;
 }
 
-size_t dgemm_partial_elems(int M, int N, int K, bool pair) {
-    const DGemmPlan p = dgemm_plan(N, K, pair);
+size_t dgemm_partial_elems(int M, int N, int K) {
+    const DGemmPlan p = dgemm_plan(N, K, false);
     return (size_t)p.S * (size_t)M * (size_t)p.Nv;
 }
 
@@ -248,71 +339,63 @@ bool dgemm_prefers_half_height(const DGemmPlan &p, int cus) {
     return half < full;
 }
 
-void launch_dgemm_partials(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p, bool narrow) {
-    constexpr int lds = 2 * DS_CH * 2048;
-    const dim3 grid(p.cols, p.S), grid_narrow(2 * p.cols, p.S), block(256);
+constexpr int ds_lds(int mt) { return 2 * DS_CH * mt * 1024; }
+
+template <int MT>
+static void launch_dstream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &f, bool narrow) {
+    const dim3 grid(narrow ? 2 * p.cols : p.cols, p.S), block(256);
     const bool rows = a.X_rows != nullptr;
-    if (p.pair && narrow) {
-        if (rows) hipLaunchKernelGGL((dstream_kernel<1, 1, false, 8, true>), grid_narrow, block, lds, st, a, p.kb_per_wg, p.Nv);
-        else hipLaunchKernelGGL((dstream_kernel<0, 1, false, 8, true>), grid_narrow, block, lds, st, a, p.kb_per_wg, p.Nv);
-    } else if (p.pair) {
-        if (rows) hipLaunchKernelGGL((dstream_kernel<1, 2, true, 8>), grid, block, lds, st, a, p.kb_per_wg, p.Nv);
-        else hipLaunchKernelGGL((dstream_kernel<0, 2, true, 8>), grid, block, lds, st, a, p.kb_per_wg, p.Nv);
-    } else if (narrow) {
-        if (rows) hipLaunchKernelGGL((dstream_kernel<1, 1, false, 8>), grid_narrow, block, lds, st, a, p.kb_per_wg, p.Nv);
-        else hipLaunchKernelGGL((dstream_kernel<0, 1, false, 8>), grid_narrow, block, lds, st, a, p.kb_per_wg, p.Nv);
-    } else {
-        if (rows) hipLaunchKernelGGL((dstream_kernel<1, 2, false, 8>), grid, block, lds, st, a, p.kb_per_wg, p.Nv);
-        else hipLaunchKernelGGL((dstream_kernel<0, 2, false, 8>), grid, block, lds, st, a, p.kb_per_wg, p.Nv);
-    }
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, ds_lds(MT), st, a, p.kb_per_wg, p.Nv, f); };
+    if (p.pair) narrow ? go(dstream_kernel<0, 1, false, true, MT>) : go(dstream_kernel<0, 2, true, false, MT>);
+    else if (rows) narrow ? go(dstream_kernel<1, 1, false, false, MT>) : go(dstream_kernel<1, 2, false, false, MT>);
+    else narrow ? go(dstream_kernel<0, 1, false, false, MT>) : go(dstream_kernel<0, 2, false, false, MT>);
+}
+
+void launch_dgemm_stream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &f, bool narrow) {
+    if (a.M <= 32) launch_dstream<1>(st, a, p, f, narrow);
+    else launch_dstream<2>(st, a, p, f, narrow);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Epilogues: the K slices are added in slice order; where the projection's input was an RMSNorm, the
 // row's scale is formed here from the slices' sums of squares (in slice order) and applied first.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float row_scale(const float *ssq_part, int S_ssq, int m, int d, float eps) {
-    float t = 0.f;
-    for (int s = 0; s < S_ssq; ++s) t += ssq_part[s * 64 + m];
-    return 1.0f / sqrtf(t / (float)d + eps);
-}
-
-// One thread per 4 output columns.  RESIDUAL: out = resid + sum (row-major).  SWIGLU: out = silu(s g) * (s u),
-// fragment-packed for the down projection (gate and up of a feature sit 32 virtual columns apart).
-template <int EPI>
+// out = resid + sum, row-major; one thread per 4 columns, one workgroup per 1024 columns of a row.  With a gain (the
+// next RMSNorm's) also out . gain, fragment-packed, and the sum of squares of the workgroup's part of the row.
 __global__ __launch_bounds__(256) void dgemm_epilogue_kernel(DEpiArgs a) {
     const int M = a.M, N = a.N;
-    const int groups = N >> 2;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= M * groups) return;
-    const int m = idx / groups, n = (idx % groups) * 4;
-    bf16x4 v;
-    if (EPI == EPI_SWIGLU) {
-        const int col = (n >> 5) * 64 + (n & 31);
-        f32x4 g = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < a.S; ++s) {
-            const float *p = a.part + ((size_t)s * M + m) * a.Nv + col;
-            g += *(const f32x4 *)p;
-            u += *(const f32x4 *)(p + 32);
-        }
-        const float sc = a.ssq_part ? row_scale(a.ssq_part, a.S_ssq, m, a.d, a.eps) : 1.0f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(silu_f(g[i] * sc) * (u[i] * sc));
-        *(bf16x4 *)(a.out + packed_offset(m, n, packed_mt(M)) + (n & 7)) = v;
-    } else {
+    const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
+    float ss = 0.f;
+    if (n < N) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         for (int s = 0; s < a.S; ++s) acc += *(const f32x4 *)(a.part + ((size_t)s * M + m) * a.Nv + n);
         const bf16x4 r = *(const bf16x4 *)(a.resid + (size_t)m * N + n);
+        bf16x4 v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(acc[i] + (float)r[i]);
         *(bf16x4 *)(a.out + (size_t)m * N + n) = v;
+        if (a.gain) {
+            const bf16x4 g = *(const bf16x4 *)(a.gain + n);
+            bf16x4 w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float f = (float)v[i];
+                ss += f * f;
+                w[i] = (bf16_t)(f * (float)g[i]);
+            }
+            *(bf16x4 *)(a.out_gain + packed_offset(m, n, packed_mt(M)) + (n & 7)) = w;
+        }
     }
+    if (!a.gain) return;
+    __shared__ float red[4];
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    if (threadIdx.x == 0) a.ssq_out[blockIdx.x * RS_SSQ_ROWS + m] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a, int epi) {
-    const int blocks = (a.M * (a.N / 4) + 255) / 256;
-    if (epi == EPI_SWIGLU) hipLaunchKernelGGL(dgemm_epilogue_kernel<EPI_SWIGLU>, dim3(blocks), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(dgemm_epilogue_kernel<EPI_RESIDUAL>, dim3(blocks), dim3(256), 0, st, a);
+void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a) {
+    hipLaunchKernelGGL(dgemm_epilogue_kernel, dim3((a.N + 1023) / 1024, a.M), dim3(256), 0, st, a);
 }
 
 // QKV epilogue of a decode step: sums the K slices, applies the first RMSNorm's row scale, rotates q and k
@@ -393,14 +476,17 @@ void launch_qkv_rope_epilogue(hipStream_t st, const QkvEpiArgs &a) {
     }
 }
 
+template <int MT>
+static void dstream_init() {
+    auto set = [](const void *f) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, ds_lds(MT)); };
+    set((const void *)dstream_kernel<0, 1, false, true, MT>);
+    set((const void *)dstream_kernel<0, 2, true, false, MT>);
+    set((const void *)dstream_kernel<1, 1, false, false, MT>);
+    set((const void *)dstream_kernel<1, 2, false, false, MT>);
+    set((const void *)dstream_kernel<0, 1, false, false, MT>);
+    set((const void *)dstream_kernel<0, 2, false, false, MT>);
+}
 void decode_gemm_kernels_init() {
-    auto set = [](const void *f) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * DS_CH * 2048); };
-    set((const void *)dstream_kernel<0, 2, false, 8>);
-    set((const void *)dstream_kernel<1, 2, false, 8>);
-    set((const void *)dstream_kernel<0, 2, true, 8>);
-    set((const void *)dstream_kernel<1, 2, true, 8>);
-    set((const void *)dstream_kernel<0, 1, false, 8>);
-    set((const void *)dstream_kernel<1, 1, false, 8>);
-    set((const void *)dstream_kernel<0, 1, false, 8, true>);
-    set((const void *)dstream_kernel<1, 1, false, 8, true>);
+    dstream_init<1>();
+    dstream_init<2>();
 }

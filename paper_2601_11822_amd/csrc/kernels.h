@@ -107,14 +107,21 @@ size_t packed_weight_elems(int N, int K);
 void launch_pack_weights(hipStream_t st, const bf16_t *W, bf16_t *Wp, int N, int K);
 
 // ---- decode-side projections (decode_gemm.hip): at most 64 rows, weights streamed once, RMSNorm folded in ----
+#define RS_SSQ_ROWS 64   // row stride of the sums of squares below
 struct DGemmArgs {
-    const bf16_t *A_packed;   // activations fragment-packed with two row tiles (packed_mt(M) == 2), or
+    const bf16_t *A_packed;   // activations fragment-packed (packed_mt(M) row tiles), or
     const bf16_t *X_rows;     // row-major [M][K] hidden state: multiplied by gain[K] on the way in, and
     const bf16_t *gain;       //   the sums of squares of each row over each K slice go to
-    float *ssq_part;          //   ssq_part[slice][64]  (the epilogue turns them into the RMSNorm scale)
+    float *ssq_part;          //   ssq_part[slice][RS_SSQ_ROWS]  (the epilogue turns them into the RMSNorm scale)
     const bf16_t *Wp, *Wp2;   // fragment-packed weights [N][K]; Wp2: the up matrix of a gate/up pair
-    float *part;              // out: float32 partial products [S][M][Nv]
+    float *part;              // out: float32 partial products [S][M][Nv]  (not for a pair)
     int M, N, K;
+};
+struct DFuseArgs {            // a gate/up pair: out = silu(s g) * (s u) with the row's RMSNorm scale s
+    const float *ssq_part = nullptr;    // [S_ssq][RS_SSQ_ROWS] sums of squares of the parts of each row of K elements
+    int S_ssq = 0;
+    float eps = 0.f;
+    bf16_t *out = nullptr;              // fragment-packed [M][N]
 };
 struct DGemmPlan {
     bool pair;
@@ -123,25 +130,28 @@ struct DGemmPlan {
 // True if the streaming kernel takes this projection (K a multiple of 256, N a multiple of 4 and at least 128).
 bool dgemm_applies(int N, int K);
 DGemmPlan dgemm_plan(int N, int K, bool pair);
-size_t dgemm_partial_elems(int M, int N, int K, bool pair);
+size_t dgemm_partial_elems(int M, int N, int K);
+// The stream: partial products of a plain projection, or a pair's finished output (f).
 // narrow: half-height workgroups, twice as many (same sums, same bits); dgemm_prefers_half_height says when, from the
 // number of compute units the side owns
-void launch_dgemm_partials(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p, bool narrow);
+void launch_dgemm_stream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &f, bool narrow);
 bool dgemm_prefers_half_height(const DGemmPlan &p, int cus);
 struct DEpiArgs {
     const float *part;        // [S][M][Nv]
     int S, Nv;
-    const float *ssq_part;    // [S_ssq][64] or nullptr: no row scale
-    int S_ssq, d;
-    float eps;
-    const bf16_t *resid;      // EPI_RESIDUAL: row-major [M][N]
-    bf16_t *out;              // EPI_RESIDUAL: row-major [M][N]; EPI_SWIGLU: fragment-packed [M][N]
+    const bf16_t *resid;      // row-major [M][N]
+    bf16_t *out;              // row-major [M][N]
     int M, N;
+    // or nullptr: the next RMSNorm's gain [N]; out . gain goes fragment-packed to out_gain and the sums of squares of
+    // out's rows to ssq_out [ceil(N / 1024)][RS_SSQ_ROWS]
+    const bf16_t *gain = nullptr;
+    bf16_t *out_gain = nullptr;
+    float *ssq_out = nullptr;
 };
-void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a, int epi);
+void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a);
 struct QkvEpiArgs {
     const float *part;        // [S][M][Nv] partial q | k | v
-    const float *ssq_part;    // [S][64]
+    const float *ssq_part;    // [S][RS_SSQ_ROWS]
     int S, Nv, d;
     float eps;
     bf16_t *qkv;              // out: [M][(Hq+2Hkv)*hd] with q and k rotated

@@ -339,9 +339,8 @@ size_t fused_partial_elems(const rs_ctx *c, int M) {
     if (!fused_decode_applies(c)) return 0;
     const rs_model_desc &m = c->m;
     const int d = m.d_model, qd = m.n_q_heads * m.head_dim, nqkv = qd + 2 * m.n_kv_heads * m.head_dim, f = m.ffn_dim;
-    size_t pe = std::max(dgemm_partial_elems(M, nqkv, d, false), dgemm_partial_elems(M, d, qd, false));
-    pe = std::max(pe, dgemm_partial_elems(M, f, d, true));
-    if (dgemm_applies(d, f)) pe = std::max(pe, dgemm_partial_elems(M, d, f, false));
+    size_t pe = std::max(dgemm_partial_elems(M, nqkv, d), dgemm_partial_elems(M, d, qd));
+    if (dgemm_applies(d, f)) pe = std::max(pe, dgemm_partial_elems(M, d, f));
     return pe;
 }
 
@@ -383,7 +382,7 @@ int32_t alloc_ws(rs_ctx *c, Workspace &w, int rows, bool decode) {
         HIP_TRY(hipMalloc(&w.part_ml, br * m.n_q_heads * nch * 2 * sizeof(float)));
     }
     if (decode) {
-        HIP_TRY(hipMalloc(&w.ssq, 2 * 64 * 64 * sizeof(float)));
+        HIP_TRY(hipMalloc(&w.ssq, 2 * 64 * RS_SSQ_ROWS * sizeof(float)));
         const size_t nch = (c->lim.max_context + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
         HIP_TRY(hipMalloc(&w.part_o, (size_t)rows * m.n_q_heads * nch * m.head_dim * sizeof(float)));
         HIP_TRY(hipMalloc(&w.part_ml, (size_t)rows * m.n_q_heads * nch * 2 * sizeof(float)));
@@ -421,7 +420,7 @@ size_t carve_decode_ws(const rs_ctx *c, Workspace &w, unsigned char *base, int r
     pe = std::max(pe, skinny_partial_elems(Mmax, (int)f, (int)d, EPI_SWIGLU));
     pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)f, EPI_RESIDUAL));
     pe = std::max(pe, fused_partial_elems(c, Mmax));
-    w.ssq = (float *)take(2 * 64 * 64 * sizeof(float));
+    w.ssq = (float *)take(2 * 64 * RS_SSQ_ROWS * sizeof(float));
     w.partials = (float *)take(pe * sizeof(float));
     w.partial_cap = pe;
     const size_t nch = (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
@@ -755,16 +754,19 @@ int32_t decode_layer(rs_ctx *c, Workspace &w, int32_t layer, const void *x_in, v
     c->decode_fused = skinny && c->moe[layer].E == 0 && fused_decode_applies(c);
     if (c->decode_fused) {
         // At most 64 rows: every projection is a stream of its weights with the RMSNorm of its input folded in
-        // (decode_gemm.hip).  10 launches: QKV stream, its epilogue (row scale, rotary, cache append), attention,
-        // chunk merge, O stream + residual, gate/up stream + SwiGLU, down stream + residual.
+        // (decode_gemm.hip).  9 launches: QKV stream, its epilogue (row scale, rotary, cache append), attention,
+        // chunk merge, O stream + residual, gate/up stream with SwiGLU, down stream + residual.
         const rs_ctx::PackedLayer &pl = c->packed[layer];
         const int f = m.ffn_dim;
-        float *ssq1 = w.ssq, *ssq2 = w.ssq + 64 * 64;
+        float *ssq1 = w.ssq, *ssq2 = w.ssq + 64 * RS_SSQ_ROWS;
         const int dcus = c->side[RS_SIDE_DECODE].cus;
         tick(c, RS_SIDE_DECODE, 0);
         tick(c, RS_SIDE_DECODE, 1);
+        auto stream = [&](const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &f = DFuseArgs{}) {
+            launch_dgemm_stream(st, a, p, f, dgemm_prefers_half_height(p, dcus));
+        };
         const DGemmPlan pq = dgemm_plan(nqkv, d, false);
-        launch_dgemm_partials(st, DGemmArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, ssq1, pl.wqkv, nullptr, w.partials, B, nqkv, d}, pq, dgemm_prefers_half_height(pq, dcus));
+        stream(DGemmArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, ssq1, pl.wqkv, nullptr, w.partials, B, nqkv, d}, pq);
         launch_qkv_rope_epilogue(st, QkvEpiArgs{w.partials, ssq1, pq.S, pq.Nv, d, m.rms_eps, w.qkv, c->rope, kp, vp, tables, ctx_lens,
                                                 c->err_flag + RS_SIDE_DECODE, B, m.n_q_heads, m.n_kv_heads, hd, max_blk,
                                                 c->pool.n_blocks, m.max_pos});
@@ -777,18 +779,18 @@ int32_t decode_layer(rs_ctx *c, Workspace &w, int32_t layer, const void *x_in, v
         launch_decode_attention(st, da);
         tick(c, RS_SIDE_DECODE, 4);
         const DGemmPlan po = dgemm_plan(d, qd, false);
-        launch_dgemm_partials(st, DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, B, d, qd}, po, dgemm_prefers_half_height(po, dcus));
-        launch_dgemm_epilogue(st, DEpiArgs{w.partials, po.S, po.Nv, nullptr, 0, d, m.rms_eps, (const bf16_t *)x_in, w.x1, B, d}, EPI_RESIDUAL);
+        stream(DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, B, d, qd}, po);
+        // x1 = x + attn Wo, and with it the gate/up projection's operand: x1 . g2 (packed) and the rows' sums of squares
+        launch_dgemm_epilogue(st, DEpiArgs{w.partials, po.S, po.Nv, (const bf16_t *)x_in, w.x1, B, d, (const bf16_t *)lw.g2, w.h, ssq2});
         tick(c, RS_SIDE_DECODE, 5);
         tick(c, RS_SIDE_DECODE, 6);
-        const DGemmPlan pg = dgemm_plan(f, d, true);
-        launch_dgemm_partials(st, DGemmArgs{nullptr, w.x1, (const bf16_t *)lw.g2, ssq2, pl.wg, pl.wu, w.partials, B, f, d}, pg, dgemm_prefers_half_height(pg, dcus));
-        launch_dgemm_epilogue(st, DEpiArgs{w.partials, pg.S, pg.Nv, ssq2, pg.S, d, m.rms_eps, nullptr, w.act, B, f}, EPI_SWIGLU);
+        stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wg, pl.wu, nullptr, B, f, d}, dgemm_plan(f, d, true),
+               DFuseArgs{ssq2, (d + 1023) / 1024, m.rms_eps, w.act});
         tick(c, RS_SIDE_DECODE, 7);
         if (dgemm_applies(d, f)) {
             const DGemmPlan pd = dgemm_plan(d, f, false);
-            launch_dgemm_partials(st, DGemmArgs{w.act, nullptr, nullptr, nullptr, pl.wd, nullptr, w.partials, B, d, f}, pd, dgemm_prefers_half_height(pd, dcus));
-            launch_dgemm_epilogue(st, DEpiArgs{w.partials, pd.S, pd.Nv, nullptr, 0, d, m.rms_eps, w.x1, (bf16_t *)x_out, B, d}, EPI_RESIDUAL);
+            stream(DGemmArgs{w.act, nullptr, nullptr, nullptr, pl.wd, nullptr, w.partials, B, d, f}, pd);
+            launch_dgemm_epilogue(st, DEpiArgs{w.partials, pd.S, pd.Nv, w.x1, (bf16_t *)x_out, B, d});
         } else {
             GemmArgs gd{w.act, (const bf16_t *)lw.wd, nullptr, pl.wd, nullptr, w.x1, (bf16_t *)x_out, B, d, f, EPI_RESIDUAL,
                         0, c->side[RS_SIDE_DECODE].cus, w.partials, w.partial_cap};
