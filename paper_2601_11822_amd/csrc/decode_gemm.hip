@@ -1,8 +1,8 @@
-// Decode-side projections (at most 64 rows): weight-streaming GEMMs with the RMSNorm folded in.
+// Projections of a pass of at most RS_STREAM_ROWS rows: weight-streaming GEMMs with the RMSNorm folded in.
 //
-// A decode step multiplies a few rows by every weight of the layer once (paper section 2.1: decode is
-// bound by reading weights and cache, not by arithmetic), so each of the four projections is a stream of
-// its matrix through the matrix cores at the rate the partition's memory path allows, and everything
+// Such a pass multiplies a few rows by every weight of the layer once (paper section 2.1: decode is
+// bound by reading weights and cache, not by arithmetic; so is a prompt this short), so each of the four projections
+// is a stream of its matrix through the matrix cores at the rate the partition's memory path allows, and everything
 // around that stream is overhead to be removed:
 //
 //   * RMSNorm needs a whole row before it can scale an element, which would cost a kernel of its own in
@@ -39,6 +39,7 @@ __device__ __forceinline__ float row_scale(const float *ssq_part, int S_ssq, int
     return 1.0f / sqrtf(t / (float)d + eps);
 }
 
+#define DS_INLINE_PIECES 12
 #define DS_CH 16   // k-blocks per activation chunk: two slabs of MT x 16 KB in LDS
 
 // ACT 0: activations fragment-packed (packed_mt(M) row tiles per k-block), as their producers write them.
@@ -352,8 +353,12 @@ static void launch_dstream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &
 }
 
 void launch_dgemm_stream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &f, bool narrow) {
-    if (a.M <= 32) launch_dstream<1>(st, a, p, f, narrow);
-    else launch_dstream<2>(st, a, p, f, narrow);
+    switch ((a.M + 31) / 32) {
+        case 1: launch_dstream<1>(st, a, p, f, narrow); break;
+        case 2: launch_dstream<2>(st, a, p, f, narrow); break;
+        case 3: launch_dstream<3>(st, a, p, f, narrow); break;
+        default: launch_dstream<4>(st, a, p, f, narrow); break;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -394,13 +399,48 @@ __global__ __launch_bounds__(256) void dgemm_epilogue_kernel(DEpiArgs a) {
     if (threadIdx.x == 0) a.ssq_out[blockIdx.x * RS_SSQ_ROWS + m] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// The operand of a projection behind an RMSNorm, made in front of its stream: x . gain fragment-packed and the sums of
+// squares of each row's parts (as dgemm_epilogue_kernel leaves them).
+__global__ __launch_bounds__(256) void gain_pack_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ gain, bf16_t *__restrict__ out,
+                                                        float *__restrict__ ssq_out, int M, int N) {
+    const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
+    float ss = 0.f;
+    if (n < N) {
+        const bf16x4 v = *(const bf16x4 *)(x + (size_t)m * N + n), g = *(const bf16x4 *)(gain + n);
+        bf16x4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float f = (float)v[i];
+            ss += f * f;
+            w[i] = (bf16_t)(f * (float)g[i]);
+        }
+        *(bf16x4 *)(out + packed_offset(m, n, packed_mt(M)) + (n & 7)) = w;
+    }
+    __shared__ float red[4];
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    if (threadIdx.x == 0) ssq_out[blockIdx.x * RS_SSQ_ROWS + m] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+void launch_gain_pack(hipStream_t st, const bf16_t *x, const bf16_t *gain, bf16_t *out, float *ssq_out, int M, int N) {
+    hipLaunchKernelGGL(gain_pack_kernel, dim3((N + 1023) / 1024, M), dim3(256), 0, st, x, gain, out, ssq_out, M, N);
+}
+
+// Whether the stream forms x . gain itself.  That costs a workgroup 0.3 to 0.5 us per staged chunk and row tile (vector
+// instructions in front of its matrix instructions); launch_gain_pack is a launch of 5 us.  QKV on 256 CUs, inline /
+// packed first: 8B shape (4 chunks) at 64 rows 16.8 / 14.4 + 4.8 us, at 77 rows 20.1 / 15.6 + 5.0 (equal in the layer's
+// time); 70B shape (16 chunks) at 101 rows 76 / 45 + 5 us.
+bool dgemm_gains_inline(int M, const DGemmPlan &p) { return (p.kb_per_wg / DS_CH) * ((M + 31) / 32) <= DS_INLINE_PIECES; }
+
 void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a) {
     hipLaunchKernelGGL(dgemm_epilogue_kernel, dim3((a.N + 1023) / 1024, a.M), dim3(256), 0, st, a);
 }
 
-// QKV epilogue of a decode step: sums the K slices, applies the first RMSNorm's row scale, rotates q and k
-// at the row's position (rotate-half pairs (i, i + hd/2), angles from the host-built table), stores q | k | v
-// as bf16 rows for the attention kernel, and appends k and v to the paged cache through the block table:
+// QKV epilogue: sums the K slices, applies the first RMSNorm's row scale, rotates q and k at the row's position
+// (rotate-half pairs (i, i + hd/2), angles from the host-built table), stores q | k | v as bf16 rows for the
+// attention kernels, and writes k and v to the paged cache through the block table (rows [0, T) are prompt rows,
+// the rest decode rows):
 // K in the pool's fragment order (kpool_chunk_offset), V token-minor.  One thread owns 4 dims of a pair's
 // lower half and the matching 4 of the upper half.  A position outside the rotary table or a block id
 // outside the pool is never used as an index: the row's cache write is skipped and the error word raised.
@@ -413,7 +453,19 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
     const int n_heads = a.Hq + 2 * a.Hkv;
     if (head >= n_heads) return;
     const int i0 = (tid % TPH) * 4, half = HD / 2;
-    const int pos = a.ctx_lens[m];
+    int pos, max_blk;
+    const int32_t *tab_row;
+    if (m < a.T) {
+        int req = 0;
+        while (req + 1 < a.seq.n_req && m >= a.seq.cu[req + 1]) ++req;
+        pos = a.seq.start[req] + m - a.seq.cu[req];
+        max_blk = a.max_blk_p;
+        tab_row = a.ptables + (size_t)req * max_blk;
+    } else {
+        pos = a.ctx_lens[m - a.T];
+        max_blk = a.max_blk;
+        tab_row = a.tables + (size_t)(m - a.T) * max_blk;
+    }
     const bool pos_ok = pos >= 0 && pos < a.max_pos;
     if (!pos_ok && tid == 0 && blockIdx.y == 0) atomicOr(a.err_flag, 1);
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
@@ -422,7 +474,7 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
         lo += *(const f32x4 *)p;
         hi += *(const f32x4 *)(p + half);
     }
-    const float sc = row_scale(a.ssq_part, a.S, m, a.d, a.eps);
+    const float sc = row_scale(a.ssq_part, a.S_ssq, m, a.d, a.eps);
     lo *= sc;
     hi *= sc;
     bf16x4 olo, ohi;
@@ -448,7 +500,7 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
     if (head < a.Hq || !pos_ok) return;
     const int bi = pos / RS_BLOCK_TOKENS, slot = pos % RS_BLOCK_TOKENS;
     int blk = -1;
-    if (bi < a.max_blk) blk = a.tables[(size_t)m * a.max_blk + bi];
+    if (bi < max_blk) blk = tab_row[bi];
     if ((unsigned)blk >= (unsigned)a.n_blocks) {
         if (tid % TPH == 0 && head == a.Hq) atomicOr(a.err_flag, 2);
         return;
@@ -489,4 +541,6 @@ static void dstream_init() {
 void decode_gemm_kernels_init() {
     dstream_init<1>();
     dstream_init<2>();
+    dstream_init<3>();
+    dstream_init<4>();
 }

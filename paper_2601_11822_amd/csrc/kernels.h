@@ -106,8 +106,9 @@ void launch_gemm_head(hipStream_t st, const GemmArgs &a, const HeadOut &o);
 size_t packed_weight_elems(int N, int K);
 void launch_pack_weights(hipStream_t st, const bf16_t *W, bf16_t *Wp, int N, int K);
 
-// ---- decode-side projections (decode_gemm.hip): at most 64 rows, weights streamed once, RMSNorm folded in ----
-#define RS_SSQ_ROWS 64   // row stride of the sums of squares below
+// ---- projections of a pass of few rows (decode_gemm.hip): weights streamed once, RMSNorm folded in ----
+#define RS_STREAM_ROWS 128   // most rows of such a pass
+#define RS_SSQ_ROWS RS_STREAM_ROWS   // row stride of the sums of squares below
 struct DGemmArgs {
     const bf16_t *A_packed;   // activations fragment-packed (packed_mt(M) row tiles), or
     const bf16_t *X_rows;     // row-major [M][K] hidden state: multiplied by gain[K] on the way in, and
@@ -135,6 +136,8 @@ size_t dgemm_partial_elems(int M, int N, int K);
 // narrow: half-height workgroups, twice as many (same sums, same bits); dgemm_prefers_half_height says when, from the
 // number of compute units the side owns
 void launch_dgemm_stream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &f, bool narrow);
+bool dgemm_gains_inline(int M, const DGemmPlan &p);
+void launch_gain_pack(hipStream_t st, const bf16_t *x, const bf16_t *gain, bf16_t *out, float *ssq_out, int M, int N);
 bool dgemm_prefers_half_height(const DGemmPlan &p, int cus);
 struct DEpiArgs {
     const float *part;        // [S][M][Nv]
@@ -151,15 +154,20 @@ struct DEpiArgs {
 void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a);
 struct QkvEpiArgs {
     const float *part;        // [S][M][Nv] partial q | k | v
-    const float *ssq_part;    // [S][RS_SSQ_ROWS]
-    int S, Nv, d;
+    const float *ssq_part;    // [S_ssq][RS_SSQ_ROWS]
+    int S, S_ssq, Nv, d;
     float eps;
     bf16_t *qkv;              // out: [M][(Hq+2Hkv)*hd] with q and k rotated
     const CosSin *table;
     bf16_t *k_pool, *v_pool;  // this layer
-    const int32_t *tables, *ctx_lens;
+    const int32_t *tables, *ctx_lens;   // of the decode rows [T, M)
     int32_t *err_flag;
     int M, Hq, Hkv, hd, max_blk, n_blocks, max_pos;
+    // rows [0, T): prompts, delimited and placed by seq
+    int T = 0;
+    const int32_t *ptables = nullptr;
+    int max_blk_p = 0;
+    SeqInfo seq{};
 };
 void launch_qkv_rope_epilogue(hipStream_t st, const QkvEpiArgs &a);
 void decode_gemm_kernels_init();

@@ -52,7 +52,7 @@ std::mutex g_static_scratch_mu;
 struct Workspace {
     bf16_t *h = nullptr, *qkv = nullptr, *attn = nullptr, *x1 = nullptr, *act = nullptr, *xbuf = nullptr;
     float *partials = nullptr, *part_o = nullptr, *part_ml = nullptr;
-    float *ssq = nullptr;   // decode side: per-slice sums of squares of the two normalised inputs, 2 x [64 slices][64 rows]
+    float *ssq = nullptr;   // per-slice sums of squares of the two normalised inputs of a streamed pass, 2 x [64 slices][RS_SSQ_ROWS]
     size_t partial_cap = 0;
     int rows = 0;
     // sparse feed-forward block (allocated by the first rs_set_moe_weights)
@@ -179,7 +179,7 @@ struct rs_ctx {
     int32_t step_err = 0;            // bits met by serving steps and not yet reported
     Workspace ws[2];
     int last_rows[2] = {0, 0};   // rows of each side's last layer call: fixes the packed layout of h/attn/act
-    bool decode_fused = false;   // the decode side's last layer call folded its RMSNorms into the projections (no h buffer)
+    bool streamed[2] = {false, false};   // each side's last layer call folded its RMSNorms into the projections (no h buffer)
     // captured decode steps, keyed by everything a captured launch bakes in (rs_decode_layer_graph)
     struct GraphKey {
         int32_t layer, max_blk, B, max_ctx;
@@ -328,15 +328,15 @@ int32_t get_stream(rs_ctx *c, int side, int cus, hipStream_t *out) {
     return RS_OK;
 }
 
-// Whether a decode step of at most 64 rows takes the weight-streaming projections with the RMSNorm folded in
-// (a function of the model's shape), and the partial-product elements they need.
-bool fused_decode_applies(const rs_ctx *c) {
+// Whether a pass of at most RS_STREAM_ROWS rows through a dense layer takes the weight-streaming projections with the
+// RMSNorm folded in (a function of the model's shape), and the partial-product elements they need.
+bool stream_applies(const rs_ctx *c) {
     const rs_model_desc &m = c->m;
     const int d = m.d_model, qd = m.n_q_heads * m.head_dim, nqkv = qd + 2 * m.n_kv_heads * m.head_dim, f = m.ffn_dim;
     return dgemm_applies(nqkv, d) && dgemm_applies(d, qd) && dgemm_applies(f, d);
 }
-size_t fused_partial_elems(const rs_ctx *c, int M) {
-    if (!fused_decode_applies(c)) return 0;
+size_t stream_partial_elems(const rs_ctx *c, int M) {
+    if (!stream_applies(c)) return 0;
     const rs_model_desc &m = c->m;
     const int d = m.d_model, qd = m.n_q_heads * m.head_dim, nqkv = qd + 2 * m.n_kv_heads * m.head_dim, f = m.ffn_dim;
     size_t pe = std::max(dgemm_partial_elems(M, nqkv, d), dgemm_partial_elems(M, d, qd));
@@ -370,7 +370,7 @@ int32_t alloc_ws(rs_ctx *c, Workspace &w, int rows, bool decode) {
         pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)qd, EPI_RESIDUAL));
         pe = std::max(pe, skinny_partial_elems(Mmax, (int)f, (int)d, EPI_SWIGLU));
         pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)f, EPI_RESIDUAL));
-        if (decode) pe = std::max(pe, fused_partial_elems(c, Mmax));
+        pe = std::max(pe, stream_partial_elems(c, std::min(rows, RS_STREAM_ROWS)));
         HIP_TRY(hipMalloc(&w.partials, pe * sizeof(float)));
         w.partial_cap = pe;
     }
@@ -381,8 +381,8 @@ int32_t alloc_ws(rs_ctx *c, Workspace &w, int rows, bool decode) {
         HIP_TRY(hipMalloc(&w.part_o, br * m.n_q_heads * nch * m.head_dim * sizeof(float)));
         HIP_TRY(hipMalloc(&w.part_ml, br * m.n_q_heads * nch * 2 * sizeof(float)));
     }
+    HIP_TRY(hipMalloc(&w.ssq, 2 * 64 * RS_SSQ_ROWS * sizeof(float)));
     if (decode) {
-        HIP_TRY(hipMalloc(&w.ssq, 2 * 64 * RS_SSQ_ROWS * sizeof(float)));
         const size_t nch = (c->lim.max_context + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
         HIP_TRY(hipMalloc(&w.part_o, (size_t)rows * m.n_q_heads * nch * m.head_dim * sizeof(float)));
         HIP_TRY(hipMalloc(&w.part_ml, (size_t)rows * m.n_q_heads * nch * 2 * sizeof(float)));
@@ -419,7 +419,7 @@ size_t carve_decode_ws(const rs_ctx *c, Workspace &w, unsigned char *base, int r
     pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)qd, EPI_RESIDUAL));
     pe = std::max(pe, skinny_partial_elems(Mmax, (int)f, (int)d, EPI_SWIGLU));
     pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)f, EPI_RESIDUAL));
-    pe = std::max(pe, fused_partial_elems(c, Mmax));
+    pe = std::max(pe, stream_partial_elems(c, std::min(rows, RS_STREAM_ROWS)));
     w.ssq = (float *)take(2 * 64 * RS_SSQ_ROWS * sizeof(float));
     w.partials = (float *)take(pe * sizeof(float));
     w.partial_cap = pe;
@@ -598,6 +598,89 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     return !released_needed;
 }
 
+// A pass of at most RS_STREAM_ROWS rows through a dense layer: T prompt rows (prompts or later chunks of them, placed by
+// seq), then B decode rows.  Every projection is a stream of its weights with the RMSNorm of its input folded in
+// (decode_gemm.hip), and the kernels in between belong to their producers: QKV stream, its epilogue (row scale, rotary,
+// cache write), attention of each kind of row, O stream, its epilogue (residual, gate/up's operand), gate/up stream with
+// SwiGLU, down stream, residual.  Against the K-sliced large-tile kernels with norm, rotary and SwiGLU launches of their
+// own, on 256 CUs: 8B layer at 77 prompt rows 171 -> 126 us, 70B layer at 101 decode rows 682 -> 640 us.
+bool streams(const rs_ctx *c, int layer, int rows) { return rows <= RS_STREAM_ROWS && c->moe[layer].E == 0 && stream_applies(c); }
+
+int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const void *x_in, void *x_out, int T, const SeqInfo &seq,
+                     const int32_t *ptables, int32_t max_blk_p, int B, const int32_t *ctx_lens, const int32_t *dtables,
+                     int32_t max_blk_d, int32_t max_ctx) {
+    const rs_model_desc &m = c->m;
+    const rs_layer_weights &lw = c->weights[layer];
+    const rs_ctx::PackedLayer &pl = c->packed[layer];
+    hipStream_t st = c->side[side].stream;
+    const int d = m.d_model, hd = m.head_dim, qd = m.n_q_heads * hd, nqkv = qd + 2 * m.n_kv_heads * hd, f = m.ffn_dim, M = T + B;
+    bf16_t *kp = (bf16_t *)c->pool.k_pool + (size_t)layer * c->pool.layer_stride;
+    bf16_t *vp = (bf16_t *)c->pool.v_pool + (size_t)layer * c->pool.layer_stride;
+    int32_t *err = c->err_flag + side;
+    const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
+    float *ssq1 = w.ssq, *ssq2 = w.ssq + 64 * RS_SSQ_ROWS;
+    const int cus = c->side[side].cus;
+    c->last_rows[side] = M;
+    c->streamed[side] = true;
+    auto stream = [&](const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &fz = DFuseArgs{}) {
+        launch_dgemm_stream(st, a, p, fz, dgemm_prefers_half_height(p, cus));
+    };
+    tick(c, side, 0);
+    tick(c, side, 1);
+    const DGemmPlan pq = dgemm_plan(nqkv, d, false);
+    int S_ssq = pq.S;
+    if (dgemm_gains_inline(M, pq)) {
+        stream(DGemmArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, ssq1, pl.wqkv, nullptr, w.partials, M, nqkv, d}, pq);
+    } else {
+        launch_gain_pack(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, ssq1, M, d);
+        tick(c, side, 1);
+        S_ssq = (d + 1023) / 1024;
+        stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wqkv, nullptr, w.partials, M, nqkv, d}, pq);
+    }
+    launch_qkv_rope_epilogue(st, QkvEpiArgs{w.partials, ssq1, pq.S, S_ssq, pq.Nv, d, m.rms_eps, w.qkv, c->rope, kp, vp, dtables, ctx_lens, err, M,
+                                            m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq});
+    tick(c, side, 2);
+    tick(c, side, 3);
+    if (T > 0) {
+        PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd, max_blk_p, c->pool.n_blocks, sl2, seq};
+        pa.Mt_out = packed_mt(M);
+        launch_prefill_attention(st, pa);
+    }
+    if (B > 0) {
+        DecodeAttnArgs da{w.qkv + (size_t)T * nqkv, nqkv, w.attn, kp, vp, dtables, ctx_lens, err, w.part_o, w.part_ml,
+                          B, m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, max_ctx,
+                          (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, sl2, cus < RS_TOTAL_CUS};
+        da.out_row0 = T;
+        da.out_Mt = packed_mt(M);
+        launch_decode_attention(st, da);
+    }
+    tick(c, side, 4);
+    const DGemmPlan po = dgemm_plan(d, qd, false);
+    stream(DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, M, d, qd}, po);
+    // x1 = x + attn Wo, and with it the gate/up projection's operand: x1 . g2 (packed) and the rows' sums of squares
+    launch_dgemm_epilogue(st, DEpiArgs{w.partials, po.S, po.Nv, (const bf16_t *)x_in, w.x1, M, d, (const bf16_t *)lw.g2, w.h, ssq2});
+    tick(c, side, 5);
+    tick(c, side, 6);
+    stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wg, pl.wu, nullptr, M, f, d}, dgemm_plan(f, d, true),
+           DFuseArgs{ssq2, (d + 1023) / 1024, m.rms_eps, w.act});
+    tick(c, side, 7);
+    bool ok = true;
+    if (dgemm_applies(d, f)) {
+        const DGemmPlan pd = dgemm_plan(d, f, false);
+        stream(DGemmArgs{w.act, nullptr, nullptr, nullptr, pl.wd, nullptr, w.partials, M, d, f}, pd);
+        launch_dgemm_epilogue(st, DEpiArgs{w.partials, pd.S, pd.Nv, w.x1, (bf16_t *)x_out, M, d});
+    } else {
+        GemmArgs gd{w.act, (const bf16_t *)lw.wd, nullptr, pl.wd, nullptr, w.x1, (bf16_t *)x_out, M, d, f, EPI_RESIDUAL,
+                    0, cus, w.partials, w.partial_cap};
+        if (M <= 64) launch_gemm_skinny(st, gd, w.partials);
+        else ok = launch_gemm_tiled(st, gd);
+    }
+    tick(c, side, 8);
+    HIP_TRY(hipGetLastError());
+    if (!ok) return fail(RS_ERR_STATE, "layer %d: a GEMM of this pass needs the row-major matrices that were released", layer);
+    return RS_OK;
+}
+
 int32_t prefill_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, const int32_t *cu,
                       int32_t n_req, const int32_t *tables, int32_t max_blk) {
     const rs_model_desc &m = c->m;
@@ -625,8 +708,10 @@ int32_t prefill_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, c
     bf16_t *kp = (bf16_t *)c->pool.k_pool + (size_t)layer * c->pool.layer_stride;
     bf16_t *vp = (bf16_t *)c->pool.v_pool + (size_t)layer * c->pool.layer_stride;
 
+    if (streams(c, layer, T)) return stream_layer(c, RS_SIDE_PREFILL, w, layer, x_in, x_out, T, seq, tables, max_blk, 0, nullptr, nullptr, 0, 0);
     tick(c, RS_SIDE_PREFILL, 0);
     c->last_rows[RS_SIDE_PREFILL] = T;
+    c->streamed[RS_SIDE_PREFILL] = false;
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, T, d, m.rms_eps);
     tick(c, RS_SIDE_PREFILL, 1);
     // a pass of at most 64 rows is bound by reading the weights once: it takes the weight-streaming kernels
@@ -695,8 +780,11 @@ int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, co
     int32_t *err = c->err_flag + RS_SIDE_PREFILL;
     const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
 
+    if (streams(c, layer, M))
+        return stream_layer(c, RS_SIDE_PREFILL, w, layer, x_in, x_out, T, seq, ptables, max_blk_p, B, ctx_lens, dtables, max_blk_d, max_ctx);
     tick(c, RS_SIDE_PREFILL, 0);
     c->last_rows[RS_SIDE_PREFILL] = M;
+    c->streamed[RS_SIDE_PREFILL] = false;
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, M, d, m.rms_eps);
     tick(c, RS_SIDE_PREFILL, 1);
     const bool skinny = M <= 64;
@@ -749,58 +837,13 @@ int32_t decode_layer(rs_ctx *c, Workspace &w, int32_t layer, const void *x_in, v
     const int d = m.d_model, hd = m.head_dim, qd = m.n_q_heads * hd, nqkv = qd + 2 * m.n_kv_heads * hd;
     bf16_t *kp = (bf16_t *)c->pool.k_pool + (size_t)layer * c->pool.layer_stride;
     bf16_t *vp = (bf16_t *)c->pool.v_pool + (size_t)layer * c->pool.layer_stride;
+    if (streams(c, layer, B)) {
+        const SeqInfo none{};
+        return stream_layer(c, RS_SIDE_DECODE, w, layer, x_in, x_out, 0, none, nullptr, 0, B, ctx_lens, tables, max_blk, max_ctx);
+    }
     const bool skinny = B <= 64;
     c->last_rows[RS_SIDE_DECODE] = B;
-    c->decode_fused = skinny && c->moe[layer].E == 0 && fused_decode_applies(c);
-    if (c->decode_fused) {
-        // At most 64 rows: every projection is a stream of its weights with the RMSNorm of its input folded in
-        // (decode_gemm.hip).  9 launches: QKV stream, its epilogue (row scale, rotary, cache append), attention,
-        // chunk merge, O stream + residual, gate/up stream with SwiGLU, down stream + residual.
-        const rs_ctx::PackedLayer &pl = c->packed[layer];
-        const int f = m.ffn_dim;
-        float *ssq1 = w.ssq, *ssq2 = w.ssq + 64 * RS_SSQ_ROWS;
-        const int dcus = c->side[RS_SIDE_DECODE].cus;
-        tick(c, RS_SIDE_DECODE, 0);
-        tick(c, RS_SIDE_DECODE, 1);
-        auto stream = [&](const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &f = DFuseArgs{}) {
-            launch_dgemm_stream(st, a, p, f, dgemm_prefers_half_height(p, dcus));
-        };
-        const DGemmPlan pq = dgemm_plan(nqkv, d, false);
-        stream(DGemmArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, ssq1, pl.wqkv, nullptr, w.partials, B, nqkv, d}, pq);
-        launch_qkv_rope_epilogue(st, QkvEpiArgs{w.partials, ssq1, pq.S, pq.Nv, d, m.rms_eps, w.qkv, c->rope, kp, vp, tables, ctx_lens,
-                                                c->err_flag + RS_SIDE_DECODE, B, m.n_q_heads, m.n_kv_heads, hd, max_blk,
-                                                c->pool.n_blocks, m.max_pos});
-        tick(c, RS_SIDE_DECODE, 2);
-        tick(c, RS_SIDE_DECODE, 3);
-        DecodeAttnArgs da{w.qkv, nqkv, w.attn, kp, vp, tables, ctx_lens, c->err_flag + RS_SIDE_DECODE, w.part_o, w.part_ml,
-                          B, m.n_q_heads, m.n_kv_heads, hd, max_blk, c->pool.n_blocks, max_ctx,
-                          (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK,
-                          (float)(1.4426950408889634 / std::sqrt((double)hd)), c->side[RS_SIDE_DECODE].cus < RS_TOTAL_CUS};
-        launch_decode_attention(st, da);
-        tick(c, RS_SIDE_DECODE, 4);
-        const DGemmPlan po = dgemm_plan(d, qd, false);
-        stream(DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, B, d, qd}, po);
-        // x1 = x + attn Wo, and with it the gate/up projection's operand: x1 . g2 (packed) and the rows' sums of squares
-        launch_dgemm_epilogue(st, DEpiArgs{w.partials, po.S, po.Nv, (const bf16_t *)x_in, w.x1, B, d, (const bf16_t *)lw.g2, w.h, ssq2});
-        tick(c, RS_SIDE_DECODE, 5);
-        tick(c, RS_SIDE_DECODE, 6);
-        stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wg, pl.wu, nullptr, B, f, d}, dgemm_plan(f, d, true),
-               DFuseArgs{ssq2, (d + 1023) / 1024, m.rms_eps, w.act});
-        tick(c, RS_SIDE_DECODE, 7);
-        if (dgemm_applies(d, f)) {
-            const DGemmPlan pd = dgemm_plan(d, f, false);
-            stream(DGemmArgs{w.act, nullptr, nullptr, nullptr, pl.wd, nullptr, w.partials, B, d, f}, pd);
-            launch_dgemm_epilogue(st, DEpiArgs{w.partials, pd.S, pd.Nv, w.x1, (bf16_t *)x_out, B, d});
-        } else {
-            GemmArgs gd{w.act, (const bf16_t *)lw.wd, nullptr, pl.wd, nullptr, w.x1, (bf16_t *)x_out, B, d, f, EPI_RESIDUAL,
-                        0, c->side[RS_SIDE_DECODE].cus, w.partials, w.partial_cap};
-            launch_gemm_skinny(st, gd, w.partials);
-        }
-        tick(c, RS_SIDE_DECODE, 8);
-        HIP_TRY(hipGetLastError());
-        return RS_OK;
-    }
-
+    c->streamed[RS_SIDE_DECODE] = false;
     tick(c, RS_SIDE_DECODE, 0);
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, B, d, m.rms_eps);
     tick(c, RS_SIDE_DECODE, 1);
@@ -1546,8 +1589,8 @@ int32_t rs_debug_read_workspace(rs_ctx *c, int32_t side, int32_t which, void *ho
     size_t cap = 0;
     switch (which) {
         case 0:
-            if (side == RS_SIDE_DECODE && c->decode_fused)
-                return fail(RS_ERR_STATE, "this decode step folded its RMSNorms into the projections: no normalised rows were written");
+            if (c->streamed[side])
+                return fail(RS_ERR_STATE, "this pass folded its RMSNorms into the projections: no normalised rows were written");
             src = w.h; cap = (size_t)w.rows * m.d_model * 2; break;  // (decode buffers are at least 64 rows)
         case 1: src = w.qkv; cap = (size_t)w.rows * nqkv * 2; break;
         case 2: src = w.attn; cap = (size_t)w.rows * qd * 2; break;

@@ -7,7 +7,7 @@ import torch
 import paper_2601_11822_amd as rs
 import rs_synth as S
 from oracle import lm
-from tests.gpu_util import Rig, check_tensor, to_dev
+from tests.gpu_util import END_TO_END, Rig, check_cache_against_oracle, check_tensor, to_dev
 
 pytestmark = pytest.mark.gpu
 f32 = S.bf16_bits_to_f32
@@ -40,5 +40,47 @@ def test_head_logits_and_choice(shape, vocab, n):
         check_tensor("logits", got, lm.head_logits(f32(x_bits), hb["final_norm"], lm_head, shape.rms_eps))
         assert np.array_equal(tok, np.argmax(got, axis=1)) and tok[row] == 7
         assert torch.equal(out, out2)
+    finally:
+        rig.close()
+
+
+# the weight-streaming pass at the edges of its 32-row tiles (one to four of them), its largest pass and the first one
+# beyond; prompt rows, decode rows and both
+@pytest.mark.parametrize("shape", [S.WIDE, S.TINY])
+@pytest.mark.parametrize("lens,starts,ctx", [([31], [0], []), ([1, 32], [0, 0], []), ([64], [16], [7]), ([40, 25], [0, 32], []),
+                                             ([5], [0], [0, 15, 16] + list(range(1, 93))), ([128], [0], []), ([100], [48], list(range(3, 31))),
+                                             ([], [], list(range(0, 128))), ([129], [0], [])])
+def test_streamed_pass(shape, lens, starts, ctx):
+    orc_sent = np.float32(-777.0)
+    B, T = len(ctx), sum(lens)
+    held = [s + n for s, n in zip(starts, lens)] + [c + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 4
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=9)
+    ptab, dtab = tabs[:len(lens)], tabs[len(lens):]
+    rig = Rig(shape, n_blocks, max(T + B, sum(starts), sum(ctx), 1), max(B, 1), max(max(held), 2))
+    try:
+        L = rig.olayers[0]
+        Kc, Vc = L.new_cache(n_blocks, fill=orc_sent)
+        for tab, before, stream in ((ptab, starts, 60), (dtab, ctx, 61)):     # what is cached before the pass
+            keep = [i for i, n in enumerate(before) if n > 0]
+            for at in range(0, len(keep), rs.RS_MAX_PREFILL_REQS):
+                part = keep[at:at + rs.RS_MAX_PREFILL_REQS]
+                cu = np.concatenate([[0], np.cumsum([before[i] for i in part])]).astype(np.int32)
+                xb = S.hidden_states(int(cu[-1]), shape.d_model, stream=stream + 10 * at)
+                rig.prefill(xb, cu, tab[part])
+                L.prefill(f32(xb), cu, tab[part], Kc, Vc)
+        xb = S.hidden_states(T + B, shape.d_model, stream=62)
+        x, cu = f32(xb), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        if not lens:
+            y_bits = rig.decode(xb, np.asarray(ctx, np.int32), dtab)
+        elif not B and not any(starts):
+            y_bits = rig.prefill(xb, cu, ptab)
+        else:
+            y_bits = rig.hybrid(xb, cu, starts, ptab, np.asarray(ctx, np.int32) if B else None, dtab if B else None)
+        if lens:
+            check_tensor("prompt rows", f32(y_bits)[:T], L.prefill_chunk(x[:T], cu, starts, ptab, Kc, Vc), x[:T], 2, elem_mult=END_TO_END)
+        if B:
+            check_tensor("decode rows", f32(y_bits)[T:], L.decode(x[T:], np.asarray(ctx, np.int32), dtab, Kc, Vc), x[T:], 2, elem_mult=END_TO_END)
+        check_cache_against_oracle(rig, Kc, Vc, orc_sent)
     finally:
         rig.close()
