@@ -75,9 +75,9 @@ struct GemmArgs {
     // float32 scratch for launch_gemm_tiled's K-sliced path (few tiles, long K); without it that path is not taken
     float *partials = nullptr;
     size_t partial_cap = 0;   // elements
-    // grouped form (launch_gemm_grouped): the expert whose weights each 128-row tile multiplies (-1: skip the
-    // tile), and the distance in elements between consecutive experts' packed matrices (Wp and Wp2 alike)
-    const int32_t *tile_expert = nullptr;
+    // grouped form (launch_gemm_grouped): the work list, and the distance in elements between consecutive experts'
+    // packed matrices (Wp and Wp2 alike)
+    const int32_t *units = nullptr;
     size_t expert_stride = 0;
 };
 // Upper bound of what the K-sliced path of launch_gemm_tiled needs, for any M: S * M * N <= this.
@@ -172,15 +172,14 @@ struct QkvEpiArgs {
 void launch_qkv_rope_epilogue(hipStream_t st, const QkvEpiArgs &a);
 void decode_gemm_kernels_init();
 
-// Grouped GEMM over 128-row tiles that each belong to one expert: STORE or SWIGLU epilogue, a.M = the padded
-// row capacity (a multiple of 128), a.expert_stride and a.tile_expert set, the latter followed by the work list
-// that moe_plan_kernel writes behind the a.M / 128 tile entries.  Needs K % 32 == 0 and N >= 1024.
+// Grouped GEMM over tiles that each belong to one expert: STORE or SWIGLU epilogue, a.M = the padded row capacity (a
+// multiple of 128), a.expert_stride set and a.units the work list that moe_plan_kernel writes.  Needs K % 32 == 0 and
+// N >= 1024.
 bool launch_gemm_grouped(hipStream_t st, const GemmArgs &a);
 
 #define RS_MOE_MAX_EXPERTS 16
-// Rows of the grouped (expert-major) layout that M rows with two experts each can need: every expert's segment
-// is padded to whole 128-row tiles, and a segment of two or more tiles may be preceded by one idle tile so that
-// it starts on a 256-row boundary.
+// Rows of the grouped (expert-major) layout that M rows with two experts each can need: an expert's segment is less than
+// 256 rows longer than its rows.
 static inline int moe_row_cap(int M, int E) { return ((2 * M + 255 * E + 127) / 128) * 128; }
 struct MoeArgs {
     const bf16_t *h;        // normalised rows, fragment-packed with packed_mt(M) row tiles
@@ -189,7 +188,7 @@ struct MoeArgs {
     float *wt;              // [M][2] their weights
     int32_t *pos;           // [M][2] grouped row of each assignment
     int32_t *src;           // [Mg_cap] source row of each grouped row, -1 for padding
-    int32_t *tile_expert;   // [2 * (Mg_cap / 128) + 1]: expert of each tile, then the grouped GEMM's work list
+    int32_t *units;         // [2 + Mg_cap / 128]: units, rows in use, first row / 64 << 8 | height / 64 << 5 | expert of each
     bf16_t *a_g;            // gathered rows, fragment-packed with Mg_cap / 32 row tiles
     const bf16_t *out_g;    // [Mg_cap][d] expert outputs, row-major
     const bf16_t *x1;       // [M][d]

@@ -1,6 +1,6 @@
 // Sparse (mixture-of-experts) feed-forward block around the grouped form of the large-tile GEMM:
 // route each row to its two experts, lay the (row, expert) assignments out expert by expert in
-// whole 128-row tiles, gather the normalised rows into that order, run gate/up and down once over
+// whole tiles, gather the normalised rows into that order, run gate/up and down once over
 // all tiles (each tile reads its own expert's weights), and add the two weighted results back.
 #include "kernels.h"
 
@@ -65,9 +65,9 @@ __global__ __launch_bounds__(1024) void moe_router_kernel(MoeArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Plan (one workgroup): per-expert counts, each expert's segment padded to whole 128-row tiles (a
-// segment of two or more tiles starts on a 256-row boundary, after an idle tile if need be, so that
-// the grouped GEMM can take its tiles in pairs), the expert of every tile (-1 for a tile not in use), the source row of every grouped row
+// Plan (one workgroup): per-expert counts, each expert's segment in whole tiles (of one height per expert: as few tiles of
+// at most 256 rows as hold it, each no higher than needed, in steps of 64 rows and at least 128), the grouped GEMM's work
+// list (units, rows in use, then per unit its first row / 64, height / 64 and expert), the source row of every grouped row
 // (-1 for padding) and the grouped position of every assignment.  The order of rows inside a
 // segment is arbitrary (an atomic cursor): a row's result does not depend on where it sits.
 // ---------------------------------------------------------------------------------------------
@@ -80,28 +80,14 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoeArgs a) {
     for (int i = tid; i < a.Mg_cap; i += 1024) a.src[i] = -1;
     __syncthreads();
     if (tid == 0) {
-        int t = 0;
+        int row = 0, nu = 0;
         for (int e = 0; e < a.E; ++e) {
-            const int nt = (cnt[e] + 127) >> 7;
-            if (nt >= 2 && (t & 1)) a.tile_expert[t++] = -1;   // longer segments start on a 256-row boundary
-            off[e] = t * 128;
-            for (int j = 0; j < nt; ++j) a.tile_expert[t + j] = e;
-            t += nt;
+            const int k = (cnt[e] + 255) >> 8, h64 = k ? max(2, (cnt[e] + 64 * k - 1) / (64 * k)) : 0;
+            off[e] = row;
+            for (int j = 0; j < k; ++j, row += 64 * h64) a.units[2 + nu++] = (row >> 6) << 8 | h64 << 5 | e;
         }
-        const int n128 = a.Mg_cap / 128;
-        for (int j = t; j < n128; ++j) a.tile_expert[j] = -1;
-        // the grouped GEMM's work list, behind the tile table: aligned pairs of one expert, else single tiles
-        int32_t *units = a.tile_expert + n128;
-        int nu = 0;
-        for (int e = 0, j = 0; e < a.E; ++e) {
-            const int nt = (cnt[e] + 127) >> 7;
-            if (nt >= 2 && (j & 1)) ++j;
-            int k = 0;
-            for (; k + 2 <= nt && !((j + k) & 1); k += 2) units[1 + nu++] = 2 * (j + k) + 1;
-            for (; k < nt; ++k) units[1 + nu++] = 2 * (j + k);
-            j += nt;
-        }
-        units[0] = nu;
+        a.units[0] = nu;
+        a.units[1] = row;
     }
     __syncthreads();
     for (int i = tid; i < 2 * a.M; i += 1024) {
@@ -119,7 +105,7 @@ __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
     if (idx >= (long)a.Mg_cap * chunks) return;
     // consecutive threads take consecutive rows of one k chunk: whole 128-byte lines on the writing side
     const int g = (int)(idx % a.Mg_cap), c = (int)(idx / a.Mg_cap);
-    if (a.tile_expert[g >> 7] < 0) return;   // tile not in use: the GEMMs skip it too
+    if (g >= a.units[1]) return;   // past the last tile in use
     const int s = a.src[g];
     const bf16x8 v = s >= 0 ? ld_bf16x8(a.h + packed_offset(s, c * 8, packed_mt(a.M))) : zero_bf16x8();
     st_bf16x8(a.a_g + packed_offset(g, c * 8, a.Mg_cap >> 5), v);

@@ -56,7 +56,7 @@ struct Workspace {
     size_t partial_cap = 0;
     int rows = 0;
     // sparse feed-forward block (allocated by the first rs_set_moe_weights)
-    int32_t *m_sel = nullptr, *m_pos = nullptr, *m_src = nullptr, *m_tile = nullptr;
+    int32_t *m_sel = nullptr, *m_pos = nullptr, *m_src = nullptr, *m_units = nullptr;
     float *m_wt = nullptr;
     bf16_t *m_a = nullptr, *m_act = nullptr, *m_out = nullptr;
     int m_cap = 0;   // grouped row capacity (a multiple of 128)
@@ -431,7 +431,7 @@ size_t carve_decode_ws(const rs_ctx *c, Workspace &w, unsigned char *base, int r
 
 void free_ws(Workspace &w) {
     void *ptrs[] = {w.h, w.qkv, w.attn, w.x1, w.act, w.xbuf, w.partials, w.part_o, w.part_ml, w.ssq,
-                    w.m_sel, w.m_pos, w.m_src, w.m_tile, w.m_wt, w.m_a, w.m_act, w.m_out};
+                    w.m_sel, w.m_pos, w.m_src, w.m_units, w.m_wt, w.m_a, w.m_act, w.m_out};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     w = Workspace{};
@@ -576,15 +576,15 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     if (ml.E > 0) {
         // sparse block: route, gather expert by expert, two grouped GEMMs over all tiles, weighted sum
         const int cap = std::min(w.m_cap, moe_row_cap(M, ml.E));
-        MoeArgs ma{w.h, ml.router, w.m_sel, w.m_wt, w.m_pos, w.m_src, w.m_tile, w.m_a, w.m_out, w.x1, y, M, d, ml.E, cap};
+        MoeArgs ma{w.h, ml.router, w.m_sel, w.m_wt, w.m_pos, w.m_src, w.m_units, w.m_a, w.m_out, w.x1, y, M, d, ml.E, cap};
         launch_moe_route_and_gather(st, ma);
         GemmArgs gu{w.m_a, nullptr, nullptr, ml.wg, ml.wu, nullptr, w.m_act, cap, f, d, EPI_SWIGLU, 1, c->side[side].cus};
-        gu.tile_expert = w.m_tile;
+        gu.units = w.m_units;
         gu.expert_stride = ml.stride_gu;
         bool ok = launch_gemm_grouped(st, gu);
         tick(c, side, 7);
         GemmArgs gd{w.m_act, nullptr, nullptr, ml.wd, nullptr, nullptr, w.m_out, cap, d, f, EPI_STORE, 0, c->side[side].cus};
-        gd.tile_expert = w.m_tile;
+        gd.units = w.m_units;
         gd.expert_stride = ml.stride_d;
         ok = launch_gemm_grouped(st, gd) && ok;
         launch_moe_combine(st, ma);
@@ -1203,7 +1203,7 @@ int32_t rs_set_moe_weights(rs_ctx *c, int32_t layer, const rs_moe_weights *w) {
             HIP_TRY(hipMalloc((void **)&ws.m_pos, (size_t)ws.rows * 2 * sizeof(int32_t)));
             HIP_TRY(hipMalloc((void **)&ws.m_wt, (size_t)ws.rows * 2 * sizeof(float)));
             HIP_TRY(hipMalloc((void **)&ws.m_src, (size_t)cap * sizeof(int32_t)));
-            HIP_TRY(hipMalloc((void **)&ws.m_tile, (size_t)(2 * (cap / 128) + 1) * sizeof(int32_t)));   // tile table + work list
+            HIP_TRY(hipMalloc((void **)&ws.m_units, (size_t)(2 + cap / 128) * sizeof(int32_t)));
             HIP_TRY(hipMalloc((void **)&ws.m_a, (size_t)cap * d * sizeof(bf16_t)));
             HIP_TRY(hipMalloc((void **)&ws.m_act, (size_t)cap * f * sizeof(bf16_t)));
             HIP_TRY(hipMalloc((void **)&ws.m_out, (size_t)cap * d * sizeof(bf16_t)));

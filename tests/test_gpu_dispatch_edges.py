@@ -4,10 +4,12 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2601_11822_amd as rs
 import rs_synth as S
-from oracle import lm
-from tests.gpu_util import END_TO_END, Rig, check_cache_against_oracle, check_tensor, to_dev
+from oracle import lm, moe
+from tests.gpu_util import END_TO_END, TOL, Rig, check_cache_against_oracle, check_tensor, to_dev
+from tests.test_gpu_moe import _moe_rig
 
 pytestmark = pytest.mark.gpu
 f32 = S.bf16_bits_to_f32
@@ -82,5 +84,27 @@ def test_streamed_pass(shape, lens, starts, ctx):
         if B:
             check_tensor("decode rows", f32(y_bits)[T:], L.decode(x[T:], np.asarray(ctx, np.int32), dtab, Kc, Vc), x[T:], 2, elem_mult=END_TO_END)
         check_cache_against_oracle(rig, Kc, Vc, orc_sent)
+    finally:
+        rig.close()
+
+
+# the sparse block's tiles: with two experts every row goes to both, so an expert has exactly `n` rows: each height of
+# tile (128, 192, 256 rows) at its edges, one tile an expert and several; 32 rows a router workgroup
+@pytest.mark.parametrize("n", [1, 32, 33, 128, 129, 192, 193, 256, 257, 384, 385, 513, 577])
+def test_sparse_block_tiles(n):
+    rig, mw, L = _moe_rig(S.WIDE, 2, S.blocks_for(n) + 2, n, 1, n + 1)
+    try:
+        tabs = S.shuffled_block_tables([n], S.blocks_for(n) + 2, stream=23)
+        xb, cu = S.hidden_states(n, S.WIDE.d_model, stream=23), np.array([0, n], np.int32)
+        y_bits = rig.prefill(xb, cu, tabs)
+        Kc, Vc = L.new_cache(S.blocks_for(n) + 2)
+        x = f32(xb)
+        _, x1_ref, _, _ = L.prefill(x, cu, tabs, Kc, Vc)
+        sel, wt_got = rig.ctx.debug_read_moe_routing(rs.RS_SIDE_PREFILL, n)
+        lg = moe.router_logits(oracle.rmsnorm(x1_ref, L.g2, S.WIDE.rms_eps), mw["router"]).astype(np.float64)
+        wt = (1.0 / (1.0 + np.exp(lg[:, ::-1] - lg)))[np.arange(n)[:, None], sel]
+        assert np.all(np.sort(sel, axis=1) == [0, 1]) and np.abs(wt_got - wt).max() <= TOL
+        y_ref, _, _, _ = L.prefill(x, cu, tabs, Kc, Vc, sel=sel, wt=wt.astype(np.float32))
+        check_tensor("y", f32(y_bits), y_ref, x, 2, elem_mult=END_TO_END)
     finally:
         rig.close()
