@@ -251,10 +251,21 @@ __global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a) {
     }
 }
 
-// Merges the per-chunk partial results of one (request, query head) in chunk order.
+// Merges the per-chunk partial results of one (request, query head).  Bound by memory round trips: the maxima and sums of
+// 64 chunks are read by a lane each, beside the context length; a quarter of the threads each takes every fourth chunk's
+// outputs, 16 bytes a thread, eight chunks requested together, and the quarters are added in order.  With one thread per
+// column and one chunk after the other: 23 us for 32 contexts of up to 32K tokens (8B shape), 6.5 now; 101 of up to
+// 8K (70B shape) 14, 9.5 now; 64 of up to 4K 5.3, 4.9 now.
 template <int HD>
 __global__ __launch_bounds__(HD) void decode_combine_kernel(DecodeAttnArgs a) {
-    const int hq = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
+    constexpr int Q = HD / 4;   // threads of a quarter
+    __shared__ float s_e[64];
+    __shared__ f32x4 s_acc[4 * Q];
+    const int hq = blockIdx.x, b = blockIdx.y, d = threadIdx.x, lane = d & 63, quarter = d / Q;
+    const size_t p0 = ((size_t)b * a.Hq + hq) * a.n_chunks;
+    const float2 *ml = (const float2 *)a.part_ml + p0;
+    const f32x4 *po = (const f32x4 *)(a.part_o + p0 * HD) + d % Q;
+    float2 mine = ml[min(lane, a.n_chunks - 1)];   // looked at only if the chunk is one of this context's
     int n_keys = a.ctx_lens[b] + 1;
     const int col = hq * HD + d;
     bf16_t *op = a.out + packed_offset(a.out_row0 + b, col, a.out_Mt ? a.out_Mt : packed_mt(a.B)) + (col & 7);   // feeds the output projection
@@ -264,17 +275,47 @@ __global__ __launch_bounds__(HD) void decode_combine_kernel(DecodeAttnArgs a) {
     }
     if (n_keys > a.max_ctx) n_keys = a.max_ctx;
     const int nch = (n_keys + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
-    const size_t p0 = ((size_t)b * a.Hq + hq) * a.n_chunks;
-    float mx = NEG_INF;
-    for (int c = 0; c < nch; ++c) mx = fmaxf(mx, a.part_ml[(p0 + c) * 2]);
-    const float ms = (mx == NEG_INF) ? 0.f : mx;
-    float acc = 0.f, l = 0.f;
-    for (int c = 0; c < nch; ++c) {
-        const float e = exp2f((a.part_ml[(p0 + c) * 2] - ms) * a.scale_log2);   // maxima are raw scores
-        acc += a.part_o[(p0 + c) * HD + d] * e;
-        l += a.part_ml[(p0 + c) * 2 + 1] * e;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float mx = NEG_INF, l = 0.f;
+    for (int c0 = 64; c0 < nch; c0 += 64) mx = fmaxf(mx, c0 + lane < nch ? ml[c0 + lane].x : NEG_INF);
+    for (int c0 = 0; c0 < nch; c0 += 64) {
+        const int nc = min(64, nch - c0);
+        f32x4 v[8];
+        auto request = [&](int first) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (first - quarter + 4 * j < nc) v[j] = po[(size_t)(c0 + min(first + 4 * j, nc - 1)) * Q];   // (uniform)
+        };
+        auto add = [&](int first) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (first + 4 * j < nc) acc += v[j] * s_e[first + 4 * j];
+        };
+        request(quarter);
+        if (c0 == 0) {
+            mx = fmaxf(mx, lane < nch ? mine.x : NEG_INF);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        } else {
+            mine = ml[c0 + min(lane, nc - 1)];
+            __syncthreads();   // s_e of the 64 chunks before has been read
+        }
+        const float e = lane < nc ? exp2f((mine.x - (mx == NEG_INF ? 0.f : mx)) * a.scale_log2) : 0.f;   // maxima are raw scores
+        l += lane < nc ? mine.y * e : 0.f;
+        if (d < 64) s_e[lane] = e;
+        __syncthreads();
+        add(quarter);
+        if (nc > 32) {
+            request(32 + quarter);
+            add(32 + quarter);
+        }
     }
-    *op = (bf16_t)(l > 0.f ? acc / l : 0.f);
+    l = wave_sum(l);
+    s_acc[d] = acc;
+    __syncthreads();
+    const float *col_sums = (const float *)s_acc + d;
+    const float sum = (col_sums[0] + col_sums[HD]) + (col_sums[2 * HD] + col_sums[3 * HD]);
+    *op = (bf16_t)(l > 0.f ? sum / l : 0.f);
 }
 
 void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {

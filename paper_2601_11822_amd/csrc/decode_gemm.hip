@@ -32,11 +32,44 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // ten more vector instructions per element of a 256x256 epilogue, for digits far below the bf16 the result is rounded to
 __device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 
-// The RMSNorm scale of row m from the sums of squares of its parts, added in order.
-__device__ __forceinline__ float row_scale(const float *ssq_part, int S_ssq, int m, int d, float eps) {
-    float t = 0.f;
-    for (int s = 0; s < S_ssq; ++s) t += ssq_part[s * RS_SSQ_ROWS + m];
-    return 1.0f / sqrtf(t / (float)d + eps);
+// The RMSNorm scale of row m from the sums of squares of its parts, added in order.  The first SSQ_BATCH parts (all of them
+// up to a width of 8192) are requested together, wherever the caller has something to do meanwhile, and added later.
+#define SSQ_BATCH 8
+struct RowSsq {
+    float v[SSQ_BATCH];
+    __device__ __forceinline__ void request(const float *ssq_part, int S_ssq, int m) {
+#pragma unroll
+        for (int s = 0; s < SSQ_BATCH; ++s) v[s] = ssq_part[min(s, S_ssq - 1) * RS_SSQ_ROWS + m];
+    }
+    __device__ __forceinline__ float scale(const float *ssq_part, int S_ssq, int m, int d, float eps) const {
+        float t = 0.f;
+#pragma unroll
+        for (int s = 0; s < SSQ_BATCH; ++s)
+            if (s < S_ssq) t += v[s];
+        for (int s = SSQ_BATCH; s < S_ssq; ++s) t += ssq_part[s * RS_SSQ_ROWS + m];
+        return 1.0f / sqrtf(t / (float)d + eps);
+    }
+};
+
+// Sum over the K slices, in slice order, of NV 4-float columns at p[0], p[off], ...; slices are requested SB at a time (one
+// after the other they are a chain of memory round trips, which is all that bounds the small kernels here: a layer of one
+// decode row 103.5 -> 97 us with this, RowSsq and decode_combine_kernel's batches).
+template <int SB, int NV>
+__device__ __forceinline__ void sum_slices(const float *p, int off, size_t stride, int S, f32x4 (&acc)[NV]) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < S; s0 += SB) {
+        f32x4 v[SB][NV];
+#pragma unroll
+        for (int s = 0; s < SB; ++s)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) v[s][i] = *(const f32x4 *)(p + (size_t)min(s0 + s, S - 1) * stride + i * off);
+#pragma unroll
+        for (int s = 0; s < SB; ++s)
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+                if (s0 + s < S) acc[i] += v[s][i];
+    }
 }
 
 #define DS_INLINE_PIECES 12
@@ -146,10 +179,10 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs 
             *(bf16x8 *)&dst_slab[(((k8 >> 1) * MT + (m >> 5)) * 64 + (k8 & 1) * 32 + (m & 31)) * 8] = hv;
         }
     };
-    float sc[MT];   // FUSED: RMSNorm scales of this lane's rows
+    RowSsq rs[MT];   // FUSED: what this lane's rows' RMSNorm scales are made of
     if (FUSED) {
 #pragma unroll
-        for (int tm = 0; tm < MT; ++tm) sc[tm] = row_scale(fz.ssq_part, fz.S_ssq, 32 * tm + c32, K, fz.eps);
+        for (int tm = 0; tm < MT; ++tm) rs[tm].request(fz.ssq_part, fz.S_ssq, 32 * tm + c32);
     }
     float gf[8];
     auto gains = [&](bf16x8 g) {
@@ -172,6 +205,11 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs 
     };
 #pragma unroll
     for (int p = 0; p < PD; ++p) load_w(p, p);
+    float sc[MT];
+    if (FUSED) {
+#pragma unroll
+        for (int tm = 0; tm < MT; ++tm) sc[tm] = rs[tm].scale(fz.ssq_part, fz.S_ssq, 32 * tm + c32, K, fz.eps);
+    }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     for (int c = 0; c < nchunks; ++c) {
@@ -367,20 +405,21 @@ void launch_dgemm_stream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &p,
 // ---------------------------------------------------------------------------------------------
 // out = resid + sum, row-major; one thread per 4 columns, one workgroup per 1024 columns of a row.  With a gain (the
 // next RMSNorm's) also out . gain, fragment-packed, and the sum of squares of the workgroup's part of the row.
+template <int SB>
 __global__ __launch_bounds__(256) void dgemm_epilogue_kernel(DEpiArgs a) {
     const int M = a.M, N = a.N;
     const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
     float ss = 0.f;
     if (n < N) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < a.S; ++s) acc += *(const f32x4 *)(a.part + ((size_t)s * M + m) * a.Nv + n);
         const bf16x4 r = *(const bf16x4 *)(a.resid + (size_t)m * N + n);
+        const bf16x4 g = *(const bf16x4 *)((a.gain ? a.gain : a.resid) + n);
+        f32x4 acc[1];
+        sum_slices<SB, 1>(a.part + (size_t)m * a.Nv + n, 0, (size_t)M * a.Nv, a.S, acc);
         bf16x4 v;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(acc[i] + (float)r[i]);
+        for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(acc[0][i] + (float)r[i]);
         *(bf16x4 *)(a.out + (size_t)m * N + n) = v;
         if (a.gain) {
-            const bf16x4 g = *(const bf16x4 *)(a.gain + n);
             bf16x4 w;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -434,7 +473,9 @@ void launch_gain_pack(hipStream_t st, const bf16_t *x, const bf16_t *gain, bf16_
 bool dgemm_gains_inline(int M, const DGemmPlan &p) { return (p.kb_per_wg / DS_CH) * ((M + 31) / 32) <= DS_INLINE_PIECES; }
 
 void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a) {
-    hipLaunchKernelGGL(dgemm_epilogue_kernel, dim3((a.N + 1023) / 1024, a.M), dim3(256), 0, st, a);
+    const dim3 grid((a.N + 1023) / 1024, a.M);
+    if (a.S <= 4) hipLaunchKernelGGL(dgemm_epilogue_kernel<4>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(dgemm_epilogue_kernel<8>, grid, dim3(256), 0, st, a);
 }
 
 // QKV epilogue: sums the K slices, applies the first RMSNorm's row scale, rotates q and k at the row's position
@@ -468,24 +509,27 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
     }
     const bool pos_ok = pos >= 0 && pos < a.max_pos;
     if (!pos_ok && tid == 0 && blockIdx.y == 0) atomicOr(a.err_flag, 1);
-    f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < a.S; ++s) {
-        const float *p = a.part + ((size_t)s * a.M + m) * a.Nv + head * HD + i0;
-        lo += *(const f32x4 *)p;
-        hi += *(const f32x4 *)(p + half);
-    }
-    const float sc = row_scale(a.ssq_part, a.S_ssq, m, a.d, a.eps);
-    lo *= sc;
-    hi *= sc;
+    // everything that depends on the position alone is requested before the sums are waited for
+    const int bi = pos_ok ? pos / RS_BLOCK_TOKENS : 0, slot = pos % RS_BLOCK_TOKENS;
+    int blk = -1;
+    if (head >= a.Hq && bi < max_blk) blk = tab_row[bi];
+    const f32x4 *tab = (const f32x4 *)(a.table + (size_t)(pos_ok ? pos : 0) * half + i0);
+    const f32x4 cs01 = tab[0], cs23 = tab[1];
+    RowSsq rs;
+    rs.request(a.ssq_part, a.S_ssq, m);
+    f32x4 sum[2];
+    sum_slices<4, 2>(a.part + (size_t)m * a.Nv + head * HD + i0, half, (size_t)a.M * a.Nv, a.S, sum);
+    const float sc = rs.scale(a.ssq_part, a.S_ssq, m, a.d, a.eps);
+    const f32x4 lo = sum[0] * sc, hi = sum[1] * sc;
     bf16x4 olo, ohi;
     if (head < a.Hq + a.Hkv) {
         if (!pos_ok) return;
-        const CosSin *tab = a.table + (size_t)pos * half + i0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const CosSin cs = tab[i];
-            olo[i] = (bf16_t)(lo[i] * cs.c - hi[i] * cs.s);
-            ohi[i] = (bf16_t)(hi[i] * cs.c + lo[i] * cs.s);
+            const f32x4 &t = i < 2 ? cs01 : cs23;
+            const float cc = t[2 * (i & 1)], ss = t[2 * (i & 1) + 1];
+            olo[i] = (bf16_t)(lo[i] * cc - hi[i] * ss);
+            ohi[i] = (bf16_t)(hi[i] * cc + lo[i] * ss);
         }
     } else {
 #pragma unroll
@@ -498,9 +542,6 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
     *(bf16x4 *)(row + i0) = olo;
     *(bf16x4 *)(row + half + i0) = ohi;
     if (head < a.Hq || !pos_ok) return;
-    const int bi = pos / RS_BLOCK_TOKENS, slot = pos % RS_BLOCK_TOKENS;
-    int blk = -1;
-    if (bi < max_blk) blk = tab_row[bi];
     if ((unsigned)blk >= (unsigned)a.n_blocks) {
         if (tid % TPH == 0 && head == a.Hq) atomicOr(a.err_flag, 2);
         return;
