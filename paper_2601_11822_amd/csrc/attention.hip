@@ -47,22 +47,14 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // one block, exactly the contraction slice k' = 8h..8h+7 that lane supplies to the 16x16x32 P V
 // product, and the matching V fragment V[block h>>1][d][8(h&1)..+8] is one 16-byte load.
 // =============================================================================================
+static __host__ __device__ inline int decode_attn_lds_floats(int hd, int G) { return 4 * hd * G + 8 * G; }   // <= 33 KB at G = 16
+
+// One (kv head, request, chunk), by 256 threads; smem_dec: [4][HD][G] partial outputs, then [4][G] max, [4][G] sum
 template <int HD>
-__global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a) {
+__device__ __forceinline__ void decode_attn_chunk(const DecodeAttnArgs &a, const int hk, const int b, const int chunk, const int tid, float *smem_dec) {
     constexpr int KS = HD / 32;  // 16x16x32 steps over head_dim for S^T
     constexpr int DT = HD / 16;  // 16-row tiles of O^T
-    extern __shared__ float smem_dec[];   // [4][HD][G] partial outputs, then [4][G] max, [4][G] sum
-
-    // kv head fastest: consecutive workgroup ids are dealt to the 8 XCDs in turn, and every kv head
-    // carries the same work, whereas chunk c only exists for contexts longer than c chunks.  With the chunk
-    // index slowest the workgroups that have nothing to do (chunks past a request's context) gather at
-    // the end of the grid instead of following each request: on a CU partition that measured 5 % faster
-    // (128 CUs: 160 -> 152 us), on the whole chip 2 % slower, so the launcher chooses by partition size.
-    // (Consecutive ids go to the 8 XCDs in turn, so the kv heads of one block are read through 8 different L2s
-    // at about the same time; putting them on ONE XCD instead measured 7-10 % slower on every partition.)
-    const int hk = blockIdx.x;
-    const int b = a.chunk_major ? blockIdx.y : blockIdx.z, chunk = a.chunk_major ? blockIdx.z : blockIdx.y;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wave = tid >> 6, lane = tid & 63;
     const int c16 = lane & 15, h = lane >> 4;
     const int G = a.Hq / a.Hkv;
     float *s_o = smem_dec;
@@ -251,6 +243,19 @@ __global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a) {
     }
 }
 
+template <int HD>
+__global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a) {
+    extern __shared__ float smem_dec[];
+    // kv head fastest: consecutive workgroup ids are dealt to the 8 XCDs in turn, and every kv head
+    // carries the same work, whereas chunk c only exists for contexts longer than c chunks.  With the chunk
+    // index slowest the workgroups that have nothing to do (chunks past a request's context) gather at
+    // the end of the grid instead of following each request: on a CU partition that measured 5 % faster
+    // (128 CUs: 160 -> 152 us), on the whole chip 2 % slower, so the launcher chooses by partition size.
+    // (Consecutive ids go to the 8 XCDs in turn, so the kv heads of one block are read through 8 different L2s
+    // at about the same time; putting them on ONE XCD instead measured 7-10 % slower on every partition.)
+    decode_attn_chunk<HD>(a, blockIdx.x, a.chunk_major ? blockIdx.y : blockIdx.z, a.chunk_major ? blockIdx.z : blockIdx.y, threadIdx.x, smem_dec);
+}
+
 // Merges the per-chunk partial results of one (request, query head).  Bound by memory round trips: the maxima and sums of
 // 64 chunks are read by a lane each, beside the context length; a quarter of the threads each takes every fourth chunk's
 // outputs, 16 bytes a thread, eight chunks requested together, and the quarters are added in order.  With one thread per
@@ -318,19 +323,18 @@ __global__ __launch_bounds__(HD) void decode_combine_kernel(DecodeAttnArgs a) {
     *op = (bf16_t)(l > 0.f ? sum / l : 0.f);
 }
 
+static void launch_decode_combine(hipStream_t st, const DecodeAttnArgs &a) {
+    if (a.hd == 128) hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(a.Hq, a.B), dim3(128), 0, st, a);
+    else hipLaunchKernelGGL(decode_combine_kernel<64>, dim3(a.Hq, a.B), dim3(64), 0, st, a);
+}
+
 void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
     if (a.B <= 0) return;
     dim3 grid(a.Hkv, a.chunk_major ? a.B : a.n_chunks, a.chunk_major ? a.n_chunks : a.B);
-    dim3 cgrid(a.Hq, a.B);
-    const int G = a.Hq / a.Hkv;
-    const size_t lds = (size_t)(4 * a.hd * G + 8 * G) * sizeof(float);   // <= 33 KB at G = 16
-    if (a.hd == 128) {
-        hipLaunchKernelGGL(decode_attn_kernel<128>, grid, dim3(256), lds, st, a);
-        hipLaunchKernelGGL(decode_combine_kernel<128>, cgrid, dim3(128), 0, st, a);
-    } else {
-        hipLaunchKernelGGL(decode_attn_kernel<64>, grid, dim3(256), lds, st, a);
-        hipLaunchKernelGGL(decode_combine_kernel<64>, cgrid, dim3(64), 0, st, a);
-    }
+    const size_t lds = (size_t)decode_attn_lds_floats(a.hd, a.Hq / a.Hkv) * sizeof(float);
+    if (a.hd == 128) hipLaunchKernelGGL(decode_attn_kernel<128>, grid, dim3(256), lds, st, a);
+    else hipLaunchKernelGGL(decode_attn_kernel<64>, grid, dim3(256), lds, st, a);
+    launch_decode_combine(st, a);
 }
 
 // =============================================================================================
@@ -346,6 +350,11 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 // read address is a per-lane base plus a constant, and a whole tile comes in by LDS-DMA (global -> LDS, no
 // staging registers, no LDS stores).
 //
+// A launch that leaves compute units idle or with one workgroup (256 workgroups or fewer: a 2048-token prompt of 32 heads, a
+// 512-token chunk) takes two teams of four waves a workgroup, which share out the key tiles: with one wave per SIMD every
+// wait is exposed.  On 256 CUs, one team / two (8B heads): 2048 tokens 83 / 68 us, a 512-token chunk behind 1024 cached
+// tokens 76 / about 50.  Above 256 one team: two workgroups on a unit overlap better than two teams at one barrier.
+//
 // What bounds it on long prompts: every wave reads the whole 32 KB K/V tile from LDS for its 32 queries, one
 // kilobyte of LDS reads per MFMA, which with four matrix cores per CU is the LDS's whole bandwidth (128 bytes
 // per cycle); and per score there are about as many vector cycles (scale, exponential at quarter rate, sum,
@@ -358,42 +367,43 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 // rescale decision) is exposed, and what the second wave hides here for nothing would have to be software
 // pipelined by hand across key tiles.
 // =============================================================================================
-template <int HD>
-__global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillAttnArgs a) {
+// The units of a launch: with `pairs` the pairs of 128-query tiles of all prompts, else the tiles themselves, heaviest first.
+__device__ __forceinline__ int prefill_units(int rows, bool pairs) { const int nt = (rows + 127) >> 7; return pairs ? (nt + 1) >> 1 : nt; }
+
+// KW: teams of four waves that take every KW-th key tile each, with K/V buffers of their own, and are merged at the end.
+template <int HD, int KW>
+__device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int pr, const int hq, bf16_t *smem_attn) {
     constexpr int CPR = HD / 8;   // 16-byte chunks per K row
     constexpr int KS = HD / 16;   // 32x32x16 steps over head_dim
     constexpr int DT = HD / 32;   // 32-row tiles of O^T
     constexpr int NKC = (64 * CPR) / 256, NVC = (HD * 8) / 256;  // chunks per thread per tile
-    extern __shared__ __attribute__((aligned(1024))) bf16_t smem_attn[];
-    bf16_t *Ks = smem_attn;                 // [2][64 * HD]
-    bf16_t *Vs = smem_attn + 2 * 64 * HD;   // [2][HD * 64]
-    int32_t *s_tab = (int32_t *)(smem_attn + 4 * 64 * HD);   // [PREFILL_TAB_LDS] block ids of this prompt
-
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x & 255, wave = tid >> 6, lane = tid & 63;
+    const int team = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
     const int c32 = lane & 31, h = lane >> 5;
+    bf16_t *Ks = smem_attn + team * (4 * 64 * HD);   // [2][64 * HD]
+    bf16_t *Vs = Ks + 2 * 64 * HD;                   // [2][HD * 64]
+    int32_t *s_tab = (int32_t *)(smem_attn + KW * 4 * 64 * HD);   // [PREFILL_TAB_LDS] block ids of this prompt
 
-    // (request, pair) of this workgroup
-    int pr = blockIdx.x, req = 0, nt = 0;
+    // (request, unit of it) of this workgroup
+    int req = 0, np = 0;
     for (;; ++req) {
-        nt = (a.seq.cu[req + 1] - a.seq.cu[req] + 127) >> 7;
-        const int np = (nt + 1) >> 1;
+        np = prefill_units(a.seq.cu[req + 1] - a.seq.cu[req], a.pairs);
         if (pr < np || req + 1 >= a.seq.n_req) break;
         pr -= np;
     }
-    if (pr >= ((nt + 1) >> 1)) return;
+    if (pr >= np) return;
+    const int nt = (a.seq.cu[req + 1] - a.seq.cu[req] + 127) >> 7;
     const int row0 = a.seq.cu[req];
     const int len = a.seq.cu[req + 1] - row0;
     // a later chunk of a prompt: its first row sits at position `prior`, and the positions before it are keys too
     // (read from the cache like the chunk's own); key positions below are absolute, query rows relative to the chunk
     const int prior = a.seq.start[req];
     const int tot = prior + len;
-    const int hq = blockIdx.y;
-    const int G = a.Hq / a.Hkv;
-    const int hk = hq / G;
+    const int hk = hq / (a.Hq / a.Hkv);
     const int32_t *tab = a.tables + (size_t)req * a.max_blk;
     const float sc = a.scale_log2;
     const int n_blk = (tot + 15) >> 4;
-    for (int i = tid; i < min(n_blk, PREFILL_TAB_LDS); i += 256) s_tab[i] = tab[i];
+    for (int i = threadIdx.x; i < min(n_blk, PREFILL_TAB_LDS); i += 256 * KW) s_tab[i] = tab[i];
     // (two separate loads: a pointer chosen between the LDS copy and the table would become a generic-address
     // load, which waits for every outstanding LDS and global access)
     auto block_of = [&](int bi) {
@@ -499,7 +509,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillAttnArgs a)
 
     for (int which = 0; which < 2; ++which) {
         const int tile = which == 0 ? nt - 1 - pr : pr;   // the heavier tile first
-        if (which == 1 && tile == nt - 1 - pr) break;
+        if (which == 1 && (!a.pairs || tile == nt - 1 - pr)) break;
         const int q0 = tile * 128;
         const int q_local = q0 + wave * 32 + c32;
         const bool q_valid = q_local < len;
@@ -524,16 +534,16 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillAttnArgs a)
             for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
 
         __syncthreads();   // s_tab visible; the previous tile's last reads done before buffer 0 is refilled
-        load_tile(0, 0);
+        if (team < n_kv_tiles) load_tile(64 * team, 0);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the LDS-DMA loads have landed
         __syncthreads();
-        for (int kt = 0; kt < n_kv_tiles; ++kt) {
+        for (int it = 0; it * KW < n_kv_tiles; ++it) {   // (as many iterations for every team: the barriers are the workgroup's)
+            const int kt = it * KW + team;
             const int kv0 = kt * 64;
-            const bool more = kt + 1 < n_kv_tiles;
-            if (more) load_tile(kv0 + 64, (kt + 1) & 1);
-            if (kv0 <= wave_q_max) {
-                const bf16_t *ks = Ks + (kt & 1) * 64 * HD;
-                const bf16_t *vs = Vs + (kt & 1) * HD * 64;
+            if (kt + KW < n_kv_tiles) load_tile(kv0 + 64 * KW, (it + 1) & 1);
+            if (kt < n_kv_tiles && kv0 <= wave_q_max) {
+                const bf16_t *ks = Ks + (it & 1) * 64 * HD;
+                const bf16_t *vs = Vs + (it & 1) * HD * 64;
                 f32x16 st[2];
 #pragma unroll
                 for (int t2 = 0; t2 < 2; ++t2)
@@ -627,44 +637,141 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PrefillAttnArgs a)
             __syncthreads();
         }
         l_run += __shfl_xor(l_run, 32, 64);
+        if (KW == 2) {
+            // The teams' halves of a row: both rescale to the common maximum; team 0 finishes the first half of head_dim,
+            // team 1 the second, each with the other's part through the K/V buffers (nobody reads those any more).
+            float *x_ml = (float *)s_tab + PREFILL_TAB_LDS;   // [KW][4 waves][32][2]
+            f32x4 *x_o = (f32x4 *)smem_attn;                  // [KW][4 waves][2 DT][64]
+            float *mine = x_ml + (team * 4 + wave) * 64, *theirs = x_ml + ((1 - team) * 4 + wave) * 64;
+            if (h == 0) {
+                mine[2 * c32] = m_run;
+                mine[2 * c32 + 1] = l_run;
+            }
+#pragma unroll
+            for (int dt = 0; dt < DT / 2; ++dt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    f32x4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = team == 0 ? o[DT / 2 + dt][4 * j + i] : o[dt][4 * j + i];
+                    x_o[((team * 4 + wave) * (2 * DT) + dt * 4 + j) * 64 + lane] = v;
+                }
+            __syncthreads();
+            const float m_o = theirs[2 * c32], l_o = theirs[2 * c32 + 1];
+            const float m = fmaxf(m_run, m_o), m_safe = m == NEG_INF ? 0.f : m;
+            const float e = __builtin_amdgcn_exp2f((m_run - m_safe) * sc), e_o = __builtin_amdgcn_exp2f((m_o - m_safe) * sc);
+            l_run = l_run * e + l_o * e_o;
+#pragma unroll
+            for (int dt = 0; dt < DT / 2; ++dt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const f32x4 v = x_o[(((1 - team) * 4 + wave) * (2 * DT) + dt * 4 + j) * 64 + lane];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[dt][4 * j + i] = (team == 0 ? o[dt][4 * j + i] : o[DT / 2 + dt][4 * j + i]) * e + v[i] * e_o;
+                }
+        }
         if (q_valid) {
             const float inv = 1.0f / l_run;
             // the output feeds the output projection: fragment-packed operand layout
             const int Mt = a.Mt_out ? a.Mt_out : packed_mt(a.seq.cu[a.seq.n_req]);
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+            for (int dt = 0; dt < DT / KW; ++dt)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     bf16x4 v;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(o[dt][4 * j + i] * inv);
-                    const int col = hq * HD + 32 * dt + 8 * j + 4 * h;
+                    const int col = hq * HD + 32 * (team * (DT / KW) + dt) + 8 * j + 4 * h;
                     *(bf16x4 *)(a.out + packed_offset(row0 + q_local, col, Mt) + (col & 7)) = v;
                 }
         }
     }
 }
 
-void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &a) {
-    int pairs = 0;
-    for (int r = 0; r < a.seq.n_req; ++r) pairs += ((a.seq.cu[r + 1] - a.seq.cu[r] + 127) / 128 + 1) / 2;
-    if (pairs <= 0) return;
-    dim3 grid(pairs, a.Hq);
+constexpr int prefill_lds(int hd, int kw) { return kw * 4 * 64 * hd * 2 + PREFILL_TAB_LDS * 4 + (kw > 1 ? kw * 4 * 64 * 4 : 0); }
+
+// Workgroup w of a launch: the heads of one kv head run on one XCD where there are eight of them (ids go to the XCDs in
+// turn), so that their keys and values stay in its L2 (5444 rows of 4 prompts, 70B heads: 352 -> 268 us; with one head after
+// the other every XCD read all of them).
+template <int HD, int KW>
+__device__ __forceinline__ void prefill_attn_wg(const PrefillAttnArgs &a, int w, bf16_t *smem) {
+    const int G = a.Hq / a.Hkv, hk = w % a.Hkv, r = w / a.Hkv;
+    prefill_attn_unit<HD, KW>(a, r / G, hk * G + r % G, smem);
+}
+
+template <int HD, int KW>
+__global__ __launch_bounds__(256 * KW, 2) void prefill_attn_kernel(PrefillAttnArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem_attn[];
+    prefill_attn_wg<HD, KW>(a, blockIdx.x, smem_attn);
+}
+
+// The prompt rows and the decode rows of a hybrid batch in one launch: the first n_prefill workgroups are
+// prefill_attn_kernel's, the others two kv heads of decode_attn_kernel's (request, chunk) each.  The two kinds of work need
+// different parts of the machine (matrix and vector units; memory), and a chunk's workgroups fill a quarter of the chip:
+// 512 rows behind 1024 cached tokens beside 64 decode rows (8B heads) 76 + 103 us one after the other, 134 us together.
+template <int HD>
+__global__ __launch_bounds__(512, 2) void hybrid_attn_kernel(PrefillAttnArgs p, DecodeAttnArgs d, int n_prefill) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem_attn[];
+    if ((int)blockIdx.x < n_prefill) {
+        prefill_attn_wg<HD, 2>(p, blockIdx.x, smem_attn);
+        return;
+    }
+    const int w = blockIdx.x - n_prefill, half = threadIdx.x >> 8, pairs = (d.Hkv + 1) >> 1;
+    const int hk = min(2 * (w % pairs) + half, d.Hkv - 1);   // (of an odd number the last is computed twice)
+    const int r = w / pairs, inner = d.chunk_major ? d.B : d.n_chunks;
+    const int b = d.chunk_major ? r % inner : r / inner, chunk = d.chunk_major ? r / inner : r % inner;
+    decode_attn_chunk<HD>(d, hk, b, chunk, threadIdx.x & 255, (float *)smem_attn + half * decode_attn_lds_floats(HD, d.Hq / d.Hkv));
+}
+
+static int prefill_unit_count(const PrefillAttnArgs &a, bool pairs) {
+    int n = 0;
+    for (int r = 0; r < a.seq.n_req; ++r) {
+        const int nt = (a.seq.cu[r + 1] - a.seq.cu[r] + 127) / 128;
+        n += pairs ? (nt + 1) / 2 : nt;
+    }
+    return n;
+}
+
+// Pairs of tiles even out the causal work once single tiles no longer all run at a time.
+static int prefill_choose_units(PrefillAttnArgs &a) {
+    const int tiles = prefill_unit_count(a, false) * a.Hq;
+    a.pairs = tiles > 256;
+    return a.pairs ? prefill_unit_count(a, true) * a.Hq : tiles;
+}
+
+void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &args) {
+    PrefillAttnArgs a = args;
+    const int wgs = prefill_choose_units(a);
+    if (wgs <= 0) return;
+    const bool teams = wgs <= 256;
     if (a.hd == 128) {
-        constexpr int lds = 4 * 64 * 128 * 2 + PREFILL_TAB_LDS * 4;
-        static bool set = false;
-        if (!set) {
-            (void)hipFuncSetAttribute((const void *)prefill_attn_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            set = true;
-        }
-        hipLaunchKernelGGL(prefill_attn_kernel<128>, grid, dim3(256), lds, st, a);
+        if (teams) hipLaunchKernelGGL((prefill_attn_kernel<128, 2>), dim3(wgs), dim3(512), prefill_lds(128, 2), st, a);
+        else hipLaunchKernelGGL((prefill_attn_kernel<128, 1>), dim3(wgs), dim3(256), prefill_lds(128, 1), st, a);
     } else {
-        hipLaunchKernelGGL(prefill_attn_kernel<64>, grid, dim3(256), 4 * 64 * 64 * 2 + PREFILL_TAB_LDS * 4, st, a);
+        if (teams) hipLaunchKernelGGL((prefill_attn_kernel<64, 2>), dim3(wgs), dim3(512), prefill_lds(64, 2), st, a);
+        else hipLaunchKernelGGL((prefill_attn_kernel<64, 1>), dim3(wgs), dim3(256), prefill_lds(64, 1), st, a);
     }
 }
 
-void attention_kernels_init() {
-    (void)hipFuncSetAttribute((const void *)prefill_attn_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              4 * 64 * 128 * 2 + PREFILL_TAB_LDS * 4);
+void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &pargs, const DecodeAttnArgs &d) {
+    PrefillAttnArgs p = pargs;
+    const int n_prefill = prefill_choose_units(p);
+    if (n_prefill <= 0 || d.B <= 0) {
+        launch_prefill_attention(st, pargs);
+        launch_decode_attention(st, d);
+        return;
+    }
+    const dim3 grid(n_prefill + (d.Hkv + 1) / 2 * d.n_chunks * d.B);
+    if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_kernel<128>, grid, dim3(512), prefill_lds(128, 2), st, p, d, n_prefill);
+    else hipLaunchKernelGGL(hybrid_attn_kernel<64>, grid, dim3(512), prefill_lds(64, 2), st, p, d, n_prefill);
+    launch_decode_combine(st, d);
 }
 
+void attention_kernels_init() {
+    auto set = [](const void *f, int lds) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+    set((const void *)prefill_attn_kernel<128, 1>, prefill_lds(128, 1));
+    set((const void *)prefill_attn_kernel<128, 2>, prefill_lds(128, 2));
+    set((const void *)prefill_attn_kernel<64, 2>, prefill_lds(64, 2));
+    set((const void *)hybrid_attn_kernel<128>, prefill_lds(128, 2));
+    set((const void *)hybrid_attn_kernel<64>, prefill_lds(64, 2));
+}

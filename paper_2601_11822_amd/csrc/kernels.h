@@ -33,6 +33,7 @@ struct PrefillAttnArgs {
     float scale_log2;  // log2(e)/sqrt(hd)
     SeqInfo seq;       // seq.start[r] > 0: the rows are a later chunk of prompt r and also attend to its cached positions before them
     int Mt_out = 0;    // row tiles of the packed output matrix when it holds more rows than this call's (0: packed_mt of this call's rows)
+    bool pairs = true; // set by the launchers
 };
 void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &a);
 
@@ -54,6 +55,7 @@ struct DecodeAttnArgs {
 #define RS_SKINNY_TARGET_WGS 384  // the skinny GEMM splits K until it has about this many workgroups
 #define RS_DECODE_CHUNK 512  // tokens per workgroup of the decode attention
 void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a);
+void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &p, const DecodeAttnArgs &d);   // both, in one launch
 
 enum GemmEpilogue { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2 };
 

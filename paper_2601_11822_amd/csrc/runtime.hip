@@ -641,19 +641,16 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
                                             m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq});
     tick(c, side, 2);
     tick(c, side, 3);
-    if (T > 0) {
-        PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd, max_blk_p, c->pool.n_blocks, sl2, seq};
-        pa.Mt_out = packed_mt(M);
-        launch_prefill_attention(st, pa);
-    }
-    if (B > 0) {
-        DecodeAttnArgs da{w.qkv + (size_t)T * nqkv, nqkv, w.attn, kp, vp, dtables, ctx_lens, err, w.part_o, w.part_ml,
-                          B, m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, max_ctx,
-                          (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, sl2, cus < RS_TOTAL_CUS};
-        da.out_row0 = T;
-        da.out_Mt = packed_mt(M);
-        launch_decode_attention(st, da);
-    }
+    PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd, max_blk_p, c->pool.n_blocks, sl2, seq};
+    pa.Mt_out = packed_mt(M);
+    DecodeAttnArgs da{w.qkv + (size_t)T * nqkv, nqkv, w.attn, kp, vp, dtables, ctx_lens, err, w.part_o, w.part_ml,
+                      B, m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, max_ctx,
+                      (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, sl2, cus < RS_TOTAL_CUS};
+    da.out_row0 = T;
+    da.out_Mt = packed_mt(M);
+    if (T > 0 && B > 0) launch_hybrid_attention(st, pa, da);
+    else if (T > 0) launch_prefill_attention(st, pa);
+    else launch_decode_attention(st, da);
     tick(c, side, 4);
     const DGemmPlan po = dgemm_plan(d, qd, false);
     stream(DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, M, d, qd}, po);
@@ -805,14 +802,15 @@ int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, co
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd,
                        max_blk_p, c->pool.n_blocks, sl2, seq};
     pa.Mt_out = packed_mt(M);
-    launch_prefill_attention(st, pa);
     if (B > 0) {
         DecodeAttnArgs da{w.qkv + (size_t)T * nqkv, nqkv, w.attn, kp, vp, dtables, ctx_lens, err, w.part_o, w.part_ml,
                           B, m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, max_ctx,
                           (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, sl2, c->side[RS_SIDE_PREFILL].cus < RS_TOTAL_CUS};
         da.out_row0 = T;
         da.out_Mt = packed_mt(M);
-        launch_decode_attention(st, da);
+        launch_hybrid_attention(st, pa, da);
+    } else {
+        launch_prefill_attention(st, pa);
     }
     tick(c, RS_SIDE_PREFILL, 4);
     ok = run_post_attention(c, RS_SIDE_PREFILL, st, w, lw, c->packed[layer], c->moe[layer], (const bf16_t *)x_in, (bf16_t *)x_out, M, skinny) && ok;

@@ -8,7 +8,8 @@ import oracle
 import paper_2601_11822_amd as rs
 import rs_synth as S
 from oracle import lm, moe
-from tests.gpu_util import END_TO_END, TOL, Rig, check_cache_against_oracle, check_tensor, to_dev
+from tests.gpu_util import END_TO_END, TOL, Rig, check_cache_against_oracle, check_tensor, gather_prompt_kv, to_dev
+from tests.test_gpu_hybrid import _hybrid_case
 from tests.test_gpu_moe import _moe_rig
 
 pytestmark = pytest.mark.gpu
@@ -108,3 +109,35 @@ def test_sparse_block_tiles(n):
         check_tensor("y", f32(y_bits), y_ref, x, 2, elem_mult=END_TO_END)
     finally:
         rig.close()
+
+
+# prompt attention: single 128-query tiles and pairs of them, one and two teams over the key tiles, at odd and even numbers
+# of 64-key tiles; own operands (the kernel's q and cache, the oracle's attention)
+@pytest.mark.parametrize("gain", [1.0])
+@pytest.mark.parametrize("shape,lens", [(S.TINY, [64]), (S.MID, [65]), (S.MID, [129]), (S.TINY, [700]), (S.MID, [300, 1, 200]),
+                                        (S.MID, [4100]), (S.MID, [4224]), (S.MID, [130] * 63 + [257]), (S.TINY, [130] * 64), (S.ODD, [200])])
+def test_prompt_attention_units(shape, lens, gain):
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, n_blocks = int(cu[-1]), sum(S.blocks_for(n) for n in lens) + 2
+    tabs = S.shuffled_block_tables(lens, n_blocks, stream=24)
+    rig = Rig(shape, n_blocks, T, 1, max(lens) + 1, with_oracle=False)
+    try:
+        w = rig.wdev[0]
+        g1 = w["g1"] * gain
+        rig.ctx.set_weights(0, g1, w["wqkv"], w["wo"], w["g2"], w["wg"], w["wu"], w["wd"])
+        rig.prefill(S.hidden_states(T, shape.d_model, stream=24), cu, tabs)
+        read = lambda which, width: f32(rig.ctx.debug_read_workspace(rs.RS_SIDE_PREFILL, which, (T, width)))
+        q, got = read(1, shape.qkv_dim)[:, :shape.q_dim].reshape(T, shape.n_q_heads, shape.head_dim), read(2, shape.q_dim)
+        k, v = gather_prompt_kv(rig, cu, tabs)
+        rows = np.unique(np.concatenate([cu[1:] - 1, cu[:-1], np.arange(min(T, 256)), np.arange(max(T - 140, 0), T)]))
+        ref = oracle.attn_causal(q, k, v, cu, rows=rows).reshape(T, shape.q_dim)
+        check_tensor("attention", got[rows], ref[rows])
+    finally:
+        rig.close()
+
+
+# a hybrid batch whose decode rows have one and several chunks of keys, with an even and an odd number of kv heads (the one
+# launch takes them two at a time), and with as many prompt rows as one team of waves would take alone
+@pytest.mark.parametrize("shape,lens,starts,ctx", [(S.ODD, [70], [32], [600, 5, 511, 512]), (S.MID, [200], [48], [1, 1025]), (S.TINY, [90, 300], [0, 16], [0, 700])])
+def test_hybrid_attention_in_one_launch(shape, lens, starts, ctx):
+    _hybrid_case(shape, lens, starts, ctx)
