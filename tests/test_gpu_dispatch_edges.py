@@ -112,8 +112,9 @@ def test_sparse_block_tiles(n):
 
 
 # prompt attention: single 128-query tiles and pairs of them, one and two teams over the key tiles, at odd and even numbers
-# of 64-key tiles; own operands (the kernel's q and cache, the oracle's attention)
-@pytest.mark.parametrize("gain", [1.0])
+# of 64-key tiles; own operands (the kernel's q and cache, the oracle's attention).  A gain of 8 makes the scores large
+# enough (tens of powers of two) that the reference of the exponentials has to follow the maximum.
+@pytest.mark.parametrize("gain", [1.0, 8.0])
 @pytest.mark.parametrize("shape,lens", [(S.TINY, [64]), (S.MID, [65]), (S.MID, [129]), (S.TINY, [700]), (S.MID, [300, 1, 200]),
                                         (S.MID, [4100]), (S.MID, [4224]), (S.MID, [130] * 63 + [257]), (S.TINY, [130] * 64), (S.ODD, [200])])
 def test_prompt_attention_units(shape, lens, gain):
