@@ -243,6 +243,12 @@ __device__ __forceinline__ void decode_attn_chunk(const DecodeAttnArgs &a, const
     }
 }
 
+// With requests slowest, the y-th workgroup of request b takes this chunk.  An XCD deals its workgroups to four shader engines
+// in turn, so with two or four chunks a fixed order gives an engine the same chunk of every request, and the engine with the
+// last one, which few requests reach, idles (256 rows of 64 to 2047 cached tokens, 8B heads: 228 us, 198 with the order
+// turned from request to request; 200 rows of 16 to 700: 75 and 61; 64 rows of 512 to 4096, nine chunks: 102 either way).
+__device__ __forceinline__ int decode_chunk_of(int y, int b, int n_chunks) { return (y + b + (b >> 1)) % n_chunks; }
+
 template <int HD>
 __global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a) {
     extern __shared__ float smem_dec[];
@@ -253,7 +259,8 @@ __global__ __launch_bounds__(256, 2) void decode_attn_kernel(DecodeAttnArgs a) {
     // (128 CUs: 160 -> 152 us), on the whole chip 2 % slower, so the launcher chooses by partition size.
     // (Consecutive ids go to the 8 XCDs in turn, so the kv heads of one block are read through 8 different L2s
     // at about the same time; putting them on ONE XCD instead measured 7-10 % slower on every partition.)
-    decode_attn_chunk<HD>(a, blockIdx.x, a.chunk_major ? blockIdx.y : blockIdx.z, a.chunk_major ? blockIdx.z : blockIdx.y, threadIdx.x, smem_dec);
+    const int b = a.chunk_major ? blockIdx.y : blockIdx.z;
+    decode_attn_chunk<HD>(a, blockIdx.x, b, a.chunk_major ? (int)blockIdx.z : decode_chunk_of(blockIdx.y, b, a.n_chunks), threadIdx.x, smem_dec);
 }
 
 // Merges the per-chunk partial results of one (request, query head).  Bound by memory round trips: the maxima and sums of
@@ -707,7 +714,7 @@ __global__ __launch_bounds__(256 * KW, 2) void prefill_attn_kernel(PrefillAttnAr
 // The prompt rows and the decode rows of a hybrid batch in one launch: the first n_prefill workgroups are
 // prefill_attn_kernel's, the others two kv heads of decode_attn_kernel's (request, chunk) each.  The two kinds of work need
 // different parts of the machine (matrix and vector units; memory), and a chunk's workgroups fill a quarter of the chip:
-// 512 rows behind 1024 cached tokens beside 64 decode rows (8B heads) 76 + 103 us one after the other, 134 us together.
+// 512 rows behind 1024 cached tokens beside 64 decode rows (8B heads) 76 + 103 us one after the other, 128 us together.
 template <int HD>
 __global__ __launch_bounds__(512, 2) void hybrid_attn_kernel(PrefillAttnArgs p, DecodeAttnArgs d, int n_prefill) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem_attn[];
@@ -717,8 +724,7 @@ __global__ __launch_bounds__(512, 2) void hybrid_attn_kernel(PrefillAttnArgs p, 
     }
     const int w = blockIdx.x - n_prefill, half = threadIdx.x >> 8, pairs = (d.Hkv + 1) >> 1;
     const int hk = min(2 * (w % pairs) + half, d.Hkv - 1);   // (of an odd number the last is computed twice)
-    const int r = w / pairs, inner = d.chunk_major ? d.B : d.n_chunks;
-    const int b = d.chunk_major ? r % inner : r / inner, chunk = d.chunk_major ? r / inner : r % inner;
+    const int r = w / pairs, b = r % d.B, chunk = r / d.B;   // chunks slowest: 128 us against 133 to 147 in the two other orders
     decode_attn_chunk<HD>(d, hk, b, chunk, threadIdx.x & 255, (float *)smem_attn + half * decode_attn_lds_floats(HD, d.Hq / d.Hkv));
 }
 
