@@ -538,16 +538,32 @@ size_t direct_partial_elems(int M, int N, int K) { return (size_t)direct_splits(
 template <int EPI>
 __global__ __launch_bounds__(256) void skinny_epilogue_kernel(GemmArgs a, const float *__restrict__ part, int S, int Nv);
 
-static void launch_direct_splitk(hipStream_t st, const GemmArgs &a, int S) {
+static void launch_direct_splitk_main(hipStream_t st, const GemmArgs &a, int S) {
     const int m_tiles = (a.M + 127) / 128, n_tiles = (a.N + 255) / 256;
     const int nk_total = a.K / 32, nk_per = (nk_total + S - 1) / S;
     constexpr int lds = 5 * (128 + 256) * 32 * 2;
     hipLaunchKernelGGL(gemm_direct_splitk_kernel, dim3(m_tiles * n_tiles * S), dim3(256), lds, st, a, m_tiles, n_tiles, nk_per, a.partials);
+}
+
+static void launch_direct_splitk(hipStream_t st, const GemmArgs &a, int S) {
+    launch_direct_splitk_main(st, a, S);
     const int eblocks = (a.M * (a.N / 4) + 255) / 256;
     if (a.epi == EPI_RESIDUAL)
         hipLaunchKernelGGL(skinny_epilogue_kernel<EPI_RESIDUAL>, dim3(eblocks), dim3(256), 0, st, a, a.partials, S, a.N);
     else
         hipLaunchKernelGGL(skinny_epilogue_kernel<EPI_STORE>, dim3(eblocks), dim3(256), 0, st, a, a.partials, S, a.N);
+}
+
+static int direct_sliced(const GemmArgs &a) {   // K slices of launch_gemm_tiled's sliced path, or 0 where it is not taken
+    if (!(a.K % 32 == 0 && a.K >= 32 && a.Wp && a.M > 64 && a.N >= 1024 && a.epi != EPI_SWIGLU && a.partials && a.N % 4 == 0)) return 0;
+    const int S = direct_splits(a.M, a.N, a.K);
+    return S > 1 && direct_partial_elems(a.M, a.N, a.K) <= a.partial_cap ? S : 0;
+}
+
+int launch_gemm_tiled_partials(hipStream_t st, const GemmArgs &a) {
+    const int S = direct_sliced(a);
+    if (S) launch_direct_splitk_main(st, a, S);
+    return S;
 }
 
 // LM head of more than 64 rows: whole K per tile, all row tiles of a column tile next to each other on one XCD.
@@ -671,12 +687,9 @@ bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
     if (a.M <= 0 || a.N <= 0) return true;
     const bool aligned = (a.K % 32 == 0) && a.K >= 32;
     if (aligned && a.Wp && a.M > 64 && a.N >= 1024) {
-        if (a.epi != EPI_SWIGLU && a.partials && a.N % 4 == 0) {
-            const int S = direct_splits(a.M, a.N, a.K);
-            if (S > 1 && direct_partial_elems(a.M, a.N, a.K) <= a.partial_cap) {
-                launch_direct_splitk(st, a, S);
-                return true;
-            }
+        if (const int S = direct_sliced(a)) {
+            launch_direct_splitk(st, a, S);
+            return true;
         }
         const int cus = a.cus > 0 ? a.cus : 256;
         const int nv = a.epi == EPI_SWIGLU ? 2 * a.N : a.N;

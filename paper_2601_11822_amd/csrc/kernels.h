@@ -86,6 +86,9 @@ struct GemmArgs {
 #define RS_DIRECT_PARTIAL_ELEMS ((size_t)10 << 20)
 // false (nothing launched): the shape needs the generic kernel, which reads a.W / a.W2, and they are null
 bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a);
+// The main pass alone where launch_gemm_tiled would cut K into slices: leaves part[s][M][N] in a.partials and returns the
+// number of slices; otherwise launches nothing and returns 0.
+int launch_gemm_tiled_partials(hipStream_t st, const GemmArgs &a);
 
 // Skinny variant for M <= 64 (decode): weight-streaming, deterministic split-K through
 // `partials` (fp32, at least skinny_partial_elems(...) elements).  Reads A, Wp and Wp2.
@@ -156,7 +159,7 @@ struct DEpiArgs {
 void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a);
 struct QkvEpiArgs {
     const float *part;        // [S][M][Nv] partial q | k | v
-    const float *ssq_part;    // [S_ssq][RS_SSQ_ROWS]
+    const float *ssq_part;    // [S_ssq][RS_SSQ_ROWS]; S_ssq 0: the product's input was normalised already
     int S, S_ssq, Nv, d;
     float eps;
     bf16_t *qkv;              // out: [M][(Hq+2Hkv)*hd] with q and k rotated
@@ -172,6 +175,18 @@ struct QkvEpiArgs {
     SeqInfo seq{};
 };
 void launch_qkv_rope_epilogue(hipStream_t st, const QkvEpiArgs &a);
+// x1 = resid + the slices' sum (row-major) and h = RMSNorm(x1; gain) (fragment-packed), a row a workgroup.  Needs
+// residual_norm_applies: rows of at most 8192, a multiple of 8.
+struct ResidualNormArgs {
+    const float *part;        // [S][M][N]
+    int S;
+    const bf16_t *resid, *gain;
+    bf16_t *x1, *h;
+    int M, N;
+    float eps;
+};
+bool residual_norm_applies(int N);
+void launch_residual_norm(hipStream_t st, const ResidualNormArgs &a);
 void decode_gemm_kernels_init();
 
 // Grouped GEMM over tiles that each belong to one expert: STORE or SWIGLU epilogue, a.M = the padded row capacity (a

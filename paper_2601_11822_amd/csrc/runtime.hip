@@ -569,9 +569,16 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     };
     // h, attn and act are fragment-packed by their producers; x1 and y are row-major
     const bf16_t *wo = (const bf16_t *)lw.wo, *wg = (const bf16_t *)lw.wg, *wu = (const bf16_t *)lw.wu, *wd = (const bf16_t *)lw.wd;
-    gemm(GemmArgs{w.attn, wo, nullptr, pl.wo, nullptr, x, w.x1, M, d, qd, EPI_RESIDUAL});
-    tick(c, side, 5);
-    launch_rmsnorm(st, w.x1, (const bf16_t *)lw.g2, w.h, M, d, m.rms_eps);
+    GemmArgs go{w.attn, wo, nullptr, pl.wo, nullptr, x, w.x1, M, d, qd, EPI_RESIDUAL, 0, 0, w.partials, w.partial_cap};
+    const int So = !skinny && residual_norm_applies(d) ? launch_gemm_tiled_partials(st, go) : 0;
+    if (So) {
+        launch_residual_norm(st, ResidualNormArgs{w.partials, So, x, (const bf16_t *)lw.g2, w.x1, w.h, M, d, m.rms_eps});
+        tick(c, side, 5);
+    } else {
+        gemm(go);
+        tick(c, side, 5);
+        launch_rmsnorm(st, w.x1, (const bf16_t *)lw.g2, w.h, M, d, m.rms_eps);
+    }
     tick(c, side, 6);
     if (ml.E > 0) {
         // sparse block: route, gather expert by expert, two grouped GEMMs over all tiles, weighted sum
@@ -678,6 +685,41 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     return RS_OK;
 }
 
+// QKV projection of normalised rows (w.h), rotary embedding and cache write: T prompt rows, then B decode rows.  Where the
+// product is cut into K slices its epilogue rotates and writes the cache (512 prompt rows and 64 decode rows of the 8B shape:
+// epilogue and two rotary kernels 7.3 + 9.5 + 6.5 us, 14.2 now); elsewhere that is a kernel of its own.  False: the product
+// needed row-major weights that were released.
+bool qkv_project(rs_ctx *c, int side, Workspace &w, int32_t layer, bool skinny, int T, const SeqInfo &seq, const int32_t *ptables,
+                 int32_t max_blk_p, int B, const int32_t *ctx_lens, const int32_t *dtables, int32_t max_blk_d) {
+    const rs_model_desc &m = c->m;
+    hipStream_t st = c->side[side].stream;
+    const int d = m.d_model, hd = m.head_dim, nqkv = (m.n_q_heads + 2 * m.n_kv_heads) * hd, M = T + B;
+    bf16_t *kp = (bf16_t *)c->pool.k_pool + (size_t)layer * c->pool.layer_stride;
+    bf16_t *vp = (bf16_t *)c->pool.v_pool + (size_t)layer * c->pool.layer_stride;
+    int32_t *err = c->err_flag + side;
+    GemmArgs g{w.h, (const bf16_t *)c->weights[layer].wqkv, nullptr, c->packed[layer].wqkv, nullptr, nullptr, w.qkv,
+               M, nqkv, d, EPI_STORE, 0, c->side[side].cus, w.partials, w.partial_cap};
+    if (const int S = skinny ? 0 : launch_gemm_tiled_partials(st, g)) {
+        launch_qkv_rope_epilogue(st, QkvEpiArgs{w.partials, nullptr, S, 0, nqkv, d, m.rms_eps, w.qkv, c->rope, kp, vp, dtables, ctx_lens, err, M,
+                                                m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq});
+        tick(c, side, 2);
+        tick(c, side, 3);
+        return true;
+    }
+    bool ok = true;
+    if (skinny) launch_gemm_skinny(st, g, w.partials);
+    else ok = launch_gemm_tiled(st, g);
+    tick(c, side, 2);
+    if (T > 0)
+        launch_rope_kvwrite(st, RopeKvArgs{w.qkv, c->rope, kp, vp, ptables, nullptr, err, T, m.n_q_heads, m.n_kv_heads, hd,
+                                           max_blk_p, c->pool.n_blocks, m.max_pos, seq});
+    if (B > 0)
+        launch_rope_kvwrite(st, RopeKvArgs{w.qkv + (size_t)T * nqkv, c->rope, kp, vp, dtables, ctx_lens, err, B, m.n_q_heads,
+                                           m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, SeqInfo{}});
+    tick(c, side, 3);
+    return ok;
+}
+
 int32_t prefill_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, const int32_t *cu,
                       int32_t n_req, const int32_t *tables, int32_t max_blk) {
     const rs_model_desc &m = c->m;
@@ -713,16 +755,7 @@ int32_t prefill_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, c
     tick(c, RS_SIDE_PREFILL, 1);
     // a pass of at most 64 rows is bound by reading the weights once: it takes the weight-streaming kernels
     const bool skinny = T <= 64;
-    GemmArgs gq{w.h, (const bf16_t *)lw.wqkv, nullptr, c->packed[layer].wqkv, nullptr, nullptr, w.qkv,
-                T, nqkv, d, EPI_STORE, 0, c->side[RS_SIDE_PREFILL].cus, w.partials, w.partial_cap};
-    bool ok = true;
-    if (skinny) launch_gemm_skinny(st, gq, w.partials);
-    else ok = launch_gemm_tiled(st, gq);
-    tick(c, RS_SIDE_PREFILL, 2);
-    RopeKvArgs ra{w.qkv, c->rope, kp, vp, tables, nullptr, c->err_flag + RS_SIDE_PREFILL, T, m.n_q_heads, m.n_kv_heads, hd,
-                  max_blk, c->pool.n_blocks, m.max_pos, seq};
-    launch_rope_kvwrite(st, ra);
-    tick(c, RS_SIDE_PREFILL, 3);
+    bool ok = qkv_project(c, RS_SIDE_PREFILL, w, layer, skinny, T, seq, tables, max_blk, 0, nullptr, nullptr, 0);
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, tables, c->err_flag + RS_SIDE_PREFILL, m.n_q_heads, m.n_kv_heads, hd,
                        max_blk, c->pool.n_blocks, (float)(1.4426950408889634 / std::sqrt((double)hd)), seq};
     launch_prefill_attention(st, pa);
@@ -785,20 +818,7 @@ int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, co
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, M, d, m.rms_eps);
     tick(c, RS_SIDE_PREFILL, 1);
     const bool skinny = M <= 64;
-    GemmArgs gq{w.h, (const bf16_t *)lw.wqkv, nullptr, c->packed[layer].wqkv, nullptr, nullptr, w.qkv,
-                M, nqkv, d, EPI_STORE, 0, c->side[RS_SIDE_PREFILL].cus, w.partials, w.partial_cap};
-    bool ok = true;
-    if (skinny) launch_gemm_skinny(st, gq, w.partials);
-    else ok = launch_gemm_tiled(st, gq);
-    tick(c, RS_SIDE_PREFILL, 2);
-    launch_rope_kvwrite(st, RopeKvArgs{w.qkv, c->rope, kp, vp, ptables, nullptr, err, T, m.n_q_heads, m.n_kv_heads, hd,
-                                       max_blk_p, c->pool.n_blocks, m.max_pos, seq});
-    if (B > 0) {
-        SeqInfo none{};
-        launch_rope_kvwrite(st, RopeKvArgs{w.qkv + (size_t)T * nqkv, c->rope, kp, vp, dtables, ctx_lens, err, B, m.n_q_heads,
-                                           m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, none});
-    }
-    tick(c, RS_SIDE_PREFILL, 3);
+    bool ok = qkv_project(c, RS_SIDE_PREFILL, w, layer, skinny, T, seq, ptables, max_blk_p, B, ctx_lens, dtables, max_blk_d);
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd,
                        max_blk_p, c->pool.n_blocks, sl2, seq};
     pa.Mt_out = packed_mt(M);
@@ -845,17 +865,8 @@ int32_t decode_layer(rs_ctx *c, Workspace &w, int32_t layer, const void *x_in, v
     tick(c, RS_SIDE_DECODE, 0);
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, B, d, m.rms_eps);
     tick(c, RS_SIDE_DECODE, 1);
-    GemmArgs g{w.h, (const bf16_t *)lw.wqkv, nullptr, c->packed[layer].wqkv, nullptr, nullptr, w.qkv, B, nqkv, d, EPI_STORE,
-               0, c->side[RS_SIDE_DECODE].cus, w.partials, w.partial_cap};
-    bool ok = true;
-    if (skinny) launch_gemm_skinny(st, g, w.partials);
-    else ok = launch_gemm_tiled(st, g);
-    tick(c, RS_SIDE_DECODE, 2);
-    SeqInfo none{};
-    RopeKvArgs ra{w.qkv, c->rope, kp, vp, tables, ctx_lens, c->err_flag + RS_SIDE_DECODE, B, m.n_q_heads, m.n_kv_heads, hd,
-                  max_blk, c->pool.n_blocks, m.max_pos, none};
-    launch_rope_kvwrite(st, ra);
-    tick(c, RS_SIDE_DECODE, 3);
+    const SeqInfo none{};
+    bool ok = qkv_project(c, RS_SIDE_DECODE, w, layer, skinny, 0, none, nullptr, 0, B, ctx_lens, tables, max_blk);
     DecodeAttnArgs da{w.qkv, nqkv, w.attn, kp, vp, tables, ctx_lens, c->err_flag + RS_SIDE_DECODE, w.part_o, w.part_ml,
                       B, m.n_q_heads, m.n_kv_heads, hd, max_blk, c->pool.n_blocks, max_ctx,
                       (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK,
