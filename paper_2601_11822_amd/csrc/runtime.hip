@@ -52,7 +52,7 @@ std::mutex g_static_scratch_mu;
 struct Workspace {
     bf16_t *h = nullptr, *qkv = nullptr, *attn = nullptr, *x1 = nullptr, *act = nullptr, *xbuf = nullptr;
     float *partials = nullptr, *part_o = nullptr, *part_ml = nullptr;
-    float *ssq = nullptr;   // per-slice sums of squares of the two normalised inputs of a streamed pass, 2 x [64 slices][RS_SSQ_ROWS]
+    float *ssq = nullptr;   // per-slice sums of squares of the two normalised inputs of a streamed pass, 2 x [ssq_slices][RS_SSQ_ROWS]
     size_t partial_cap = 0;
     int rows = 0;
     // sparse feed-forward block (allocated by the first rs_set_moe_weights)
@@ -335,6 +335,12 @@ bool stream_applies(const rs_ctx *c) {
     const int d = m.d_model, qd = m.n_q_heads * m.head_dim, nqkv = qd + 2 * m.n_kv_heads * m.head_dim, f = m.ffn_dim;
     return dgemm_applies(nqkv, d) && dgemm_applies(d, qd) && dgemm_applies(f, d);
 }
+// Parts that a row's sum of squares can come in (K slices of the QKV stream, or 1024-column pieces); 32 covers every usual shape.
+int ssq_slices(const rs_ctx *c) {
+    const rs_model_desc &m = c->m;
+    const int d = m.d_model, nqkv = (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
+    return std::max(std::max(32, (d + 1023) / 1024), stream_applies(c) ? dgemm_plan(nqkv, d, false).S : 0);
+}
 size_t stream_partial_elems(const rs_ctx *c, int M) {
     if (!stream_applies(c)) return 0;
     const rs_model_desc &m = c->m;
@@ -381,7 +387,7 @@ int32_t alloc_ws(rs_ctx *c, Workspace &w, int rows, bool decode) {
         HIP_TRY(hipMalloc(&w.part_o, br * m.n_q_heads * nch * m.head_dim * sizeof(float)));
         HIP_TRY(hipMalloc(&w.part_ml, br * m.n_q_heads * nch * 2 * sizeof(float)));
     }
-    HIP_TRY(hipMalloc(&w.ssq, 2 * 64 * RS_SSQ_ROWS * sizeof(float)));
+    HIP_TRY(hipMalloc(&w.ssq, 2 * (size_t)ssq_slices(c) * RS_SSQ_ROWS * sizeof(float)));
     if (decode) {
         const size_t nch = (c->lim.max_context + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
         HIP_TRY(hipMalloc(&w.part_o, (size_t)rows * m.n_q_heads * nch * m.head_dim * sizeof(float)));
@@ -420,7 +426,7 @@ size_t carve_decode_ws(const rs_ctx *c, Workspace &w, unsigned char *base, int r
     pe = std::max(pe, skinny_partial_elems(Mmax, (int)f, (int)d, EPI_SWIGLU));
     pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)f, EPI_RESIDUAL));
     pe = std::max(pe, stream_partial_elems(c, std::min(rows, RS_STREAM_ROWS)));
-    w.ssq = (float *)take(2 * 64 * RS_SSQ_ROWS * sizeof(float));
+    w.ssq = (float *)take(2 * (size_t)ssq_slices(c) * RS_SSQ_ROWS * sizeof(float));
     w.partials = (float *)take(pe * sizeof(float));
     w.partial_cap = pe;
     const size_t nch = (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
@@ -625,7 +631,7 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     bf16_t *vp = (bf16_t *)c->pool.v_pool + (size_t)layer * c->pool.layer_stride;
     int32_t *err = c->err_flag + side;
     const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
-    float *ssq1 = w.ssq, *ssq2 = w.ssq + 64 * RS_SSQ_ROWS;
+    float *ssq1 = w.ssq, *ssq2 = w.ssq + (size_t)ssq_slices(c) * RS_SSQ_ROWS;
     const int cus = c->side[side].cus;
     c->last_rows[side] = M;
     c->streamed[side] = true;
