@@ -618,38 +618,27 @@ static void launch_direct(hipStream_t st, const GemmArgs &a) {
 // An expert's rows are cut into units of one height, so that the units that share its weights run through K at one pace
 // and fetch them together.  A 256-row tile beside a shorter one that runs ahead of it had every weight leave the L2 in
 // between (8 experts of 275 rows of the 8B widths, 256 + 128 rows each against 192 + 192: gate/up 801 -> 649 us, down 395 -> 324 us).
-// Order: jobs of up to 4 consecutive units (neighbours in the list, mostly of one expert) by GC column tiles, what the 32
-// units of an XCD hold at a time, dealt to the XCDs in turn: a job reads 4 activation slabs and, with two units an
-// expert, 16 weight slabs, where all units of one column tile after another read 16 and 32 for as many tiles.  When there
-// are fewer tiles than two for each compute unit (GC 1), single columns are dealt instead, so that all XCDs get some.
-#define RS_GROUP_UNITS 4
-#define RS_GROUP_COLS 8
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_tiles) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     const int nu = __builtin_amdgcn_readfirstlane(a.units[0]);
-    const int gu = min(nu, RS_GROUP_UNITS), gc = nu * n_tiles >= 512 ? RS_GROUP_COLS : 1;
     if (nu <= 0) return;
-    const int cbs = (n_tiles + gc - 1) / gc, per_job = gu * gc;
-    const int i = blockIdx.x >> 3, job = i / per_job * 8 + (blockIdx.x & 7), v = i % per_job;
-    const int u = job / cbs * gu + v % gu, nb = job % cbs * gc + v / gu;
-    if (nb >= n_tiles || u >= nu) return;
-    const int code = __builtin_amdgcn_readfirstlane(a.units[2 + u]);
+    const GroupTile t = grouped_tile(blockIdx.x & 7, blockIdx.x >> 3, nu, n_tiles);
+    if (t.u < 0) return;
+    const int code = __builtin_amdgcn_readfirstlane(a.units[2 + t.u]);
     const int row0 = (code >> 8) * 64, height = (code >> 5) & 7;
     GemmArgs g = a;
     g.Wp += (size_t)(code & 31) * a.expert_stride;
     if (EPI == EPI_SWIGLU) g.Wp2 += (size_t)(code & 31) * a.expert_stride;
-    if (height == 4) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4>(g, row0, nb, smem);
-    else if (height == 3) gemm_direct_tile<192, 256, EPI, 4, 4>(g, row0, nb, smem);
-    else gemm_direct_tile<128, 256, EPI, 5, 4>(g, row0, nb, smem);
+    if (height == 4) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4>(g, row0, t.nb, smem);
+    else if (height == 3) gemm_direct_tile<192, 256, EPI, 4, 4>(g, row0, t.nb, smem);
+    else gemm_direct_tile<128, 256, EPI, 5, 4>(g, row0, t.nb, smem);
 }
 
 template <int EPI>
 static void launch_grouped_epi(hipStream_t st, const GemmArgs &a) {
     const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + 127) / 128 : (a.N + 255) / 256;
-    // workgroups per XCD for as many units as there can be, in either size of job
-    const int groups = ((a.M >> 7) + RS_GROUP_UNITS - 1) / RS_GROUP_UNITS, jobs = groups * ((n_tiles + RS_GROUP_COLS - 1) / RS_GROUP_COLS);
-    const int per_xcd = std::max((jobs + 7) / 8 * (RS_GROUP_UNITS * RS_GROUP_COLS), (groups * n_tiles + 7) / 8 * RS_GROUP_UNITS);
+    const int per_xcd = ((a.M >> 7) * n_tiles + 7) / 8;   // of as many units as there can be
     hipLaunchKernelGGL((gemm_grouped_kernel<EPI>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
 }
 

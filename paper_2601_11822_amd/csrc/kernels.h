@@ -194,6 +194,30 @@ void decode_gemm_kernels_init();
 // N >= 1024.
 bool launch_gemm_grouped(hipStream_t st, const GemmArgs &a);
 
+// The grouped GEMM's order of tiles.  An XCD takes an eighth of them, counted column by column, so that every one has the same
+// number of them and its share of every expert.  (Dealt in jobs of 4 units by 8 columns some XCDs had four jobs and others
+// three, or three and two; 8 experts of the 8B widths, jobs / this: gate/up of 16 rows on 64 CUs 923 / 820 us and on 128 532 /
+// 492, down of 4000 rows on 64 CUs 2872 / 2194, gate/up of 300 rows of which most share an expert on 256 CUs 483 / 395.)
+// An XCD's whole columns go in blocks of 8, four units (neighbours in the list, mostly of one expert) at a time: 32 tiles in
+// flight then read 4 activation slabs and, with two units an expert, 16 weight slabs, where all units of one column
+// after another read 16 and 32 for as many tiles.
+#define RS_GROUP_UNITS 4
+#define RS_GROUP_COLS 8
+struct GroupTile { int u, nb; };   // unit, column tile
+// The i-th tile (0 <= i) of XCD x, or u = -1 past its share.
+__host__ __device__ inline GroupTile grouped_tile(int x, int i, int nu, int n_tiles) {
+    const int total = nu * n_tiles, per = (total + 7) >> 3;
+    const int first = x * per, end = first + per < total ? first + per : total;
+    if (i >= end - first) return {-1, 0};
+    const int col0 = (first + nu - 1) / nu, col1 = end / nu;   // its whole columns [col0, col1)
+    const int t = first + i, j = t - col0 * nu;
+    if (j < 0 || t >= col1 * nu) return {t % nu, t / nu};      // of a column shared with a neighbour
+    const int block = j / (RS_GROUP_COLS * nu), c0 = col0 + block * RS_GROUP_COLS, cols = col1 - c0 < RS_GROUP_COLS ? col1 - c0 : RS_GROUP_COLS;
+    const int r = j - block * (RS_GROUP_COLS * nu), g = r / (RS_GROUP_UNITS * cols);
+    const int units = nu - g * RS_GROUP_UNITS < RS_GROUP_UNITS ? nu - g * RS_GROUP_UNITS : RS_GROUP_UNITS, v = r - g * (RS_GROUP_UNITS * cols);
+    return {g * RS_GROUP_UNITS + v % units, c0 + v / units};
+}
+
 #define RS_MOE_MAX_EXPERTS 16
 // Rows of the grouped (expert-major) layout that M rows with two experts each can need: an expert's segment is less than
 // 256 rows longer than its rows.

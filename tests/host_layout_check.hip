@@ -1,10 +1,11 @@
 // Host-side check of the operand layouts that kernels and host code share (no GPU call).
 // Built and run by tests/test_host_abi.py.
 #include <cstdio>
+#include <algorithm>
 #include <set>
 #include <vector>
 
-#include "../paper_2601_11822_amd/csrc/common.h"
+#include "../paper_2601_11822_amd/csrc/kernels.h"
 
 static int fails = 0;
 #define CHECK(c, ...) do { if (!(c)) { if (fails++ < 10) { std::printf("FAIL %s:%d: ", __FILE__, __LINE__); std::printf(__VA_ARGS__); std::printf("\n"); } } } while (0)
@@ -44,6 +45,28 @@ int main() {
             }
         CHECK((int)seen.size() == 2 * hd, "kpool not a bijection hd=%d", hd);
     }
+    // grouped GEMM: the eight XCDs' tiles are every (unit, column) once, an eighth each, and no XCD has more than its
+    // share of any unit by more than a column
+    for (int nu : {1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 33, 47, 143})
+        for (int n_tiles : {4, 5, 8, 11, 16, 17, 25, 112, 113}) {
+            const int total = nu * n_tiles, per = (total + 7) / 8;
+            std::set<int> seen;
+            for (int x = 0; x < 8; ++x) {
+                std::vector<int> of_unit(nu, 0);
+                int n = 0;
+                for (int i = 0; i < per + 3; ++i) {
+                    const GroupTile t = grouped_tile(x, i, nu, n_tiles);
+                    if (t.u < 0) continue;
+                    CHECK(i < per, "tile past the launched workgroups nu=%d n_tiles=%d", nu, n_tiles);
+                    CHECK(t.u < nu && t.nb >= 0 && t.nb < n_tiles, "tile out of range nu=%d n_tiles=%d", nu, n_tiles);
+                    CHECK(seen.insert(t.u * n_tiles + t.nb).second, "tile taken twice nu=%d n_tiles=%d", nu, n_tiles);
+                    ++of_unit[t.u], ++n;
+                }
+                CHECK(n == std::max(0, std::min(per, total - x * per)), "XCD %d has %d of %d tiles nu=%d", x, n, total, nu);
+                for (int c : of_unit) CHECK(c <= (n + nu - 1) / nu + 1, "XCD %d has %d columns of a unit nu=%d n_tiles=%d", x, c, nu, n_tiles);
+            }
+            CHECK((int)seen.size() == total, "%zu of %d tiles nu=%d n_tiles=%d", seen.size(), total, nu, n_tiles);
+        }
     if (fails) { std::printf("%d checks failed\n", fails); return 1; }
     std::printf("layouts ok\n");
     return 0;

@@ -207,7 +207,7 @@ def test_decode_batch_cap_and_fcfs_promotion():
 
 def test_operand_layouts_shared_by_host_and_kernels(tmp_path):
     """packed_offset / packed_mt / kpool_chunk_offset are bijections with the fragment structure the
-    kernels assume; checked on the host by a small program compiled against the kernels' own header."""
+    kernels assume, and grouped_tile deals every tile once, evenly; checked on the host by a small program compiled against the kernels' own header."""
     import shutil
     import subprocess
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
