@@ -357,10 +357,10 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 // read address is a per-lane base plus a constant, and a whole tile comes in by LDS-DMA (global -> LDS, no
 // staging registers, no LDS stores).
 //
-// A launch that leaves compute units idle or with one workgroup (256 workgroups or fewer: a 2048-token prompt of 32 heads, a
-// 512-token chunk) takes two teams of four waves a workgroup, which share out the key tiles: with one wave per SIMD every
-// wait is exposed.  On 256 CUs, one team / two (8B heads): 2048 tokens 83 / 68 us, a 512-token chunk behind 1024 cached
-// tokens 76 / about 50.  Above 256 one team: two workgroups on a unit overlap better than two teams at one barrier.
+// A launch that leaves compute units idle or with one workgroup takes two teams of four waves a workgroup, which share out the
+// key tiles: with one wave per SIMD every wait is exposed.  On 256 CUs, one team / two (8B heads): 2048 tokens 83 / 68 us, a
+// 512-token chunk behind 1024 cached tokens 76 / about 50.  Where there are more workgroups than units it takes one team: two
+// workgroups on a unit overlap better than two teams at one barrier (prefill_form below).
 //
 // What bounds it on long prompts: every wave reads the whole 32 KB K/V tile from LDS for its 32 queries, one
 // kilobyte of LDS reads per MFMA, which with four matrix cores per CU is the LDS's whole bandwidth (128 bytes
@@ -374,12 +374,29 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 // rescale decision) is exposed, and what the second wave hides here for nothing would have to be software
 // pipelined by hand across key tiles.
 // =============================================================================================
+// Sums over the even and over the odd key tiles of a row, each relative to a maximum of its own, brought together.  Which
+// product is rounded is written out, so that every form gets the same bits.
+struct Merge {
+    float e_even, e_odd, l;
+    __device__ __forceinline__ Merge(float m, float l_mine, float m_other, float l_other, bool even, float sc) {
+        const float top = fmaxf(m, m_other), ref = top == NEG_INF ? 0.f : top;
+        const float e = __builtin_amdgcn_exp2f((m - ref) * sc), e_other = __builtin_amdgcn_exp2f((m_other - ref) * sc);
+        e_even = even ? e : e_other;
+        e_odd = even ? e_other : e;
+        l = (*this)(even ? l_mine : l_other, even ? l_other : l_mine);
+    }
+    __device__ __forceinline__ float operator()(float even, float odd) const { return __builtin_fmaf(even, e_even, odd * e_odd); }
+};
+
 // The units of a launch: with `pairs` the pairs of 128-query tiles of all prompts, else the tiles themselves, heaviest first.
 __device__ __forceinline__ int prefill_units(int rows, bool pairs) { const int nt = (rows + 127) >> 7; return pairs ? (nt + 1) >> 1 : nt; }
 
 // KW: teams of four waves that take every KW-th key tile each, with K/V buffers of their own, and are merged at the end.
-template <int HD, int KW>
-__device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int pr, const int hq, bf16_t *smem_attn) {
+// SEQ: one team that computes what two would, the same bits: the even key tiles, then (their sums put away in `park`,
+// float32, 128 x HD of them) the odd ones, then the same merge.
+template <int HD, int KW, bool SEQ>
+__device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int pr, const int hq, bf16_t *smem_attn, float *park) {
+    static_assert(KW == 1 || !SEQ, "two teams put nothing away");
     constexpr int CPR = HD / 8;   // 16-byte chunks per K row
     constexpr int KS = HD / 16;   // 32x32x16 steps over head_dim
     constexpr int DT = HD / 32;   // 32-row tiles of O^T
@@ -533,21 +550,39 @@ __device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int 
         const int kv_end = prior + min(q0 + 128, len);
         const int n_kv_tiles = (kv_end + 63) >> 6;
 
+        // the key tile of iteration `it`; as many iterations for every team: the barriers are the workgroup's
+        const int n_even = (n_kv_tiles + 1) >> 1, n_it = KW == 2 ? n_even : n_kv_tiles;
+        auto tile_at = [&](int it) { return KW == 2 ? 2 * it + team : !SEQ ? it : it < n_even ? 2 * it : 2 * (it - n_even) + 1; };
+
         float m_run = NEG_INF, l_run = 0.f;   // running max of raw scores, running sum
+        float m_put = NEG_INF, l_put = 0.f;   // SEQ: those of the even tiles
+        f32x4 *o_put = (f32x4 *)park + wave * (4 * DT * 64) + lane;
         f32x16 o[DT];
+        auto reset = [&]() {
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+            for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
+                for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
+        };
+        reset();
 
         __syncthreads();   // s_tab visible; the previous tile's last reads done before buffer 0 is refilled
         if (team < n_kv_tiles) load_tile(64 * team, 0);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the LDS-DMA loads have landed
         __syncthreads();
-        for (int it = 0; it * KW < n_kv_tiles; ++it) {   // (as many iterations for every team: the barriers are the workgroup's)
-            const int kt = it * KW + team;
+        for (int it = 0; it < n_it; ++it) {
+            const int kt = tile_at(it);
             const int kv0 = kt * 64;
-            if (kt + KW < n_kv_tiles) load_tile(kv0 + 64 * KW, (it + 1) & 1);
+            if (it + 1 < n_it && tile_at(it + 1) < n_kv_tiles) load_tile(64 * tile_at(it + 1), (it + 1) & 1);
+            if (SEQ && it == n_even) {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o_put[(dt * 4 + j) * 64] = f32x4{o[dt][4 * j], o[dt][4 * j + 1], o[dt][4 * j + 2], o[dt][4 * j + 3]};
+                m_put = m_run, l_put = l_run;
+                m_run = NEG_INF, l_run = 0.f;
+                reset();
+            }
             if (kt < n_kv_tiles && kv0 <= wave_q_max) {
                 const bf16_t *ks = Ks + (it & 1) * 64 * HD;
                 const bf16_t *vs = Vs + (it & 1) * HD * 64;
@@ -663,17 +698,30 @@ __device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int 
                     x_o[((team * 4 + wave) * (2 * DT) + dt * 4 + j) * 64 + lane] = v;
                 }
             __syncthreads();
-            const float m_o = theirs[2 * c32], l_o = theirs[2 * c32 + 1];
-            const float m = fmaxf(m_run, m_o), m_safe = m == NEG_INF ? 0.f : m;
-            const float e = __builtin_amdgcn_exp2f((m_run - m_safe) * sc), e_o = __builtin_amdgcn_exp2f((m_o - m_safe) * sc);
-            l_run = l_run * e + l_o * e_o;
+            const Merge g(m_run, l_run, theirs[2 * c32], theirs[2 * c32 + 1], team == 0, sc);
+            l_run = g.l;
 #pragma unroll
             for (int dt = 0; dt < DT / 2; ++dt)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const f32x4 v = x_o[(((1 - team) * 4 + wave) * (2 * DT) + dt * 4 + j) * 64 + lane];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[dt][4 * j + i] = (team == 0 ? o[dt][4 * j + i] : o[DT / 2 + dt][4 * j + i]) * e + v[i] * e_o;
+                    for (int i = 0; i < 4; ++i) o[dt][4 * j + i] = team == 0 ? g(o[dt][4 * j + i], v[i]) : g(v[i], o[DT / 2 + dt][4 * j + i]);
+                }
+        }
+        if (SEQ) {
+            l_put += __shfl_xor(l_put, 32, 64);
+            const bool two = n_kv_tiles > 1;   // else there are even tiles only, and they are still here
+            const Merge g = two ? Merge(m_put, l_put, m_run, l_run, true, sc) : Merge(m_run, l_run, m_put, l_put, true, sc);
+            l_run = g.l;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                    if (two) v = o_put[(dt * 4 + j) * 64];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[dt][4 * j + i] = two ? g(v[i], o[dt][4 * j + i]) : g(o[dt][4 * j + i], v[i]);
                 }
         }
         if (q_valid) {
@@ -699,16 +747,16 @@ constexpr int prefill_lds(int hd, int kw) { return kw * 4 * 64 * hd * 2 + PREFIL
 // Workgroup w of a launch: the heads of one kv head run on one XCD where there are eight of them (ids go to the XCDs in
 // turn), so that their keys and values stay in its L2 (5444 rows of 4 prompts, 70B heads: 352 -> 268 us; with one head after
 // the other every XCD read all of them).
-template <int HD, int KW>
+template <int HD, int KW, bool SEQ>
 __device__ __forceinline__ void prefill_attn_wg(const PrefillAttnArgs &a, int w, bf16_t *smem) {
     const int G = a.Hq / a.Hkv, hk = w % a.Hkv, r = w / a.Hkv;
-    prefill_attn_unit<HD, KW>(a, r / G, hk * G + r % G, smem);
+    prefill_attn_unit<HD, KW, SEQ>(a, r / G, hk * G + r % G, smem, SEQ ? a.park + (size_t)w * (128 * HD) : nullptr);
 }
 
-template <int HD, int KW>
+template <int HD, int KW, bool SEQ>
 __global__ __launch_bounds__(256 * KW, 2) void prefill_attn_kernel(PrefillAttnArgs a) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem_attn[];
-    prefill_attn_wg<HD, KW>(a, blockIdx.x, smem_attn);
+    prefill_attn_wg<HD, KW, SEQ>(a, blockIdx.x, smem_attn);
 }
 
 // The prompt rows and the decode rows of a hybrid batch in one launch: the first n_prefill workgroups are
@@ -719,7 +767,7 @@ template <int HD>
 __global__ __launch_bounds__(512, 2) void hybrid_attn_kernel(PrefillAttnArgs p, DecodeAttnArgs d, int n_prefill) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem_attn[];
     if ((int)blockIdx.x < n_prefill) {
-        prefill_attn_wg<HD, 2>(p, blockIdx.x, smem_attn);
+        prefill_attn_wg<HD, 2, false>(p, blockIdx.x, smem_attn);
         return;
     }
     const int w = blockIdx.x - n_prefill, half = threadIdx.x >> 8, pairs = (d.Hkv + 1) >> 1;
@@ -737,35 +785,49 @@ static int prefill_unit_count(const PrefillAttnArgs &a, bool pairs) {
     return n;
 }
 
-// Pairs of tiles even out the causal work once single tiles no longer all run at a time.
-static int prefill_choose_units(PrefillAttnArgs &a) {
-    const int tiles = prefill_unit_count(a, false) * a.Hq;
-    a.pairs = tiles > 256;
-    return a.pairs ? prefill_unit_count(a, true) * a.Hq : tiles;
+// How a launch goes about its tiles.  Whether a row's sums are cut into even and odd key tiles (`split`) follows from the sizes
+// alone: 256 workgroups or fewer, what the whole chip takes at a time.  By whom they are computed, and in what order, from
+// the compute units `cus` too, with the same bits.  A unit holds one workgroup of two teams or two of one team, so two teams
+// only where all pairs of tiles fit at a time: 2048 rows of 32 heads (256 pairs) on 256 / 192 / 128 / 64 CUs 56 / 88 /
+// 86 / 166 us with two teams, 71 / 61 / 80 / 146 with one.  Pairs of tiles where they about fill the places, else single ones, heaviest first:
+// those even out whatever the number (3000 rows, 384 pairs, on 256 CUs 117 / 97 us, on 192 CUs, all places filled, 114 / 118;
+// 1536 rows on 128 CUs 65 / 56).
+struct PrefillForm { bool split, teams, pairs; int tiles, wgs; };
+static bool prefill_pairs_fill(int pairs, int places) { return pairs <= places && 10 * pairs > 9 * places; }
+static int prefill_cus(const PrefillAttnArgs &a) { return a.cus > 0 ? a.cus : 256; }
+static PrefillForm prefill_form(const PrefillAttnArgs &a) {
+    const int pairs = prefill_unit_count(a, true) * a.Hq, cus = prefill_cus(a);
+    PrefillForm f{};
+    f.tiles = prefill_unit_count(a, false) * a.Hq;
+    f.split = pairs <= 256;
+    const size_t parked = (size_t)f.tiles * 128 * a.hd;
+    f.teams = f.split && (pairs <= cus || !a.park || parked > a.park_cap);
+    f.pairs = prefill_pairs_fill(pairs, f.teams ? cus : 2 * cus);
+    f.wgs = f.pairs ? pairs : f.tiles;
+    return f;
+}
+
+template <int HD>
+static void launch_prefill_form(hipStream_t st, const PrefillAttnArgs &a, const PrefillForm &f) {
+    if (f.teams) hipLaunchKernelGGL((prefill_attn_kernel<HD, 2, false>), dim3(f.wgs), dim3(512), prefill_lds(HD, 2), st, a);
+    else if (f.split) hipLaunchKernelGGL((prefill_attn_kernel<HD, 1, true>), dim3(f.wgs), dim3(256), prefill_lds(HD, 1), st, a);
+    else hipLaunchKernelGGL((prefill_attn_kernel<HD, 1, false>), dim3(f.wgs), dim3(256), prefill_lds(HD, 1), st, a);
 }
 
 void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &args) {
     PrefillAttnArgs a = args;
-    const int wgs = prefill_choose_units(a);
-    if (wgs <= 0) return;
-    const bool teams = wgs <= 256;
-    if (a.hd == 128) {
-        if (teams) hipLaunchKernelGGL((prefill_attn_kernel<128, 2>), dim3(wgs), dim3(512), prefill_lds(128, 2), st, a);
-        else hipLaunchKernelGGL((prefill_attn_kernel<128, 1>), dim3(wgs), dim3(256), prefill_lds(128, 1), st, a);
-    } else {
-        if (teams) hipLaunchKernelGGL((prefill_attn_kernel<64, 2>), dim3(wgs), dim3(512), prefill_lds(64, 2), st, a);
-        else hipLaunchKernelGGL((prefill_attn_kernel<64, 1>), dim3(wgs), dim3(256), prefill_lds(64, 1), st, a);
-    }
+    const PrefillForm f = prefill_form(a);
+    if (f.wgs <= 0) return;
+    a.pairs = f.pairs;
+    if (a.hd == 128) launch_prefill_form<128>(st, a, f);
+    else launch_prefill_form<64>(st, a, f);
 }
 
 void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &pargs, const DecodeAttnArgs &d) {
     PrefillAttnArgs p = pargs;
-    const int n_prefill = prefill_choose_units(p);
-    if (n_prefill <= 0 || d.B <= 0) {
-        launch_prefill_attention(st, pargs);
-        launch_decode_attention(st, d);
-        return;
-    }
+    const int tiles = prefill_unit_count(p, false) * p.Hq;
+    p.pairs = tiles > 256;
+    const int n_prefill = p.pairs ? prefill_unit_count(p, true) * p.Hq : tiles;
     const dim3 grid(n_prefill + (d.Hkv + 1) / 2 * d.n_chunks * d.B);
     if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_kernel<128>, grid, dim3(512), prefill_lds(128, 2), st, p, d, n_prefill);
     else hipLaunchKernelGGL(hybrid_attn_kernel<64>, grid, dim3(512), prefill_lds(64, 2), st, p, d, n_prefill);
@@ -774,9 +836,10 @@ void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &pargs, const
 
 void attention_kernels_init() {
     auto set = [](const void *f, int lds) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
-    set((const void *)prefill_attn_kernel<128, 1>, prefill_lds(128, 1));
-    set((const void *)prefill_attn_kernel<128, 2>, prefill_lds(128, 2));
-    set((const void *)prefill_attn_kernel<64, 2>, prefill_lds(64, 2));
+    set((const void *)prefill_attn_kernel<128, 1, false>, prefill_lds(128, 1));
+    set((const void *)prefill_attn_kernel<128, 1, true>, prefill_lds(128, 1));
+    set((const void *)prefill_attn_kernel<128, 2, false>, prefill_lds(128, 2));
+    set((const void *)prefill_attn_kernel<64, 2, false>, prefill_lds(64, 2));
     set((const void *)hybrid_attn_kernel<128>, prefill_lds(128, 2));
     set((const void *)hybrid_attn_kernel<64>, prefill_lds(64, 2));
 }

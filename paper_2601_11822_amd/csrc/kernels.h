@@ -33,6 +33,9 @@ struct PrefillAttnArgs {
     float scale_log2;  // log2(e)/sqrt(hd)
     SeqInfo seq;       // seq.start[r] > 0: the rows are a later chunk of prompt r and also attend to its cached positions before them
     int Mt_out = 0;    // row tiles of the packed output matrix when it holds more rows than this call's (0: packed_mt of this call's rows)
+    int cus = 0;       // compute units of the launching stream's partition (0: the whole chip); scheduling only
+    float *park = nullptr;   // float32 scratch, free until the launch is done: without it two teams of waves where one would be faster
+    size_t park_cap = 0;     // elements
     bool pairs = true; // set by the launchers
 };
 void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &a);

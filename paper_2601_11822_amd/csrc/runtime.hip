@@ -611,6 +611,13 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     return !released_needed;
 }
 
+// Prompt attention's scratch: the projections' partial sums, which nobody needs between the QKV epilogue and the output projection.
+void lend_partials(PrefillAttnArgs &pa, const Workspace &w, int cus) {
+    pa.cus = cus;
+    pa.park = w.partials;
+    pa.park_cap = w.partial_cap;
+}
+
 // A pass of at most RS_STREAM_ROWS rows through a dense layer: T prompt rows (prompts or later chunks of them, placed by
 // seq), then B decode rows.  Every projection is a stream of its weights with the RMSNorm of its input folded in
 // (decode_gemm.hip), and the kernels in between belong to their producers: QKV stream, its epilogue (row scale, rotary,
@@ -656,6 +663,7 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     tick(c, side, 3);
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd, max_blk_p, c->pool.n_blocks, sl2, seq};
     pa.Mt_out = packed_mt(M);
+    lend_partials(pa, w, cus);
     DecodeAttnArgs da{w.qkv + (size_t)T * nqkv, nqkv, w.attn, kp, vp, dtables, ctx_lens, err, w.part_o, w.part_ml,
                       B, m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, max_ctx,
                       (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, sl2, cus < RS_TOTAL_CUS};
@@ -764,6 +772,7 @@ int32_t prefill_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, c
     bool ok = qkv_project(c, RS_SIDE_PREFILL, w, layer, skinny, T, seq, tables, max_blk, 0, nullptr, nullptr, 0);
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, tables, c->err_flag + RS_SIDE_PREFILL, m.n_q_heads, m.n_kv_heads, hd,
                        max_blk, c->pool.n_blocks, (float)(1.4426950408889634 / std::sqrt((double)hd)), seq};
+    lend_partials(pa, w, c->side[RS_SIDE_PREFILL].cus);
     launch_prefill_attention(st, pa);
     tick(c, RS_SIDE_PREFILL, 4);
     ok = run_post_attention(c, RS_SIDE_PREFILL, st, w, lw, c->packed[layer], c->moe[layer], (const bf16_t *)x_in, (bf16_t *)x_out, T, skinny) && ok;
@@ -828,6 +837,7 @@ int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, co
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd,
                        max_blk_p, c->pool.n_blocks, sl2, seq};
     pa.Mt_out = packed_mt(M);
+    lend_partials(pa, w, c->side[RS_SIDE_PREFILL].cus);
     if (B > 0) {
         DecodeAttnArgs da{w.qkv + (size_t)T * nqkv, nqkv, w.attn, kp, vp, dtables, ctx_lens, err, w.part_o, w.part_ml,
                           B, m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, max_ctx,

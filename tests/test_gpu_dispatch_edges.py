@@ -142,3 +142,33 @@ def test_prompt_attention_units(shape, lens, gain):
 @pytest.mark.parametrize("shape,lens,starts,ctx", [(S.ODD, [70], [32], [600, 5, 511, 512]), (S.MID, [200], [48], [1, 1025]), (S.TINY, [90, 300], [0, 16], [0, 700])])
 def test_hybrid_attention_in_one_launch(shape, lens, starts, ctx):
     _hybrid_case(shape, lens, starts, ctx)
+
+
+# the forms that prompt attention takes as the side's compute units become few: two teams of waves, one that does both
+# teams' work one after the other, tiles and pairs of tiles, decode rows in the same launch and in one of their own; with
+# one key tile a row, and with chunks that have earlier keys.  The same bits in all of them.
+@pytest.mark.parametrize("shape,lens,starts,ctx", [(S.MID, [4100], [0], []), (S.MID, [2200], [0], []), (S.MID, [64] * 24, [0] * 24, []), (S.MID, [1100, 65], [0, 0], []),
+                                                   (S.TINY, [130] * 40, [0] * 40, []), (S.MID, [1500], [272], [5, 700, 1030]), (S.ODD, [900, 40], [0, 64], [300]),
+                                                   (S.TINY, [2000, 700], [16, 48], [40, 512])])
+def test_prompt_attention_same_bits_on_every_partition(shape, lens, starts, ctx):
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, B = int(cu[-1]), len(ctx)
+    held = [s + n for s, n in zip(starts, lens)] + [c + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=26)
+    rig = Rig(shape, n_blocks, T + B, max(B, 1), max(held) + 1, with_oracle=False)
+    try:
+        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
+        rig.load_pools_from_logical(S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2))
+        xb = S.hidden_states(T + B, shape.d_model, stream=26)
+        want = None
+        for split in ((256, 256), (192, 64), (128, 128), (96, 160), (64, 192)):
+            print("split", split, flush=True)
+            rig.ctx.set_cu_split(*split)
+            y = rig.hybrid(xb, cu, starts, tabs[:len(lens)], np.asarray(ctx, np.int32) if B else None, tabs[len(lens):] if B else None)
+            got = (rig.ctx.debug_read_workspace(rs.RS_SIDE_PREFILL, 2, (T + B, shape.q_dim)), y)
+            want = want or got
+            for name, a, b in zip(("attention", "y"), got, want):
+                assert np.array_equal(a, b), f"{name} differs at split {split}"
+    finally:
+        rig.close()
