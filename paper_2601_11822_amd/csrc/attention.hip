@@ -823,12 +823,24 @@ void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &args) {
     else launch_prefill_form<64>(st, a, f);
 }
 
+// One launch for both kinds of rows while the prompt rows leave most units to the others: half of the whole chip (512 rows of
+// 32 heads behind 1024 cached tokens beside 64 decode rows: 131 us, 141 in two launches; 2048 rows 132 and 121), a quarter of a
+// partition, where decode rows need every unit for themselves (the 512 rows on 128 CUs 215 and 173 us; 100 rows beside 28: 48 and
+// 59).  Or beside so few decode workgroups that it is the launch that counts (200 and 300 rows beside one: 29 and 35 us).
 void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &pargs, const DecodeAttnArgs &d) {
     PrefillAttnArgs p = pargs;
-    const int tiles = prefill_unit_count(p, false) * p.Hq;
-    p.pairs = tiles > 256;
-    const int n_prefill = p.pairs ? prefill_unit_count(p, true) * p.Hq : tiles;
-    const dim3 grid(n_prefill + (d.Hkv + 1) / 2 * d.n_chunks * d.B);
+    const PrefillForm f = prefill_form(p);
+    const int pairs = prefill_unit_count(p, true) * p.Hq, n_decode = (d.Hkv + 1) / 2 * d.n_chunks * d.B;
+    const int cus = prefill_cus(p), most = cus >= 256 ? cus / 2 : cus / 4;
+    const bool light = f.teams && (8 * n_decode <= cus || f.tiles + n_decode <= cus);
+    if (!f.split || !(light || pairs <= most)) {
+        launch_prefill_attention(st, pargs);
+        launch_decode_attention(st, d);
+        return;
+    }
+    p.pairs = light ? f.pairs : f.tiles > most;
+    const int n_prefill = p.pairs ? pairs : f.tiles;
+    const dim3 grid(n_prefill + n_decode);
     if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_kernel<128>, grid, dim3(512), prefill_lds(128, 2), st, p, d, n_prefill);
     else hipLaunchKernelGGL(hybrid_attn_kernel<64>, grid, dim3(512), prefill_lds(64, 2), st, p, d, n_prefill);
     launch_decode_combine(st, d);

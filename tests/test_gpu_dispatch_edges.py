@@ -148,7 +148,7 @@ def test_hybrid_attention_in_one_launch(shape, lens, starts, ctx):
 # teams' work one after the other, tiles and pairs of tiles, decode rows in the same launch and in one of their own; with
 # one key tile a row, and with chunks that have earlier keys.  The same bits in all of them.
 @pytest.mark.parametrize("shape,lens,starts,ctx", [(S.MID, [4100], [0], []), (S.MID, [2200], [0], []), (S.MID, [64] * 24, [0] * 24, []), (S.MID, [1100, 65], [0, 0], []),
-                                                   (S.TINY, [130] * 40, [0] * 40, []), (S.MID, [1500], [272], [5, 700, 1030]), (S.ODD, [900, 40], [0, 64], [300]),
+                                                   (S.TINY, [130] * 40, [0] * 40, []), (S.MID, [4100], [0], [3, 600]), (S.MID, [1500], [272], [5, 700, 1030]), (S.ODD, [900, 40], [0, 64], [300]),
                                                    (S.TINY, [2000, 700], [16, 48], [40, 512])])
 def test_prompt_attention_same_bits_on_every_partition(shape, lens, starts, ctx):
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -170,5 +170,28 @@ def test_prompt_attention_same_bits_on_every_partition(shape, lens, starts, ctx)
             want = want or got
             for name, a, b in zip(("attention", "y"), got, want):
                 assert np.array_equal(a, b), f"{name} differs at split {split}"
+    finally:
+        rig.close()
+
+
+# the sums of a prompt's rows are cut into even and odd key tiles by the prompts alone, whether decode rows are beside them or
+# not: few prompt workgroups, as many as one launch takes, more than that, and more than are cut at all
+@pytest.mark.parametrize("lens", [[1100], [2100], [4100], [130] * 33])
+def test_prompt_attention_same_bits_beside_decode_rows(lens):
+    shape, ctx = S.MID, [3, 600]
+    cu, starts = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), [0] * len(lens)
+    T, held = int(cu[-1]), lens + [c + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=27)
+    rig = Rig(shape, n_blocks, T + len(ctx), len(ctx), max(held) + 1, with_oracle=False)
+    try:
+        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
+        rig.load_pools_from_logical(S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2))
+        xb = S.hidden_states(T + len(ctx), shape.d_model, stream=27)
+        read = lambda: rig.ctx.debug_read_workspace(rs.RS_SIDE_PREFILL, 2, (T, shape.q_dim))
+        rig.hybrid(xb[:T], cu, starts, tabs[:len(lens)])
+        alone = read()
+        rig.hybrid(xb, cu, starts, tabs[:len(lens)], np.asarray(ctx, np.int32), tabs[len(lens):])
+        assert np.array_equal(read(), alone)
     finally:
         rig.close()
