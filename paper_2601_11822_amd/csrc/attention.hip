@@ -330,7 +330,62 @@ __global__ __launch_bounds__(HD) void decode_combine_kernel(DecodeAttnArgs a) {
     *op = (bf16_t)(l > 0.f ? sum / l : 0.f);
 }
 
+// The same sums, to the bit, where no context has more than RS_FEW_CHUNKS chunks (NC: 1, 2 or 4, the most that the bound of the
+// contexts allows): a thread per column, everything it needs requested together.  Few registers and no barriers: with hundreds
+// of short contexts that is what counts (decode attention of 256 rows of 511 tokens, 8B heads, 64 CUs: 197 us with the kernel
+// above, 188 with this; 128 CUs 135 and 129).
+#define RS_FEW_CHUNKS 4
+template <int HD, int NC>
+__global__ __launch_bounds__(256) void decode_combine_few_kernel(DecodeAttnArgs a) {
+    const int b = blockIdx.y, col = blockIdx.x * 256 + threadIdx.x, hq = col / HD;
+    if (hq >= a.Hq) return;
+    const size_t p0 = ((size_t)b * a.Hq + hq) * a.n_chunks;
+    const float2 *ml = (const float2 *)a.part_ml + p0;
+    const float *po = a.part_o + p0 * HD + col % HD;
+    float2 c[NC];
+    float v[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const int ci = min(i, a.n_chunks - 1);
+        c[i] = ml[ci];
+        v[i] = po[(size_t)ci * HD];
+    }
+    const int n_keys = a.ctx_lens[b] + 1;
+    bf16_t *op = a.out + packed_offset(a.out_row0 + b, col, a.out_Mt ? a.out_Mt : packed_mt(a.B)) + (col & 7);
+    if (n_keys < 1) {
+        *op = (bf16_t)0.f;
+        return;
+    }
+    const int nch = (min(n_keys, a.max_ctx) + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
+    float mx = NEG_INF;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) mx = fmaxf(mx, i < nch ? c[i].x : NEG_INF);
+    float s[RS_FEW_CHUNKS] = {}, l[RS_FEW_CHUNKS] = {};
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const float e = i < nch ? exp2f((c[i].x - (mx == NEG_INF ? 0.f : mx)) * a.scale_log2) : 0.f;
+        s[i] = i < nch ? __builtin_fmaf(v[i], e, 0.f) : 0.f;   // (products of their own: not to be contracted with the sums)
+        l[i] = i < nch ? __builtin_fmaf(c[i].y, e, 0.f) : 0.f;
+    }
+    static_assert(RS_FEW_CHUNKS == 4, "a chunk a quarter there, a lane of the wave's sum each");
+    const float sum = (s[0] + s[1]) + (s[2] + s[3]), tot = (l[0] + l[2]) + (l[1] + l[3]);
+    *op = (bf16_t)(tot > 0.f ? sum / tot : 0.f);
+}
+
+template <int HD>
+static void launch_decode_combine_few(hipStream_t st, const DecodeAttnArgs &a) {
+    const dim3 grid((a.Hq * HD + 255) / 256, a.B);
+    if (a.n_chunks == 1) hipLaunchKernelGGL((decode_combine_few_kernel<HD, 1>), grid, dim3(256), 0, st, a);
+    else if (a.n_chunks == 2) hipLaunchKernelGGL((decode_combine_few_kernel<HD, 2>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((decode_combine_few_kernel<HD, RS_FEW_CHUNKS>), grid, dim3(256), 0, st, a);
+}
+
 static void launch_decode_combine(hipStream_t st, const DecodeAttnArgs &a) {
+    if (a.n_chunks <= RS_FEW_CHUNKS) {
+        if (a.hd == 128) launch_decode_combine_few<128>(st, a);
+        else launch_decode_combine_few<64>(st, a);
+        return;
+    }
     if (a.hd == 128) hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(a.Hq, a.B), dim3(128), 0, st, a);
     else hipLaunchKernelGGL(decode_combine_kernel<64>, dim3(a.Hq, a.B), dim3(64), 0, st, a);
 }

@@ -195,3 +195,37 @@ def test_prompt_attention_same_bits_beside_decode_rows(lens):
         assert np.array_equal(read(), alone)
     finally:
         rig.close()
+
+
+# merging the chunks of a context: a launch for few chunks and one for any number, the same bits for a context that both take
+# (the bound of the batch's contexts chooses); empty, one-chunk, edge and longest contexts, odd numbers of heads, more than 64 chunks
+@pytest.mark.parametrize("shape", [S.TINY, S.MID, S.ODD])
+def test_decode_chunk_merge(shape):
+    ctx = np.array([0, 1, 510, 511, 512, 1023, 1024, 1535, 1536, 2047, 700], np.int32)
+    B, far = len(ctx), 34000
+    n_blocks = int(sum(S.blocks_for(int(c) + 1) for c in ctx)) + S.blocks_for(far + 1) + 2
+    tabs = S.shuffled_block_tables([int(c) + 1 for c in ctx] + [far + 1], n_blocks, stream=28)
+    rig = Rig(shape, n_blocks, 16, B + 1, far + 1)
+    try:
+        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
+        kb, vb = S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2)
+        xb = S.hidden_states(B + 1, shape.d_model, stream=28)
+        read = lambda n: rig.ctx.debug_read_workspace(rs.RS_SIDE_DECODE, 2, (n, shape.q_dim))
+        got = []
+        for max_ctx in (512, 1024, 2048, 2560, 20000):
+            rows = np.flatnonzero(ctx < max_ctx)
+            rig.load_pools_from_logical(kb, vb)
+            rig.decode(xb[:B], np.minimum(ctx, max_ctx - 1), tabs[:B], max_ctx=max_ctx)
+            got.append((rows, read(B)))
+        for rows, bits in got:
+            assert np.array_equal(bits[rows], got[-1][1][rows])
+        # and against the oracle's attention on the kernel's own operands, with a context of 67 chunks among them
+        ctx2 = np.concatenate([ctx, [far]]).astype(np.int32)
+        rig.load_pools_from_logical(kb, vb)
+        rig.decode(xb, ctx2, tabs)
+        q = f32(rig.ctx.debug_read_workspace(rs.RS_SIDE_DECODE, 1, (B + 1, shape.qkv_dim)))[:, :shape.q_dim].reshape(B + 1, shape.n_q_heads, shape.head_dim)
+        K, V = f32(rig.k_bits_logical()), f32(rig.v_bits_logical())
+        ref = oracle.attn_paged(q, K, V, tabs, ctx2 + 1).reshape(B + 1, shape.q_dim)
+        check_tensor("attention", f32(read(B + 1)), ref)
+    finally:
+        rig.close()
