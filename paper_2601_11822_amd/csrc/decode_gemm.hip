@@ -489,7 +489,8 @@ static int row_grid(int M) { return M < 128 ? M : (M + 127) / 128 * 128; }
 // the rest decode rows):
 // K in the pool's fragment order (kpool_chunk_offset), V token-minor.  One thread owns 4 dims of a pair's
 // lower half and the matching 4 of the upper half.  A position outside the rotary table or a block id
-// outside the pool is never used as an index: the row's cache write is skipped and the error word raised.
+// outside the pool is never used as an index: the row's cache write is skipped (without a position q and k stay as they are) and
+// the error word raised.
 template <int HD>
 __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
     constexpr int TPH = HD / 8;           // threads per head
@@ -527,8 +528,7 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
     const float sc = a.S_ssq ? rs.scale(a.ssq_part, a.S_ssq, m, a.d, a.eps) : 1.0f;
     const f32x4 lo = sum[0] * sc, hi = sum[1] * sc;
     bf16x4 olo, ohi;
-    if (head < a.Hq + a.Hkv) {
-        if (!pos_ok) return;
+    if (head < a.Hq + a.Hkv && pos_ok) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const f32x4 &t = i < 2 ? cs01 : cs23;

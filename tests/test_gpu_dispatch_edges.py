@@ -263,3 +263,34 @@ def test_normalised_rows_can_be_read_back(T, B):
             assert np.array_equal(first, read(0)) and np.array_equal(act, rig.ctx.debug_read_workspace(side, 4, (M, shape.ffn_dim)))
     finally:
         rig.close()
+
+
+# a decode row whose position is outside the rotary table is reported; what comes out for it, and for the rows beside it, is a
+# function of the inputs and not of what the buffers held before
+@pytest.mark.parametrize("B", [3, 100, 130])
+def test_row_without_a_position_depends_on_its_inputs_alone(B):
+    shape, longest = S.WIDE, 48
+    ctx = (np.arange(B) % longest).astype(np.int32)
+    ctx[1] = longest                                              # the first position past the table
+    held = [longest + 1] * B
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=30)
+    rig = Rig(shape, n_blocks, 16, B, longest, max_pos=longest, with_oracle=False)
+    try:
+        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
+        cl, tab = torch.from_numpy(ctx).cuda(), torch.from_numpy(np.ascontiguousarray(tabs, np.int32)).cuda()
+        got = []
+        for other in (31, 32):
+            rig.decode(S.hidden_states(B, shape.d_model, stream=other), ctx % longest, tabs, max_ctx=longest)
+            rig.load_pools_from_logical(S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2))
+            x = to_dev(S.hidden_states(B, shape.d_model, stream=30))
+            y = torch.empty_like(x)
+            torch.cuda.synchronize()
+            rig.ctx.decode_layer(0, x, y, cl, tab, tab.shape[1], B, longest)
+            with pytest.raises(rs.RapidServeError) as e:
+                rig.ctx.sync(rs.RS_SIDE_DECODE)
+            assert e.value.code == rs.RS_ERR_BAD_BLOCK
+            got.append(y.clone())
+        assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
+    finally:
+        rig.close()
