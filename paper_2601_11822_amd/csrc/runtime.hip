@@ -179,8 +179,7 @@ struct rs_ctx {
     int32_t step_err = 0;            // bits met by serving steps and not yet reported
     Workspace ws[2];
     int last_rows[2] = {0, 0};   // rows of each side's last layer call: fixes the packed layout of h/attn/act
-    int folded_layer[2] = {-1, -1};   // the layer of each side's last call if that folded its RMSNorms into the projections (no normalised rows in h)
-    bool decode_folded = false;       // the decode side's last layer call did, with at most 64 rows
+    bool streamed[2] = {false, false};   // each side's last layer call folded its RMSNorms into the projections (no h buffer)
     // captured decode steps, keyed by everything a captured launch bakes in (rs_decode_layer_graph)
     struct GraphKey {
         int32_t layer, max_blk, B, max_ctx;
@@ -642,8 +641,7 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     float *ssq1 = w.ssq, *ssq2 = w.ssq + (size_t)ssq_slices(c) * RS_SSQ_ROWS;
     const int cus = c->side[side].cus;
     c->last_rows[side] = M;
-    c->folded_layer[side] = layer;
-    if (side == RS_SIDE_DECODE) c->decode_folded = M <= 64;
+    c->streamed[side] = true;
     auto stream = [&](const DGemmArgs &a, const DGemmPlan &p, const DFuseArgs &fz = DFuseArgs{}) {
         launch_dgemm_stream(st, a, p, fz, dgemm_prefers_half_height(p, cus));
     };
@@ -766,7 +764,7 @@ int32_t prefill_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, c
     if (streams(c, layer, T)) return stream_layer(c, RS_SIDE_PREFILL, w, layer, x_in, x_out, T, seq, tables, max_blk, 0, nullptr, nullptr, 0, 0);
     tick(c, RS_SIDE_PREFILL, 0);
     c->last_rows[RS_SIDE_PREFILL] = T;
-    c->folded_layer[RS_SIDE_PREFILL] = -1;
+    c->streamed[RS_SIDE_PREFILL] = false;
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, T, d, m.rms_eps);
     tick(c, RS_SIDE_PREFILL, 1);
     // a pass of at most 64 rows is bound by reading the weights once: it takes the weight-streaming kernels
@@ -831,7 +829,7 @@ int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, co
         return stream_layer(c, RS_SIDE_PREFILL, w, layer, x_in, x_out, T, seq, ptables, max_blk_p, B, ctx_lens, dtables, max_blk_d, max_ctx);
     tick(c, RS_SIDE_PREFILL, 0);
     c->last_rows[RS_SIDE_PREFILL] = M;
-    c->folded_layer[RS_SIDE_PREFILL] = -1;
+    c->streamed[RS_SIDE_PREFILL] = false;
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, M, d, m.rms_eps);
     tick(c, RS_SIDE_PREFILL, 1);
     const bool skinny = M <= 64;
@@ -879,8 +877,7 @@ int32_t decode_layer(rs_ctx *c, Workspace &w, int32_t layer, const void *x_in, v
     }
     const bool skinny = B <= 64;
     c->last_rows[RS_SIDE_DECODE] = B;
-    c->folded_layer[RS_SIDE_DECODE] = -1;
-    c->decode_folded = false;
+    c->streamed[RS_SIDE_DECODE] = false;
     tick(c, RS_SIDE_DECODE, 0);
     launch_rmsnorm(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, B, d, m.rms_eps);
     tick(c, RS_SIDE_DECODE, 1);
@@ -910,7 +907,6 @@ int32_t head_greedy(rs_ctx *c, int side, const bf16_t *x, int n, float *logits, 
     for (int g0 = 0; g0 < n; g0 += group) {
         const int mg = std::min(group, n - g0);
         c->last_rows[side] = mg;
-        c->folded_layer[side] = -1;
         launch_rmsnorm(st, x + (size_t)g0 * d, (const bf16_t *)c->head.final_norm, w.h, mg, d, m.rms_eps);
         GemmArgs g{w.h, (const bf16_t *)c->head.lm_head, nullptr, c->packed_lm, nullptr, nullptr, nullptr, mg, V, d, EPI_STORE,
                    0, c->side[side].cus};
@@ -1618,8 +1614,8 @@ int32_t rs_debug_read_workspace(rs_ctx *c, int32_t side, int32_t which, void *ho
     size_t cap = 0;
     switch (which) {
         case 0:
-            if (side == RS_SIDE_DECODE && c->decode_folded)
-                return fail(RS_ERR_STATE, "this decode step folded its RMSNorms into the projections: no normalised rows were written");
+            if (c->streamed[side])
+                return fail(RS_ERR_STATE, "this pass folded its RMSNorms into the projections: no normalised rows were written");
             src = w.h; cap = (size_t)w.rows * m.d_model * 2; break;  // (decode buffers are at least 64 rows)
         case 1: src = w.qkv; cap = (size_t)w.rows * nqkv * 2; break;
         case 2: src = w.attn; cap = (size_t)w.rows * qd * 2; break;
@@ -1629,12 +1625,6 @@ int32_t rs_debug_read_workspace(rs_ctx *c, int32_t side, int32_t which, void *ho
     }
     if (!src || (size_t)n_bytes > cap) return fail(RS_ERR_BAD_ARG, "workspace buffer %d holds %zu bytes", which, cap);
     if (c->side[side].stream) HIP_TRY(hipStreamSynchronize(c->side[side].stream));
-    if (which == 0 && c->folded_layer[side] >= 0) {   // h holds the gate/up stream's operand instead: the rows are made now
-        HIP_TRY(hipSetDevice(c->device));
-        launch_rmsnorm(c->side[side].stream, w.x1, (const bf16_t *)c->weights[c->folded_layer[side]].g2, w.h, c->last_rows[side], m.d_model, m.rms_eps);
-        HIP_TRY(hipStreamSynchronize(c->side[side].stream));
-        c->folded_layer[side] = -1;
-    }
     if (which == 0 || which == 2 || which == 4) {
         // undo the fragment-packed layout of the GEMM inputs: row-major out
         const int width = which == 0 ? m.d_model : which == 2 ? (int)qd : m.ffn_dim;

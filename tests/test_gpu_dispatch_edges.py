@@ -231,40 +231,6 @@ def test_decode_chunk_merge(shape):
         rig.close()
 
 
-# the normalised rows in front of the feed-forward block can be read back after every pass, also where the pass itself needs
-# none; only decode steps of at most 64 rows never had any
-@pytest.mark.parametrize("T,B", [(40, 0), (128, 0), (150, 0), (30, 20), (0, 100), (0, 150), (0, 64)])
-def test_normalised_rows_can_be_read_back(T, B):
-    shape, M = S.WIDE, T + B
-    ctx = np.arange(B, dtype=np.int32)
-    held = ([T] if T else []) + [int(c) + 1 for c in ctx]
-    n_blocks = sum(S.blocks_for(n) for n in held) + 2
-    tabs = S.shuffled_block_tables(held, n_blocks, stream=29)
-    rig = Rig(shape, n_blocks, max(M, 1), max(B, 1), max(held) + 1, n_layers=2, with_oracle=False)
-    try:
-        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
-        xb, side = S.hidden_states(M, shape.d_model, stream=29), rs.RS_SIDE_PREFILL if T else rs.RS_SIDE_DECODE
-        for layer in (0, 1):
-            rig.load_pools_from_logical(S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2), layer)
-            if not T:
-                rig.decode(xb, ctx, tabs, layer=layer)
-            elif not B:
-                rig.prefill(xb, [0, T], tabs, layer=layer)
-            else:
-                rig.hybrid(xb, [0, T], [0], tabs[:1], ctx, tabs[1:], layer=layer)
-            read = lambda which: rig.ctx.debug_read_workspace(side, which, (M, shape.d_model))
-            if not T and B <= 64:
-                with pytest.raises(rs.RapidServeError) as e:
-                    read(0)
-                assert e.value.code == rs.RS_ERR_STATE
-                continue
-            first, act = read(0), rig.ctx.debug_read_workspace(side, 4, (M, shape.ffn_dim))
-            check_tensor("normalised rows", f32(first), oracle.rmsnorm(f32(read(3)), f32(rig.wbits[layer]["g2"]), shape.rms_eps))
-            assert np.array_equal(first, read(0)) and np.array_equal(act, rig.ctx.debug_read_workspace(side, 4, (M, shape.ffn_dim)))
-    finally:
-        rig.close()
-
-
 # a decode row whose position is outside the rotary table is reported; what comes out for it, and for the rows beside it, is a
 # function of the inputs and not of what the buffers held before
 @pytest.mark.parametrize("B", [3, 100, 130])
