@@ -324,7 +324,9 @@ int32_t rs_debug_mfma_probe(rs_ctx *ctx, int32_t side, float *tflops_out);
 int32_t rs_debug_cu_histogram_graph(rs_ctx *ctx, int32_t side, int32_t n_workgroups, int32_t *hist_out);
 
 /* Copies an intermediate activation buffer of a side's last layer call to host memory (after
- * waiting for that side): which = 0 first RMSNorm output [M,d]; 1 q|k|v with rotated q and k
+ * waiting for that side): which = 0 the normalised rows that the feed-forward block read [M,d]
+ * (RS_ERR_STATE after a pass of at most 128 rows through a dense layer of usual widths: it folds
+ * its RMSNorms into the projections and makes none); 1 q|k|v with rotated q and k
  * [M,(Hq+2Hkv)hd]; 2 attention output [M,Hq*hd]; 3 hidden state after the attention residual
  * [M,d]; 4 silu(gate)*up [M,ffn].  All bf16, row-major whatever the library's internal layout
  * (n_bytes = whole rows, at most the rows of that call).  For stage-by-stage checks. */

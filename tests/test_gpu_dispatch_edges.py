@@ -260,3 +260,33 @@ def test_row_without_a_position_depends_on_its_inputs_alone(B):
         assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
     finally:
         rig.close()
+
+
+# the normalised rows can be read back where the pass made some, as the header says; a pass that folds its norms has none
+@pytest.mark.parametrize("T,B", [(40, 0), (128, 0), (129, 0), (30, 20), (100, 60), (0, 1), (0, 128), (0, 129)])
+def test_normalised_rows_where_there_are_some(T, B):
+    shape, M = S.WIDE, T + B
+    ctx = np.arange(B, dtype=np.int32)
+    held = ([T] if T else []) + [int(c) + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=29)
+    rig = Rig(shape, n_blocks, max(M, 1), max(B, 1), max(held) + 1, with_oracle=False)
+    try:
+        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
+        rig.load_pools_from_logical(S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2))
+        xb, side = S.hidden_states(M, shape.d_model, stream=29), rs.RS_SIDE_PREFILL if T else rs.RS_SIDE_DECODE
+        if not T:
+            rig.decode(xb, ctx, tabs)
+        elif not B:
+            rig.prefill(xb, [0, T], tabs)
+        else:
+            rig.hybrid(xb, [0, T], [0], tabs[:1], ctx, tabs[1:])
+        read = lambda which: rig.ctx.debug_read_workspace(side, which, (M, shape.d_model))
+        if M <= 128:
+            with pytest.raises(rs.RapidServeError) as e:
+                read(0)
+            assert e.value.code == rs.RS_ERR_STATE
+        else:
+            check_tensor("normalised rows", f32(read(0)), oracle.rmsnorm(f32(read(3)), f32(rig.wbits[0]["g2"]), shape.rms_eps))
+    finally:
+        rig.close()
