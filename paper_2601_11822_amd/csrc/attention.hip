@@ -413,8 +413,8 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 // staging registers, no LDS stores).
 //
 // A launch that leaves compute units idle or with one workgroup takes two teams of four waves a workgroup, which share out the
-// key tiles: with one wave per SIMD every wait is exposed.  On 256 CUs, one team / two (8B heads): 2048 tokens 83 / 68 us, a
-// 512-token chunk behind 1024 cached tokens 76 / about 50.  Where there are more workgroups than units it takes one team: two
+// key tiles: with one wave per SIMD every wait is exposed.  On 256 CUs, one team / two (8B heads): 2048 tokens 64 / 57 us,
+// 1536 tokens 46 / 38, 1024 tokens 33 / 30.  Where there are more workgroups than units it takes one team: two
 // workgroups on a unit overlap better than two teams at one barrier (prefill_form below).
 //
 // What bounds it on long prompts: every wave reads the whole 32 KB K/V tile from LDS for its 32 queries, one
@@ -681,19 +681,20 @@ __device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int 
                     const auto sw = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
                     m_tile = fmaxf(__builtin_bit_cast(float, (uint32_t)sw[0]), __builtin_bit_cast(float, (uint32_t)sw[1]));
                 }
-                // The reference of the exponentials follows the running maximum only once it is more than 2^8 behind in some
-                // row: until then no weight exceeds 256 and nothing is rescaled (the weights' precision is relative).
-                // With random scores one of a wave's 32 rows has a new maximum in two tiles of three (16384 tokens, 8B heads:
-                // 2500 -> 2360 us with this and the exponentials of a block under the products of the one before).
-                if (__any((m_tile - m_run) * sc > 8.f)) {
-                    const float m_new = fmaxf(m_run, m_tile);
-                    const float alpha = __builtin_amdgcn_exp2f((m_run - (m_new == NEG_INF ? 0.f : m_new)) * sc);
+                // The reference of the exponentials is the running maximum itself: the largest weights then sit at the top of a
+                // binade, where bf16 is finest, the largest of all exactly.  A reference that is followed only once it is 2^8
+                // behind saves the rescaling of two tiles in three (16384 tokens, 8B heads: 2314 -> 2211 us) and was taken back:
+                // the attention's error against float64 was 5 to 12 % larger (4096 tokens 0.00193 -> 0.00216 of the result).
+                const float m_new = fmaxf(m_run, m_tile);
+                const float m_safe = m_new == NEG_INF ? 0.f : m_new;
+                if (__any(m_new != m_run)) {
+                    const float alpha = __builtin_amdgcn_exp2f((m_run - m_safe) * sc);
                     l_run *= alpha;
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) o[dt] = o[dt] * alpha;
                     m_run = m_new;
                 }
-                const float ms = (m_run == NEG_INF ? 0.f : m_run) * sc;
+                const float ms = m_safe * sc;
                 float psum = 0.f;
                 // V fragments are read one block (DT fragments) ahead of their MFMAs
                 bf16x8 vfr[2][DT];
@@ -843,10 +844,10 @@ static int prefill_unit_count(const PrefillAttnArgs &a, bool pairs) {
 // How a launch goes about its tiles.  Whether a row's sums are cut into even and odd key tiles (`split`) follows from the sizes
 // alone: 256 workgroups or fewer, what the whole chip takes at a time.  By whom they are computed, and in what order, from
 // the compute units `cus` too, with the same bits.  A unit holds one workgroup of two teams or two of one team, so two teams
-// only where all pairs of tiles fit at a time: 2048 rows of 32 heads (256 pairs) on 256 / 192 / 128 / 64 CUs 56 / 88 /
-// 86 / 166 us with two teams, 71 / 61 / 80 / 146 with one.  Pairs of tiles where they about fill the places, else single ones, heaviest first:
-// those even out whatever the number (3000 rows, 384 pairs, on 256 CUs 117 / 97 us, on 192 CUs, all places filled, 114 / 118;
-// 1536 rows on 128 CUs 65 / 56).
+// only where all pairs of tiles fit at a time: 2048 rows of 32 heads (256 pairs) on 256 / 192 / 128 / 64 CUs 57 / 72 /
+// 91 / 176 us with two teams, 66 / 63 / 84 / 153 with one (putting the even tiles' sums away costs it 2 us a tile).  Pairs of
+// tiles where they about fill the places, else single ones, heaviest first: those even out whatever the number (3000 rows, 384
+// pairs, on 256 CUs 125 / 102 us, on 192 CUs, all places filled, 122 / 126; 1536 rows on 128 CUs 69 / 58).
 struct PrefillForm { bool split, teams, pairs; int tiles, wgs; };
 static bool prefill_pairs_fill(int pairs, int places) { return pairs <= places && 10 * pairs > 9 * places; }
 static int prefill_cus(const PrefillAttnArgs &a) { return a.cus > 0 ? a.cus : 256; }

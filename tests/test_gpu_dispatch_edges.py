@@ -113,7 +113,7 @@ def test_sparse_block_tiles(n):
 
 # prompt attention: single 128-query tiles and pairs of them, one and two teams over the key tiles, at odd and even numbers
 # of 64-key tiles; own operands (the kernel's q and cache, the oracle's attention).  A gain of 8 makes the scores large
-# enough (tens of powers of two) that the reference of the exponentials has to follow the maximum.
+# (tens of powers of two): the maximum moves far from tile to tile.
 @pytest.mark.parametrize("gain", [1.0, 8.0])
 @pytest.mark.parametrize("shape,lens", [(S.TINY, [64]), (S.MID, [65]), (S.MID, [129]), (S.TINY, [700]), (S.MID, [300, 1, 200]),
                                         (S.MID, [4100]), (S.MID, [4224]), (S.MID, [130] * 63 + [257]), (S.TINY, [130] * 64), (S.ODD, [200])])
@@ -288,5 +288,38 @@ def test_normalised_rows_where_there_are_some(T, B):
             assert e.value.code == rs.RS_ERR_STATE
         else:
             check_tensor("normalised rows", f32(read(0)), oracle.rmsnorm(f32(read(3)), f32(rig.wbits[0]["g2"]), shape.rms_eps))
+    finally:
+        rig.close()
+
+
+# prompt attention rounds two things to bf16: the weights, relative to the row's maximum (the largest is exactly 1, those next to
+# it sit where bf16 is finest), and the output.  Its error is no larger than that of a float64 evaluation with these two roundings
+# (2 % for the sample; weights relative to a lagging maximum, anywhere in their binades, showed 5 to 6 % more)
+@pytest.mark.parametrize("shape,T", [(S.TINY, 1500), (S.MID, 2048), (S.MID, 4300), (S.MID, 8300)])
+def test_prompt_attention_error(shape, T):
+    n_blocks = S.blocks_for(T) + 2
+    tabs, cu = S.shuffled_block_tables([T], n_blocks, stream=33), np.array([0, T], np.int32)
+    rig = Rig(shape, n_blocks, T, 1, T + 1, with_oracle=False)
+    try:
+        w, gain = rig.wdev[0], (4096 / shape.d_model) ** 0.5        # scores as spread as those of a 4096-wide layer
+        rig.ctx.set_weights(0, w["g1"] * gain, w["wqkv"], w["wo"], w["g2"], w["wg"], w["wu"], w["wd"])
+        rig.prefill(S.hidden_states(T, shape.d_model, stream=33), cu, tabs)
+        dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda().double()
+        read = lambda which, width: dev(f32(rig.ctx.debug_read_workspace(rs.RS_SIDE_PREFILL, which, (T, width))))
+        q, got = read(1, shape.qkv_dim)[:, :shape.q_dim].reshape(T, shape.n_q_heads, shape.head_dim), read(2, shape.q_dim).reshape(T, shape.n_q_heads, shape.head_dim)
+        k, v = (dev(t) for t in gather_prompt_kv(rig, cu, tabs))
+        later = torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1)
+        err = ideal = 0.0
+        for h in range(shape.n_q_heads):
+            kv = h * shape.n_kv_heads // shape.n_q_heads
+            s = (q[:, h] @ k[:, kv].t().contiguous() / shape.head_dim ** 0.5).masked_fill(later, float("-inf"))
+            p = (s - s.max(1, keepdim=True).values).exp()
+            total = p.sum(1, keepdim=True)
+            exact = p @ v[:, kv].contiguous() / total
+            rounded = (p.bfloat16().double() @ v[:, kv].contiguous() / total).bfloat16().double()
+            err += float((got[:, h] - exact).square().sum())
+            ideal += float((rounded - exact).square().sum())
+        print(f"error {(err / ideal) ** 0.5:.4f} of the two roundings'", flush=True)
+        assert err <= 1.02 ** 2 * ideal
     finally:
         rig.close()
