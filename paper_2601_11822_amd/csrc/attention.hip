@@ -413,9 +413,9 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 // staging registers, no LDS stores).
 //
 // A launch that leaves compute units idle or with one workgroup takes two teams of four waves a workgroup, which share out the
-// key tiles: with one wave per SIMD every wait is exposed.  On 256 CUs, one team / two (8B heads): 2048 tokens 64 / 57 us,
-// 1536 tokens 46 / 38, 1024 tokens 33 / 30.  Where there are more workgroups than units it takes one team: two
-// workgroups on a unit overlap better than two teams at one barrier (prefill_form below).
+// key tiles: with one wave per SIMD every wait is exposed.  On 256 CUs, one team / two (8B heads): 1024 tokens 33 / 30 us, 512
+// 20 / 19, a 512-token chunk behind 1024 cached tokens 52 / 46, behind 4000 118 / 100.  Where there are more workgroups than
+// units it takes one team: two workgroups on a unit overlap better than two teams at one barrier (prefill_form below).
 //
 // What bounds it on long prompts: every wave reads the whole 32 KB K/V tile from LDS for its 32 queries, one
 // kilobyte of LDS reads per MFMA, which with four matrix cores per CU is the LDS's whole bandwidth (128 bytes
@@ -842,12 +842,14 @@ static int prefill_unit_count(const PrefillAttnArgs &a, bool pairs) {
 }
 
 // How a launch goes about its tiles.  Whether a row's sums are cut into even and odd key tiles (`split`) follows from the sizes
-// alone: 256 workgroups or fewer, what the whole chip takes at a time.  By whom they are computed, and in what order, from
-// the compute units `cus` too, with the same bits.  A unit holds one workgroup of two teams or two of one team, so two teams
-// only where all pairs of tiles fit at a time: 2048 rows of 32 heads (256 pairs) on 256 / 192 / 128 / 64 CUs 57 / 72 /
-// 91 / 176 us with two teams, 66 / 63 / 84 / 153 with one (putting the even tiles' sums away costs it 2 us a tile).  Pairs of
-// tiles where they about fill the places, else single ones, heaviest first: those even out whatever the number (3000 rows, 384
-// pairs, on 256 CUs 125 / 102 us, on 192 CUs, all places filled, 122 / 126; 1536 rows on 128 CUs 69 / 58).
+// alone: no more tiles than the whole chip has units.  By whom they are computed, and in what order, from the compute units
+// `cus` too, with the same bits.  A unit holds one workgroup of two teams or two of one team, so two teams only where all
+// pairs of tiles fit at a time: 1024 rows of 32 heads (256 tiles, 128 pairs) on 256 / 128 / 96 / 64 CUs 30 / 33 / 47 / 60 us
+// with two teams, 36 / 36 / 41 / 54 with one that cuts (putting the even tiles' sums away costs it 2 us a tile), 33 / 33 / 35 / 47 with
+// one that does not.  Not cut: 2048 rows on 256 / 192 / 128 / 64 CUs 64 / 58 / 78 / 138 us, where two teams and a team that cuts
+// took 57 / 63 / 84 / 153; with earlier keys two teams are ahead for longer (1024 rows behind 4000 tokens on 256 CUs 118 / 142).
+// Pairs of tiles where they about fill the places, else single ones, heaviest first: those even out whatever the number
+// (3000 rows, 384 pairs, on 256 CUs 125 / 102 us, on 192 CUs, all places filled, 122 / 126; 1536 rows on 128 CUs 62 / 51).
 struct PrefillForm { bool split, teams, pairs; int tiles, wgs; };
 static bool prefill_pairs_fill(int pairs, int places) { return pairs <= places && 10 * pairs > 9 * places; }
 static int prefill_cus(const PrefillAttnArgs &a) { return a.cus > 0 ? a.cus : 256; }
@@ -855,7 +857,7 @@ static PrefillForm prefill_form(const PrefillAttnArgs &a) {
     const int pairs = prefill_unit_count(a, true) * a.Hq, cus = prefill_cus(a);
     PrefillForm f{};
     f.tiles = prefill_unit_count(a, false) * a.Hq;
-    f.split = pairs <= 256;
+    f.split = f.tiles <= 256;
     const size_t parked = (size_t)f.tiles * 128 * a.hd;
     f.teams = f.split && (pairs <= cus || !a.park || parked > a.park_cap);
     f.pairs = prefill_pairs_fill(pairs, f.teams ? cus : 2 * cus);

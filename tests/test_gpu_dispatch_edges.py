@@ -147,8 +147,8 @@ def test_hybrid_attention_in_one_launch(shape, lens, starts, ctx):
 # the forms that prompt attention takes as the side's compute units become few: two teams of waves, one that does both
 # teams' work one after the other, tiles and pairs of tiles, decode rows in the same launch and in one of their own; with
 # one key tile a row, and with chunks that have earlier keys.  The same bits in all of them.
-@pytest.mark.parametrize("shape,lens,starts,ctx", [(S.MID, [4100], [0], []), (S.MID, [2200], [0], []), (S.MID, [64] * 24, [0] * 24, []), (S.MID, [1100, 65], [0, 0], []),
-                                                   (S.TINY, [130] * 40, [0] * 40, []), (S.MID, [4100], [0], [3, 600]), (S.MID, [1500], [272], [5, 700, 1030]), (S.ODD, [900, 40], [0, 64], [300]),
+@pytest.mark.parametrize("shape,lens,starts,ctx", [(S.MID, [4100], [0], []), (S.MID, [4000], [0], []), (S.MID, [2200], [0], []), (S.MID, [64] * 24, [0] * 24, []), (S.MID, [1100, 65], [0, 0], []),
+                                                   (S.TINY, [130] * 40, [0] * 40, []), (S.TINY, [130] * 30, [0] * 30, []), (S.MID, [4100], [0], [3, 600]), (S.MID, [1500], [272], [5, 700, 1030]), (S.ODD, [900, 40], [0, 64], [300]),
                                                    (S.TINY, [2000, 700], [16, 48], [40, 512])])
 def test_prompt_attention_same_bits_on_every_partition(shape, lens, starts, ctx):
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -176,7 +176,7 @@ def test_prompt_attention_same_bits_on_every_partition(shape, lens, starts, ctx)
 
 # the sums of a prompt's rows are cut into even and odd key tiles by the prompts alone, whether decode rows are beside them or
 # not: few prompt workgroups, as many as one launch takes, more than that, and more than are cut at all
-@pytest.mark.parametrize("lens", [[1100], [2100], [4100], [130] * 33])
+@pytest.mark.parametrize("lens", [[1100], [2100], [4000], [4100], [130] * 33])
 def test_prompt_attention_same_bits_beside_decode_rows(lens):
     shape, ctx = S.MID, [3, 600]
     cu, starts = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), [0] * len(lens)
