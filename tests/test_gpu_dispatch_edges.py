@@ -1,5 +1,5 @@
-"""Each branch of the kernels' dispatch at the sizes where it can go wrong: the edges of its tiles, remainders, the
-smallest and largest of its range."""
+"""Branches of the kernels' dispatch at the sizes where they can go wrong: the edges of their tiles, remainders, the
+smallest and largest of their range, and what must not depend on the branch."""
 import numpy as np
 import pytest
 import torch
@@ -321,5 +321,49 @@ def test_prompt_attention_error(shape, T):
             ideal += float((rounded - exact).square().sum())
         print(f"error {(err / ideal) ** 0.5:.4f} of the two roundings'", flush=True)
         assert err <= 1.02 ** 2 * ideal
+    finally:
+        rig.close()
+
+
+# passes of the large layer shapes at row counts and partitions that take every form of their streams and epilogues: three and
+# four row tiles with full-height and half-height workgroups, the gain folded in while the rows are staged or by a launch in front,
+# and above 128 rows the K-sliced projections with the output projection's residual and norm in one (widths up to 4096 and
+# above).  The same bits on every partition; sampled rows against the oracle.
+@pytest.mark.parametrize("shape,passes", [(S.LLAMA8B, [([96], 0), ([70, 58], 0), ([], 65), ([], 128), ([60], 68), ([129], 0), ([100], 60)]),
+                                          (S.LLAMA70B, [([33], 0), ([128], 0), ([], 101), ([150, 50], 0), ([300], 0)])])
+def test_large_layer_passes_same_bits_on_every_partition(shape, passes):
+    B_max, T_max = max(B for _, B in passes), max(sum(lens) for lens, _ in passes)
+    ctx_all = np.array([(37 * i + 5) % 600 for i in range(max(B_max, 1))], np.int32)
+    n_blocks = sum(S.blocks_for(int(c) + 1) for c in ctx_all) + T_max // 16 + 8
+    rig = Rig(shape, n_blocks, max(T + B for T, B in ((sum(l), b) for l, b in passes)), max(B_max, 1), 608)
+    try:
+        L = rig.olayers[0]
+        kb, vb = S.kv_cache_bits(n_blocks, shape.n_kv_heads, shape.head_dim)
+        for lens, B in passes:
+            T, ctx = sum(lens), ctx_all[:B]
+            cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+            tabs = S.shuffled_block_tables(list(lens) + [int(c) + 1 for c in ctx], n_blocks, stream=34)
+            ptab, dtab = tabs[:len(lens)], tabs[len(lens):]
+            xb = S.hidden_states(T + B, shape.d_model, stream=34)
+            want = None
+            for split in ((256, 256), (128, 128), (160, 96), (64, 192), (192, 64)):
+                print(shape.name, lens, B, split, flush=True)
+                rig.ctx.set_cu_split(*split)
+                rig.load_pools_from_logical(kb, vb)
+                if not T:
+                    y = rig.decode(xb, ctx, dtab)
+                elif not B:
+                    y = rig.prefill(xb, cu, ptab)
+                else:
+                    y = rig.hybrid(xb, cu, [0] * len(lens), ptab, ctx, dtab)
+                want = y if want is None else want
+                assert np.array_equal(y, want), f"y differs at split {split}"
+            x, Kc, Vc = f32(xb), f32(kb), f32(vb)
+            if T:
+                rows = np.unique(np.array([0, T // 2, T - 1], np.int32))
+                check_tensor("prompt rows", f32(want)[rows], L.prefill(x[:T], cu, ptab, Kc, Vc, rows=rows), x[rows], 2, elem_mult=END_TO_END)
+            if B:
+                rows = np.unique(np.array([0, B // 2, B - 1]))
+                check_tensor("decode rows", f32(want)[T + rows], L.decode(x[T + rows], ctx[rows], dtab[rows], Kc, Vc), x[T + rows], 2, elem_mult=END_TO_END)
     finally:
         rig.close()

@@ -354,11 +354,11 @@ def test_serving_step_small_stack_matches_oracle():
         rig.close()
 
 
-@pytest.mark.parametrize("lens", [[40], [33, 31], [150, 50], [65]])
+@pytest.mark.parametrize("lens", [[40], [33, 31], [150, 50], [65], [129]])
 def test_8b_layer_short_prefill_passes(lens):
-    """Llama-3-8B-shaped layer with a few dozen to a few hundred rows: up to 64 rows the pass takes the
-    weight-streaming GEMMs, above that the large-tile kernel with its K range cut into slices for the
-    projections back to d_model (few output tiles, long K).  Every stage and every row against the oracle.
+    """Llama-3-8B-shaped layer with a few dozen to a few hundred rows: up to 128 rows the pass streams its
+    weights, above that (129 rows the first) it takes the large-tile kernel with its K range cut into slices
+    where there are few output tiles.  Every stage and every row against the oracle.
 
     Every stage downstream of the QKV projection holds the stated 2e-2 element by element against the oracle's
     routine for that stage fed the kernel's own bf16 operands (check_stages_own_operands).  Against the fp32

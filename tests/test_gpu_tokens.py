@@ -398,9 +398,8 @@ def test_engine_generation_matches_oracle(n_blocks):
 
 
 def test_closed_loop_8b_shaped_layer_and_edge_prompts():
-    """One Llama-3-8B-shaped layer with a 32000-token vocabulary: prompts of 1 token, of 20 tokens (the pass
-    takes the weight-streaming GEMMs), of 70 tokens (large-tile GEMMs with a sliced K range) and of exactly
-    max_prefill_tokens, generated through the engine and checked token by token against the oracle."""
+    """One Llama-3-8B-shaped layer with a 32000-token vocabulary: prompts of 1 token, of 20 tokens, of 70 tokens
+    and of exactly max_prefill_tokens (all of them streamed passes, of one to three row tiles), generated through the engine and checked token by token against the oracle."""
     shape, n_layers, vocab = S.LLAMA8B, 1, 32000
     prompts = [(1, 70, 5, 0), (2, 20, 5, 0), (3, 1, 4, 1), (4, 96, 3, 2)]
     requests = [(rid, S.prompt_tokens(pl, vocab, rid), mn, arr) for rid, pl, mn, arr in prompts]
