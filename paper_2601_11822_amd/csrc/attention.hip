@@ -401,8 +401,8 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 
 // =============================================================================================
 // Prefill: causal attention of whole prompts, reading the K/V the same layer call has just
-// written to the pools.  A workgroup owns one query head and a PAIR of 128-query tiles of one
-// prompt, tile n-1-p then tile p, so that every workgroup does the same amount of causal work.
+// written to the pools.  A workgroup owns one query head and one 128-query tile of a prompt, or a PAIR of
+// them, tile n-1-p then tile p, so that every workgroup does the same amount of causal work.
 // Wave w owns 32 query rows of the tile; keys are consumed 64 (= 4 blocks) at a time through two
 // LDS buffers: the next key tile's global loads are in flight while the current one is multiplied,
 // one barrier per key tile.  The prompt's block ids are copied to LDS once, so a key tile costs one
