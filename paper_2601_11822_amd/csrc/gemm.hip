@@ -615,8 +615,8 @@ static void launch_direct(hipStream_t st, const GemmArgs &a) {
 
 // Grouped GEMM: rows laid out expert by expert, every unit of the work list (moe_plan_kernel) a tile of 128, 192 or 256
 // rows of one expert by 256 columns.  The arithmetic of an output element does not depend on the tile that holds it.
-// An expert's rows are cut into units of one height (two from four units on), so that the units that share its weights run through K at one pace
-// and fetch them together.  A 256-row tile beside a shorter one that runs ahead of it had every weight leave the L2 in
+// An expert's rows are cut into units of one height (two from four units on), so that the units that share its weights run
+// through K at one pace and fetch them together.  A 256-row tile beside a shorter one that runs ahead of it had every weight leave the L2 in
 // between (8 experts of 275 rows of the 8B widths, 256 + 128 rows each against 192 + 192: gate/up 801 -> 649 us, down 395 -> 324 us).
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_tiles) {
