@@ -517,39 +517,43 @@ __global__ __launch_bounds__(64 * NW) void gemm_direct_kernel(GemmArgs a, int m_
     gemm_direct_tile<BM, BN, EPI, NS, NW>(a, r * BM, c, smem);
 }
 
-// Whole rounds of 256x256 tiles, then a last half round: when the 256x256 tiles do not divide by
-// the number of compute units, the first n_full workgroups (a multiple of the unit count) take
-// whole tiles and the remaining tiles are cut into their two 128-row halves, one workgroup each,
-// which are dispatched last.  The arithmetic of an output element does not depend on the tile
+// Whole rounds of large tiles, then a last half round: when the tiles do not divide by the number of compute units, the first
+// n_full workgroups (a multiple of the unit count) take whole tiles and the remaining tiles are cut in two, one workgroup each,
+// which are dispatched last: 256x256 into two of 128x256, 192x256 (TALL false) into two of 192x128.
+// The arithmetic of an output element does not depend on the tile
 // that holds it, so the schedule may follow the size of the partition.
-template <int EPI>
+template <int EPI, bool TALL>
 __global__ __launch_bounds__(256) void gemm_direct_mixed_kernel(GemmArgs a, int m_tiles, int n_full, int n_half) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    constexpr int BM = TALL ? 256 : 192;
     const int id = blockIdx.x;
     const int n_tiles = (n_full + (n_half >> 1)) / m_tiles;   // column tiles
+    int r, c;
     if (id < n_full) {
         const int t = (id & 7) * (n_full >> 3) + (id >> 3);          // n_full is a multiple of 8
-        int r, c;
         tile_rc(t, m_tiles, n_tiles, r, c);
-        gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4>(a, r * 256, c, smem);
+        gemm_direct_tile<BM, 256, EPI, RS_NS_FULL, 4>(a, r * BM, c, smem);
     } else {
         const int j = id - n_full;
         const int u = (j & 7) * ((n_half + 7) >> 3) + (j >> 3);
         if (u >= n_half) return;
         const int t = n_full + (u >> 1);
-        int r, c;
         tile_rc(t, m_tiles, n_tiles, r, c);
-        const int bm = r * 256 + (u & 1) * 128;
-        if (bm >= a.M) return;
-        gemm_direct_tile<128, 256, EPI, 5, 4>(a, bm, c, smem);
+        if (TALL) {
+            const int bm = r * 256 + (u & 1) * 128;
+            if (bm < a.M) gemm_direct_tile<128, 256, EPI, 5, 4>(a, bm, c, smem);
+        } else {
+            const int nb = 2 * c + (u & 1);
+            if (nb * (EPI == EPI_SWIGLU ? 64 : 128) < a.N) gemm_direct_tile<192, 128, EPI, 5, 4>(a, r * 192, nb, smem);
+        }
     }
 }
 
-// Few output tiles and a long K (the projections back to d_model at a few hundred rows): the K range is
-// cut into S slices, one workgroup per (tile, slice), and skinny_epilogue_kernel adds the slices in order
-// and applies the epilogue.  S follows from (M, N, K) alone, so results do not depend on the CU share.  Workgroups that run on one
-// XCD own a contiguous run of tiles of one slice in tile_rc's order, as in gemm_direct_kernel: dealt out in turn every XCD fetched
-// every slab (576x6144x4096 in two slices: 318 MB past the L2s for operands of 55, 49 -> 40 us).
+// Few output tiles and a long K (the projections at a few hundred rows): the K range is cut into S slices, one workgroup per
+// (tile, slice), and an epilogue kernel adds the slices in order.  Workgroups that run on one XCD own a contiguous run of tiles of
+// one slice in tile_rc's order, as in gemm_direct_kernel: dealt out in turn every XCD fetched every slab (576x6144x4096 in two
+// slices: 318 MB past the L2s for operands of 55, 49 -> 40 us).
+template <int BM, int NS>
 __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int m_tiles, int n_tiles, int S, int nk_per, float *part) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     const int tiles = m_tiles * n_tiles, total = tiles * S, per_xcd = (total + 7) >> 3;
@@ -559,28 +563,92 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
     const int kt0 = z * nk_per;
     int r, c;
     tile_rc(t, m_tiles, n_tiles, r, c);
-    gemm_direct_tile<128, 256, EPI_STORE, 5, 4, true>(a, r * 128, c, smem, kt0, min(nk_per, a.K / 32 - kt0), part, z);
+    gemm_direct_tile<BM, 256, EPI_STORE, NS, 4, true>(a, r * BM, c, smem, kt0, min(nk_per, a.K / 32 - kt0), part, z);
 }
 
-static inline int direct_splits(int M, int N, int K) {
-    const long tiles = (long)((M + 127) / 128) * ((N + 255) / 256);
-    const int nk = K / 32;
+// ---------------------------------------------------------------------------------------------
+// The schedule of a large-tile product: tile shape and K slices by what they are expected to cost.
+// A round of w workgroups of one tile shape takes 4.8 + nk * (a + b * w / 256) us for nk K tiles: 4.8 are the first loads and the
+// tile's stores, b is what the units cost one another (fabric, power).  Fitted to 1215 timings of cold weights on 64, 96, 128,
+// 192 and 256 CUs (150 to 2048 rows; K 4096, 8192, 14336; N 4096 to 28672 pairs; every shape below, 1 to 6 slices): 6 % rms.  A slice
+// adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.  Among the shapes timed for one
+// product and slice count the rule's choice is 0.2 % slower than the fastest on average, 14 % at most.
+// Against the rule before it (128-row tiles for slices, their count a power of two up to half the chip; no 192-row tiles), product and
+// epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
+// 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
+// ---------------------------------------------------------------------------------------------
+enum DirectForm { FORM_128x256, FORM_192x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192 };
+
+static double direct_round_us(DirectForm f, int nk, long w) {
+    constexpr double A[] = {0.30, 0.38, 0.44, 0.36, 0.225}, B[] = {0.10, 0.145, 0.25, 0.165, 0.09};
+    return 4.8 + nk * (A[f] + B[f] * (double)w / 256.0);
+}
+static long direct_tiles(DirectForm f, int M, int nv) {
+    constexpr int BM[] = {128, 192, 256, 256, 192}, BN[] = {256, 256, 256, 192, 128};
+    return (long)((M + BM[f] - 1) / BM[f]) * ((nv + BN[f] - 1) / BN[f]);
+}
+static double direct_rounds_us(DirectForm f, int nk, long wgs, int cus) {
+    return (double)(wgs / cus) * direct_round_us(f, nk, cus) + (wgs % cus ? direct_round_us(f, nk, wgs % cus) : 0.0);
+}
+// Whole rounds of `full` tiles and one round of `half` ones: cost, or a huge one where there is no such schedule.
+static double direct_mixed_us(DirectForm full, DirectForm half, int nk, long tiles, int cus, int &n_full) {
+    n_full = (int)(tiles / cus) * cus;
+    const long rest = tiles - n_full;
+    if (!n_full || n_full % 8 || !rest || 2 * rest > cus) return 1e30;
+    return (double)(n_full / cus) * direct_round_us(full, nk, cus) + direct_round_us(half, nk, 2 * rest);
+}
+
+// The fastest form for S slices (1: the finished product) on `cus` compute units, and its cost.
+static double direct_best_form(int M, int N, int K, int epi, int S, int cus, DirectForm &form) {
+    const int nv = epi == EPI_SWIGLU ? (N + 127) / 128 * 256 : N, nk = (K / 32 + S - 1) / S;
+    double best = 1e30;
+    auto consider = [&](DirectForm f, double us) { if (us < best) { best = us; form = f; } };
+    for (DirectForm f : {FORM_256x256, FORM_192x256, FORM_128x256}) consider(f, direct_rounds_us(f, nk, S * direct_tiles(f, M, nv), cus));
+    if (S > 1) return best;
+    int n_full;
+    if (epi == EPI_SWIGLU) {
+        consider(FORM_192x128, direct_rounds_us(FORM_192x128, nk, direct_tiles(FORM_192x128, M, nv), cus));
+        consider(FORM_MIXED_192, direct_mixed_us(FORM_192x256, FORM_192x128, nk, direct_tiles(FORM_192x256, M, nv), cus, n_full));
+    } else {
+        consider(FORM_256x192, direct_rounds_us(FORM_256x192, nk, direct_tiles(FORM_256x192, M, nv), cus));
+    }
+    consider(FORM_MIXED_256, direct_mixed_us(FORM_256x256, FORM_128x256, nk, direct_tiles(FORM_256x256, M, nv), cus, n_full));
+    return best;
+}
+
+// K slices: from (M, N, K) alone, so that results do not depend on the CU share; the whole chip's time counts four times what half
+// of it takes.  At least 16 K tiles a slice, one round of workgroups, and no more partial sums than RS_DIRECT_PARTIAL_ELEMS.
+// (With the whole chip alone 576 to 1150 rows lost up to 15 % of a product on 128 CUs; now one of the products timed does, 1150x4096x14336,
+// which gains 45 us on 256 CUs and loses 28 on 128.)
+static int direct_splits(int M, int N, int K) {
+    DirectForm f;
+    auto us = [&](int epi, int S) { return direct_best_form(M, N, K, epi, S, 256, f) + 0.25 * direct_best_form(M, N, K, epi, S, 128, f); };
     int S = 1;
-    // until about half of a whole chip's compute units have a workgroup; at least 16 K tiles per slice
-    while (tiles * S * 2 <= 256 && S < 8 && nk / (S * 2) >= 16) S *= 2;
+    double best = us(EPI_RESIDUAL, 1);
+    const int nk = K / 32;
+    for (int s = 2; s <= 8 && nk / s >= 16 && (size_t)s * M * N <= RS_DIRECT_PARTIAL_ELEMS; ++s) {
+        if ((nk + s - 1) / s * (s - 1) >= nk || s * direct_tiles(FORM_256x256, M, N) > 256) continue;   // no empty slice, no second round
+        const double t = us(EPI_STORE, s) + 1.25 * (1.2e-6 * s * M * N + 2.0 + 0.3 * s);
+        if (t < best) { best = t; S = s; }
+    }
     return S;
 }
-size_t direct_partial_elems(int M, int N, int K) { return (size_t)direct_splits(M, N, K) * (size_t)M * (size_t)N; }
 
 template <int EPI>
 __global__ __launch_bounds__(256) void skinny_epilogue_kernel(GemmArgs a, const float *__restrict__ part, int S, int Nv);
 
+template <int BM, int NS>
+static void launch_direct_splitk_tiles(hipStream_t st, const GemmArgs &a, int S) {
+    const int m_tiles = (a.M + BM - 1) / BM, n_tiles = (a.N + 255) / 256, nk_per = (a.K / 32 + S - 1) / S;
+    hipLaunchKernelGGL((gemm_direct_splitk_kernel<BM, NS>), dim3((m_tiles * n_tiles * S + 7) / 8 * 8), dim3(256), NS * (BM + 256) * 64, st, a,
+                       m_tiles, n_tiles, S, nk_per, a.partials);
+}
 static void launch_direct_splitk_main(hipStream_t st, const GemmArgs &a, int S) {
-    const int m_tiles = (a.M + 127) / 128, n_tiles = (a.N + 255) / 256;
-    const int nk_total = a.K / 32, nk_per = (nk_total + S - 1) / S;
-    constexpr int lds = 5 * (128 + 256) * 32 * 2;
-    hipLaunchKernelGGL(gemm_direct_splitk_kernel, dim3((m_tiles * n_tiles * S + 7) / 8 * 8), dim3(256), lds, st, a, m_tiles, n_tiles, S, nk_per,
-                       a.partials);
+    DirectForm f;
+    direct_best_form(a.M, a.N, a.K, EPI_STORE, S, a.cus > 0 ? a.cus : 256, f);
+    if (f == FORM_256x256) launch_direct_splitk_tiles<256, RS_NS_FULL>(st, a, S);
+    else if (f == FORM_192x256) launch_direct_splitk_tiles<192, 4>(st, a, S);
+    else launch_direct_splitk_tiles<128, 5>(st, a, S);
 }
 
 static void launch_direct_splitk(hipStream_t st, const GemmArgs &a, int S) {
@@ -595,7 +663,7 @@ static void launch_direct_splitk(hipStream_t st, const GemmArgs &a, int S) {
 static int direct_sliced(const GemmArgs &a) {   // K slices of launch_gemm_tiled's sliced path, or 0 where it is not taken
     if (!(a.K % 32 == 0 && a.K >= 32 && a.Wp && a.M > 64 && a.N >= 1024 && a.epi != EPI_SWIGLU && a.partials && a.N % 4 == 0)) return 0;
     const int S = direct_splits(a.M, a.N, a.K);
-    return S > 1 && direct_partial_elems(a.M, a.N, a.K) <= a.partial_cap ? S : 0;
+    return S > 1 && (size_t)S * a.M * a.N <= a.partial_cap ? S : 0;
 }
 
 int launch_gemm_tiled_partials(hipStream_t st, const GemmArgs &a) {
@@ -614,16 +682,13 @@ __global__ __launch_bounds__(256) void gemm_head_kernel(GemmArgs a, HeadOut o, i
     gemm_direct_tile<BM, 256, EPI_STORE, NS, 4, false, true>(a, (t % m_tiles) * BM, t / m_tiles, smem, 0, 0, nullptr, 0, &o);
 }
 
-template <int EPI>
-static void launch_direct_mixed_epi(hipStream_t st, const GemmArgs &a, int m_tiles, int n_full, int n_half) {
-    constexpr int lds = RS_NS_FULL * 512 * 32 * 2;   // the larger of the two rings
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)gemm_direct_mixed_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        attr_set = true;
-    }
-    const int grid = n_full + ((n_half + 7) / 8) * 8;
-    hipLaunchKernelGGL((gemm_direct_mixed_kernel<EPI>), dim3(grid), dim3(256), lds, st, a, m_tiles, n_full, n_half);
+template <int EPI, bool TALL>
+static void launch_direct_mixed(hipStream_t st, const GemmArgs &a, int cus) {
+    constexpr int BM = TALL ? 256 : 192;
+    const int m_tiles = (a.M + BM - 1) / BM, n_tiles = EPI == EPI_SWIGLU ? (a.N + 127) / 128 : (a.N + 255) / 256;
+    const int n_full = m_tiles * n_tiles / cus * cus, n_half = 2 * (m_tiles * n_tiles - n_full);
+    hipLaunchKernelGGL((gemm_direct_mixed_kernel<EPI, TALL>), dim3(n_full + (n_half + 7) / 8 * 8), dim3(256), RS_NS_FULL * (BM + 256) * 64, st, a,
+                       m_tiles, n_full, n_half);
 }
 
 template <int BM, int BN, int EPI, int NS, int NW>
@@ -633,12 +698,6 @@ static void launch_direct_epi(hipStream_t st, const GemmArgs &a) {
     const int total = m_tiles * n_tiles;
     const int grid = ((total + 7) / 8) * 8;
     constexpr int lds = NS * (BM + BN) * 32 * 2;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)gemm_direct_kernel<BM, BN, EPI, NS, NW>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        attr_set = true;
-    }
     hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, EPI, NS, NW>), dim3(grid), dim3(64 * NW), lds, st, a, m_tiles, n_tiles);
 }
 
@@ -707,9 +766,6 @@ static void launch_tiled(hipStream_t st, const GemmArgs &a) {
     }
 }
 
-// Tile shapes of the direct kernel and their cost per tile relative to a 256x256 tile (area over
-// measured relative efficiency).  The schedule with the fewest weighted rounds on the partition's
-// compute units wins; the arithmetic of an output element is the same in all of them.
 bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
     if (a.M <= 0 || a.N <= 0) return true;
     const bool aligned = (a.K % 32 == 0) && a.K >= 32;
@@ -719,31 +775,22 @@ bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
             return true;
         }
         const int cus = a.cus > 0 ? a.cus : 256;
-        const int nv = a.epi == EPI_SWIGLU ? 2 * a.N : a.N;
-        const int mt256 = (a.M + 255) / 256, mt128 = (a.M + 127) / 128;
-        const long t_full = (long)mt256 * ((nv + 255) / 256), t_half = (long)mt128 * ((nv + 255) / 256);
-        const long t_192 = (long)mt256 * ((a.N + 191) / 192);
-        auto rounds = [&](long t) { return (double)((t + cus - 1) / cus); };
-        constexpr double C_HALF = 0.59, C_192 = 0.79;
-        const double cost_full = rounds(t_full), cost_half = rounds(t_half) * C_HALF;
-        const double cost_192 = a.epi == EPI_SWIGLU ? 1e30 : rounds(t_192) * C_192;
-        const int n_full = (int)(t_full / cus) * cus, rest = (int)t_full - n_full;
-        const bool mixed_ok = n_full > 0 && n_full % 8 == 0 && rest > 0 && 2 * rest <= cus;
-        const double cost_mixed = mixed_ok ? n_full / cus + C_HALF : 1e30;
-        const double best = std::min(std::min(cost_full, cost_mixed), std::min(cost_half, cost_192));
-        if (best == cost_full) {
-            launch_direct<256, 256, RS_NS_FULL, 4>(st, a);   // RS_NS_FULL x 32 KB of LDS
-        } else if (best == cost_mixed) {
-            switch (a.epi) {
-                case EPI_STORE: launch_direct_mixed_epi<EPI_STORE>(st, a, mt256, n_full, 2 * rest); break;
-                case EPI_RESIDUAL: launch_direct_mixed_epi<EPI_RESIDUAL>(st, a, mt256, n_full, 2 * rest); break;
-                default: launch_direct_mixed_epi<EPI_SWIGLU>(st, a, mt256, n_full, 2 * rest); break;
-            }
-        } else if (best == cost_192) {
-            if (a.epi == EPI_STORE) launch_direct_epi<256, 192, EPI_STORE, 4, 4>(st, a);   // 4 x 28 KB
-            else launch_direct_epi<256, 192, EPI_RESIDUAL, 4, 4>(st, a);
-        } else {
-            launch_direct<128, 256, 5, 4>(st, a);   // 5 x 24 KB of LDS
+        DirectForm f;
+        direct_best_form(a.M, a.N, a.K, a.epi, 1, cus, f);
+        switch (f) {
+            case FORM_256x256: launch_direct<256, 256, RS_NS_FULL, 4>(st, a); break;   // RS_NS_FULL x 32 KB of LDS
+            case FORM_192x256: launch_direct<192, 256, 4, 4>(st, a); break;            // 4 x 28 KB
+            case FORM_128x256: launch_direct<128, 256, 5, 4>(st, a); break;            // 5 x 24 KB
+            case FORM_256x192:                                                         // 4 x 28 KB
+                if (a.epi == EPI_STORE) launch_direct_epi<256, 192, EPI_STORE, 4, 4>(st, a);
+                else launch_direct_epi<256, 192, EPI_RESIDUAL, 4, 4>(st, a);
+                break;
+            case FORM_192x128: launch_direct_epi<192, 128, EPI_SWIGLU, 5, 4>(st, a); break;   // 5 x 20 KB
+            case FORM_MIXED_192: launch_direct_mixed<EPI_SWIGLU, false>(st, a, cus); break;
+            default:
+                if (a.epi == EPI_STORE) launch_direct_mixed<EPI_STORE, true>(st, a, cus);
+                else if (a.epi == EPI_RESIDUAL) launch_direct_mixed<EPI_RESIDUAL, true>(st, a, cus);
+                else launch_direct_mixed<EPI_SWIGLU, true>(st, a, cus);
         }
     } else {
         // the generic kernel reads the caller's row-major matrices: refuse when they have been released
@@ -1177,7 +1224,7 @@ void launch_gemm_skinny(hipStream_t st, const GemmArgs &a, float *partials) {
     if (a.epi == EPI_RESIDUAL && !skinny_shared_applies(a) && a.K % 32 == 0 && a.K >= 512 && a.Wp && a.N >= 1024 && a.N % 4 == 0 &&
         a.partials == partials && a.partial_cap > 0) {
         const int S = direct_splits(a.M, a.N, a.K);
-        if (S > 1 && direct_partial_elems(a.M, a.N, a.K) <= a.partial_cap) {
+        if (S > 1 && (size_t)S * a.M * a.N <= a.partial_cap) {
             launch_direct_splitk(st, a, S);
             return;
         }
@@ -1203,18 +1250,25 @@ void gemm_kernels_init() {
     set((const void *)gemm_head_kernel<128, 5>, 122880);
     set((const void *)gemm_head_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
     set((const void *)gemm_skinny_shared_kernel<EPI_RESIDUAL, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
-    set((const void *)gemm_direct_splitk_kernel, 5 * (128 + 256) * 32 * 2);
+    set((const void *)gemm_direct_splitk_kernel<128, 5>, 122880);
+    set((const void *)gemm_direct_splitk_kernel<192, 4>, 114688);
+    set((const void *)gemm_direct_splitk_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_STORE>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_SWIGLU>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_mixed_kernel<EPI_STORE>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_mixed_kernel<EPI_RESIDUAL>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU>, RS_NS_FULL * 32768);
+    set((const void *)gemm_direct_mixed_kernel<EPI_STORE, true>, RS_NS_FULL * 32768);
+    set((const void *)gemm_direct_mixed_kernel<EPI_RESIDUAL, true>, RS_NS_FULL * 32768);
+    set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5, 4>, 122880);
+    set((const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4, 4>, 114688);
     set((const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5, 4>, 122880);
+    set((const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4, 4>, 114688);
     set((const void *)gemm_direct_kernel<128, 256, EPI_SWIGLU, 5, 4>, 122880);
+    set((const void *)gemm_direct_kernel<192, 256, EPI_SWIGLU, 4, 4>, 114688);
+    set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, false>, RS_NS_FULL * 28672);
+    set((const void *)gemm_direct_kernel<192, 128, EPI_SWIGLU, 5, 4>, 102400);
     set((const void *)gemm_direct_kernel<256, 192, EPI_STORE, 4, 4>, 114688);
     set((const void *)gemm_direct_kernel<256, 192, EPI_RESIDUAL, 4, 4>, 114688);
 }

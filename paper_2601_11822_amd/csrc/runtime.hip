@@ -575,7 +575,7 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     };
     // h, attn and act are fragment-packed by their producers; x1 and y are row-major
     const bf16_t *wo = (const bf16_t *)lw.wo, *wg = (const bf16_t *)lw.wg, *wu = (const bf16_t *)lw.wu, *wd = (const bf16_t *)lw.wd;
-    GemmArgs go{w.attn, wo, nullptr, pl.wo, nullptr, x, w.x1, M, d, qd, EPI_RESIDUAL, 0, 0, w.partials, w.partial_cap};
+    GemmArgs go{w.attn, wo, nullptr, pl.wo, nullptr, x, w.x1, M, d, qd, EPI_RESIDUAL, 0, c->side[side].cus, w.partials, w.partial_cap};
     const int So = !skinny && residual_norm_applies(d) ? launch_gemm_tiled_partials(st, go) : 0;
     if (So) {
         launch_residual_norm(st, ResidualNormArgs{w.partials, So, x, (const bf16_t *)lw.g2, w.x1, w.h, M, d, m.rms_eps});

@@ -367,3 +367,45 @@ def test_large_layer_passes_same_bits_on_every_partition(shape, passes):
                 check_tensor("decode rows", f32(want)[T + rows], L.decode(x[T + rows], ctx[rows], dtab[rows], Kc, Vc), x[T + rows], 2, elem_mult=END_TO_END)
     finally:
         rig.close()
+
+
+# the large-tile products at row counts that take every form of their schedule on some partition: tiles of 128, 192 and 256 rows
+# and of 192 columns, whole rounds with a last one of halves along either side, one to eight slices; the last row tile nearly
+# empty (129, 193, 385, 577) and full (576).  Each product against float32 products of its own bf16 operands: an output is one
+# rounding of a float32 sum (2^-8 of its value; 2^-7 for gate/up, whose reciprocal and exponential are approximate) and the
+# order of up to 14336 terms (1e-4 of the outputs' size).  The same bits on every partition.
+@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [129, 193, 300, 385, 576, 577, 900, 1025, 1300]), (S.LLAMA70B, [160, 333, 577, 1153]), (S.ODD, [150, 700])])
+def test_large_tile_products(shape, rows):
+    n_blocks = S.blocks_for(max(rows)) + 4
+    rig = Rig(shape, n_blocks, max(rows), 1, max(rows) + 1, with_oracle=False)
+    w = rig.wdev[0]
+    try:
+        for T in rows:
+            cu, tabs = np.array([0, T], np.int32), S.shuffled_block_tables([T], n_blocks, stream=35)
+            xb, first = S.hidden_states(T, shape.d_model, stream=35), None
+            for split in ((256, 256), (128, 128), (64, 192), (96, 160)):
+                print(shape.name, T, split, flush=True)
+                rig.ctx.set_cu_split(*split)
+                y = rig.prefill(xb, cu, tabs)
+                widths = {0: shape.d_model, 1: shape.qkv_dim, 2: shape.q_dim, 3: shape.d_model, 4: shape.ffn_dim}
+                got = {k: rig.ctx.debug_read_workspace(rs.RS_SIDE_PREFILL, k, (T, n)) for k, n in widths.items()}
+                got[5] = y
+                first = got if first is None else first
+                assert all(np.array_equal(got[k], first[k]) for k in got), f"differs at split {split}"
+            t = {k: to_dev(v).float() for k, v in first.items()}
+            x = to_dev(xb).float()
+            norm = (x * torch.rsqrt((x * x).mean(1, keepdim=True) + shape.rms_eps) * w["g1"].float()).bfloat16().float()
+            v0 = shape.q_dim + (shape.qkv_dim - shape.q_dim) // 2
+            act = t[0] @ w["wg"].float().t()
+            act = act * torch.sigmoid(act) * (t[0] @ w["wu"].float().t())
+            for name, g, ref, ulp in (("v", t[1][:, v0:], norm @ w["wqkv"][v0:].float().t(), 2 ** -8), ("x1", t[3], x + t[2] @ w["wo"].float().t(), 2 ** -8),
+                                      ("act", t[4], act, 2 ** -7), ("y", t[5], t[3] + t[4] @ w["wd"].float().t(), 2 ** -8)):
+                size = ref.square().mean().sqrt()
+                # v's operand is formed again here, and one element in some 10^4 is so near the middle of two bf16 that it rounds
+                # the other way: 2^-8 of a term of size / sqrt(d), whose two factors reach five sigma each (25 terms); two of those
+                slack = 1e-4 * size if name != "v" else 2 * 25 * 2 ** -8 * size / shape.d_model ** 0.5
+                worst = ((g - ref).abs() / (ulp * ref.abs() + slack)).max().item()
+                print(f"  {name}: {worst:.3f} of the allowed error", flush=True)
+                assert worst <= 1.0, name
+    finally:
+        rig.close()
