@@ -282,11 +282,14 @@ __device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x16 (&acc
 // One output tile: rows [bm, bm + BM), column tile nb (of width BN; BN/2 output columns for SwiGLU).
 // HEAD: the epilogue is head_row above.  PARTIAL: the tile covers K tiles [kt0, kt0 + nk_part) only and stores its raw float32 sums to
 // part[z][m][n] (row stride N), for an epilogue pass that adds the slices in order.
+// NT: the weights are fetched as a stream (non-temporal: first out of the L2).  Right where few row tiles share a slab and all of
+// them run at once: K slices, the head, expert tiles (below).  Whole products gain 1 % at some sizes and lose 2 to 5 at others (1300 rows of
+// the 8B layer 634 -> 663 us): their later rounds read the slabs again.
 // LDS stages of the 256x256 tile's ring (32 KB each): a K tile is requested three tiles ahead.  A fifth stage (the
 // whole 160 KB of a compute unit) measured the same, alone and beside a bandwidth-bound kernel on the other
 // partition: what that neighbour costs is not memory latency the ring could cover.
 #define RS_NS_FULL 4
-template <int BM, int BN, int EPI, int NS, int NW, bool PARTIAL = false, bool HEAD = false>
+template <int BM, int BN, int EPI, int NS, int NW, bool PARTIAL = false, bool HEAD = false, bool NT = PARTIAL || HEAD>
 __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem,
                                                  const int kt0 = 0, const int nk_part = 0, float *part = nullptr, const int z = 0,
                                                  const HeadOut *ho = nullptr) {
@@ -372,7 +375,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
                     const char *g = up ? gb2 : gb;
                     asm volatile("" : "+s"(g));
                     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + ob[j - LA]),
-                                                     (__attribute__((address_space(3))) void *)(sb + (W * LB + j - LA) * 512), 16, 0, 0);
+                                                     (__attribute__((address_space(3))) void *)(sb + (W * LB + j - LA) * 512), 16, 0, NT ? 2 : 0);
                 }
             }
         };
@@ -715,7 +718,7 @@ static void launch_direct(hipStream_t st, const GemmArgs &a) {
 // An expert's rows are cut into units of one height (two from four units on), so that the units that share its weights run
 // through K at one pace and fetch them together.  A 256-row tile beside a shorter one that runs ahead of it had every weight leave the L2 in
 // between (8 experts of 275 rows of the 8B widths, 256 + 128 rows each against 192 + 192: gate/up 801 -> 649 us, down 395 -> 324 us).
-template <int EPI>
+template <int EPI, bool NT>
 __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_tiles) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     const int nu = __builtin_amdgcn_readfirstlane(a.units[0]);
@@ -727,16 +730,21 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_til
     GemmArgs g = a;
     g.Wp += (size_t)(code & 31) * a.expert_stride;
     if (EPI == EPI_SWIGLU) g.Wp2 += (size_t)(code & 31) * a.expert_stride;
-    if (height == 4) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4>(g, row0, t.nb, smem);
-    else if (height == 3) gemm_direct_tile<192, 256, EPI, 4, 4>(g, row0, t.nb, smem);
-    else gemm_direct_tile<128, 256, EPI, 5, 4>(g, row0, t.nb, smem);
+    if (height == 4) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4, false, false, NT>(g, row0, t.nb, smem);
+    else if (height == 3) gemm_direct_tile<192, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
+    else gemm_direct_tile<128, 256, EPI, 5, 4, false, false, NT>(g, row0, t.nb, smem);
 }
 
+// Up to this many padded rows (all experts') the expert weights are fetched as a stream: an expert then has one tile or two.  The
+// layer of the 8B widths with 8 experts, with it and without: 100 rows 662 -> 635 us, 600 rows 817 -> 772, decode of 64 rows 703 ->
+// 679; 2048 rows of the same length 1657 -> 1646 but 1785 -> 1795 where the experts are uneven, 3000 rows 2322 -> 2359.
+#define RS_GROUPED_NT_ROWS 4096
 template <int EPI>
 static void launch_grouped_epi(hipStream_t st, const GemmArgs &a) {
     const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + 127) / 128 : (a.N + 255) / 256;
     const int per_xcd = ((a.M >> 7) * n_tiles + 7) / 8;   // of as many units as there can be
-    hipLaunchKernelGGL((gemm_grouped_kernel<EPI>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
+    if (a.M <= RS_GROUPED_NT_ROWS) hipLaunchKernelGGL((gemm_grouped_kernel<EPI, true>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
+    else hipLaunchKernelGGL((gemm_grouped_kernel<EPI, false>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
 }
 
 bool launch_gemm_grouped(hipStream_t st, const GemmArgs &a) {
@@ -1253,8 +1261,10 @@ void gemm_kernels_init() {
     set((const void *)gemm_direct_splitk_kernel<128, 5>, 122880);
     set((const void *)gemm_direct_splitk_kernel<192, 4>, 114688);
     set((const void *)gemm_direct_splitk_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
-    set((const void *)gemm_grouped_kernel<EPI_STORE>, RS_NS_FULL * 32768);
-    set((const void *)gemm_grouped_kernel<EPI_SWIGLU>, RS_NS_FULL * 32768);
+    set((const void *)gemm_grouped_kernel<EPI_STORE, true>, RS_NS_FULL * 32768);
+    set((const void *)gemm_grouped_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
+    set((const void *)gemm_grouped_kernel<EPI_STORE, false>, RS_NS_FULL * 32768);
+    set((const void *)gemm_grouped_kernel<EPI_SWIGLU, false>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_mixed_kernel<EPI_STORE, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_mixed_kernel<EPI_RESIDUAL, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
