@@ -294,11 +294,12 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
                                                  const int kt0 = 0, const int nk_part = 0, float *part = nullptr, const int z = 0,
                                                  const HeadOut *ho = nullptr) {
     constexpr int BK = 32;
-    constexpr int WGN = NW / 2;                      // waves: 2 along M x NW/2 along N
-    constexpr int WM = BM / 2, WN = BN / WGN;
+    constexpr int WGM = BM % 64 ? 1 : 2;             // waves: 2 along M x NW/2 along N, or all along N (a height of an odd number of row blocks)
+    constexpr int WGN = NW / WGM;
+    constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 32, TN = WN / 32;
     constexpr int TA = BM / 32, TB = BN / 32;        // 32-row blocks per k block of the tile
-    constexpr int LA = 2 * TA / NW, LB = 2 * TB / NW;   // wave-wide loads per wave per stage
+    constexpr int LB = 2 * TB / NW;                  // wave-wide loads of weights per wave per stage
     constexpr int STAGE = (BM + BN) * BK;            // elements per stage: [2][TA] A blocks, then [2][TB] B blocks
     constexpr int D = NS - 1;                        // prefetch distance in K tiles
     static_assert(TN + TM + 1 <= TN * TM, "a step must have a slot per fragment read");
@@ -320,9 +321,11 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    constexpr int SL = 2 * TN * TM, LT = LA + LB, SP = SL / LT;
     auto k_loop = [&](auto wtag) {
         constexpr int W = decltype(wtag)::value;
+        // loads of activations per stage: the 2 TA blocks in order, the first waves one more where they do not divide
+        constexpr int LA = 2 * TA / NW + (W < 2 * TA % NW ? 1 : 0), A0 = W * (2 * TA / NW) + (W < 2 * TA % NW ? W : 2 * TA % NW);
+        constexpr int SL = 2 * TN * TM, LT = LA + LB, SP = SL / LT;
         constexpr int CWM = W / WGN, CWN = W % WGN;
         // The LT loads of a K tile are spread evenly over its SL MFMA slots, and wave w places its own w
         // quarter-spacings later than wave 0: the lock-stepped waves never queue behind one another at the
@@ -335,7 +338,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
         uint32_t oa[LA], ob[LB];
 #pragma unroll
         for (int j = 0; j < LA; ++j) {
-            const int q = W * LA + j, s = q / TA, t = q % TA;
+            const int q = A0 + j, s = q / TA, t = q % TA;
             oa[j] = (uint32_t)(((s * Mt + min((bm >> 5) + t, Mt - 1)) * 512 + lane * 8) * 2);
         }
 #pragma unroll
@@ -369,7 +372,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
                     const char *g = ga;
                     asm volatile("" : "+s"(g));   // the address is formed here, next to its load, not at the top of the K tile
                     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + oa[j]),
-                                                     (__attribute__((address_space(3))) void *)(sa + (W * LA + j) * 512), 16, 0, 0);
+                                                     (__attribute__((address_space(3))) void *)(sa + (A0 + j) * 512), 16, 0, 0);
                 } else {
                     const bool up = EPI == EPI_SWIGLU && (((W * LB + j - LA) % TB) & 1);
                     const char *g = up ? gb2 : gb;
@@ -713,8 +716,8 @@ static void launch_direct(hipStream_t st, const GemmArgs &a) {
     }
 }
 
-// Grouped GEMM: rows laid out expert by expert, every unit of the work list (moe_plan_kernel) a tile of 128, 192 or 256
-// rows of one expert by 256 columns.  The arithmetic of an output element does not depend on the tile that holds it.
+// Grouped GEMM: rows laid out expert by expert, every unit of the work list (moe_plan_kernel) a tile of 128 to 256
+// rows, in steps of 32, of one expert by 256 columns.  The arithmetic of an output element does not depend on the tile that holds it.
 // An expert's rows are cut into units of one height (two from four units on), so that the units that share its weights run
 // through K at one pace and fetch them together.  A 256-row tile beside a shorter one that runs ahead of it had every weight leave the L2 in
 // between (8 experts of 275 rows of the 8B widths, 256 + 128 rows each against 192 + 192: gate/up 801 -> 649 us, down 395 -> 324 us).
@@ -726,12 +729,14 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_til
     const GroupTile t = grouped_tile(blockIdx.x & 7, blockIdx.x >> 3, nu, n_tiles);
     if (t.u < 0) return;
     const int code = __builtin_amdgcn_readfirstlane(a.units[2 + t.u]);
-    const int row0 = (code >> 8) * 64, height = (code >> 5) & 7;
+    const int row0 = (code >> 9) * 32, height = (code >> 5) & 15;
     GemmArgs g = a;
     g.Wp += (size_t)(code & 31) * a.expert_stride;
     if (EPI == EPI_SWIGLU) g.Wp2 += (size_t)(code & 31) * a.expert_stride;
-    if (height == 4) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4, false, false, NT>(g, row0, t.nb, smem);
-    else if (height == 3) gemm_direct_tile<192, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
+    if (height == 8) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4, false, false, NT>(g, row0, t.nb, smem);
+    else if (height == 7) gemm_direct_tile<224, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
+    else if (height == 6) gemm_direct_tile<192, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
+    else if (height == 5) gemm_direct_tile<160, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
     else gemm_direct_tile<128, 256, EPI, 5, 4, false, false, NT>(g, row0, t.nb, smem);
 }
 

@@ -232,7 +232,7 @@ struct MoeArgs {
     float *wt;              // [M][2] their weights
     int32_t *pos;           // [M][2] grouped row of each assignment
     int32_t *src;           // [Mg_cap] source row of each grouped row, -1 for padding
-    int32_t *units;         // [2 + Mg_cap / 128]: units, rows in use, first row / 64 << 8 | height / 64 << 5 | expert of each
+    int32_t *units;         // [2 + Mg_cap / 128]: units, rows in use, first row / 32 << 9 | height / 32 << 5 | expert of each
     bf16_t *a_g;            // gathered rows, fragment-packed with Mg_cap / 32 row tiles
     const bf16_t *out_g;    // [Mg_cap][d] expert outputs, row-major
     const bf16_t *x1;       // [M][d]

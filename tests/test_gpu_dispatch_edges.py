@@ -90,8 +90,9 @@ def test_streamed_pass(shape, lens, starts, ctx):
 
 
 # the sparse block's tiles: with two experts every row goes to both, so an expert has exactly `n` rows: each height of
-# tile (128, 192, 256 rows) at its edges, one tile an expert and several, four and more of two heights; 32 rows a router workgroup
-@pytest.mark.parametrize("n", [1, 32, 33, 128, 129, 192, 193, 256, 257, 384, 385, 513, 577, 768, 769, 833, 1025])
+# tile (128 to 256 rows in steps of 32) at its edges, one tile an expert and several, four and more of two heights; 32 rows a
+# router workgroup
+@pytest.mark.parametrize("n", [1, 32, 33, 128, 129, 160, 161, 192, 193, 224, 225, 256, 257, 384, 385, 513, 577, 672, 768, 769, 833, 1025])
 def test_sparse_block_tiles(n):
     rig, mw, L = _moe_rig(S.WIDE, 2, S.blocks_for(n) + 2, n, 1, n + 1)
     try:
