@@ -302,6 +302,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
     constexpr int LB = 2 * TB / NW;                  // wave-wide loads of weights per wave per stage
     constexpr int STAGE = (BM + BN) * BK;            // elements per stage: [2][TA] A blocks, then [2][TB] B blocks
     constexpr int D = NS - 1;                        // prefetch distance in K tiles
+    static_assert(!HEAD || WGN == 2, "two candidates per row and column tile");
     static_assert(TN + TM + 1 <= TN * TM, "a step must have a slot per fragment read");
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -1208,7 +1209,8 @@ void launch_gemm_skinny_partials(hipStream_t st, const GemmArgs &a, float *parti
 
 // LM head with the greedy choice begun in the epilogue.  Up to 64 rows the weight-streaming kernel, one workgroup per 256
 // columns over the whole K (a vocabulary too narrow to fill the chip that way takes K slices and launch_head_argmax);
-// above that the large-tile kernel, 128- or 256-row tiles.
+// above that the large-tile kernel, tiles of 128, 192 or 256 rows (a decode step of one layer and the head, without and with
+// 192: 130 rows 429 -> 400 us, 150 rows 464 -> 408, 192 rows 484 -> 451).
 // The product used to leave its float32 sums in a scratch matrix that one workgroup per row read back, chose from and
 // copied to the caller's logits: at 256 rows of a 128256-wide head 106 us of argmax behind 323 us of product (131 MB
 // written, read and written again, and 1002 tiles of 128x256 where 501 of 256x256 are two rounds); now 280 + 5 us.
@@ -1223,10 +1225,14 @@ void launch_gemm_head(hipStream_t st, const GemmArgs &a, const HeadOut &o) {
                            2 * RS_SHARED_CH * 2048, st, a, (float *)nullptr, skinny_kblocks(a.K), skinny_kblocks(a.K), 0, o);
         return;
     }
-    const int n_tiles = (a.N + 255) / 256, m_tiles = a.M <= 128 ? 1 : (a.M + 255) / 256;
+    // as few row tiles of at most 256 rows as hold the batch, each no higher than needed (of heights whose waves stand two by
+    // two: head_candidates counts on two column halves)
+    const int n_tiles = (a.N + 255) / 256, m_tiles = (a.M + 255) / 256, height = (a.M + 32 * m_tiles - 1) / (32 * m_tiles);
     const dim3 grid((m_tiles * n_tiles + 7) / 8 * 8);
-    if (a.M <= 128) hipLaunchKernelGGL((gemm_head_kernel<128, 5>), grid, dim3(256), 5 * 384 * 64, st, a, o, m_tiles, n_tiles);
-    else hipLaunchKernelGGL((gemm_head_kernel<256, RS_NS_FULL>), grid, dim3(256), RS_NS_FULL * 32768, st, a, o, m_tiles, n_tiles);
+    auto go = [&](auto kernel, int bm, int ns) { hipLaunchKernelGGL(kernel, grid, dim3(256), ns * (bm + 256) * 64, st, a, o, m_tiles, n_tiles); };
+    if (height <= 4) go(gemm_head_kernel<128, 5>, 128, 5);
+    else if (height <= 6) go(gemm_head_kernel<192, 4>, 192, 4);
+    else go(gemm_head_kernel<256, RS_NS_FULL>, 256, RS_NS_FULL);
 }
 
 void launch_gemm_skinny(hipStream_t st, const GemmArgs &a, float *partials) {
@@ -1261,6 +1267,7 @@ void gemm_kernels_init() {
     set((const void *)gemm_skinny_shared_kernel<EPI_STORE, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
     set((const void *)gemm_skinny_shared_kernel<EPI_STORE, RS_SHARED_CH, true>, 2 * RS_SHARED_CH * 2048);
     set((const void *)gemm_head_kernel<128, 5>, 122880);
+    set((const void *)gemm_head_kernel<192, 4>, 114688);
     set((const void *)gemm_head_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
     set((const void *)gemm_skinny_shared_kernel<EPI_RESIDUAL, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
     set((const void *)gemm_direct_splitk_kernel<128, 5>, 122880);

@@ -17,9 +17,10 @@ f32 = S.bf16_bits_to_f32
 
 
 # rows and columns around the tiles of the head's passes: the weight-streaming one (up to 64 rows, 256 columns a
-# workgroup), the 128-row and the 256-row tiles; every column count leaves a partly empty last tile
+# workgroup), the tiles of 128, 192 and 256 rows; every column count leaves a partly empty last tile
 @pytest.mark.parametrize("shape,vocab,n", [(S.WIDE, 4228, 1), (S.WIDE, 4228, 64), (S.MID, 1028, 33), (S.MID, 1028, 65),
-                                           (S.MID, 1284, 128), (S.MID, 2052, 129), (S.MID, 2052, 256), (S.MID, 1028, 300)])
+                                           (S.MID, 1284, 128), (S.MID, 2052, 129), (S.MID, 1028, 192), (S.MID, 2052, 193), (S.MID, 2052, 256),
+                                           (S.MID, 1028, 300), (S.MID, 1028, 385)])
 def test_head_logits_and_choice(shape, vocab, n):
     rig = Rig(shape, n_blocks=4, max_prefill_tokens=16, max_decode_batch=n, max_context=64, with_oracle=False)
     try:
