@@ -577,21 +577,23 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // The schedule of a large-tile product: tile shape and K slices by what they are expected to cost.
 // A round of w workgroups of one tile shape takes 4.8 + nk * (a + b * w / 256) us for nk K tiles: 4.8 are the first loads and the
 // tile's stores, b is what the units cost one another (fabric, power).  Fitted to 1215 timings of cold weights on 64, 96, 128,
-// 192 and 256 CUs (150 to 2048 rows; K 4096, 8192, 14336; N 4096 to 28672 pairs; every shape below, 1 to 6 slices): 6 % rms.  A slice
+// 192 and 256 CUs (150 to 2048 rows; K 4096, 8192, 14336; N 4096 to 28672 pairs; the shapes of 128, 192 and 256 rows, 1 to 6 slices): 6 % rms.
+// 160 and 224 rows, whose waves stand side by side and read more LDS per product, are set by passes of one layer at 150 to 2500 rows: against
+// the next height they take 10 % off a round on 256 CUs, 1 to 2 on 128, and on 64 they cost 3.  A slice
 // adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.  Among the shapes timed for one
 // product and slice count the rule's choice is 0.2 % slower than the fastest on average, 14 % at most.
 // Against the rule before it (128-row tiles for slices, their count a power of two up to half the chip; no 192-row tiles), product and
 // epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
 // 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
 // ---------------------------------------------------------------------------------------------
-enum DirectForm { FORM_128x256, FORM_192x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192 };
+enum DirectForm { FORM_128x256, FORM_160x256, FORM_192x256, FORM_224x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192 };
 
 static double direct_round_us(DirectForm f, int nk, long w) {
-    constexpr double A[] = {0.30, 0.38, 0.44, 0.36, 0.225}, B[] = {0.10, 0.145, 0.25, 0.165, 0.09};
+    constexpr double A[] = {0.30, 0.415, 0.38, 0.495, 0.44, 0.36, 0.225}, B[] = {0.10, 0.055, 0.145, 0.12, 0.25, 0.165, 0.09};
     return 4.8 + nk * (A[f] + B[f] * (double)w / 256.0);
 }
 static long direct_tiles(DirectForm f, int M, int nv) {
-    constexpr int BM[] = {128, 192, 256, 256, 192}, BN[] = {256, 256, 256, 192, 128};
+    constexpr int BM[] = {128, 160, 192, 224, 256, 256, 192}, BN[] = {256, 256, 256, 256, 256, 192, 128};
     return (long)((M + BM[f] - 1) / BM[f]) * ((nv + BN[f] - 1) / BN[f]);
 }
 static double direct_rounds_us(DirectForm f, int nk, long wgs, int cus) {
@@ -605,12 +607,14 @@ static double direct_mixed_us(DirectForm full, DirectForm half, int nk, long til
     return (double)(n_full / cus) * direct_round_us(full, nk, cus) + direct_round_us(half, nk, 2 * rest);
 }
 
-// The fastest form for S slices (1: the finished product) on `cus` compute units, and its cost.
-static double direct_best_form(int M, int N, int K, int epi, int S, int cus, DirectForm &form) {
+// The fastest form for S slices (1: the finished product) on `cus` compute units, and its cost.  odd: with the heights of an odd
+// number of row blocks.
+static double direct_best_form(int M, int N, int K, int epi, int S, int cus, DirectForm &form, bool odd = true) {
     const int nv = epi == EPI_SWIGLU ? (N + 127) / 128 * 256 : N, nk = (K / 32 + S - 1) / S;
     double best = 1e30;
     auto consider = [&](DirectForm f, double us) { if (us < best) { best = us; form = f; } };
-    for (DirectForm f : {FORM_256x256, FORM_192x256, FORM_128x256}) consider(f, direct_rounds_us(f, nk, S * direct_tiles(f, M, nv), cus));
+    for (DirectForm f : {FORM_256x256, FORM_224x256, FORM_192x256, FORM_160x256, FORM_128x256})
+        if (odd || (f != FORM_160x256 && f != FORM_224x256)) consider(f, direct_rounds_us(f, nk, S * direct_tiles(f, M, nv), cus));
     if (S > 1) return best;
     int n_full;
     if (epi == EPI_SWIGLU) {
@@ -626,10 +630,11 @@ static double direct_best_form(int M, int N, int K, int epi, int S, int cus, Dir
 // K slices: from (M, N, K) alone, so that results do not depend on the CU share; the whole chip's time counts four times what half
 // of it takes.  At least 16 K tiles a slice, one round of workgroups, and no more partial sums than RS_DIRECT_PARTIAL_ELEMS.
 // (With the whole chip alone 576 to 1150 rows lost up to 15 % of a product on 128 CUs; now one of the products timed does, 1150x4096x14336,
-// which gains 45 us on 256 CUs and loses 28 on 128.)
+// which gains 45 us on 256 CUs and loses 28 on 128.)  Heights of an odd number of row blocks take no part in the choice: counted in, they
+// raised the slices of 680 to 770 rows of a 4096-wide down projection from two to three, 2 % of the layer on 256 CUs for 8 % on 128.
 static int direct_splits(int M, int N, int K) {
     DirectForm f;
-    auto us = [&](int epi, int S) { return direct_best_form(M, N, K, epi, S, 256, f) + 0.25 * direct_best_form(M, N, K, epi, S, 128, f); };
+    auto us = [&](int epi, int S) { return direct_best_form(M, N, K, epi, S, 256, f, false) + 0.25 * direct_best_form(M, N, K, epi, S, 128, f, false); };
     int S = 1;
     double best = us(EPI_RESIDUAL, 1);
     const int nk = K / 32;
@@ -654,7 +659,9 @@ static void launch_direct_splitk_main(hipStream_t st, const GemmArgs &a, int S) 
     DirectForm f;
     direct_best_form(a.M, a.N, a.K, EPI_STORE, S, a.cus > 0 ? a.cus : 256, f);
     if (f == FORM_256x256) launch_direct_splitk_tiles<256, RS_NS_FULL>(st, a, S);
+    else if (f == FORM_224x256) launch_direct_splitk_tiles<224, 4>(st, a, S);
     else if (f == FORM_192x256) launch_direct_splitk_tiles<192, 4>(st, a, S);
+    else if (f == FORM_160x256) launch_direct_splitk_tiles<160, 4>(st, a, S);
     else launch_direct_splitk_tiles<128, 5>(st, a, S);
 }
 
@@ -793,7 +800,9 @@ bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
         direct_best_form(a.M, a.N, a.K, a.epi, 1, cus, f);
         switch (f) {
             case FORM_256x256: launch_direct<256, 256, RS_NS_FULL, 4>(st, a); break;   // RS_NS_FULL x 32 KB of LDS
+            case FORM_224x256: launch_direct<224, 256, 4, 4>(st, a); break;            // 4 x 30 KB
             case FORM_192x256: launch_direct<192, 256, 4, 4>(st, a); break;            // 4 x 28 KB
+            case FORM_160x256: launch_direct<160, 256, 4, 4>(st, a); break;            // 4 x 26 KB
             case FORM_128x256: launch_direct<128, 256, 5, 4>(st, a); break;            // 5 x 24 KB
             case FORM_256x192:                                                         // 4 x 28 KB
                 if (a.epi == EPI_STORE) launch_direct_epi<256, 192, EPI_STORE, 4, 4>(st, a);
@@ -1271,7 +1280,9 @@ void gemm_kernels_init() {
     set((const void *)gemm_head_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
     set((const void *)gemm_skinny_shared_kernel<EPI_RESIDUAL, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
     set((const void *)gemm_direct_splitk_kernel<128, 5>, 122880);
+    set((const void *)gemm_direct_splitk_kernel<160, 4>, 106496);
     set((const void *)gemm_direct_splitk_kernel<192, 4>, 114688);
+    set((const void *)gemm_direct_splitk_kernel<224, 4>, 122880);
     set((const void *)gemm_direct_splitk_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_STORE, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
@@ -1284,11 +1295,17 @@ void gemm_kernels_init() {
     set((const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5, 4>, 122880);
+    set((const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4, 4>, 106496);
     set((const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4, 4>, 114688);
+    set((const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4, 4>, 122880);
     set((const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5, 4>, 122880);
+    set((const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4, 4>, 106496);
     set((const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4, 4>, 114688);
+    set((const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4, 4>, 122880);
     set((const void *)gemm_direct_kernel<128, 256, EPI_SWIGLU, 5, 4>, 122880);
+    set((const void *)gemm_direct_kernel<160, 256, EPI_SWIGLU, 4, 4>, 106496);
     set((const void *)gemm_direct_kernel<192, 256, EPI_SWIGLU, 4, 4>, 114688);
+    set((const void *)gemm_direct_kernel<224, 256, EPI_SWIGLU, 4, 4>, 122880);
     set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, false>, RS_NS_FULL * 28672);
     set((const void *)gemm_direct_kernel<192, 128, EPI_SWIGLU, 5, 4>, 102400);
     set((const void *)gemm_direct_kernel<256, 192, EPI_STORE, 4, 4>, 114688);
