@@ -371,7 +371,7 @@ def test_large_layer_passes_same_bits_on_every_partition(shape, passes):
         rig.close()
 
 
-# the large-tile products at row counts that take every form of their schedule on some partition: tiles of 128, 192 and 256 rows
+# the large-tile products at row counts that take every form of their schedule on some partition: tiles of 128 to 256 rows
 # and of 192 columns, whole rounds with a last one of halves along either side, one to eight slices; the last row tile nearly
 # empty (129, 193, 385, 577) and full (576).  Each product against float32 products of its own bf16 operands: an output is one
 # rounding of a float32 sum (2^-8 of its value; 2^-7 for gate/up, whose reciprocal and exponential are approximate) and the
