@@ -646,6 +646,15 @@ static int direct_splits(int M, int N, int K) {
     return S;
 }
 
+// Slices for a pass of at most 64 rows (launch_gemm_skinny): doubled while the chip has a unit for every 256-column tile, at least 16
+// K tiles each.  Not the rows: a row's sums are in the same order whatever else is in its batch, and the costs above are fitted
+// from 150 rows on (by them 6144x6144 took 8 slices up to 55 rows and 5 from 56).
+static int skinny_direct_splits(int N, int K) {
+    int S = 1;
+    while ((N + 255) / 256 * S * 2 <= 256 && S < 8 && K / 32 / (S * 2) >= 16) S *= 2;
+    return S;
+}
+
 template <int EPI>
 __global__ __launch_bounds__(256) void skinny_epilogue_kernel(GemmArgs a, const float *__restrict__ part, int S, int Nv);
 
@@ -1251,8 +1260,9 @@ void launch_gemm_skinny(hipStream_t st, const GemmArgs &a, float *partials) {
     // on a partition (8B layer, 64 rows: 27 -> 21 us on 128 CUs, equal on 256).  A function of the shape alone.
     if (a.epi == EPI_RESIDUAL && !skinny_shared_applies(a) && a.K % 32 == 0 && a.K >= 512 && a.Wp && a.N >= 1024 && a.N % 4 == 0 &&
         a.partials == partials && a.partial_cap > 0) {
-        const int S = direct_splits(a.M, a.N, a.K);
-        if (S > 1 && (size_t)S * a.M * a.N <= a.partial_cap) {
+        int S = skinny_direct_splits(a.N, a.K);
+        while (S > 1 && (size_t)S * a.M * a.N > a.partial_cap) S /= 2;
+        if (S > 1) {
             launch_direct_splitk(st, a, S);
             return;
         }

@@ -95,6 +95,7 @@ int launch_gemm_tiled_partials(hipStream_t st, const GemmArgs &a);
 
 // Skinny variant for M <= 64 (decode): weight-streaming, deterministic split-K through
 // `partials` (fp32, at least skinny_partial_elems(...) elements).  Reads A, Wp and Wp2.
+// a.partial_cap (elements, in proportion to M) limits the slices of a residual projection that takes the large tiles.
 size_t skinny_partial_elems(int M, int N, int K, int epi);
 void launch_gemm_skinny(hipStream_t st, const GemmArgs &a, float *partials);
 // Main pass only (a.epi must be EPI_STORE): leaves part[s][m][n], s < *S_out K-slices, row stride

@@ -53,7 +53,7 @@ struct Workspace {
     bf16_t *h = nullptr, *qkv = nullptr, *attn = nullptr, *x1 = nullptr, *act = nullptr, *xbuf = nullptr;
     float *partials = nullptr, *part_o = nullptr, *part_ml = nullptr;
     float *ssq = nullptr;   // per-slice sums of squares of the two normalised inputs of a streamed pass, 2 x [ssq_slices][RS_SSQ_ROWS]
-    size_t partial_cap = 0;
+    size_t partial_cap = 0, row_partials = 0;   // partial_elems
     int rows = 0;
     // sparse feed-forward block (allocated by the first rs_set_moe_weights)
     int32_t *m_sel = nullptr, *m_pos = nullptr, *m_src = nullptr, *m_units = nullptr;
@@ -350,6 +350,17 @@ size_t stream_partial_elems(const rs_ctx *c, int M) {
     return pe;
 }
 
+// Floats of a workspace's partial sums for passes of up to `rows` rows, and of those the share of each row of a pass of at most 64: what
+// such a pass does follows from the share (from the shape alone), not from how much of the buffer it happens to leave free.
+size_t partial_elems(const rs_ctx *c, int rows, size_t &per_row) {
+    const rs_model_desc &m = c->m;
+    const int d = m.d_model, qd = m.n_q_heads * m.head_dim, nqkv = qd + 2 * m.n_kv_heads * m.head_dim, f = m.ffn_dim;
+    per_row = std::max(skinny_partial_elems(1, nqkv, d, EPI_STORE), skinny_partial_elems(1, d, qd, EPI_RESIDUAL));
+    per_row = std::max(per_row, std::max(skinny_partial_elems(1, f, d, EPI_SWIGLU), skinny_partial_elems(1, d, f, EPI_RESIDUAL)));
+    const size_t pe = std::max(std::min(rows, 64) * per_row, stream_partial_elems(c, std::min(rows, RS_STREAM_ROWS)));
+    return rows > 64 ? std::max(pe, RS_DIRECT_PARTIAL_ELEMS) : pe;   // more than 64 rows: also the K-sliced path of the large-tile GEMM
+}
+
 int32_t alloc_ws(rs_ctx *c, Workspace &w, int rows, bool decode) {
     const rs_model_desc &m = c->m;
     const size_t d = m.d_model, qd = (size_t)m.n_q_heads * m.head_dim;
@@ -369,17 +380,8 @@ int32_t alloc_ws(rs_ctx *c, Workspace &w, int rows, bool decode) {
     HIP_TRY(hipMalloc(&w.act, prow * r16(f) * 2));
     HIP_TRY(hipMemset(w.act, 0, prow * r16(f) * 2));
     HIP_TRY(hipMalloc(&w.xbuf, rows * d * 2));
-    {
-        const int Mmax = std::min(rows, 64);
-        size_t pe = rows > 64 ? RS_DIRECT_PARTIAL_ELEMS : 0;   // more than 64 rows: also the K-sliced path of the large-tile GEMM
-        pe = std::max(pe, skinny_partial_elems(Mmax, (int)nqkv, (int)d, EPI_STORE));
-        pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)qd, EPI_RESIDUAL));
-        pe = std::max(pe, skinny_partial_elems(Mmax, (int)f, (int)d, EPI_SWIGLU));
-        pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)f, EPI_RESIDUAL));
-        pe = std::max(pe, stream_partial_elems(c, std::min(rows, RS_STREAM_ROWS)));
-        HIP_TRY(hipMalloc(&w.partials, pe * sizeof(float)));
-        w.partial_cap = pe;
-    }
+    w.partial_cap = partial_elems(c, rows, w.row_partials);
+    HIP_TRY(hipMalloc(&w.partials, w.partial_cap * sizeof(float)));
     if (!decode && c->lim.max_decode_batch > 0) {
         // a hybrid batch (rs_hybrid_layer) runs decode rows through the prefill side's workspace
         const size_t nch = (c->lim.max_context + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
@@ -419,16 +421,9 @@ size_t carve_decode_ws(const rs_ctx *c, Workspace &w, unsigned char *base, int r
     if (packed_bytes) *packed_bytes = off;
     w.qkv = (bf16_t *)take(rows * nqkv * 2);
     w.x1 = (bf16_t *)take(rows * d * 2);
-    const int Mmax = std::min(rows, 64);
-    size_t pe = rows > 64 ? RS_DIRECT_PARTIAL_ELEMS : 0;
-    pe = std::max(pe, skinny_partial_elems(Mmax, (int)nqkv, (int)d, EPI_STORE));
-    pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)qd, EPI_RESIDUAL));
-    pe = std::max(pe, skinny_partial_elems(Mmax, (int)f, (int)d, EPI_SWIGLU));
-    pe = std::max(pe, skinny_partial_elems(Mmax, (int)d, (int)f, EPI_RESIDUAL));
-    pe = std::max(pe, stream_partial_elems(c, std::min(rows, RS_STREAM_ROWS)));
     w.ssq = (float *)take(2 * (size_t)ssq_slices(c) * RS_SSQ_ROWS * sizeof(float));
-    w.partials = (float *)take(pe * sizeof(float));
-    w.partial_cap = pe;
+    w.partial_cap = partial_elems(c, rows, w.row_partials);
+    w.partials = (float *)take(w.partial_cap * sizeof(float));
     const size_t nch = (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK;
     w.part_o = (float *)take((size_t)rows * m.n_q_heads * nch * m.head_dim * sizeof(float));
     w.part_ml = (float *)take((size_t)rows * m.n_q_heads * nch * 2 * sizeof(float));
@@ -569,7 +564,7 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     auto gemm = [&](GemmArgs g) {
         g.cus = c->side[side].cus;
         g.partials = w.partials;
-        g.partial_cap = w.partial_cap;
+        g.partial_cap = skinny ? M * w.row_partials : w.partial_cap;
         if (skinny) launch_gemm_skinny(st, g, w.partials);
         else if (!launch_gemm_tiled(st, g)) released_needed = true;
     };
@@ -689,7 +684,7 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
         launch_dgemm_epilogue(st, DEpiArgs{w.partials, pd.S, pd.Nv, w.x1, (bf16_t *)x_out, M, d});
     } else {
         GemmArgs gd{w.act, (const bf16_t *)lw.wd, nullptr, pl.wd, nullptr, w.x1, (bf16_t *)x_out, M, d, f, EPI_RESIDUAL,
-                    0, cus, w.partials, w.partial_cap};
+                    0, cus, w.partials, M <= 64 ? M * w.row_partials : w.partial_cap};
         if (M <= 64) launch_gemm_skinny(st, gd, w.partials);
         else ok = launch_gemm_tiled(st, gd);
     }

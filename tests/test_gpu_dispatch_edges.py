@@ -113,6 +113,27 @@ def test_sparse_block_tiles(n):
         rig.close()
 
 
+# a decode row of a sparse layer is the same bits alone and in a batch of up to 64: the output projection's K slices follow from the
+# layer's widths (3584x3840, and 6144x6144, where what the workspace holds for a row leaves fewer of them), not from the rows
+@pytest.mark.parametrize("shape", [S.LayerShape("slices-3584", 3584, 30, 10, 128, 1024), S.LayerShape("slices-6144", 6144, 48, 12, 128, 1024)])
+def test_decode_rows_do_not_depend_on_their_batch(shape):
+    ctx = np.array([(7 * i) % 40 for i in range(64)], np.int32)
+    held = [int(c) + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=36)
+    rig, mw, L = _moe_rig(shape, 2, n_blocks, 16, 64, 40)
+    try:
+        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
+        rig.load_pools_from_logical(S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2))
+        xb = S.hidden_states(64, shape.d_model, stream=36)
+        whole = rig.decode(xb, ctx, tabs, max_ctx=40)
+        for n in (1, 8, 9, 61, 62):
+            print(shape.name, n, flush=True)
+            assert np.array_equal(rig.decode(xb[:n], ctx[:n], tabs[:n], max_ctx=40), whole[:n]), f"a batch of {n}"
+    finally:
+        rig.close()
+
+
 # prompt attention: single 128-query tiles and pairs of them, one and two teams over the key tiles, at odd and even numbers
 # of 64-key tiles; own operands (the kernel's q and cache, the oracle's attention).  A gain of 8 makes the scores large
 # (tens of powers of two): the maximum moves far from tile to tile.
