@@ -283,7 +283,7 @@ __device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x16 (&acc
 // HEAD: the epilogue is head_row above.  PARTIAL: the tile covers K tiles [kt0, kt0 + nk_part) only and stores its raw float32 sums to
 // part[z][m][n] (row stride N), for an epilogue pass that adds the slices in order.
 // NT: the weights are fetched as a stream (non-temporal: first out of the L2).  Right where few row tiles share a slab and all of
-// them run at once: K slices, the head, expert tiles (below).  Whole products gain 1 % at some sizes and lose 2 to 5 at others (1300 rows of
+// them run at once: K slices, the head, expert tiles (grouped_streams_weights).  Whole products gain 1 % at some sizes and lose 2 to 5 at others (1300 rows of
 // the 8B layer 634 -> 663 us): their later rounds read the slabs again.
 // LDS stages of the 256x256 tile's ring (32 KB each): a K tile is requested three tiles ahead.  A fifth stage (the
 // whole 160 KB of a compute unit) measured the same, alone and beside a bandwidth-bound kernel on the other
@@ -757,15 +757,11 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_til
     else gemm_direct_tile<128, 256, EPI, 5, 4, false, false, NT>(g, row0, t.nb, smem);
 }
 
-// Up to this many padded rows (all experts') the expert weights are fetched as a stream: an expert then has one tile or two.  The
-// layer of the 8B widths with 8 experts, with it and without: 100 rows 662 -> 635 us, 600 rows 817 -> 772, decode of 64 rows 703 ->
-// 679; 2048 rows of the same length 1657 -> 1646 but 1785 -> 1795 where the experts are uneven, 3000 rows 2322 -> 2359.
-#define RS_GROUPED_NT_ROWS 4096
 template <int EPI>
 static void launch_grouped_epi(hipStream_t st, const GemmArgs &a) {
     const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + 127) / 128 : (a.N + 255) / 256;
     const int per_xcd = ((a.M >> 7) * n_tiles + 7) / 8;   // of as many units as there can be
-    if (a.M <= RS_GROUPED_NT_ROWS) hipLaunchKernelGGL((gemm_grouped_kernel<EPI, true>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
+    if (a.stream_weights) hipLaunchKernelGGL((gemm_grouped_kernel<EPI, true>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
     else hipLaunchKernelGGL((gemm_grouped_kernel<EPI, false>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
 }
 

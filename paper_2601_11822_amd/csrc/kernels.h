@@ -84,6 +84,7 @@ struct GemmArgs {
     // packed matrices (Wp and Wp2 alike)
     const int32_t *units = nullptr;
     size_t expert_stride = 0;
+    bool stream_weights = false;   // grouped_streams_weights
 };
 // Upper bound of what the K-sliced path of launch_gemm_tiled needs, for any M: S * M * N <= this.
 #define RS_DIRECT_PARTIAL_ELEMS ((size_t)10 << 20)
@@ -223,6 +224,13 @@ __host__ __device__ inline GroupTile grouped_tile(int x, int i, int nu, int n_ti
 }
 
 #define RS_MOE_MAX_EXPERTS 16
+// Whether the grouped GEMM fetches the weights as a stream (non-temporal): `rows` rows go to two of E experts each, and where an expert
+// has one tile or two on average (at most 512 rows) they run at once and nobody reads its weights again.  The layer of the 8B widths,
+// not streamed / streamed: decode of 64 rows through 2, 4, 16 experts 369 / 355, 472 / 451, 1154 / 1096 us; prefill through 2 experts
+// of 300, 500, 900, 1500 rows 456 / 443, 582 / 574, 823 / 825, 1134 / 1155; through 4 of 600, 1000, 1500 rows 659 / 639, 893 / 889,
+// 1178 / 1180; through 8 of 900, 1100, 1500, 2048 rows 971 / 952, 1018 / 1011, 1224 / 1212, 1707 / 1710, of 3000 2322 / 2359; through 16
+// of 600, 1500, 2500, 3000 rows 1191 / 1121, 1461 / 1424, 2124 / 2104, 2474 / 2457.
+static inline bool grouped_streams_weights(int rows, int E) { return rows <= 256 * E; }
 // Rows of the grouped (expert-major) layout that M rows with two experts each can need: an expert's segment is less than
 // 256 rows longer than its rows.
 static inline int moe_row_cap(int M, int E) { return ((2 * M + 255 * E + 127) / 128) * 128; }

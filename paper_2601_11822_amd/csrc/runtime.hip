@@ -589,11 +589,13 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
         GemmArgs gu{w.m_a, nullptr, nullptr, ml.wg, ml.wu, nullptr, w.m_act, cap, f, d, EPI_SWIGLU, 1, c->side[side].cus};
         gu.units = w.m_units;
         gu.expert_stride = ml.stride_gu;
+        gu.stream_weights = grouped_streams_weights(M, ml.E);
         bool ok = launch_gemm_grouped(st, gu);
         tick(c, side, 7);
         GemmArgs gd{w.m_act, nullptr, nullptr, ml.wd, nullptr, nullptr, w.m_out, cap, d, f, EPI_STORE, 0, c->side[side].cus};
         gd.units = w.m_units;
         gd.expert_stride = ml.stride_d;
+        gd.stream_weights = grouped_streams_weights(M, ml.E);
         ok = launch_gemm_grouped(st, gd) && ok;
         launch_moe_combine(st, ma);
         tick(c, side, 8);

@@ -67,6 +67,10 @@ int main() {
             }
             CHECK((int)seen.size() == total, "%zu of %d tiles nu=%d n_tiles=%d", seen.size(), total, nu, n_tiles);
         }
+    // expert weights are a stream up to two whole tiles an expert, whatever the number of experts
+    for (int E = 2; E <= RS_MOE_MAX_EXPERTS; ++E)
+        for (int rows = 1; rows <= 6000; ++rows)
+            CHECK(grouped_streams_weights(rows, E) == ((2 * rows + E - 1) / E <= 512), "%d rows of %d experts", rows, E);
     if (fails) { std::printf("%d checks failed\n", fails); return 1; }
     std::printf("layouts ok\n");
     return 0;

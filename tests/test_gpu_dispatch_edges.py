@@ -10,7 +10,7 @@ import rs_synth as S
 from oracle import lm, moe
 from tests.gpu_util import END_TO_END, TOL, Rig, check_cache_against_oracle, check_tensor, gather_prompt_kv, to_dev
 from tests.test_gpu_hybrid import _hybrid_case
-from tests.test_gpu_moe import _moe_rig
+from tests.test_gpu_moe import _check_routing, _moe_rig
 
 pytestmark = pytest.mark.gpu
 f32 = S.bf16_bits_to_f32
@@ -91,9 +91,9 @@ def test_streamed_pass(shape, lens, starts, ctx):
 
 
 # the sparse block's tiles: with two experts every row goes to both, so an expert has exactly `n` rows: each height of
-# tile (128 to 256 rows in steps of 32) at its edges, one tile an expert and several, four and more of two heights; 32 rows a
-# router workgroup
-@pytest.mark.parametrize("n", [1, 32, 33, 128, 129, 160, 161, 192, 193, 224, 225, 256, 257, 384, 385, 513, 577, 672, 768, 769, 833, 1025])
+# tile (128 to 256 rows in steps of 32) at its edges, one tile an expert and several, four and more of two heights, up to 512 rows
+# with streamed weights; 32 rows a router workgroup
+@pytest.mark.parametrize("n", [1, 32, 33, 128, 129, 160, 161, 192, 193, 224, 225, 256, 257, 384, 385, 512, 513, 577, 672, 768, 769, 833, 1025])
 def test_sparse_block_tiles(n):
     rig, mw, L = _moe_rig(S.WIDE, 2, S.blocks_for(n) + 2, n, 1, n + 1)
     try:
@@ -108,6 +108,33 @@ def test_sparse_block_tiles(n):
         wt = (1.0 / (1.0 + np.exp(lg[:, ::-1] - lg)))[np.arange(n)[:, None], sel]
         assert np.all(np.sort(sel, axis=1) == [0, 1]) and np.abs(wt_got - wt).max() <= TOL
         y_ref, _, _, _ = L.prefill(x, cu, tabs, Kc, Vc, sel=sel, wt=wt.astype(np.float32))
+        check_tensor("y", f32(y_bits), y_ref, x, 2, elem_mult=END_TO_END)
+    finally:
+        rig.close()
+
+
+# uneven experts: tiles of 128 and 160 rows beside those of the large ones, in a pass that streams the expert weights (up to 256
+# rows times the experts) and in one that does not
+@pytest.mark.parametrize("n", [1024, 1025, 1600])
+def test_sparse_block_uneven_experts(n):
+    shape, E, few = S.WIDE, 4, [150, 100]
+    n_blocks = S.blocks_for(n) + 2
+    rig, mw, L = _moe_rig(shape, E, n_blocks, n, 1, n + 1)
+    try:
+        two = np.tile([0, 1], (n, 1))
+        for e, rows in zip((2, 3), few):                          # experts 2 and 3 get these many rows, the others the rest
+            two[np.arange(rows) * 4 + e, 1] = e
+        tabs, cu = S.shuffled_block_tables([n], n_blocks, stream=37), np.array([0, n], np.int32)
+        xb = S.f32_to_bf16_bits(f32(S.hidden_states(n, shape.d_model, stream=37)) + 1.5 * f32(mw["router"])[two].sum(1))
+        y_bits = rig.prefill(xb, cu, tabs)
+        Kc, Vc = L.new_cache(n_blocks)
+        x = f32(xb)
+        _, x1_ref, _, _ = L.prefill(x, cu, tabs, Kc, Vc)
+        sel, wt = _check_routing(rs.RS_SIDE_PREFILL, rig, L, mw, x1_ref, n)
+        # a row in some hundreds leans elsewhere after attention: what counts is that the two experts have a tile of 5 and of 4 row blocks
+        rows = np.bincount(sel.ravel(), minlength=E)[2:]
+        assert 128 < rows[0] <= 160 and 96 < rows[1] <= 128
+        y_ref, _, _, _ = L.prefill(x, cu, tabs, Kc, Vc, sel=sel, wt=wt)
         check_tensor("y", f32(y_bits), y_ref, x, 2, elem_mult=END_TO_END)
     finally:
         rig.close()
