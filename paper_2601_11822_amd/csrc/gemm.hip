@@ -578,10 +578,12 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // A round of w workgroups of one tile shape takes 4.8 + nk * (a + b * w / 256) us for nk K tiles: 4.8 are the first loads and the
 // tile's stores, b is what the units cost one another (fabric, power).  Fitted to 1215 timings of cold weights on 64, 96, 128,
 // 192 and 256 CUs (150 to 2048 rows; K 4096, 8192, 14336; N 4096 to 28672 pairs; the shapes of 128, 192 and 256 rows, 1 to 6 slices): 6 % rms.
-// 160 and 224 rows, whose waves stand side by side and read more LDS per product, are set by passes of one layer at 150 to 2500 rows: against
-// the next height they take 10 % off a round on 256 CUs, 1 to 2 on 128, and on 64 they cost 3.  A slice
-// adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.  Among the shapes timed for one
-// product and slice count the rule's choice is 0.2 % slower than the fastest on average, 14 % at most.
+// 160 and 224 rows, whose waves stand side by side and read more LDS per product, follow from 1176 products of one layer of the 8B and 70B
+// widths (150 to 4000 rows, 64 to 256 CUs, each with every form): over these the rule's choice is 0.2 % slower than the fastest form on
+// average, 10 % at most.  With constants found on 256 CUs (0.415 + 0.055 and 0.495 + 0.12) it was 1.4 % and 21 %, nearly all on half of the
+// chip and less; layers at those and these: 8B 1150 rows on 128 CUs 773 -> 750 us, 576 rows 483 -> 466, 800 rows on 96 CUs 762 -> 715,
+// 70B 1153 rows on 128 CUs 2723 -> 2555, 620 rows on 96 1869 -> 1785.
+// A slice adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.
 // Against the rule before it (128-row tiles for slices, their count a power of two up to half the chip; no 192-row tiles), product and
 // epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
 // 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 enum DirectForm { FORM_128x256, FORM_160x256, FORM_192x256, FORM_224x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192 };
 
 static double direct_round_us(DirectForm f, int nk, long w) {
-    constexpr double A[] = {0.30, 0.415, 0.38, 0.495, 0.44, 0.36, 0.225}, B[] = {0.10, 0.055, 0.145, 0.12, 0.25, 0.165, 0.09};
+    constexpr double A[] = {0.30, 0.365, 0.38, 0.44, 0.44, 0.36, 0.225}, B[] = {0.10, 0.10, 0.145, 0.17, 0.25, 0.165, 0.09};
     return 4.8 + nk * (A[f] + B[f] * (double)w / 256.0);
 }
 static long direct_tiles(DirectForm f, int M, int nv) {
@@ -629,8 +631,8 @@ static double direct_best_form(int M, int N, int K, int epi, int S, int cus, Dir
 
 // K slices: from (M, N, K) alone, so that results do not depend on the CU share; the whole chip's time counts four times what half
 // of it takes.  At least 16 K tiles a slice, one round of workgroups, and no more partial sums than RS_DIRECT_PARTIAL_ELEMS.
-// (With the whole chip alone 576 to 1150 rows lost up to 15 % of a product on 128 CUs; now one of the products timed does, 1150x4096x14336,
-// which gains 45 us on 256 CUs and loses 28 on 128.)  Heights of an odd number of row blocks take no part in the choice: counted in, they
+// (With the whole chip alone 576 to 1150 rows lost up to 15 % of a product on 128 CUs.  What is left: two slices of 1150x4096x14336 gain 33 us
+// of the layer on 256 CUs and cost 18 on 128.)  Heights of an odd number of row blocks take no part in the choice: counted in, they
 // raised the slices of 680 to 770 rows of a 4096-wide down projection from two to three, 2 % of the layer on 256 CUs for 8 % on 128.
 static int direct_splits(int M, int N, int K) {
     DirectForm f;
