@@ -423,8 +423,9 @@ def test_large_layer_passes_same_bits_on_every_partition(shape, passes):
 # and of 192 columns, whole rounds with a last one of halves along either side, one to eight slices; the last row tile nearly
 # empty (129, 193, 385, 577) and full (576).  Each product against float32 products of its own bf16 operands: an output is one
 # rounding of a float32 sum (2^-8 of its value; 2^-7 for gate/up, whose reciprocal and exponential are approximate) and the
-# order of up to 14336 terms (1e-4 of the outputs' size).  The same bits on every partition.
-@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [129, 193, 300, 385, 576, 577, 900, 1025, 1300]), (S.LLAMA70B, [160, 333, 577, 1153]), (S.ODD, [150, 700])])
+# order of up to 14336 terms (1e-4 of the outputs' size).  q and k are rotated: one rounding of the result and, where the product
+# was stored first, one of each of the two terms.  The same bits on every partition.
+@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [129, 193, 300, 385, 576, 577, 900, 1025, 1300]), (S.LLAMA70B, [160, 170, 333, 577, 1000, 1153]), (S.ODD, [150, 700])])
 def test_large_tile_products(shape, rows):
     n_blocks = S.blocks_for(max(rows)) + 4
     rig = Rig(shape, n_blocks, max(rows), 1, max(rows) + 1, with_oracle=False)
@@ -448,7 +449,21 @@ def test_large_tile_products(shape, rows):
             v0 = shape.q_dim + (shape.qkv_dim - shape.q_dim) // 2
             act = t[0] @ w["wg"].float().t()
             act = act * torch.sigmoid(act) * (t[0] @ w["wu"].float().t())
-            for name, g, ref, ulp in (("v", t[1][:, v0:], norm @ w["wqkv"][v0:].float().t(), 2 ** -8), ("x1", t[3], x + t[2] @ w["wo"].float().t(), 2 ** -8),
+            qkv = norm @ w["wqkv"].float().t()
+            half, n_rot = shape.head_dim // 2, v0 // shape.head_dim
+            phi = torch.arange(T, device="cuda").double()[:, None] * shape.rope_base ** (-torch.arange(half, device="cuda").double() / half)
+            cos, sin = phi.cos().float()[:, None], phi.sin().float()[:, None]
+            lo, hi = qkv[:, :v0].reshape(T, n_rot, 2, half).unbind(2)
+            rot = torch.stack((lo * cos - hi * sin, hi * cos + lo * sin), 2).reshape(T, v0)
+            terms = torch.stack(((lo * cos).abs() + (hi * sin).abs(), (hi * cos).abs() + (lo * sin).abs()), 2).reshape(T, v0)
+            k = torch.from_numpy(gather_prompt_kv(rig, cu, tabs)[0]).cuda().reshape(T, -1)
+            for name, g, ref, two in (("q", t[1][:, :shape.q_dim], rot[:, :shape.q_dim], terms[:, :shape.q_dim]), ("k", k, rot[:, shape.q_dim:], terms[:, shape.q_dim:])):
+                # the operand is formed again here, as v's below: its slack, for the two terms
+                slack = 2 * 2 * 25 * 2 ** -8 * ref.square().mean().sqrt() / shape.d_model ** 0.5
+                worst = ((g - ref).abs() / (2 ** -8 * (ref.abs() + two) + slack)).max().item()
+                print(f"  {name}: {worst:.3f} of the allowed error", flush=True)
+                assert worst <= 1.0, name
+            for name, g, ref, ulp in (("v", t[1][:, v0:], qkv[:, v0:], 2 ** -8), ("x1", t[3], x + t[2] @ w["wo"].float().t(), 2 ** -8),
                                       ("act", t[4], act, 2 ** -7), ("y", t[5], t[3] + t[4] @ w["wd"].float().t(), 2 ** -8)):
                 size = ref.square().mean().sqrt()
                 # v's operand is formed again here, and one element in some 10^4 is so near the middle of two bf16 that it rounds
