@@ -425,7 +425,7 @@ def test_large_layer_passes_same_bits_on_every_partition(shape, passes):
 # rounding of a float32 sum (2^-8 of its value; 2^-7 for gate/up, whose reciprocal and exponential are approximate) and the
 # order of up to 14336 terms (1e-4 of the outputs' size).  q and k are rotated: one rounding of the result and, where the product
 # was stored first, one of each of the two terms.  The same bits on every partition.
-@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [129, 193, 300, 385, 576, 577, 900, 1025, 1300]), (S.LLAMA70B, [160, 170, 333, 577, 1000, 1153]), (S.ODD, [150, 700])])
+@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [129, 193, 300, 385, 576, 577, 900, 1025, 1300]), (S.LLAMA70B, [160, 170, 333, 545, 577, 1000, 1153]), (S.ODD, [150, 700])])
 def test_large_tile_products(shape, rows):
     n_blocks = S.blocks_for(max(rows)) + 4
     rig = Rig(shape, n_blocks, max(rows), 1, max(rows) + 1, with_oracle=False)
