@@ -4,7 +4,7 @@
 // of the fragment-packed operand layout (packed_offset) that the activations are always stored in.
 // The weight tile is the MFMA "row" operand and the activation tile the "column" operand:
 // a lane then owns 4 consecutive output columns of one output row, which makes the epilogues
-// (residual add, SwiGLU, bf16 pack) plain per-lane code with 8-byte stores.
+// (residual add, SwiGLU, bf16 pack) per-lane code; the direct kernel's row-major outputs pass through LDS on their way (store_rows).
 #include <algorithm>
 #include <type_traits>
 
@@ -17,8 +17,9 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // ten more vector instructions per element of a 256x256 epilogue, for digits far below the bf16 the result is rounded to
 __device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 // 4 consecutive output columns (n % 4 == 0) of row m
+template <int EPI>
 __device__ __forceinline__ void store_out4(const GemmArgs &a, int m, int n, bf16x4 v) {
-    bf16_t *dst = a.out_packed ? a.out + packed_offset(m, n, packed_mt(a.M)) + (n & 7) : a.out + (size_t)m * a.N + n;
+    bf16_t *dst = EPI == EPI_SWIGLU ? a.out + packed_offset(m, n, packed_mt(a.M)) + (n & 7) : a.out + (size_t)m * a.N + n;
     *(bf16x4 *)dst = v;
 }
 
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         v[i] = (bf16_t)(silu_f(acc[2 * p][tm][4 * j + i]) * acc[2 * p + 1][tm][4 * j + i]);
-                    store_out4(a, m, f, v);
+                    store_out4<EPI>(a, m, f, v);
                 }
         } else {
 #pragma unroll
@@ -157,14 +158,14 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) v[i] = (bf16_t)acc[tn][tm][4 * j + i];
                     }
-                    store_out4(a, m, n, v);
+                    store_out4<EPI>(a, m, n, v);
                 }
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Direct kernel (K % 32 == 0): same tiling and epilogues as the tiled kernel, but both operands
+// Direct kernel (K % 32 == 0): the tiled kernel's product with larger tiles of more shapes; both operands
 // are read in the fragment-packed layout (activations as their producers wrote them, weights from
 // the library's packed copies) and go global -> LDS with the 16-byte LDS-DMA load (no register
 // staging) through a ring of NS LDS stages of BK = 32, so that a K tile is requested NS-1 tiles
@@ -227,8 +228,9 @@ __device__ __forceinline__ void head_row(const HeadOut &o, const f32x16 (&acc)[T
 }
 
 // A wave's accumulators leave as whole rows.  In a register a lane holds 4 consecutive columns of one row, so a store from there
-// touches 32 rows, 16 (bf16) or 32 bytes (float32) of a line each; through LDS, 32 rows at a time, it writes 256- or 512-byte runs,
-// and the residual is read the same way.  The wave's strip (32 rows of 4 more floats than it has columns, so that the 16-byte
+// touches 32 rows, 16 (bf16) or 32 bytes (float32) of a line each; through LDS, 32 rows at a time, it writes runs as long as the wave's
+// columns (128 of them 256 or 512 bytes; 64, in tiles of 160 and 224 rows, half that; 96 of 256x192 192 bytes, not all on a line's
+// start), and the residual is read the same way.  The wave's strip (32 rows of 4 more floats than it has columns, so that the 16-byte
 // writes of 8 neighbouring rows fall on different banks) is its own: no barrier after the first, which frees the ring.
 // Bound by the write of the tile, once every compute unit stores at the same time.  2048x4096x4096 with residual 72 -> 62 us,
 // 2048x8192x512 30 -> 23 us; K slices of 128x256 sums 37.8 -> 34.8 us (576x6144x4096 in two).
@@ -1171,7 +1173,7 @@ __global__ __launch_bounds__(256) void skinny_epilogue_kernel(GemmArgs a, const 
             for (int i = 0; i < 4; ++i) v[i] = (bf16_t)acc[i];
         }
     }
-    store_out4(a, m, n, v);
+    store_out4<EPI>(a, m, n, v);
 }
 
 template <int EPI>

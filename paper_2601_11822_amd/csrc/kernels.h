@@ -72,10 +72,9 @@ struct GemmArgs {
     const bf16_t *W, *W2;
     const bf16_t *Wp, *Wp2;
     const bf16_t *resid;  // row-major [M][N]
-    bf16_t *out;          // row-major [M][N], or fragment-packed when it feeds another GEMM
+    bf16_t *out;          // row-major [M][N]; EPI_SWIGLU: fragment-packed (it feeds another GEMM)
     int M, N, K;
     int epi;
-    int out_packed = 0;
     int cus = 0;  // compute units of the launching stream's partition (0: the whole chip); scheduling only
     // float32 scratch for launch_gemm_tiled's K-sliced path (few tiles, long K); without it that path is not taken
     float *partials = nullptr;

@@ -570,7 +570,7 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     };
     // h, attn and act are fragment-packed by their producers; x1 and y are row-major
     const bf16_t *wo = (const bf16_t *)lw.wo, *wg = (const bf16_t *)lw.wg, *wu = (const bf16_t *)lw.wu, *wd = (const bf16_t *)lw.wd;
-    GemmArgs go{w.attn, wo, nullptr, pl.wo, nullptr, x, w.x1, M, d, qd, EPI_RESIDUAL, 0, c->side[side].cus, w.partials, w.partial_cap};
+    GemmArgs go{w.attn, wo, nullptr, pl.wo, nullptr, x, w.x1, M, d, qd, EPI_RESIDUAL, c->side[side].cus, w.partials, w.partial_cap};
     const int So = !skinny && residual_norm_applies(d) ? launch_gemm_tiled_partials(st, go) : 0;
     if (So) {
         launch_residual_norm(st, ResidualNormArgs{w.partials, So, x, (const bf16_t *)lw.g2, w.x1, w.h, M, d, m.rms_eps});
@@ -586,13 +586,13 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
         const int cap = std::min(w.m_cap, moe_row_cap(M, ml.E));
         MoeArgs ma{w.h, ml.router, w.m_sel, w.m_wt, w.m_pos, w.m_src, w.m_units, w.m_a, w.m_out, w.x1, y, M, d, ml.E, cap};
         launch_moe_route_and_gather(st, ma);
-        GemmArgs gu{w.m_a, nullptr, nullptr, ml.wg, ml.wu, nullptr, w.m_act, cap, f, d, EPI_SWIGLU, 1, c->side[side].cus};
+        GemmArgs gu{w.m_a, nullptr, nullptr, ml.wg, ml.wu, nullptr, w.m_act, cap, f, d, EPI_SWIGLU, c->side[side].cus};
         gu.units = w.m_units;
         gu.expert_stride = ml.stride_gu;
         gu.stream_weights = grouped_streams_weights(M, ml.E);
         bool ok = launch_gemm_grouped(st, gu);
         tick(c, side, 7);
-        GemmArgs gd{w.m_act, nullptr, nullptr, ml.wd, nullptr, nullptr, w.m_out, cap, d, f, EPI_STORE, 0, c->side[side].cus};
+        GemmArgs gd{w.m_act, nullptr, nullptr, ml.wd, nullptr, nullptr, w.m_out, cap, d, f, EPI_STORE, c->side[side].cus};
         gd.units = w.m_units;
         gd.expert_stride = ml.stride_d;
         gd.stream_weights = grouped_streams_weights(M, ml.E);
@@ -601,7 +601,7 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
         tick(c, side, 8);
         return ok && !released_needed;
     }
-    gemm(GemmArgs{w.h, wg, wu, pl.wg, pl.wu, nullptr, w.act, M, f, d, EPI_SWIGLU, 1});
+    gemm(GemmArgs{w.h, wg, wu, pl.wg, pl.wu, nullptr, w.act, M, f, d, EPI_SWIGLU});
     tick(c, side, 7);
     gemm(GemmArgs{w.act, wd, nullptr, pl.wd, nullptr, w.x1, y, M, d, f, EPI_RESIDUAL});
     tick(c, side, 8);
@@ -686,7 +686,7 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
         launch_dgemm_epilogue(st, DEpiArgs{w.partials, pd.S, pd.Nv, w.x1, (bf16_t *)x_out, M, d});
     } else {
         GemmArgs gd{w.act, (const bf16_t *)lw.wd, nullptr, pl.wd, nullptr, w.x1, (bf16_t *)x_out, M, d, f, EPI_RESIDUAL,
-                    0, cus, w.partials, M <= 64 ? M * w.row_partials : w.partial_cap};
+                    cus, w.partials, M <= 64 ? M * w.row_partials : w.partial_cap};
         if (M <= 64) launch_gemm_skinny(st, gd, w.partials);
         else ok = launch_gemm_tiled(st, gd);
     }
@@ -709,7 +709,7 @@ bool qkv_project(rs_ctx *c, int side, Workspace &w, int32_t layer, bool skinny, 
     bf16_t *vp = (bf16_t *)c->pool.v_pool + (size_t)layer * c->pool.layer_stride;
     int32_t *err = c->err_flag + side;
     GemmArgs g{w.h, (const bf16_t *)c->weights[layer].wqkv, nullptr, c->packed[layer].wqkv, nullptr, nullptr, w.qkv,
-               M, nqkv, d, EPI_STORE, 0, c->side[side].cus, w.partials, w.partial_cap};
+               M, nqkv, d, EPI_STORE, c->side[side].cus, w.partials, w.partial_cap};
     if (const int S = skinny ? 0 : launch_gemm_tiled_partials(st, g)) {
         launch_qkv_rope_epilogue(st, QkvEpiArgs{w.partials, nullptr, S, 0, nqkv, d, m.rms_eps, w.qkv, c->rope, kp, vp, dtables, ctx_lens, err, M,
                                                 m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq});
@@ -906,7 +906,7 @@ int32_t head_greedy(rs_ctx *c, int side, const bf16_t *x, int n, float *logits, 
         c->last_rows[side] = mg;
         launch_rmsnorm(st, x + (size_t)g0 * d, (const bf16_t *)c->head.final_norm, w.h, mg, d, m.rms_eps);
         GemmArgs g{w.h, (const bf16_t *)c->head.lm_head, nullptr, c->packed_lm, nullptr, nullptr, nullptr, mg, V, d, EPI_STORE,
-                   0, c->side[side].cus};
+                   c->side[side].cus};
         float *lg = logits ? logits + (size_t)g0 * V : nullptr;
         int32_t *tk = tokens ? tokens + g0 : nullptr;
         const int32_t *rsl = row_slot ? row_slot + g0 : nullptr;
