@@ -581,10 +581,13 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // tile's stores, b is what the units cost one another (fabric, power).  Fitted to 1215 timings of cold weights on 64, 96, 128,
 // 192 and 256 CUs (150 to 2048 rows; K 4096, 8192, 14336; N 4096 to 28672 pairs; the shapes of 128, 192 and 256 rows, 1 to 6 slices): 6 % rms.
 // 160 and 224 rows, whose waves stand side by side and read more LDS per product, follow from 1176 products of one layer of the 8B and 70B
-// widths (150 to 4000 rows, 64 to 256 CUs, each with every form): over these the rule's choice is 0.2 % slower than the fastest form on
-// average, 10 % at most.  With constants found on 256 CUs (0.415 + 0.055 and 0.495 + 0.12) it was 1.4 % and 21 %, nearly all on half of the
-// chip and less; layers at those and these: 8B 1150 rows on 128 CUs 773 -> 750 us, 576 rows 483 -> 466, 800 rows on 96 CUs 762 -> 715,
+// widths (150 to 4000 rows, 64 to 256 CUs, each with every form): with b = 0.10 and 0.17 the choice was 0.2 % slower than the fastest form
+// on average, 10 % at most.  With constants found on 256 CUs (0.415 + 0.055 and 0.495 + 0.12) it was 1.4 % and 21 %, nearly all on half of
+// the chip and less; layers at those and these: 8B 1150 rows on 128 CUs 773 -> 750 us, 576 rows 483 -> 466, 800 rows on 96 CUs 762 -> 715,
 // 70B 1153 rows on 128 CUs 2723 -> 2555, 620 rows on 96 1869 -> 1785.
+// Their b is 0.005 dearer than those timings gave: among forms that cost the same to 1 %, the larger tile is the faster one in passes back to
+// back, where power sets the clock (gate/up of 224 rows or of 256 with a last round of halves: 70B 5482 rows 7887 and 7783 us a layer,
+// 8B 7050 rows 2898 and 2876, 6460 rows on 192 CUs 3072 and 3032).
 // A slice adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.
 // Against the rule before it (128-row tiles for slices, their count a power of two up to half the chip; no 192-row tiles), product and
 // epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
@@ -593,7 +596,7 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 enum DirectForm { FORM_128x256, FORM_160x256, FORM_192x256, FORM_224x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192 };
 
 static double direct_round_us(DirectForm f, int nk, long w) {
-    constexpr double A[] = {0.30, 0.365, 0.38, 0.44, 0.44, 0.36, 0.225}, B[] = {0.10, 0.10, 0.145, 0.17, 0.25, 0.165, 0.09};
+    constexpr double A[] = {0.30, 0.365, 0.38, 0.44, 0.44, 0.36, 0.225}, B[] = {0.10, 0.105, 0.145, 0.175, 0.25, 0.165, 0.09};
     return 4.8 + nk * (A[f] + B[f] * (double)w / 256.0);
 }
 static long direct_tiles(DirectForm f, int M, int nv) {
