@@ -7,15 +7,29 @@
 // (residual add, SwiGLU, bf16 pack) per-lane code; the direct kernel's row-major outputs pass through LDS on their way (store_rows).
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "kernels.h"
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 // z * sigmoid(z); the reciprocal is the hardware's one-instruction approximation (1 ulp): an IEEE division costs
 // ten more vector instructions per element of a 256x256 epilogue, for digits far below the bf16 the result is rounded to
 __device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
+// f(integral_constant 0) .. f(integral_constant N - 1): straight-line code whose indices are constants before the optimizer runs
+template <class F, int... I>
+__device__ __forceinline__ void static_for_each(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_each(f, std::make_integer_sequence<int, N>{});
+}
+#define RS_INLINE __attribute__((always_inline))
 // 4 consecutive output columns (n % 4 == 0) of row m
 template <int EPI>
 __device__ __forceinline__ void store_out4(const GemmArgs &a, int m, int n, bf16x4 v) {
@@ -181,47 +195,55 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
 // tile (their results are never stored); K tiles past the end re-fetch the last tile into a stage
 // nobody reads, which keeps the loop body branch free.
 //
-// Per K tile (two MFMA steps, one barrier): the loads of tile kt+NS-1 trickle out between the
-// MFMAs; step 0 reads the step-1 fragments; step 1 waits until tile kt+1 has landed (vmcnt counts
-// the younger loads that may still fly), meets the other waves at the barrier and reads tile
-// kt+1's step-0 fragments.  In both steps the first MFMA is issued before the reads, so a wait
-// in front of a step is already satisfied and the barrier never sits between idle matrix cores.
+// Per K tile (one MFMA step of K = 32, one barrier): the loads of tile kt+NS-1 and the reads of tile kt+1's
+// fragments, into the register set that tile kt does not use, trickle out between the MFMAs.  The barrier stands in the
+// middle (vmcnt counts the younger loads that may still fly): tile kt+1 has landed, and every wave has read tile kt.
+// Earlier slots for it cost 0.2 to 0.5 % of a layer, other slots for the reads and loads nothing, a fifth stage nothing.
+//
+// 16x16x32 products, not 32x32x16: a product of some rounds of tiles on the whole chip runs at the power limit, and the smaller
+// accumulator tile moves half as many accumulator bits per multiplication.  Four waves a CU on random operands, registers
+// alone, hold 1.77 PFLOP/s with 32x32x16 and 2.05 with 16x16x32; with the fragment reads of this tile 1.68 and 1.92.
+// The sums are the same bits.
 //
 // One wave runs per SIMD, so every instruction issued between two MFMAs that takes longer than the
-// MFMA itself (32 cycles) leaves the matrix core idle.  The loop therefore issues at most one fragment
-// read and one load between two MFMAs, and a load costs three instructions: the slab bases of the K
-// tile being fetched are uniform (scalar registers, advanced by a constant per K tile with scalar
-// adds), each load's lane offset inside the slab is loop invariant, and the wave index is a compile-time
-// constant of the loop copy a wave runs, so the LDS address of a load is scalar too (no lane read-back).
+// MFMA itself (16 cycles) leaves the matrix core idle.  The loop therefore issues one fragment read or one load between
+// two MFMAs, and a load is one instruction: a buffer load whose constant offset counts in memory and in LDS alike, so
+// that the loads of a wave, consecutive kilobytes of one k block, share their lane offset and LDS address; the slab bases
+// advance by scalar adds once per K tile.  Layers of the 8B widths with 32x32x16 / 16x16x32 and vector addresses /
+// this: 2048 rows 818 / 784 / 750 us, 16384 rows 7870 / 7600 / 7370, 5444 rows of the 70B widths 7690 / 7400 / 7000; gate/up of the
+// latter 3908 -> 3472 us, 1.31 -> 1.47 PFLOP/s (matrix cores 80 % busy in both, at 1.61 and 1.82 GHz).
+// (One copy of the loop serves all four waves; a copy each, so that a wave could place its loads a quarter-spacing after its
+// neighbour's, costs the registers their allocation: the copies' 256 accumulators meet behind the loop, through scratch memory.)
 // ---------------------------------------------------------------------------------------------
-// LM head: the float32 logits (if wanted) and the best (value, column) of row m among the wave's columns n0 + 32 tn + 8 j
-// + 4 h + i, taken straight from the accumulators of the row.  NaN never wins; the lowest column wins among equals.
-template <int TN>
-__device__ __forceinline__ void head_row(const HeadOut &o, const f32x16 (&acc)[TN], int m, bool m_ok, int n0, int N, int h, int cand) {
+// LM head: the float32 logits (if wanted) and the best (value, column) of row m, taken straight from the accumulators: a lane has
+// the columns col(v) .. col(v) + 3 in vector v, ascending, the GROUPS lanes of equal lane % (64 / GROUPS) have the whole row between
+// them.  NaN never wins; the lowest column wins among equals.
+template <int GROUPS, int NV, class Col>
+__device__ __forceinline__ void head_row(const HeadOut &o, const f32x4 (&acc)[NV], Col col, int m, bool m_ok, int N, bool first, int cand) {
     float best = -__builtin_huge_valf();
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
+    for (int v = 0; v < NV; ++v) {
+        const int n = col(v);
+        if (n >= N) continue;
+        if (o.logits && m_ok) *(f32x4 *)(o.logits + (size_t)m * N + n) = acc[v];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + 32 * tn + 8 * j + 4 * h;
-            if (n >= N) continue;
-            if (o.logits && m_ok)
-                *(f32x4 *)(o.logits + (size_t)m * N + n) = f32x4{acc[tn][4 * j], acc[tn][4 * j + 1], acc[tn][4 * j + 2], acc[tn][4 * j + 3]};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) best = fmaxf(best, acc[tn][4 * j + i]);
-        }
+        for (int i = 0; i < 4; ++i) best = fmaxf(best, acc[v][i]);
+    }
     int arg = 0x7fffffff;
 #pragma unroll
-    for (int tn = TN - 1; tn >= 0; --tn)
+    for (int v = NV - 1; v >= 0; --v)
 #pragma unroll
-        for (int e = 15; e >= 0; --e) {
-            const int n = n0 + 32 * tn + 8 * (e >> 2) + 4 * h + (e & 3);
-            if (n < N && acc[tn][e] == best) arg = n;
+        for (int i = 3; i >= 0; --i) {
+            const int n = col(v) + i;
+            if (n < N && acc[v][i] == best) arg = n;
         }
-    const float vo = __shfl_xor(best, 32, 64);
-    const int ao = __shfl_xor(arg, 32, 64);
-    if (vo > best || (vo == best && ao < arg)) { best = vo; arg = ao; }
-    if (h == 0 && m_ok) {
+#pragma unroll
+    for (int x = 64 / GROUPS; x < 64; x *= 2) {
+        const float vo = __shfl_xor(best, x, 64);
+        const int ao = __shfl_xor(arg, x, 64);
+        if (vo > best || (vo == best && ao < arg)) { best = vo; arg = ao; }
+    }
+    if (first && m_ok) {
         o.cand_val[(size_t)m * o.n_cand + cand] = best;
         o.cand_idx[(size_t)m * o.n_cand + cand] = arg;
     }
@@ -236,9 +258,9 @@ __device__ __forceinline__ void head_row(const HeadOut &o, const f32x16 (&acc)[T
 // 2048x8192x512 30 -> 23 us; K slices of 128x256 sums 37.8 -> 34.8 us (576x6144x4096 in two).
 // F32: raw sums to dst[m][n] (row stride N, a multiple of 4), else bf16 to a.out (a multiple of 8), with the residual if RES.
 template <int TM, int TN, bool F32, bool RES>
-__device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x16 (&acc)[TN][TM], float *dst, int m_base, int n0, bf16_t *smem, int wave, int lane) {
+__device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x4 (&acc)[2 * TN][2 * TM], float *dst, int m_base, int n0, bf16_t *smem, int wave, int lane) {
     constexpr int WN = 32 * TN, LD = WN + 4, EPC = F32 ? 4 : 8, CPR = WN / EPC, IT = 32 * CPR / 64;   // 16-byte chunks: per row, per lane
-    const int c32 = lane & 31, h = lane >> 5, M = a.M, N = a.N;
+    const int c16 = lane & 15, g = lane >> 4, M = a.M, N = a.N;
     float *buf = (float *)smem + wave * (32 * LD);
     __syncthreads();
 #pragma unroll
@@ -254,10 +276,9 @@ __device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x16 (&acc
             }
         }
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
+        for (int half = 0; half < 2; ++half)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *(f32x4 *)&buf[c32 * LD + 32 * tn + 8 * j + 4 * h] = f32x4{acc[tn][tm][4 * j], acc[tn][tm][4 * j + 1], acc[tn][tm][4 * j + 2], acc[tn][tm][4 * j + 3]};
+            for (int tn = 0; tn < 2 * TN; ++tn) *(f32x4 *)&buf[(16 * half + c16) * LD + 16 * tn + 4 * g] = acc[tn][2 * tm + half];
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the strip is read by other lanes than wrote it
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
@@ -291,167 +312,144 @@ __device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x16 (&acc
 // whole 160 KB of a compute unit) measured the same, alone and beside a bandwidth-bound kernel on the other
 // partition: what that neighbour costs is not memory latency the ring could cover.
 #define RS_NS_FULL 4
-template <int BM, int BN, int EPI, int NS, int NW, bool PARTIAL = false, bool HEAD = false, bool NT = PARTIAL || HEAD>
+template <int BM, int BN, int EPI, int NS, bool PARTIAL = false, bool HEAD = false, bool NT = PARTIAL || HEAD>
 __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem,
                                                  const int kt0 = 0, const int nk_part = 0, float *part = nullptr, const int z = 0,
                                                  const HeadOut *ho = nullptr) {
     constexpr int BK = 32;
-    constexpr int WGM = BM % 64 ? 1 : 2;             // waves: 2 along M x NW/2 along N, or all along N (a height of an odd number of row blocks)
-    constexpr int WGN = NW / WGM;
+    constexpr int WGM = BM % 64 ? 1 : 2;             // four waves: 2 along M x 2 along N, or all along N (a height of an odd number of row blocks)
+    constexpr int WGN = 4 / WGM;
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 32, TN = WN / 32;
     constexpr int TA = BM / 32, TB = BN / 32;        // 32-row blocks per k block of the tile
-    constexpr int LB = 2 * TB / NW;                  // wave-wide loads of weights per wave per stage
+    constexpr int LB = TB / 2;                       // wave-wide loads of weights per wave per stage
     constexpr int STAGE = (BM + BN) * BK;            // elements per stage: [2][TA] A blocks, then [2][TB] B blocks
     constexpr int D = NS - 1;                        // prefetch distance in K tiles
+    constexpr int BAR = 2 * TN * TM, LSLOT = 2;      // the slots of a K tile that the barrier is in front of, and that its first load is behind
     static_assert(!HEAD || WGN == 2, "two candidates per row and column tile");
-    static_assert(TN + TM + 1 <= TN * TM, "a step must have a slot per fragment read");
+    static_assert(BAR + 1 + 2 * (TN + TM) <= 4 * TN * TM, "a K tile must have a slot per fragment read");
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wm = wave / WGN, wn = wave % WGN;
-    const int c32 = lane & 31, h = lane >> 5;
+    const int c16 = lane & 15, g16 = lane >> 4;
     const int M = a.M, N = a.N, K = a.K;
     const int Mt = packed_mt(M), Nt = ((N + 63) / 64) * 2;   // row tiles per k block of A and of the weights
 
     const size_t ksa = (size_t)Mt * 1024, ksb = (size_t)Nt * 1024;   // elements per K tile (2 k blocks)
     const int nk = PARTIAL ? nk_part : K / BK;
 
-    f32x16 acc[TN][TM];
+    f32x4 acc[2 * TN][2 * TM];
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
+    for (int i = 0; i < 2 * TN; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < 2 * TM; ++j) {
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            asm volatile("" : "+a"(acc[i][j]));
+        }
 
-    auto k_loop = [&](auto wtag) {
-        constexpr int W = decltype(wtag)::value;
-        // loads of activations per stage: the 2 TA blocks in order, the first waves one more where they do not divide
-        constexpr int LA = 2 * TA / NW + (W < 2 * TA % NW ? 1 : 0), A0 = W * (2 * TA / NW) + (W < 2 * TA % NW ? W : 2 * TA % NW);
-        constexpr int SL = 2 * TN * TM, LT = LA + LB, SP = SL / LT;
-        constexpr int CWM = W / WGN, CWN = W % WGN;
-        // The LT loads of a K tile are spread evenly over its SL MFMA slots, and wave w places its own w
-        // quarter-spacings later than wave 0: the lock-stepped waves never queue behind one another at the
-        // CU's one memory pipeline.
-        constexpr int SHIFT = (W * SP) / NW;
-        // loads of the current iteration already issued when the barrier of slot SL/2 is reached
-        constexpr int EARLY = ((SL / 2 - 1 - SHIFT) / SP) + 1;
-        // byte offsets of this wave's loads inside a K tile's slab: the slab bases are uniform and advance by a
-        // constant per K tile, so a load costs its own instruction and the LDS address register, nothing else
-        uint32_t oa[LA], ob[LB];
-#pragma unroll
-        for (int j = 0; j < LA; ++j) {
-            const int q = A0 + j, s = q / TA, t = q % TA;
-            oa[j] = (uint32_t)(((s * Mt + min((bm >> 5) + t, Mt - 1)) * 512 + lane * 8) * 2);
-        }
-#pragma unroll
-        for (int j = 0; j < LB; ++j) {
-            const int q = W * LB + j, s = q / TB, t = q % TB;
-            if (EPI == EPI_SWIGLU)   // blocks alternate: 32 gate rows, the 32 matching up rows
-                ob[j] = (uint32_t)(((s * Nt + min(nb * (TB / 2) + (t >> 1), Nt - 1)) * 512 + lane * 8) * 2);
-            else
-                ob[j] = (uint32_t)(((s * Nt + min(nb * TB + t, Nt - 1)) * 512 + lane * 8) * 2);
-        }
+    {
+        // A wave brings half of one k block of either operand: consecutive kilobytes in memory and in LDS, so that its loads share a
+        // lane offset and an LDS address and differ in the instruction's constant.  (An odd number of blocks: the first half is larger.)
+        constexpr int LA = (TA + 1) / 2, LEAST = TA / 2 + LB;   // loads of a K tile of the waves that have fewer
+        constexpr int SL = 4 * TN * TM, LT = LA + LB, SP = SL / LT, NF = 2 * (TN + TM);
+        // loads of the current K tile already issued when the barrier of slot BAR is reached
+        constexpr int EARLY = BAR > LSLOT ? (BAR - 1 - LSLOT) / SP + 1 : 0;
+        const int W = __builtin_amdgcn_readfirstlane(wave), kb = W >> 1, second = W & 1;
+        const bool more = !second || TA % 2 == 0;
+        constexpr int TBH = TB / 2;   // SwiGLU: a k block's first half is gate rows, its second half the matching up rows
+        const int va = (kb * Mt + (bm >> 5) + second * LA) * 1024 + lane * 16;
+        const int vb = (kb * Nt + (EPI == EPI_SWIGLU ? nb * TBH : nb * TB + second * TBH)) * 1024 + lane * 16;
         const char *ga = (const char *)(a.A + (size_t)kt0 * ksa);
-        const char *gb = (const char *)(a.Wp + (size_t)kt0 * ksb);
-        const char *gb2 = EPI == EPI_SWIGLU ? (const char *)(a.Wp2 + (size_t)kt0 * ksb) : nullptr;
+        const char *gb = (const char *)((EPI == EPI_SWIGLU && second ? a.Wp2 : a.Wp) + (size_t)kt0 * ksb);
         int fetch_kt = 0;   // the K tile the slab bases point at
-        auto advance = [&]() {   // to the next K tile, staying on the last one (its re-fetches land in a stage nobody reads)
+        auto advance = [&]() RS_INLINE {   // to the next K tile, staying on the last one (its re-fetches land in a stage nobody reads)
             const size_t in = fetch_kt + 1 < nk ? 1 : 0;
             ga += in * ksa * 2;
             gb += in * ksb * 2;
-            if (EPI == EPI_SWIGLU) gb2 += in * ksb * 2;
             ++fetch_kt;
         };
-        // loads [j0, j1) of the LA + LB wave-wide loads that bring the K tile at the slab bases into the stage at
-        // element offset so
-        auto issue = [&](int so, int j0, int j1) {
-            bf16_t *sa = smem + so;
-            bf16_t *sb = sa + BM * BK;
-#pragma unroll
-            for (int j = 0; j < LA + LB; ++j) {
-                if (j < j0 || j >= j1) continue;
-                if (j < LA) {
-                    const char *g = ga;
-                    asm volatile("" : "+s"(g));   // the address is formed here, next to its load, not at the top of the K tile
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + oa[j]),
-                                                     (__attribute__((address_space(3))) void *)(sa + (A0 + j) * 512), 16, 0, 0);
-                } else {
-                    const bool up = EPI == EPI_SWIGLU && (((W * LB + j - LA) % TB) & 1);
-                    const char *g = up ? gb2 : gb;
-                    asm volatile("" : "+s"(g));
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + ob[j - LA]),
-                                                     (__attribute__((address_space(3))) void *)(sb + (W * LB + j - LA) * 512), 16, 0, NT ? 2 : 0);
-                }
+        // the j-th of this wave's LA + LB loads that bring the K tile at the slab bases into the stage at element offset so.  The buffer
+        // is the K tile's slab: a row tile past the last one reads the next k block's first rows, or nothing behind the second (its
+        // results are never stored).
+        auto issue = [&](int so, auto jtag) RS_INLINE {
+            constexpr int j = decltype(jtag)::value;
+            if constexpr (j < LA) {
+                if (j >= TA / 2 && !more) return;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)ga, 0, (int)(ksa * 2), 0x00020000),
+                                                         (__attribute__((address_space(3))) void *)(smem + so + (kb * TA + second * LA) * 512), 16, va, 0, j * 1024, 0);
+            } else {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)gb, 0, (int)(ksb * 2), 0x00020000),
+                                                         (__attribute__((address_space(3))) void *)(smem + so + BM * BK + (kb * TB + second * TBH) * 512), 16, vb, 0,
+                                                         (j - LA) * 1024, NT ? 2 : 0);
             }
         };
-        bf16x8 wf[2][TN], xf[2][TM];
-        // fragment f (weights first, then activations) of step `step` of the K tile in the stage at element offset so
-        auto read_frag = [&](int set, int so, int step, int f) {
-            const bf16_t *sa = smem + so + lane * 8;
-            const bf16_t *sb = sa + BM * BK;
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-                if (f == tn) wf[set][tn] = *(const bf16x8 *)&sb[(step * TB + CWN * TN + tn) * 512];
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-                if (f == TN + tm) xf[set][tm] = *(const bf16x8 *)&sa[(step * TA + CWM * TM + tm) * 512];
+        bf16x8 wf[2][2 * TN], xf[2][2 * TM];
+        // A fragment of 16 rows x 32 k: lane (row c16, 8-wide k group g16) finds its 16 bytes in k block g16 >> 1
+        const int la = ((g16 >> 1) * TA + wm * TM) * 512 + ((g16 & 1) * 32 + c16) * 8;
+        const int lb = BM * BK + ((g16 >> 1) * TB + wn * (EPI == EPI_SWIGLU ? TN / 2 : TN)) * 512 + ((g16 & 1) * 32 + c16) * 8;
+        // the f-th fragment to be used of the K tile in the stage at element offset so: weights 0, all activations, the other weights
+        auto read_frag = [&](auto stag, int so, auto ftag) RS_INLINE {
+            constexpr int set = decltype(stag)::value, f = decltype(ftag)::value;
+            if constexpr (f >= 1 && f <= 2 * TM) {
+                constexpr int t = f - 1;
+                xf[set][t] = *(const bf16x8 *)&smem[so + la + (t >> 1) * 512 + (t & 1) * 128];
+            } else {
+                constexpr int t = f == 0 ? 0 : f - 2 * TM;
+                constexpr int blk = EPI == EPI_SWIGLU ? (t >> 2) + ((t >> 1) & 1) * TBH : t >> 1;   // gate and up blocks in turn
+                wf[set][t] = *(const bf16x8 *)&smem[so + lb + blk * 512 + (t & 1) * 128];
+            }
         };
         // prologue: K tiles 0 .. D-1 into stages 0 .. D-1
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            issue(i * STAGE, 0, LA + LB);
+        static_for<D>([&](auto i) RS_INLINE {
+            static_for<LT>([&](auto j) RS_INLINE { issue(decltype(i)::value * STAGE, j); });
             advance();
-        }
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((D - 1) * (LA + LB)) : "memory");
-#pragma unroll
-        for (int f = 0; f < TN + TM; ++f) read_frag(0, 0, 0, f);
+        });
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((D - 1) * LEAST) : "memory");
+        static_for<NF>([&](auto f) RS_INLINE { read_frag(std::integral_constant<int, 0>{}, 0, f); });
 
-        // One K tile = SL MFMA slots (two steps of TN x TM); its loads fill the stage before its own (tile kt + D).
-        // The fragment reads and the loads are placed one per slot between the MFMAs.
+        // One K tile = SL MFMA slots; its loads fill the stage before its own (tile kt + D), and it reads the fragments of the
+        // next tile into the other register set, both between the MFMAs.
         int so_cur = 0;   // element offset of the stage that holds K tile kt (uniform)
-        for (int kt = 0; kt < nk; ++kt) {
+        auto k_tile = [&](auto stag) RS_INLINE {
+            constexpr int SET = decltype(stag)::value;
             const int so_ld = so_cur == 0 ? (NS - 1) * STAGE : so_cur - STAGE;
             const int so_nxt = so_cur == (NS - 1) * STAGE ? 0 : so_cur + STAGE;
-#pragma unroll
-            for (int sl = 0; sl < SL; ++sl) {
-                const int step = sl / (TN * TM), tn = (sl % (TN * TM)) / TM, tm = sl % TM;
-                if (sl == SL / 2)
+            static_for<SL>([&](auto sltag) RS_INLINE {
+                constexpr int sl = decltype(sltag)::value, tn = sl / (2 * TM), tm = sl % (2 * TM);
+                if constexpr (sl == BAR)
                     // tile kt+1 has landed once only the younger loads are outstanding; this wave's
                     // LDS reads are complete before it tells the others so at the barrier
-                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((D - 2) * LT + EARLY) : "memory");
-                acc[tn][tm] = mfma32(wf[step][tn], xf[step][tm], acc[tn][tm]);
+                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((D - 2) * LEAST + EARLY) : "memory");
+                acc[tn][tm] = mfma16(wf[SET][tn], xf[SET][tm], acc[tn][tm]);
                 __builtin_amdgcn_sched_barrier(0);
-                if (sl >= 1 && sl < 1 + TN + TM) read_frag(1, so_cur, 1, sl - 1);
-                if (sl >= SL / 2 + 1 && sl < SL / 2 + 1 + TN + TM) read_frag(0, so_nxt, 0, sl - SL / 2 - 1);
-                if (sl >= SHIFT && (sl - SHIFT) % SP == 0 && (sl - SHIFT) / SP < LT)
-                    issue(so_ld, (sl - SHIFT) / SP, (sl - SHIFT) / SP + 1);
+                // read f goes behind slot BAR + f * (SL - BAR - 1) / NF
+                constexpr int f = ((sl - BAR) * NF + SL - BAR - 2) / (SL - BAR - 1);
+                if constexpr (sl >= BAR && f < NF && BAR + f * (SL - BAR - 1) / NF == sl)
+                    read_frag(std::integral_constant<int, 1 - SET>{}, so_nxt, std::integral_constant<int, f>{});
+                if constexpr (sl >= LSLOT && (sl - LSLOT) % SP == 0 && (sl - LSLOT) / SP < LT) issue(so_ld, std::integral_constant<int, (sl - LSLOT) / SP>{});
                 __builtin_amdgcn_sched_barrier(0);
-            }
+            });
             advance();
             so_cur = so_nxt;
+        };
+#pragma clang loop unroll(disable)
+        for (int kt = 0; kt < nk >> 1; ++kt) {
+            k_tile(std::integral_constant<int, 0>{});
+            k_tile(std::integral_constant<int, 1>{});
         }
-    };
-    switch (__builtin_amdgcn_readfirstlane(wave)) {
-        case 0: k_loop(std::integral_constant<int, 0>{}); break;
-        case 1: k_loop(std::integral_constant<int, 1>{}); break;
-        case 2: k_loop(std::integral_constant<int, 2>{}); break;
-        case 3: k_loop(std::integral_constant<int, 3>{}); break;
-        case 4: k_loop(std::integral_constant<int, 4 % NW>{}); break;
-        case 5: k_loop(std::integral_constant<int, 5 % NW>{}); break;
-        case 6: k_loop(std::integral_constant<int, 6 % NW>{}); break;
-        default: k_loop(std::integral_constant<int, 7 % NW>{}); break;
+        if (nk & 1) k_tile(std::integral_constant<int, 0>{});
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 
     if (HEAD) {
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-            const int m = bm + wm * WM + 32 * tm + c32;
-            f32x16 row[TN];
+        for (int tm = 0; tm < 2 * TM; ++tm) {
+            const int m = bm + wm * WM + 16 * tm + c16;
+            f32x4 row[2 * TN];
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn) row[tn] = acc[tn][tm];
-            head_row<TN>(*ho, row, m, m < M, nb * BN + wn * WN, N, h, nb * WGN + wn);
+            for (int tn = 0; tn < 2 * TN; ++tn) row[tn] = acc[tn][tm];
+            const int n0 = nb * BN + wn * WN + 4 * g16;
+            head_row<4>(*ho, row, [&](int v) { return n0 + 16 * v; }, m, m < M, N, g16 == 0, nb * WGN + wn);
         }
         return;
     }
@@ -463,31 +461,29 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
         store_rows<TM, TN, false, EPI == EPI_RESIDUAL>(a, acc, nullptr, bm + wm * WM, nb * BN + wn * WN, smem, wave, lane);
         return;
     }
-    // SwiGLU, fragment-packed, without a branch per store: the 4 columns c0 + 32q + 8j + 4h (c0 a multiple of 32) of row m sit at
-    // row_term(m) + col_term(c0, h) + (2q + j/2) * S16 + (j%2) * 256, where a step of 16 columns is S16 = Mt*512 elements.
-    // 32 rows of a store are one 512-byte run.
+    // SwiGLU, fragment-packed, without a branch per store: the 4 columns c0 + 16q + 4g (c0 a multiple of 32) of row m sit at
+    // row_term(m) + col_term(c0, g) + q * S16, where a step of 16 columns is S16 = Mt*512 elements.
+    // 16 rows of a store are two 256-byte runs.
     const size_t S16 = (size_t)Mt * 512;
     const int c0 = nb * (BN / 2) + wn * (TN / 2) * 32;
     constexpr int NQ = TN / 2;
-    const size_t col_term = (size_t)(c0 >> 4) * S16 + 4 * h;
+    const size_t col_term = (size_t)(c0 >> 4) * S16 + (g16 >> 1) * 256 + (g16 & 1) * 4;
     const bool whole = c0 + 32 * NQ <= N;     // wave-uniform: no column of this wave's tile is past the edge
     auto rows = [&](auto checked) {
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-            const int m = bm + wm * WM + 32 * tm + c32;
+        for (int tm = 0; tm < 2 * TM; ++tm) {
+            const int m = bm + wm * WM + 16 * tm + c16;
             if (m >= M) continue;
             bf16_t *dst = a.out + (size_t)(m >> 5) * 512 + (size_t)(m & 31) * 8 + col_term;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
+            for (int q = 0; q < 2 * NQ; ++q) {
+                if (decltype(checked)::value && c0 + 16 * q + 4 * g16 >= N) continue;
+                const f32x4 &gate = acc[4 * (q >> 1) + (q & 1)][tm], &up = acc[4 * (q >> 1) + 2 + (q & 1)][tm];
+                bf16x4 v;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (decltype(checked)::value && c0 + 32 * q + 8 * j + 4 * h >= N) continue;
-                    bf16x4 v;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        v[i] = (bf16_t)(silu_f(acc[2 * q][tm][4 * j + i]) * acc[2 * q + 1][tm][4 * j + i]);
-                    *(bf16x4 *)(dst + (size_t)(2 * q + (j >> 1)) * S16 + (j & 1) * 256) = v;
-                }
+                for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(silu_f(gate[i]) * up[i]);
+                *(bf16x4 *)(dst + (size_t)q * S16) = v;
+            }
         }
     };
     if (whole) rows(std::false_type{});
@@ -514,8 +510,8 @@ __device__ __forceinline__ void tile_rc(int t, int m_tiles, int n_tiles, int &r,
 
 // The flat workgroup id is remapped so that the workgroups resident on one XCD (ids congruent
 // mod 8) own a contiguous run of tiles in that order, served by that XCD's L2.
-template <int BM, int BN, int EPI, int NS, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_direct_kernel(GemmArgs a, int m_tiles, int n_tiles) {
+template <int BM, int BN, int EPI, int NS>
+__global__ __launch_bounds__(256) void gemm_direct_kernel(GemmArgs a, int m_tiles, int n_tiles) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     const int total = m_tiles * n_tiles;
     const int per_xcd = (total + 7) >> 3;
@@ -523,7 +519,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_direct_kernel(GemmArgs a, int m_
     if (t >= total) return;
     int r, c;
     tile_rc(t, m_tiles, n_tiles, r, c);
-    gemm_direct_tile<BM, BN, EPI, NS, NW>(a, r * BM, c, smem);
+    gemm_direct_tile<BM, BN, EPI, NS>(a, r * BM, c, smem);
 }
 
 // Whole rounds of large tiles, then a last half round: when the tiles do not divide by the number of compute units, the first
@@ -541,7 +537,7 @@ __global__ __launch_bounds__(256) void gemm_direct_mixed_kernel(GemmArgs a, int 
     if (id < n_full) {
         const int t = (id & 7) * (n_full >> 3) + (id >> 3);          // n_full is a multiple of 8
         tile_rc(t, m_tiles, n_tiles, r, c);
-        gemm_direct_tile<BM, 256, EPI, RS_NS_FULL, 4>(a, r * BM, c, smem);
+        gemm_direct_tile<BM, 256, EPI, RS_NS_FULL>(a, r * BM, c, smem);
     } else {
         const int j = id - n_full;
         const int u = (j & 7) * ((n_half + 7) >> 3) + (j >> 3);
@@ -550,10 +546,10 @@ __global__ __launch_bounds__(256) void gemm_direct_mixed_kernel(GemmArgs a, int 
         tile_rc(t, m_tiles, n_tiles, r, c);
         if (TALL) {
             const int bm = r * 256 + (u & 1) * 128;
-            if (bm < a.M) gemm_direct_tile<128, 256, EPI, 5, 4>(a, bm, c, smem);
+            if (bm < a.M) gemm_direct_tile<128, 256, EPI, 5>(a, bm, c, smem);
         } else {
             const int nb = 2 * c + (u & 1);
-            if (nb * (EPI == EPI_SWIGLU ? 64 : 128) < a.N) gemm_direct_tile<192, 128, EPI, 5, 4>(a, r * 192, nb, smem);
+            if (nb * (EPI == EPI_SWIGLU ? 64 : 128) < a.N) gemm_direct_tile<192, 128, EPI, 5>(a, r * 192, nb, smem);
         }
     }
 }
@@ -572,7 +568,7 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
     const int kt0 = z * nk_per;
     int r, c;
     tile_rc(t, m_tiles, n_tiles, r, c);
-    gemm_direct_tile<BM, 256, EPI_STORE, NS, 4, true>(a, r * BM, c, smem, kt0, min(nk_per, a.K / 32 - kt0), part, z);
+    gemm_direct_tile<BM, 256, EPI_STORE, NS, true>(a, r * BM, c, smem, kt0, min(nk_per, a.K / 32 - kt0), part, z);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -709,7 +705,7 @@ __global__ __launch_bounds__(256) void gemm_head_kernel(GemmArgs a, HeadOut o, i
     const int total = m_tiles * n_tiles, per_xcd = (total + 7) >> 3;
     const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (t >= total) return;
-    gemm_direct_tile<BM, 256, EPI_STORE, NS, 4, false, true>(a, (t % m_tiles) * BM, t / m_tiles, smem, 0, 0, nullptr, 0, &o);
+    gemm_direct_tile<BM, 256, EPI_STORE, NS, false, true>(a, (t % m_tiles) * BM, t / m_tiles, smem, 0, 0, nullptr, 0, &o);
 }
 
 template <int EPI, bool TALL>
@@ -721,22 +717,22 @@ static void launch_direct_mixed(hipStream_t st, const GemmArgs &a, int cus) {
                        m_tiles, n_full, n_half);
 }
 
-template <int BM, int BN, int EPI, int NS, int NW>
+template <int BM, int BN, int EPI, int NS>
 static void launch_direct_epi(hipStream_t st, const GemmArgs &a) {
     const int m_tiles = (a.M + BM - 1) / BM;
     const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + BN / 2 - 1) / (BN / 2) : (a.N + BN - 1) / BN;
     const int total = m_tiles * n_tiles;
     const int grid = ((total + 7) / 8) * 8;
     constexpr int lds = NS * (BM + BN) * 32 * 2;
-    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, EPI, NS, NW>), dim3(grid), dim3(64 * NW), lds, st, a, m_tiles, n_tiles);
+    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, EPI, NS>), dim3(grid), dim3(256), lds, st, a, m_tiles, n_tiles);
 }
 
-template <int BM, int BN, int NS, int NW>
+template <int BM, int BN, int NS>
 static void launch_direct(hipStream_t st, const GemmArgs &a) {
     switch (a.epi) {
-        case EPI_STORE: launch_direct_epi<BM, BN, EPI_STORE, NS, NW>(st, a); break;
-        case EPI_RESIDUAL: launch_direct_epi<BM, BN, EPI_RESIDUAL, NS, NW>(st, a); break;
-        default: launch_direct_epi<BM, BN, EPI_SWIGLU, NS, NW>(st, a); break;
+        case EPI_STORE: launch_direct_epi<BM, BN, EPI_STORE, NS>(st, a); break;
+        case EPI_RESIDUAL: launch_direct_epi<BM, BN, EPI_RESIDUAL, NS>(st, a); break;
+        default: launch_direct_epi<BM, BN, EPI_SWIGLU, NS>(st, a); break;
     }
 }
 
@@ -757,11 +753,11 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_til
     GemmArgs g = a;
     g.Wp += (size_t)(code & 31) * a.expert_stride;
     if (EPI == EPI_SWIGLU) g.Wp2 += (size_t)(code & 31) * a.expert_stride;
-    if (height == 8) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, 4, false, false, NT>(g, row0, t.nb, smem);
-    else if (height == 7) gemm_direct_tile<224, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
-    else if (height == 6) gemm_direct_tile<192, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
-    else if (height == 5) gemm_direct_tile<160, 256, EPI, 4, 4, false, false, NT>(g, row0, t.nb, smem);
-    else gemm_direct_tile<128, 256, EPI, 5, 4, false, false, NT>(g, row0, t.nb, smem);
+    if (height == 8) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, false, false, NT>(g, row0, t.nb, smem);
+    else if (height == 7) gemm_direct_tile<224, 256, EPI, 4, false, false, NT>(g, row0, t.nb, smem);
+    else if (height == 6) gemm_direct_tile<192, 256, EPI, 4, false, false, NT>(g, row0, t.nb, smem);
+    else if (height == 5) gemm_direct_tile<160, 256, EPI, 4, false, false, NT>(g, row0, t.nb, smem);
+    else gemm_direct_tile<128, 256, EPI, 5, false, false, NT>(g, row0, t.nb, smem);
 }
 
 template <int EPI>
@@ -811,16 +807,16 @@ bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
         DirectForm f;
         direct_best_form(a.M, a.N, a.K, a.epi, 1, cus, f);
         switch (f) {
-            case FORM_256x256: launch_direct<256, 256, RS_NS_FULL, 4>(st, a); break;   // RS_NS_FULL x 32 KB of LDS
-            case FORM_224x256: launch_direct<224, 256, 4, 4>(st, a); break;            // 4 x 30 KB
-            case FORM_192x256: launch_direct<192, 256, 4, 4>(st, a); break;            // 4 x 28 KB
-            case FORM_160x256: launch_direct<160, 256, 4, 4>(st, a); break;            // 4 x 26 KB
-            case FORM_128x256: launch_direct<128, 256, 5, 4>(st, a); break;            // 5 x 24 KB
+            case FORM_256x256: launch_direct<256, 256, RS_NS_FULL>(st, a); break;   // RS_NS_FULL x 32 KB of LDS
+            case FORM_224x256: launch_direct<224, 256, 4>(st, a); break;            // 4 x 30 KB
+            case FORM_192x256: launch_direct<192, 256, 4>(st, a); break;            // 4 x 28 KB
+            case FORM_160x256: launch_direct<160, 256, 4>(st, a); break;            // 4 x 26 KB
+            case FORM_128x256: launch_direct<128, 256, 5>(st, a); break;            // 5 x 24 KB
             case FORM_256x192:                                                         // 4 x 28 KB
-                if (a.epi == EPI_STORE) launch_direct_epi<256, 192, EPI_STORE, 4, 4>(st, a);
-                else launch_direct_epi<256, 192, EPI_RESIDUAL, 4, 4>(st, a);
+                if (a.epi == EPI_STORE) launch_direct_epi<256, 192, EPI_STORE, 4>(st, a);
+                else launch_direct_epi<256, 192, EPI_RESIDUAL, 4>(st, a);
                 break;
-            case FORM_192x128: launch_direct_epi<192, 128, EPI_SWIGLU, 5, 4>(st, a); break;   // 5 x 20 KB
+            case FORM_192x128: launch_direct_epi<192, 128, EPI_SWIGLU, 5>(st, a); break;   // 5 x 20 KB
             case FORM_MIXED_192: launch_direct_mixed<EPI_SWIGLU, false>(st, a, cus); break;
             default:
                 if (a.epi == EPI_STORE) launch_direct_mixed<EPI_STORE, true>(st, a, cus);
@@ -1122,9 +1118,13 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_shared_kernel(GemmArgs a, 
     if (HEAD) {
 #pragma unroll
         for (int tm = 0; tm < 2; ++tm) {
-            const f32x16 row[2] = {acc[0][tm], acc[1][tm]};
-            const int m = 32 * tm + c32;
-            head_row<2>(ho, row, m, m < M, blockIdx.x * 256 + wave * 64, a.N, h, blockIdx.x * 4 + wave);
+            f32x4 row[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) row[v][i] = acc[v >> 2][tm][4 * (v & 3) + i];
+            const int m = 32 * tm + c32, n0 = blockIdx.x * 256 + wave * 64 + 4 * h;
+            head_row<2>(ho, row, [&](int v) { return n0 + 8 * v; }, m, m < M, a.N, h == 0, blockIdx.x * 4 + wave);
         }
         return;
     }
@@ -1304,24 +1304,24 @@ void gemm_kernels_init() {
     set((const void *)gemm_direct_mixed_kernel<EPI_STORE, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_mixed_kernel<EPI_RESIDUAL, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL, 4>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5, 4>, 122880);
-    set((const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4, 4>, 106496);
-    set((const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4, 4>, 114688);
-    set((const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4, 4>, 122880);
-    set((const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5, 4>, 122880);
-    set((const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4, 4>, 106496);
-    set((const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4, 4>, 114688);
-    set((const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4, 4>, 122880);
-    set((const void *)gemm_direct_kernel<128, 256, EPI_SWIGLU, 5, 4>, 122880);
-    set((const void *)gemm_direct_kernel<160, 256, EPI_SWIGLU, 4, 4>, 106496);
-    set((const void *)gemm_direct_kernel<192, 256, EPI_SWIGLU, 4, 4>, 114688);
-    set((const void *)gemm_direct_kernel<224, 256, EPI_SWIGLU, 4, 4>, 122880);
+    set((const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL>, RS_NS_FULL * 32768);
+    set((const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL>, RS_NS_FULL * 32768);
+    set((const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL>, RS_NS_FULL * 32768);
+    set((const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5>, 122880);
+    set((const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4>, 106496);
+    set((const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4>, 114688);
+    set((const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4>, 122880);
+    set((const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5>, 122880);
+    set((const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4>, 106496);
+    set((const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4>, 114688);
+    set((const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4>, 122880);
+    set((const void *)gemm_direct_kernel<128, 256, EPI_SWIGLU, 5>, 122880);
+    set((const void *)gemm_direct_kernel<160, 256, EPI_SWIGLU, 4>, 106496);
+    set((const void *)gemm_direct_kernel<192, 256, EPI_SWIGLU, 4>, 114688);
+    set((const void *)gemm_direct_kernel<224, 256, EPI_SWIGLU, 4>, 122880);
     set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, false>, RS_NS_FULL * 28672);
-    set((const void *)gemm_direct_kernel<192, 128, EPI_SWIGLU, 5, 4>, 102400);
-    set((const void *)gemm_direct_kernel<256, 192, EPI_STORE, 4, 4>, 114688);
-    set((const void *)gemm_direct_kernel<256, 192, EPI_RESIDUAL, 4, 4>, 114688);
+    set((const void *)gemm_direct_kernel<192, 128, EPI_SWIGLU, 5>, 102400);
+    set((const void *)gemm_direct_kernel<256, 192, EPI_STORE, 4>, 114688);
+    set((const void *)gemm_direct_kernel<256, 192, EPI_RESIDUAL, 4>, 114688);
 }
 
