@@ -352,8 +352,8 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
         // lane offset and an LDS address and differ in the instruction's constant.  (An odd number of blocks: the first half is larger.)
         constexpr int LA = (TA + 1) / 2, LEAST = TA / 2 + LB;   // loads of a K tile of the waves that have fewer
         constexpr int SL = 4 * TN * TM, LT = LA + LB, SP = SL / LT, NF = 2 * (TN + TM);
-        // loads of the current K tile already issued when the barrier of slot BAR is reached
-        constexpr int EARLY = BAR > LSLOT ? (BAR - 1 - LSLOT) / SP + 1 : 0;
+        // loads of the current K tile already issued when the barrier of slot BAR is reached, by the waves that skip load LA - 1 too
+        constexpr int PLACED = BAR > LSLOT ? (BAR - 1 - LSLOT) / SP + 1 : 0, EARLY = PLACED - (TA % 2 && PLACED >= LA ? 1 : 0);
         const int W = __builtin_amdgcn_readfirstlane(wave), kb = W >> 1, second = W & 1;
         const bool more = !second || TA % 2 == 0;
         constexpr int TBH = TB / 2;   // SwiGLU: a k block's first half is gate rows, its second half the matching up rows
