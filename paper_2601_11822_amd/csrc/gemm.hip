@@ -315,7 +315,7 @@ __device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x4 (&acc)
 template <int BM, int BN, int EPI, int NS, bool PARTIAL = false, bool HEAD = false, bool NT = PARTIAL || HEAD>
 __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem,
                                                  const int kt0 = 0, const int nk_part = 0, float *part = nullptr, const int z = 0,
-                                                 const HeadOut *ho = nullptr) {
+                                                 const HeadOut *ho = nullptr, const int blocks = BM / 32) {
     constexpr int BK = 32;
     constexpr int WGM = BM % 64 ? 1 : 2;             // four waves: 2 along M x 2 along N, or all along N (a height of an odd number of row blocks)
     constexpr int WGN = 4 / WGM;
@@ -325,9 +325,10 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
     constexpr int LB = TB / 2;                       // wave-wide loads of weights per wave per stage
     constexpr int STAGE = (BM + BN) * BK;            // elements per stage: [2][TA] A blocks, then [2][TB] B blocks
     constexpr int D = NS - 1;                        // prefetch distance in K tiles
-    constexpr int BAR = 2 * TN * TM, LSLOT = 2;      // the slots of a K tile that the barrier is in front of, and that its first load is behind
+    // the slots of a K tile that the barrier is in front of (the fragment reads follow it), and that its first load is behind
+    constexpr int BAR = 2 * TN * TM < 4 * TN * TM - 1 - 2 * (TN + TM) ? 2 * TN * TM : 4 * TN * TM - 1 - 2 * (TN + TM), LSLOT = 2;
     static_assert(!HEAD || WGN == 2, "two candidates per row and column tile");
-    static_assert(BAR + 1 + 2 * (TN + TM) <= 4 * TN * TM, "a K tile must have a slot per fragment read");
+    static_assert(BAR > 0, "a K tile must have a slot per fragment read");
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wm = wave / WGN, wn = wave % WGN;
@@ -357,29 +358,29 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
         const int W = __builtin_amdgcn_readfirstlane(wave), kb = W >> 1, second = W & 1;
         const bool more = !second || TA % 2 == 0;
         constexpr int TBH = TB / 2;   // SwiGLU: a k block's first half is gate rows, its second half the matching up rows
-        const int va = (kb * Mt + (bm >> 5) + second * LA) * 1024 + lane * 16;
-        const int vb = (kb * Nt + (EPI == EPI_SWIGLU ? nb * TBH : nb * TB + second * TBH)) * 1024 + lane * 16;
-        const char *ga = (const char *)(a.A + (size_t)kt0 * ksa);
-        const char *gb = (const char *)((EPI == EPI_SWIGLU && second ? a.Wp2 : a.Wp) + (size_t)kt0 * ksb);
-        int fetch_kt = 0;   // the K tile the slab bases point at
+        // Its part of K tile 0: from there to the last block that there is (of a tile past the edge, or of an expert's last unit) is the
+        // buffer of its loads; what lies behind is not fetched, and the results it would give are never looked at.
+        const int t0a = (bm >> 5) + second * LA, t0b = EPI == EPI_SWIGLU ? nb * TBH : nb * TB + second * TBH;
+        const int bytes_a = max(min(Mt - t0a, blocks - second * LA), 0) * 1024, bytes_b = max(Nt - t0b, 0) * 1024;
+        const char *ga = (const char *)(a.A + (size_t)kt0 * ksa + (size_t)(kb * Mt + t0a) * 512);
+        const char *gb = (const char *)((EPI == EPI_SWIGLU && second ? a.Wp2 : a.Wp) + (size_t)kt0 * ksb + (size_t)(kb * Nt + t0b) * 512);
+        int fetch_kt = 0;   // the K tile they point at
         auto advance = [&]() RS_INLINE {   // to the next K tile, staying on the last one (its re-fetches land in a stage nobody reads)
             const size_t in = fetch_kt + 1 < nk ? 1 : 0;
             ga += in * ksa * 2;
             gb += in * ksb * 2;
             ++fetch_kt;
         };
-        // the j-th of this wave's LA + LB loads that bring the K tile at the slab bases into the stage at element offset so.  The buffer
-        // is the K tile's slab: a row tile past the last one reads the next k block's first rows, or nothing behind the second (its
-        // results are never stored).
+        // the j-th of this wave's LA + LB loads that bring the K tile at ga, gb into the stage at element offset so
         auto issue = [&](int so, auto jtag) RS_INLINE {
             constexpr int j = decltype(jtag)::value;
             if constexpr (j < LA) {
                 if (j >= TA / 2 && !more) return;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)ga, 0, (int)(ksa * 2), 0x00020000),
-                                                         (__attribute__((address_space(3))) void *)(smem + so + (kb * TA + second * LA) * 512), 16, va, 0, j * 1024, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)ga, 0, bytes_a, 0x00020000),
+                                                         (__attribute__((address_space(3))) void *)(smem + so + (kb * TA + second * LA) * 512), 16, lane * 16, 0, j * 1024, 0);
             } else {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)gb, 0, (int)(ksb * 2), 0x00020000),
-                                                         (__attribute__((address_space(3))) void *)(smem + so + BM * BK + (kb * TB + second * TBH) * 512), 16, vb, 0,
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)gb, 0, bytes_b, 0x00020000),
+                                                         (__attribute__((address_space(3))) void *)(smem + so + BM * BK + (kb * TB + second * TBH) * 512), 16, lane * 16, 0,
                                                          (j - LA) * 1024, NT ? 2 : 0);
             }
         };
@@ -738,34 +739,53 @@ static void launch_direct(hipStream_t st, const GemmArgs &a) {
 
 // Grouped GEMM: rows laid out expert by expert, every unit of the work list (moe_plan_kernel) a tile of 128 to 256
 // rows, in steps of 32, of one expert by 256 columns.  The arithmetic of an output element does not depend on the tile that holds it.
+// Blocks of 32 rows that are padding are neither fetched nor looked at (64 rows of 8 experts in tiles of 128 rows: gate/up 337 -> 333 us).
 // An expert's rows are cut into units of one height (two from four units on), so that the units that share its weights run
 // through K at one pace and fetch them together.  A 256-row tile beside a shorter one that runs ahead of it had every weight leave the L2 in
 // between (8 experts of 275 rows of the 8B widths, 256 + 128 rows each against 192 + 192: gate/up 801 -> 649 us, down 395 -> 324 us).
 template <int EPI, bool NT>
-__global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_tiles) {
+__global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_tiles, int cus) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     const int nu = __builtin_amdgcn_readfirstlane(a.units[0]);
     if (nu <= 0) return;
+    const bool narrow = grouped_narrow(EPI == EPI_STORE, nu, n_tiles, cus);
+    if (narrow) n_tiles = (a.N + 127) / 128;
     const GroupTile t = grouped_tile(blockIdx.x & 7, blockIdx.x >> 3, nu, n_tiles);
     if (t.u < 0) return;
     const int code = __builtin_amdgcn_readfirstlane(a.units[2 + t.u]);
-    const int row0 = (code >> 9) * 32, height = (code >> 5) & 15;
+    const int row0 = (code >> 13) * 32, height = (code >> 5) & 15, blocks = (code >> 9) & 15;
     GemmArgs g = a;
     g.Wp += (size_t)(code & 31) * a.expert_stride;
     if (EPI == EPI_SWIGLU) g.Wp2 += (size_t)(code & 31) * a.expert_stride;
-    if (height == 8) gemm_direct_tile<256, 256, EPI, RS_NS_FULL, false, false, NT>(g, row0, t.nb, smem);
-    else if (height == 7) gemm_direct_tile<224, 256, EPI, 4, false, false, NT>(g, row0, t.nb, smem);
-    else if (height == 6) gemm_direct_tile<192, 256, EPI, 4, false, false, NT>(g, row0, t.nb, smem);
-    else if (height == 5) gemm_direct_tile<160, 256, EPI, 4, false, false, NT>(g, row0, t.nb, smem);
-    else gemm_direct_tile<128, 256, EPI, 5, false, false, NT>(g, row0, t.nb, smem);
+    auto tile = [&](auto bm, auto bn, auto ns) {
+        gemm_direct_tile<decltype(bm)::value, decltype(bn)::value, EPI, decltype(ns)::value, false, false, NT>(g, row0, t.nb, smem, 0, 0, nullptr, 0, nullptr, blocks);
+    };
+#define RS_T(bm, bn, ns) tile(std::integral_constant<int, bm>{}, std::integral_constant<int, bn>{}, std::integral_constant<int, ns>{})
+    if constexpr (EPI == EPI_STORE) {
+        if (narrow) {
+            if (height == 8) RS_T(256, 128, 5);
+            else if (height == 7) RS_T(224, 128, 5);
+            else if (height == 6) RS_T(192, 128, 6);
+            else if (height == 5) RS_T(160, 128, 7);
+            else RS_T(128, 128, 8);
+            return;
+        }
+    }
+    if (height == 8) RS_T(256, 256, RS_NS_FULL);
+    else if (height == 7) RS_T(224, 256, 4);
+    else if (height == 6) RS_T(192, 256, 4);
+    else if (height == 5) RS_T(160, 256, 4);
+    else RS_T(128, 256, 5);
+#undef RS_T
 }
 
 template <int EPI>
 static void launch_grouped_epi(hipStream_t st, const GemmArgs &a) {
     const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + 127) / 128 : (a.N + 255) / 256;
-    const int per_xcd = ((a.M >> 7) * n_tiles + 7) / 8;   // of as many units as there can be
-    if (a.stream_weights) hipLaunchKernelGGL((gemm_grouped_kernel<EPI, true>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
-    else hipLaunchKernelGGL((gemm_grouped_kernel<EPI, false>), dim3(per_xcd * 8), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles);
+    const int cus = a.cus > 0 ? a.cus : 256;
+    const int grid = (std::max((a.M >> 7) * n_tiles, EPI == EPI_STORE ? cus : 0) + 7) / 8 * 8;   // of as many units as there can be; of narrow tiles no more than CUs
+    if (a.stream_weights) hipLaunchKernelGGL((gemm_grouped_kernel<EPI, true>), dim3(grid), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles, cus);
+    else hipLaunchKernelGGL((gemm_grouped_kernel<EPI, false>), dim3(grid), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles, cus);
 }
 
 bool launch_gemm_grouped(hipStream_t st, const GemmArgs &a) {

@@ -222,6 +222,12 @@ __host__ __device__ inline GroupTile grouped_tile(int x, int i, int nu, int n_ti
     return {g * RS_GROUP_UNITS + v % units, c0 + v / units};
 }
 
+// Whether the down projection's tiles are 128 columns wide instead of 256: where all of them then run at once, on twice as many CUs.
+// What bounds them is what a CU loads, 57 GB/s however deep the ring (from HBM and L2 alike: the times of the two add up); 8
+// experts of one unit each leave half of 256 CUs idle with 256 columns.  Down of the 8B widths through 8 experts on 256 CUs,
+// 256 / 128 columns: 64 rows 223 / 154 us, 256 rows 222 / 171, 600 rows 252 / 201, 900 rows 343 / 237.
+static __host__ __device__ inline bool grouped_narrow(bool store, int nu, int n_tiles, int cus) { return store && 2 * nu * n_tiles <= cus; }
+
 #define RS_MOE_MAX_EXPERTS 16
 // Whether the grouped GEMM fetches the weights as a stream (non-temporal): `rows` rows go to two of E experts each, and where an expert
 // has one tile or two on average (at most 512 rows) they run at once and nobody reads its weights again.  The layer of the 8B widths,
@@ -240,7 +246,7 @@ struct MoeArgs {
     float *wt;              // [M][2] their weights
     int32_t *pos;           // [M][2] grouped row of each assignment
     int32_t *src;           // [Mg_cap] source row of each grouped row, -1 for padding
-    int32_t *units;         // [2 + Mg_cap / 128]: units, rows in use, first row / 32 << 9 | height / 32 << 5 | expert of each
+    int32_t *units;         // [2 + Mg_cap / 128]: units, rows in use, first row / 32 << 13 | 32-row blocks with rows << 9 | height / 32 << 5 | expert of each
     bf16_t *a_g;            // gathered rows, fragment-packed with Mg_cap / 32 row tiles
     const bf16_t *out_g;    // [Mg_cap][d] expert outputs, row-major
     const bf16_t *x1;       // [M][d]

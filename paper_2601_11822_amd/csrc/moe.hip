@@ -70,7 +70,7 @@ __global__ __launch_bounds__(1024) void moe_router_kernel(MoeArgs a) {
 // a step lower where that still holds it: four tiles hide that one of them runs ahead, which two do not; 4000 rows through 8 experts
 // of the 8B widths 3247 -> 3130 us, on 64 CUs 8057 -> 7888, in steps of 64; steps of 32 against 64, the whole layer: 600 rows 764 -> 758 us,
 // 1100 1160 -> 1130, 1500 1273 -> 1226, 2500 2086 -> 1957, 4000 2959 -> 2922), the grouped GEMM's work
-// list (units, rows in use, then per unit its first row / 32, height / 32 and expert), the source row of every grouped row
+// list (units, rows in use, then per unit its first row / 32, blocks with rows, height / 32 and expert), the source row of every grouped row
 // (-1 for padding) and the grouped position of every assignment.  The order of rows inside a
 // segment is arbitrary (an atomic cursor): a row's result does not depend on where it sits.
 // ---------------------------------------------------------------------------------------------
@@ -88,10 +88,11 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoeArgs a) {
             const int k = (cnt[e] + 255) >> 8, h32 = k ? max(4, (cnt[e] + 32 * k - 1) / (32 * k)) : 0;
             const int lower = k >= 4 ? k * h32 - ((cnt[e] + 31) >> 5) : 0;   // this many of the last ones
             off[e] = row;
-            for (int j = 0; j < k; ++j) {
+            for (int j = 0, left = cnt[e]; j < k; ++j) {
                 const int h = j < k - lower ? h32 : h32 - 1;
-                a.units[2 + nu++] = (row >> 5) << 9 | h << 5 | e;
+                a.units[2 + nu++] = (row >> 5) << 13 | min((left + 31) >> 5, h) << 9 | h << 5 | e;
                 row += 32 * h;
+                left -= 32 * h;
             }
         }
         a.units[0] = nu;

@@ -312,6 +312,30 @@ def test_row_without_a_position_depends_on_its_inputs_alone(B):
         rig.close()
 
 
+# the experts' tiles: of every height (rows an expert 1 to about 600), blocks of padding left out, and the down projection's 128
+# columns wide where all of them run at once (256 CUs here) or 256 (32, and 64 from two units an expert).  The same bits in both;
+# the first of them against the oracle under the library's routing.
+@pytest.mark.parametrize("T,E", [(1, 8), (97, 8), (330, 4), (420, 4), (480, 4), (620, 8), (1000, 8), (760, 3)])
+def test_expert_tiles_of_either_width(T, E):
+    shape, n_blocks, ref = S.WIDE, S.blocks_for(T) + 2, None
+    tabs, xb = S.shuffled_block_tables([T], n_blocks, stream=36), S.hidden_states(T, S.WIDE.d_model, stream=36)
+    rig, mw, L = _moe_rig(shape, E, n_blocks, T, 1, T + 1)
+    try:
+        for split in ((256, 256), (32, 224), (64, 192)):
+            print(T, E, split, flush=True)
+            rig.ctx.set_cu_split(*split)
+            y = rig.prefill(xb, [0, T], tabs)
+            if ref is None:
+                ref, x = y, f32(xb)
+                _, x1, _, _ = L.prefill(x, np.array([0, T], np.int32), tabs, *L.new_cache(n_blocks))
+                sel, wt = _check_routing(rs.RS_SIDE_PREFILL, rig, L, mw, x1, T)
+                want, _, _, _ = L.prefill(x, np.array([0, T], np.int32), tabs, *L.new_cache(n_blocks), sel=sel, wt=wt)
+                check_tensor("y", f32(y), want, x, 2, elem_mult=END_TO_END)
+            assert np.array_equal(y, ref), f"differs at split {split}"
+    finally:
+        rig.close()
+
+
 # tiles of an odd number of 32-row blocks, whose waves do not all bring as many loads of a K tile: what a wave waits for is counted by the
 # waves with fewer.  Every pass gives the same bits (with one load too few waited for, one in some ten of these passes did not)
 @pytest.mark.parametrize("T,split", [(576, (256, 256)), (300, (256, 256)), (1120, (128, 128)), (650, (96, 160))])
