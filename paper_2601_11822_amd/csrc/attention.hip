@@ -427,7 +427,8 @@ void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a) {
 // against 2.44 ms on the whole chip) although strip 1's exponentials were placed under strip 0's P V MFMAs:
 // with a single wave per SIMD every dependent chain of the softmax (running maximum, half-wave exchanges, the
 // rescale decision) is exposed, and what the second wave hides here for nothing would have to be software
-// pipelined by hand across key tiles.
+// pipelined by hand across key tiles.  Dropped as well: 16x16x32 products, which the large-tile products gain from: with half as much
+// work per instruction they take twice the issue slots beside the softmax (16384 tokens 7145 -> 7250 us a layer).
 // =============================================================================================
 // Sums over the even and over the odd key tiles of a row, each relative to a maximum of its own, brought together.  Which
 // product is rounded is written out, so that every form gets the same bits.
@@ -523,18 +524,20 @@ __device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int 
                 const int w = __builtin_amdgcn_readfirstlane(wave);
                 const int bw = w == 0 ? blk[0] : w == 1 ? blk[1] : w == 2 ? blk[2] : blk[3];
                 const size_t head = ((size_t)bw * a.Hkv + hk) * 16 * HD;
-                const bf16_t *ksrc = a.k_pool + head + lane * 8;
-                const bf16_t *vsrc = a.v_pool + head + lane * 16;
+                // (Buffer loads: a global load to LDS counts as a generic access, after which the compiler has every fragment wait for all
+                // LDS reads in flight, not for its own: the layer at 16384 tokens 7260 -> 7145 us.)
+                const auto kbuf = __builtin_amdgcn_make_buffer_rsrc((void *)(a.k_pool + head), 0, 32 * HD, 0x00020000);
+                const auto vbuf = __builtin_amdgcn_make_buffer_rsrc((void *)(a.v_pool + head), 0, 32 * HD, 0x00020000);
                 bf16_t *kdst = ks + w * (16 * HD), *vdst = vs + w * (16 * HD);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(ksrc + j * 512),
-                                                     (__attribute__((address_space(3))) void *)(kdst + j * 512), 16, 0, 0);
+                auto *kd = (__attribute__((address_space(3))) void *)kdst;   // the constant offset counts in LDS too
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(kbuf, kd, 16, lane * 16, 0, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(kbuf, kd, 16, lane * 16, 0, 1024, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(kbuf, kd, 16, lane * 16, 0, 2048, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(kbuf, kd, 16, lane * 16, 0, 3072, 0);
 #pragma unroll
                 for (int j = 0; j < 4; ++j)   // j = 2 * half + i
-                    __builtin_amdgcn_global_load_lds(
-                        (const __attribute__((address_space(1))) void *)(vsrc + (j & 1) * (64 * 16) + (j >> 1) * 8),
-                        (__attribute__((address_space(3))) void *)(vdst + (j >> 1) * (8 * HD) + (j & 1) * 512), 16, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(vbuf, (__attribute__((address_space(3))) void *)(vdst + (j >> 1) * (8 * HD) + (j & 1) * 512), 16, lane * 32,
+                                                             (j & 1) * 2048 + (j >> 1) * 16, 0, 0);
                 return;
             }
         }
@@ -647,9 +650,9 @@ __device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int 
 #pragma unroll
                     for (int i = 0; i < 16; ++i) st[t2][i] = 0.f;
                 {
-                    // K fragment i = (key half i & 1, head_dim step i >> 1), read four fragments ahead of its MFMA; the
+                    // K fragment i = (key half i & 1, head_dim step i >> 1), read six fragments ahead of its MFMA; the
                     // two score tiles alternate, each still summed over the steps in order
-                    constexpr int NQK = 2 * KS, R = 4;
+                    constexpr int NQK = 2 * KS, R = 6;
                     auto kread = [&](int i) { return *(const bf16x8 *)&ks[klds(32 * (i & 1) + c32, 2 * (i >> 1) + h)]; };
                     bf16x8 kf[R];
 #pragma unroll
@@ -696,37 +699,47 @@ __device__ __forceinline__ void prefill_attn_unit(const PrefillAttnArgs &a, int 
                 }
                 const float ms = m_safe * sc;
                 float psum = 0.f;
-                // V fragments are read one block (DT fragments) ahead of their MFMAs
-                bf16x8 vfr[2][DT];
+                // The score registers give lane half h a block's tokens 4h..4h+3 and 8+4h..8+4h+3.  The two
+                // half-waves (same query column) trade their middle pieces, h = 0 then holds tokens 0-7 and
+                // h = 1 tokens 8-15: the contraction slices of V's own layout, 16 bytes per (dim, half).
+                bf16x8 pf[2];
+                auto weights = [&](int blk4, int t0, int n) {
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) vfr[0][dt] = *(const bf16x8 *)&vs[vlds(0, h, 32 * dt + c32)];
-#pragma unroll
-                for (int blk4 = 0; blk4 < 4; ++blk4) {  // one 16-token block per MFMA step
-                    // The score registers give lane half h the block's tokens 4h..4h+3 and 8+4h..8+4h+3.  The two
-                    // half-waves (same query column) trade their middle pieces, h = 0 then holds tokens 0-7 and
-                    // h = 1 tokens 8-15: the contraction slices of V's own layout, 16 bytes per (dim, half).
-                    bf16x8 pf;
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) {
+                    for (int t = t0; t < t0 + n; ++t) {
                         const float p = __builtin_amdgcn_exp2f(fmaf(st[blk4 >> 1][8 * (blk4 & 1) + t], sc, -ms));
                         psum += p;
-                        pf[t] = (bf16_t)p;
+                        pf[blk4 & 1][t] = (bf16_t)p;
                     }
+                };
+                auto trade = [&](int blk4) {
                     typedef uint32_t u32x4p __attribute__((ext_vector_type(4)));
-                    u32x4p pr4 = __builtin_bit_cast(u32x4p, pf);
+                    u32x4p pr4 = __builtin_bit_cast(u32x4p, pf[blk4 & 1]);
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {   // upper half-wave of word u <-> lower half-wave of word u + 2
                         const auto sw = __builtin_amdgcn_permlane32_swap(pr4[u], pr4[u + 2], false, false);
                         pr4[u] = sw[0];
                         pr4[u + 2] = sw[1];
                     }
-                    pf = __builtin_bit_cast(bf16x8, pr4);
+                    pf[blk4 & 1] = __builtin_bit_cast(bf16x8, pr4);
+                };
+                // V fragments are read one block (DT fragments) ahead of their MFMAs, and the weights of a block formed
+                // between the products of the one before (16384 tokens 7136 -> 7078 us)
+                bf16x8 vfr[2][DT];
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) vfr[0][dt] = *(const bf16x8 *)&vs[vlds(0, h, 32 * dt + c32)];
+                weights(0, 0, 8);
+                trade(0);
+#pragma unroll
+                for (int blk4 = 0; blk4 < 4; ++blk4) {  // one 16-token block per MFMA step
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) {
                         if (blk4 + 1 < 4) vfr[(blk4 + 1) & 1][dt] = *(const bf16x8 *)&vs[vlds(blk4 + 1, h, 32 * dt + c32)];
-                        o[dt] = mfma32(vfr[blk4 & 1][dt], pf, o[dt]);
+                        o[dt] = mfma32(vfr[blk4 & 1][dt], pf[blk4 & 1], o[dt]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (blk4 + 1 < 4) weights(blk4 + 1, dt * (8 / DT), 8 / DT);
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    if (blk4 + 1 < 4) trade(blk4 + 1);
                 }
                 l_run += psum;
             }
