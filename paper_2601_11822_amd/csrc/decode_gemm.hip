@@ -88,7 +88,7 @@ __device__ __forceinline__ void sum_slices(const float *p, int off, size_t strid
 // vector instructions per staged kilobyte, more cycles than its matrix instructions) and SwiGLU in a kernel of its own,
 // 47 us now; at one row 37.4 + 4.8 -> 38.3 us (6.2 TB/s).  A second row tile that holds no row is not staged or
 // multiplied (QKV at one row 13.0 -> 10.9 us).
-template <int ACT, int RT, bool PAIR, bool PSPLIT, int MT>
+template <int ACT, int RT, bool PAIR, bool PSPLIT, int MT, bool SELF = false>
 __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs a, int kb_per_wg, int Nv, DFuseArgs fz) {
     constexpr int CH = DS_CH, PD = 8;
     // An activation piece is stored 8 steps after its load was issued, right behind a weight fragment that is
@@ -180,7 +180,8 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs 
         }
     };
     RowSsq rs[MT];   // FUSED: what this lane's rows' RMSNorm scales are made of
-    if (FUSED) {
+    __shared__ float self_ssq[SELF ? RS_FEW_ROWS : 1][4];
+    if (FUSED && !SELF) {
 #pragma unroll
         for (int tm = 0; tm < MT; ++tm) rs[tm].request(fz.ssq_part, fz.S_ssq, 32 * tm + c32);
     }
@@ -205,12 +206,36 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs 
     };
 #pragma unroll
     for (int p = 0; p < PD; ++p) load_w(p, p);
+    if (SELF) {   // a few rows: the sums of squares are formed here, from the rows themselves, four at a time
+        for (int r0 = 0; r0 < M; r0 += 4) {
+            float s[4] = {};
+            for (int c = tid; c < K / 8; c += 256) {
+                bf16x8 v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = ld_bf16x8(fz.rows + (size_t)min(r0 + r, M - 1) * K + c * 8);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) s[r] += (float)v[r][e] * (float)v[r][e];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (r0 + r >= M) break;
+                s[r] = wave_sum(s[r]);
+                if (lane == 0) self_ssq[r0 + r][wave] = s[r];
+            }
+        }
+    }
     float sc[MT];
-    if (FUSED) {
+    if (FUSED && !SELF) {
 #pragma unroll
         for (int tm = 0; tm < MT; ++tm) sc[tm] = rs[tm].scale(fz.ssq_part, fz.S_ssq, 32 * tm + c32, K, fz.eps);
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (SELF) {
+        const float *s = self_ssq[min(c32, M - 1)];
+        sc[0] = 1.0f / sqrtf(((s[0] + s[1]) + (s[2] + s[3])) / (float)K + fz.eps);
+    }
 
     for (int c = 0; c < nchunks; ++c) {
         const bf16_t *cur = slab + (c & 1) * (CH * MT * 512) + lane * 8;
@@ -389,6 +414,12 @@ static void launch_dstream(hipStream_t st, const DGemmArgs &a, const DGemmPlan &
     const dim3 grid(narrow ? 2 * p.cols : p.cols, p.S), block(256);
     const bool rows = a.X_rows != nullptr;
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, ds_lds(MT), st, a, p.kb_per_wg, p.Nv, f); };
+    if constexpr (MT == 1) {
+        if (f.rows) {
+            narrow ? go(dstream_kernel<0, 1, false, true, 1, true>) : go(dstream_kernel<0, 2, true, false, 1, true>);
+            return;
+        }
+    }
     if (p.pair) narrow ? go(dstream_kernel<0, 1, false, true, MT>) : go(dstream_kernel<0, 2, true, false, MT>);
     else if (rows) narrow ? go(dstream_kernel<1, 1, false, false, MT>) : go(dstream_kernel<1, 2, false, false, MT>);
     else narrow ? go(dstream_kernel<0, 1, false, false, MT>) : go(dstream_kernel<0, 2, false, false, MT>);
@@ -495,47 +526,48 @@ static int row_grid(int M) { return M < 128 ? M : (M + 127) / 128 * 128; }
 // lower half and the matching 4 of the upper half.  A position outside the rotary table or a block id
 // outside the pool is never used as an index: the row's cache write is skipped (without a position q and k stay as they are) and
 // the error word raised.
+struct QkvPlace {   // of row m: what depends on its position alone, requested before the sums are waited for
+    int pos, blk;
+    bool pos_ok;
+    f32x4 cs01, cs23;   // cos and sin of the angles of dims i0 .. i0 + 3
+};
 template <int HD>
-__global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
-    constexpr int TPH = HD / 8;           // threads per head
-    constexpr int HPW = 256 / TPH;        // heads per workgroup
-    const int m = row_of(blockIdx.x, gridDim.x), tid = threadIdx.x;
-    const int head = blockIdx.y * HPW + tid / TPH;
-    const int n_heads = a.Hq + 2 * a.Hkv;
-    if (m >= a.M || head >= n_heads) return;
-    const int i0 = (tid % TPH) * 4, half = HD / 2;
-    int pos, max_blk;
+__device__ __forceinline__ QkvPlace qkv_place(const QkvEpiArgs &a, int m, int head, int i0) {
+    QkvPlace p;
+    int max_blk;
     const int32_t *tab_row;
     if (m < a.T) {
         int req = 0;
         while (req + 1 < a.seq.n_req && m >= a.seq.cu[req + 1]) ++req;
-        pos = a.seq.start[req] + m - a.seq.cu[req];
+        p.pos = a.seq.start[req] + m - a.seq.cu[req];
         max_blk = a.max_blk_p;
         tab_row = a.ptables + (size_t)req * max_blk;
     } else {
-        pos = a.ctx_lens[m - a.T];
+        p.pos = a.ctx_lens[m - a.T];
         max_blk = a.max_blk;
         tab_row = a.tables + (size_t)(m - a.T) * max_blk;
     }
-    const bool pos_ok = pos >= 0 && pos < a.max_pos;
-    if (!pos_ok && tid == 0 && blockIdx.y == 0) atomicOr(a.err_flag, 1);
-    // everything that depends on the position alone is requested before the sums are waited for
-    const int bi = pos_ok ? pos / RS_BLOCK_TOKENS : 0, slot = pos % RS_BLOCK_TOKENS;
-    int blk = -1;
-    if (head >= a.Hq && bi < max_blk) blk = tab_row[bi];
-    const f32x4 *tab = (const f32x4 *)(a.table + (size_t)(pos_ok ? pos : 0) * half + i0);
-    const f32x4 cs01 = tab[0], cs23 = tab[1];
-    RowSsq rs;
-    if (a.S_ssq) rs.request(a.ssq_part, a.S_ssq, m);
-    f32x4 sum[2];
-    sum_slices<4, 2>(a.part + (size_t)m * a.Nv + head * HD + i0, half, (size_t)a.M * a.Nv, a.S, sum);
-    const float sc = a.S_ssq ? rs.scale(a.ssq_part, a.S_ssq, m, a.d, a.eps) : 1.0f;
-    const f32x4 lo = sum[0] * sc, hi = sum[1] * sc;
+    p.pos_ok = p.pos >= 0 && p.pos < a.max_pos;
+    const int bi = p.pos_ok ? p.pos / RS_BLOCK_TOKENS : 0;
+    p.blk = -1;
+    if (head >= a.Hq && bi < max_blk) p.blk = tab_row[bi];
+    const f32x4 *tab = (const f32x4 *)(a.table + (size_t)(p.pos_ok ? p.pos : 0) * (HD / 2) + i0);
+    p.cs01 = tab[0];
+    p.cs23 = tab[1];
+    return p;
+}
+// lo, hi: dims i0 .. i0 + 3 of the head's halves.  first: one thread of the row's; of_head: one thread of the head's.
+template <int HD>
+__device__ __forceinline__ void qkv_finish(const QkvEpiArgs &a, const QkvPlace &p, int m, int head, int i0, const f32x4 &lo, const f32x4 &hi, bool first,
+                                           bool of_head) {
+    constexpr int half = HD / 2;
+    const int n_heads = a.Hq + 2 * a.Hkv;
+    if (!p.pos_ok && first) atomicOr(a.err_flag, 1);
     bf16x4 olo, ohi;
-    if (head < a.Hq + a.Hkv && pos_ok) {
+    if (head < a.Hq + a.Hkv && p.pos_ok) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const f32x4 &t = i < 2 ? cs01 : cs23;
+            const f32x4 &t = i < 2 ? p.cs01 : p.cs23;
             const float cc = t[2 * (i & 1)], ss = t[2 * (i & 1) + 1];
             olo[i] = (bf16_t)(lo[i] * cc - hi[i] * ss);
             ohi[i] = (bf16_t)(hi[i] * cc + lo[i] * ss);
@@ -550,23 +582,204 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
     bf16_t *row = a.qkv + (size_t)m * (n_heads * HD) + head * HD;
     *(bf16x4 *)(row + i0) = olo;
     *(bf16x4 *)(row + half + i0) = ohi;
-    if (head < a.Hq || !pos_ok) return;
-    if ((unsigned)blk >= (unsigned)a.n_blocks) {
-        if (tid % TPH == 0 && head == a.Hq) atomicOr(a.err_flag, 2);
+    if (head < a.Hq || !p.pos_ok) return;
+    if ((unsigned)p.blk >= (unsigned)a.n_blocks) {
+        if (of_head && head == a.Hq) atomicOr(a.err_flag, 2);
         return;
     }
+    const int slot = p.pos % RS_BLOCK_TOKENS;
     if (head < a.Hq + a.Hkv) {
-        bf16_t *dst = a.k_pool + ((size_t)blk * a.Hkv + (head - a.Hq)) * RS_BLOCK_TOKENS * HD;
+        bf16_t *dst = a.k_pool + ((size_t)p.blk * a.Hkv + (head - a.Hq)) * RS_BLOCK_TOKENS * HD;
         *(bf16x4 *)(dst + kpool_chunk_offset(slot, i0 & ~7) + (i0 & 7)) = olo;
         *(bf16x4 *)(dst + kpool_chunk_offset(slot, (half + i0) & ~7) + (i0 & 7)) = ohi;
     } else {
-        bf16_t *dst = a.v_pool + ((size_t)blk * a.Hkv + (head - a.Hq - a.Hkv)) * HD * RS_BLOCK_TOKENS + slot;
+        bf16_t *dst = a.v_pool + ((size_t)p.blk * a.Hkv + (head - a.Hq - a.Hkv)) * HD * RS_BLOCK_TOKENS + slot;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             dst[(i0 + i) * RS_BLOCK_TOKENS] = olo[i];
             dst[(half + i0 + i) * RS_BLOCK_TOKENS] = ohi[i];
         }
     }
+}
+
+template <int HD>
+__global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
+    constexpr int TPH = HD / 8;           // threads per head
+    constexpr int HPW = 256 / TPH;        // heads per workgroup
+    const int m = row_of(blockIdx.x, gridDim.x), tid = threadIdx.x;
+    const int head = blockIdx.y * HPW + tid / TPH;
+    if (m >= a.M || head >= a.Hq + 2 * a.Hkv) return;
+    const int i0 = (tid % TPH) * 4;
+    const QkvPlace place = qkv_place<HD>(a, m, head, i0);
+    RowSsq rs;
+    if (a.S_ssq) rs.request(a.ssq_part, a.S_ssq, m);
+    f32x4 sum[2];
+    sum_slices<4, 2>(a.part + (size_t)m * a.Nv + head * HD + i0, HD / 2, (size_t)a.M * a.Nv, a.S, sum);
+    const float sc = a.S_ssq ? rs.scale(a.ssq_part, a.S_ssq, m, a.d, a.eps) : 1.0f;
+    qkv_finish<HD>(a, place, m, head, i0, sum[0] * sc, sum[1] * sc, tid == 0 && blockIdx.y == 0, tid % TPH == 0);
+}
+
+// ---------------------------------------------------------------------------------------------
+// A pass of at most RS_FEW_ROWS rows: the projections that a stream cuts in K for enough workgroups, whole.  A workgroup's four waves take a
+// quarter of K each of the same R x 16 weight rows (QKV: R x 16 dims and those that they are rotated with), are summed in wave order
+// through LDS, and the workgroup finishes its columns: no partial sums in memory and no epilogue kernel that reads them.  What bounds
+// a layer of one row, beside its weights, is some 4 us of every kernel in it (launch, first bytes, last ones), and so it is six
+// of them instead of nine.  The activation fragments come with the weights from memory (the L2); of QKV every workgroup forms
+// x . gain of all rows in LDS, and the sums of squares with it.  A layer of the 8B widths on 256 CUs, streams / this: 1 row
+// of 900 cached tokens 97.9 / 89.3 us, 2 rows 95.6 / 88.0, 4 rows 98.7 / 91.7, 8 rows 100.9 / 97.5 with a rule that took them too, but
+// on 128 CUs 114.5 / 116.6: the lines that the rows' fragments touch grow with the rows.  More bytes in flight are slower (eight waves
+// of eight steps each 1.066 of the streams' rate where four of four have 1.084).
+// ---------------------------------------------------------------------------------------------
+#define FEW_WAVES 4
+#define FEW_PD 4   // 16x32 weight fragments in flight per wave and tile
+bool few_applies(int M, int N, int K) { return M <= RS_FEW_ROWS && K % (32 * FEW_WAVES * FEW_PD) == 0 && N % 32 == 0; }
+
+// HD: head_dim of the QKV projection, 0: a residual projection.  R: 16-row tiles of a workgroup (QKV: of either half of a head).
+template <int HD, int R>
+__global__ __launch_bounds__(64 * FEW_WAVES) void few_kernel(FewArgs a, QkvEpiArgs q) {
+    constexpr bool QKV = HD > 0;
+    constexpr int NT = QKV ? 2 * R : R, PD = FEW_PD;
+    extern __shared__ __attribute__((aligned(16))) bf16_t xs[];   // QKV: [M][K + 8]
+    __shared__ f32x4 red[FEW_WAVES][NT][64];
+    __shared__ float ssq[RS_FEW_ROWS][FEW_WAVES];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
+    const int M = a.M, N = a.N, K = a.K, m = min(c16, M - 1);
+    const int n = K / (32 * FEW_WAVES), k0 = wave * n;            // this wave's steps of 32
+    const int Nt = ((N + 63) / 64) * 2;
+    const size_t wstride = (size_t)Nt * 512, xstride = (size_t)packed_mt(M) * 512;   // per k block
+    // columns n0 (and n0 + HD / 2) .. + 16 R - 1; wave j finishes the j-th 16 of them
+    constexpr int GPH = QKV ? HD / (32 * R) : 1;   // workgroups per head
+    const int head = blockIdx.x / GPH, i0 = 16 * (R * (blockIdx.x % GPH) + wave) + 4 * g;
+    const int n0 = QKV ? head * HD + 16 * R * (blockIdx.x % GPH) : 16 * R * (int)blockIdx.x;
+    const bf16_t *w[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int r = n0 + 16 * (t % R) + (t / R) * (HD / 2);
+        w[t] = a.Wp + (size_t)(2 * k0 + (g >> 1)) * wstride + (size_t)(r >> 5) * 512 + ((g & 1) * 32 + (r & 16) + c16) * 8;
+    }
+    const bf16_t *x = QKV ? nullptr : a.A + (size_t)(2 * k0 + (g >> 1)) * xstride + ((g & 1) * 32 + m) * 8;
+    bf16x8 rw[PD][NT], rx[PD];
+    auto load = [&](int p, int step) {
+        const size_t s = (size_t)min(step, n - 1);   // (past the end: the last one again)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) rw[p][t] = ld_bf16x8_stream(w[t] + s * 2 * wstride);
+        if (!QKV) rx[p] = ld_bf16x8(x + s * 2 * xstride);
+    };
+    // the first part of four rows is requested in front of the weights, and waited for alone
+    bf16x8 xv[4], gv = zero_bf16x8();
+    auto request = [&](int r0, int c) {
+        c = min(c, K / 8 - 1);
+        gv = ld_bf16x8(a.gain + c * 8);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xv[r] = ld_bf16x8(a.X_rows + (size_t)min(r0 + r, M - 1) * K + c * 8);
+    };
+    if (QKV) request(0, tid);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < PD; ++p) load(p, p);
+    __builtin_amdgcn_sched_barrier(0);
+    QkvPlace place{};
+    const int ld = K + 8;
+    if (QKV) {
+        for (int r0 = 0; r0 < M; r0 += 4) {
+            float s[4] = {};
+            for (int c = tid; c < K / 8 + tid; c += 64 * FEW_WAVES) {   // (as often for every thread)
+                if (r0 > 0 || c != tid) request(r0, c);
+                if (c >= K / 8) continue;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    bf16x8 h;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        s[r] += (float)xv[r][e] * (float)xv[r][e];
+                        h[e] = (bf16_t)((float)xv[r][e] * (float)gv[e]);
+                    }
+                    if (r0 + r < M) *(bf16x8 *)&xs[(r0 + r) * ld + c * 8] = h;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (r0 + r >= M) break;
+                s[r] = wave_sum(s[r]);
+                if (lane == 0) ssq[r0 + r][wave] = s[r];
+            }
+        }
+        if (wave < R) place = qkv_place<QKV ? HD : 64>(q, m, head, i0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the weight loads stay in flight
+    }
+    f32x4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bf16_t *xr = xs + m * ld + k0 * 32 + 8 * g;
+    for (int s0 = 0; s0 < n; s0 += PD) {
+#pragma unroll
+        for (int p = 0; p < PD; ++p) {
+            const bf16x8 xf = QKV ? *(const bf16x8 *)&xr[(s0 + p) * 32] : rx[p];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rw[p][t], xf, acc[t], 0, 0, 0);
+            load(p, s0 + p + PD);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // lane: columns n0 + 4g .. + 3 of row c16
+#pragma unroll
+    for (int t = 0; t < NT; ++t) red[wave][t][lane] = acc[t];
+    __syncthreads();
+    if (wave >= R || c16 >= M) return;
+    f32x4 sum[2];
+#pragma unroll
+    for (int t = 0; t < NT / R; ++t) {
+        sum[t] = red[0][t * R + wave][lane];
+#pragma unroll
+        for (int v = 1; v < FEW_WAVES; ++v) sum[t] += red[v][t * R + wave][lane];
+    }
+    if constexpr (QKV) {
+        float t = 0.f;
+#pragma unroll
+        for (int v = 0; v < FEW_WAVES; ++v) t += ssq[m][v];
+        const float sc = 1.0f / sqrtf(t / (float)K + a.eps);
+        qkv_finish<HD>(q, place, m, head, i0, sum[0] * sc, sum[1] * sc, blockIdx.x == 0 && wave == 0 && g == 0, i0 == 0);
+    } else {
+        const int col = n0 + 16 * wave + 4 * g;
+        const bf16x4 r = *(const bf16x4 *)(a.resid + (size_t)m * N + col);
+        bf16x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(sum[0][i] + (float)r[i]);
+        *(bf16x4 *)(a.out + (size_t)m * N + col) = v;
+        if (a.gain) {
+            const bf16x4 gv = *(const bf16x4 *)(a.gain + col);
+            bf16x4 h;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) h[i] = (bf16_t)((float)v[i] * (float)gv[i]);
+            *(bf16x4 *)(a.out_gain + packed_offset(m, col, packed_mt(M)) + (col & 7)) = h;
+        }
+    }
+}
+
+// Tiles of a workgroup: rounds of workgroups (one per CU) times what a workgroup moves, its tiles of weights and `act` of one for the rows.
+// The same sums whatever the number.  One row of the 8B widths, streams / one tile throughout / this, four layers: on 128 CUs 446 / 469 / 438 us,
+// on 64 698 / 767 / 680 (four rows), on 192 437 / 459 / 428, on 96, where no number of tiles fills the CUs, 586 / 629 / 603.
+static int few_tiles(int tiles, int cus, double act, int most) {
+    int best = 1;
+    double least = 1e30;
+    for (int R = 1; R <= most; R *= 2) {
+        const double cost = (double)((tiles / R + cus - 1) / cus) * (R + act);
+        if (cost < least) { least = cost; best = R; }
+    }
+    return best;
+}
+void launch_few_residual(hipStream_t st, const FewArgs &a, int cus) {
+    const int R = few_tiles(a.N / 16, cus, 0.6, a.N % 64 ? 2 : 4);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.N / (16 * R)), dim3(64 * FEW_WAVES), 0, st, a, QkvEpiArgs{}); };
+    R == 4 ? go(few_kernel<0, 4>) : R == 2 ? go(few_kernel<0, 2>) : go(few_kernel<0, 1>);
+}
+void launch_few_qkv(hipStream_t st, const FewArgs &a, const QkvEpiArgs &q, int cus) {
+    const int R = few_tiles(a.N / 32, cus, 0.1, q.hd == 64 ? 2 : 4);
+    const dim3 grid(a.N / (32 * R)), block(64 * FEW_WAVES);
+    const size_t lds = (size_t)a.M * (a.K + 8) * sizeof(bf16_t);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a, q); };
+    if (q.hd == 128) R == 4 ? go(few_kernel<128, 4>) : R == 2 ? go(few_kernel<128, 2>) : go(few_kernel<128, 1>);
+    else R == 2 ? go(few_kernel<64, 2>) : go(few_kernel<64, 1>);
 }
 
 void launch_qkv_rope_epilogue(hipStream_t st, const QkvEpiArgs &a) {
@@ -643,6 +856,14 @@ static void dstream_init() {
     set((const void *)dstream_kernel<0, 2, false, false, MT>);
 }
 void decode_gemm_kernels_init() {
+    auto set = [](const void *f, int lds) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+    set((const void *)dstream_kernel<0, 1, false, true, 1, true>, ds_lds(1));
+    set((const void *)dstream_kernel<0, 2, true, false, 1, true>, ds_lds(1));
+    set((const void *)few_kernel<128, 1>, RS_FEW_LDS);
+    set((const void *)few_kernel<128, 2>, RS_FEW_LDS);
+    set((const void *)few_kernel<128, 4>, RS_FEW_LDS);
+    set((const void *)few_kernel<64, 1>, RS_FEW_LDS);
+    set((const void *)few_kernel<64, 2>, RS_FEW_LDS);
     dstream_init<1>();
     dstream_init<2>();
     dstream_init<3>();

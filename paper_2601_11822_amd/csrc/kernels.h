@@ -132,6 +132,7 @@ struct DFuseArgs {            // a gate/up pair: out = silu(s g) * (s u) with th
     int S_ssq = 0;
     float eps = 0.f;
     bf16_t *out = nullptr;              // fragment-packed [M][N]
+    const bf16_t *rows = nullptr;       // instead of ssq_part, up to RS_FEW_ROWS rows: the rows [M][K] themselves
 };
 struct DGemmPlan {
     bool pair;
@@ -179,6 +180,22 @@ struct QkvEpiArgs {
     SeqInfo seq{};
 };
 void launch_qkv_rope_epilogue(hipStream_t st, const QkvEpiArgs &a);
+// The projections of at most RS_FEW_ROWS rows, finished in one kernel.
+#define RS_FEW_ROWS 4
+struct FewArgs {
+    const bf16_t *A;          // fragment-packed activations, or (QKV)
+    const bf16_t *X_rows;     // the rows [M][K], normalised with
+    const bf16_t *gain;       //   this gain [K]; of a residual projection: the next RMSNorm's gain [N] or nullptr
+    const bf16_t *Wp;
+    int M, N, K;
+    float eps;
+    const bf16_t *resid;      // row-major [M][N]
+    bf16_t *out, *out_gain;   // resid + product, row-major; times the gain, fragment-packed
+};
+#define RS_FEW_LDS 98304   // most bytes of LDS for the rows; up to 33 KB more for the waves' sums
+bool few_applies(int M, int N, int K);   // K a multiple of 512, N of 32; the QKV projection's rows must fit RS_FEW_LDS too: M * (K + 8) * 2
+void launch_few_residual(hipStream_t st, const FewArgs &a, int cus);
+void launch_few_qkv(hipStream_t st, const FewArgs &a, const QkvEpiArgs &q, int cus);   // rotated q | k | v and the cache write, as launch_qkv_rope_epilogue
 // x1 = resid + the slices' sum (row-major) and h = RMSNorm(x1; gain) (fragment-packed), a row a workgroup.  Needs
 // residual_norm_applies: rows of at most 8192, a multiple of 8.
 struct ResidualNormArgs {

@@ -619,7 +619,7 @@ void lend_partials(PrefillAttnArgs &pa, const Workspace &w, int cus) {
 // seq), then B decode rows.  Every projection is a stream of its weights with the RMSNorm of its input folded in
 // (decode_gemm.hip), and the kernels in between belong to their producers: QKV stream, its epilogue (row scale, rotary,
 // cache write), attention of each kind of row, O stream, its epilogue (residual, gate/up's operand), gate/up stream with
-// SwiGLU, down stream, residual.  Against the K-sliced large-tile kernels with norm, rotary and SwiGLU launches of their
+// SwiGLU, down stream, residual; of at most RS_FEW_ROWS rows a kernel each for QKV, output and down projection.  Against the K-sliced large-tile kernels with norm, rotary and SwiGLU launches of their
 // own, on 256 CUs: 8B layer at 77 prompt rows 171 -> 126 us, 70B layer at 101 decode rows 682 -> 640 us.
 bool streams(const rs_ctx *c, int layer, int rows) { return rows <= RS_STREAM_ROWS && c->moe[layer].E == 0 && stream_applies(c); }
 
@@ -644,9 +644,16 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     };
     tick(c, side, 0);
     tick(c, side, 1);
+    // (not for wider layers, whose workgroups are more than a round of the chip: 70B widths, 1 row, on 256 CUs 279 -> 271 us, on 128 348 -> 351,
+    // on 96 458 -> 487; a function of the shapes alone, so that the sums are)
+    const bool few = d <= 16 * RS_TOTAL_CUS && few_applies(M, nqkv, d) && few_applies(M, d, qd) && few_applies(M, d, f) && (size_t)M * (d + 8) * 2 <= RS_FEW_LDS;
     const DGemmPlan pq = dgemm_plan(nqkv, d, false);
     int S_ssq = pq.S;
-    if (dgemm_gains_inline(M, pq)) {
+    QkvEpiArgs qe{w.partials, ssq1, pq.S, S_ssq, pq.Nv, d, m.rms_eps, w.qkv, c->rope, kp, vp, dtables, ctx_lens, err, M,
+                  m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq};
+    if (few) {
+        launch_few_qkv(st, FewArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, pl.wqkv, M, nqkv, d, m.rms_eps, nullptr, nullptr, nullptr}, qe, cus);
+    } else if (dgemm_gains_inline(M, pq)) {
         stream(DGemmArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, ssq1, pl.wqkv, nullptr, w.partials, M, nqkv, d}, pq);
     } else {
         launch_gain_pack(st, (const bf16_t *)x_in, (const bf16_t *)lw.g1, w.h, ssq1, M, d);
@@ -654,8 +661,8 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
         S_ssq = (d + 1023) / 1024;
         stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wqkv, nullptr, w.partials, M, nqkv, d}, pq);
     }
-    launch_qkv_rope_epilogue(st, QkvEpiArgs{w.partials, ssq1, pq.S, S_ssq, pq.Nv, d, m.rms_eps, w.qkv, c->rope, kp, vp, dtables, ctx_lens, err, M,
-                                            m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq});
+    qe.S_ssq = S_ssq;
+    if (!few) launch_qkv_rope_epilogue(st, qe);
     tick(c, side, 2);
     tick(c, side, 3);
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd, max_blk_p, c->pool.n_blocks, sl2, seq};
@@ -671,6 +678,18 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     else launch_decode_attention(st, da);
     tick(c, side, 4);
     const DGemmPlan po = dgemm_plan(d, qd, false);
+    if (few) {
+        launch_few_residual(st, FewArgs{w.attn, nullptr, (const bf16_t *)lw.g2, pl.wo, M, d, qd, m.rms_eps, (const bf16_t *)x_in, w.x1, w.h}, cus);
+        tick(c, side, 5);
+        tick(c, side, 6);
+        stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wg, pl.wu, nullptr, M, f, d}, dgemm_plan(f, d, true),
+               DFuseArgs{nullptr, 0, m.rms_eps, w.act, w.x1});
+        tick(c, side, 7);
+        launch_few_residual(st, FewArgs{w.act, nullptr, nullptr, pl.wd, M, d, f, m.rms_eps, w.x1, (bf16_t *)x_out, nullptr}, cus);
+        tick(c, side, 8);
+        HIP_TRY(hipGetLastError());
+        return RS_OK;
+    }
     stream(DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, M, d, qd}, po);
     // x1 = x + attn Wo, and with it the gate/up projection's operand: x1 . g2 (packed) and the rows' sums of squares
     launch_dgemm_epilogue(st, DEpiArgs{w.partials, po.S, po.Nv, (const bf16_t *)x_in, w.x1, M, d, (const bf16_t *)lw.g2, w.h, ssq2});

@@ -357,6 +357,38 @@ def test_large_tile_products_repeat(T, split):
         rig.close()
 
 
+# passes of one to four rows, whose projections are finished in one kernel (five rows and the next kernels beside them): prompt rows,
+# decode rows and both, head_dim 128 and 64, workgroups of one, two and four 16-column tiles.  The same bits on every partition.
+@pytest.mark.parametrize("shape", [S.LLAMA8B, S.LayerShape("few-64", 1024, 16, 4, 64, 2560, 1e-5, 10000.0)])
+@pytest.mark.parametrize("lens,starts,ctx", [([], [], [0]), ([], [], [15, 16]), ([], [], [700, 3, 31, 512]), ([], [], [5, 6, 7, 8, 300]), ([1], [32], []), ([3], [0], []),
+                                             ([1, 2], [16, 0], [40])])
+def test_passes_of_a_few_rows(shape, lens, starts, ctx):
+    B, T, ctx = len(ctx), sum(lens), np.asarray(ctx, np.int32)
+    held = [s + n for s, n in zip(starts, lens)] + [int(c) + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    cu, tabs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), S.shuffled_block_tables(held, n_blocks, stream=38)
+    ptab, dtab = tabs[:len(lens)], tabs[len(lens):]
+    rig = Rig(shape, n_blocks, T + B, max(B, 1), max(held) + 1)
+    try:
+        kb, vb = S.kv_cache_bits(n_blocks, shape.n_kv_heads, shape.head_dim)
+        xb, want = S.hidden_states(T + B, shape.d_model, stream=38), None
+        for split in ((256, 256), (128, 128), (64, 192), (192, 64), (96, 160)):
+            print(shape.name, lens, B, split, flush=True)
+            rig.ctx.set_cu_split(*split)
+            rig.load_pools_from_logical(kb, vb)
+            y = rig.hybrid(xb, cu, starts, ptab, ctx if B else None, dtab if B else None) if T else rig.decode(xb, ctx, dtab)
+            got = [y] + [p.view(torch.int16).cpu().numpy() for p in (rig.k_pool, rig.v_pool)]
+            want = got if want is None else want
+            assert all(np.array_equal(p, q) for p, q in zip(got, want)), f"differs at split {split}"
+        x, Kc, Vc = f32(xb), f32(kb), f32(vb)
+        if T:
+            check_tensor("prompt rows", f32(want[0])[:T], rig.olayers[0].prefill_chunk(x[:T], cu, starts, ptab, Kc, Vc), x[:T], 2, elem_mult=END_TO_END)
+        if B:
+            check_tensor("decode rows", f32(want[0])[T:], rig.olayers[0].decode(x[T:], ctx, dtab, Kc, Vc), x[T:], 2, elem_mult=END_TO_END)
+    finally:
+        rig.close()
+
+
 # the normalised rows can be read back where the pass made some, as the header says; a pass that folds its norms has none
 @pytest.mark.parametrize("T,B", [(40, 0), (128, 0), (129, 0), (30, 20), (100, 60), (0, 1), (0, 128), (0, 129)])
 def test_normalised_rows_where_there_are_some(T, B):
