@@ -7,6 +7,7 @@
 //
 // Both kernels evaluate S^T = K Q^T and O^T = V^T P^T, so that a lane owns one query column:
 // the running maximum and sum of the online softmax are per-lane scalars.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -845,6 +846,19 @@ __global__ __launch_bounds__(512, 2) void hybrid_attn_kernel(PrefillAttnArgs p, 
     decode_attn_chunk<HD>(d, hk, b, chunk, threadIdx.x & 255, (float *)smem_attn + half * decode_attn_lds_floats(HD, d.Hq / d.Hkv));
 }
 
+// The same with workgroups of 256 threads: one team that computes what two would, and one kv head's chunk each.  Two fit a unit, and the
+// decode rows read faster in workgroups of one head (64 rows of 512 to 4096 tokens alone: a layer of 213 us, 233 in pairs of heads).
+template <int HD>
+__global__ __launch_bounds__(256, 2) void hybrid_attn_small_kernel(PrefillAttnArgs p, DecodeAttnArgs d, int n_prefill) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem_attn[];
+    if ((int)blockIdx.x < n_prefill) {
+        prefill_attn_wg<HD, 1, true>(p, blockIdx.x, smem_attn);
+        return;
+    }
+    const int w = blockIdx.x - n_prefill, r = w / d.Hkv, b = r % d.B, chunk = r / d.B;
+    decode_attn_chunk<HD>(d, w % d.Hkv, b, chunk, threadIdx.x, (float *)smem_attn);
+}
+
 static int prefill_unit_count(const PrefillAttnArgs &a, bool pairs) {
     int n = 0;
     for (int r = 0; r < a.seq.n_req; ++r) {
@@ -894,6 +908,17 @@ void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &args) {
     else launch_prefill_form<64>(st, a, f);
 }
 
+// Which of the two: a prompt tile takes a team of its own longer than two teams (some 2.3 us a 64-key tile), so the small workgroups
+// where the decode rows, at half of the longest context on average, are read for longer than that.  The same bits in both.  Layers of the
+// 8B widths, 512 rows behind 1024 tokens beside 64 decode rows of 512 to 4096 and beside 128, large / small workgroups: 404 / 395 and 540 /
+// 525 us; where the rule takes the large ones, 512 rows behind 3072 beside 16 of up to 600 tokens 337 / 356, behind 2416 beside 11 324 / 344.
+static bool hybrid_small(const PrefillAttnArgs &p, const DecodeAttnArgs &d, const PrefillForm &f) {
+    int keys = 0;
+    for (int r = 0; r < p.seq.n_req; ++r) keys = std::max(keys, p.seq.start[r] + p.seq.cu[r + 1] - p.seq.cu[r]);
+    const double bytes = 0.5 * d.B * d.max_ctx * (4.0 * d.Hkv * d.hd), rate = std::min(6.0e6, 0.034e6 * prefill_cus(p));   // bytes a us
+    return p.park && (size_t)f.tiles * 128 * p.hd <= p.park_cap && 2.3 * keys / 64 < bytes / rate;
+}
+
 // One launch for both kinds of rows while the prompt rows leave most units to the others: half of the whole chip (512 rows of
 // 32 heads behind 1024 cached tokens beside 64 decode rows: 131 us, 141 in two launches; 2048 rows 132 and 121), a quarter of a
 // partition, where decode rows need every unit for themselves (the 512 rows on 128 CUs 215 and 173 us; 100 rows beside 28: 48 and
@@ -911,6 +936,14 @@ void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &pargs, const
     }
     p.pairs = light ? f.pairs : f.tiles > most;
     const int n_prefill = p.pairs ? pairs : f.tiles;
+    if (hybrid_small(p, d, f)) {
+        p.pairs = false;
+        const dim3 g1(f.tiles + d.Hkv * d.n_chunks * d.B);
+        if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_small_kernel<128>, g1, dim3(256), prefill_lds(128, 1), st, p, d, f.tiles);
+        else hipLaunchKernelGGL(hybrid_attn_small_kernel<64>, g1, dim3(256), prefill_lds(64, 1), st, p, d, f.tiles);
+        launch_decode_combine(st, d);
+        return;
+    }
     const dim3 grid(n_prefill + n_decode);
     if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_kernel<128>, grid, dim3(512), prefill_lds(128, 2), st, p, d, n_prefill);
     else hipLaunchKernelGGL(hybrid_attn_kernel<64>, grid, dim3(512), prefill_lds(64, 2), st, p, d, n_prefill);
@@ -923,6 +956,7 @@ void attention_kernels_init() {
     set((const void *)prefill_attn_kernel<128, 1, true>, prefill_lds(128, 1));
     set((const void *)prefill_attn_kernel<128, 2, false>, prefill_lds(128, 2));
     set((const void *)prefill_attn_kernel<64, 2, false>, prefill_lds(64, 2));
+    set((const void *)hybrid_attn_small_kernel<128>, prefill_lds(128, 1));
     set((const void *)hybrid_attn_kernel<128>, prefill_lds(128, 2));
     set((const void *)hybrid_attn_kernel<64>, prefill_lds(64, 2));
 }

@@ -194,6 +194,29 @@ def test_hybrid_attention_in_one_launch(shape, lens, starts, ctx):
     _hybrid_case(shape, lens, starts, ctx)
 
 
+# the one launch in workgroups of two teams and, where the bound of the contexts says that the decode rows are the longer part, of one:
+# the same bits, and against the oracle; head_dim 64 and 128, several prompt tiles with earlier keys, an odd number of kv heads
+@pytest.mark.parametrize("shape,lens,starts,B", [(S.MID, [90], [16], 40), (S.ODD, [200, 31], [0, 48], 50), (S.TINY, [140, 1], [32, 0], 50)])
+def test_hybrid_attention_in_small_workgroups(shape, lens, starts, B):
+    ctx, longest = np.array([(37 * i) % 300 for i in range(B)], np.int32), 2600
+    held, T = [s + n for s, n in zip(starts, lens)] + [longest] * B, sum(lens)
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=39)
+    rig = Rig(shape, n_blocks, T + B, B, longest)
+    try:
+        kb, vb = S.kv_cache_bits(n_blocks, shape.n_kv_heads, shape.head_dim)
+        cu, xb, got = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), S.hidden_states(T + B, shape.d_model, stream=39), []
+        for bound in (301, longest):
+            rig.load_pools_from_logical(kb, vb)
+            got.append(rig.hybrid(xb, cu, starts, tabs[:len(lens)], ctx, tabs[len(lens):], max_ctx=bound))
+        assert np.array_equal(got[0], got[1])
+        x, Kc, Vc = f32(xb), f32(kb), f32(vb)
+        check_tensor("prompt rows", f32(got[0])[:T], rig.olayers[0].prefill_chunk(x[:T], cu, starts, tabs[:len(lens)], Kc, Vc), x[:T], 2, elem_mult=END_TO_END)
+        check_tensor("decode rows", f32(got[0])[T:], rig.olayers[0].decode(x[T:], ctx, tabs[len(lens):], Kc, Vc), x[T:], 2, elem_mult=END_TO_END)
+    finally:
+        rig.close()
+
+
 # the forms that prompt attention takes as the side's compute units become few: two teams of waves, one that does both
 # teams' work one after the other, tiles and pairs of tiles, decode rows in the same launch and in one of their own; with
 # one key tile a row, and with chunks that have earlier keys.  The same bits in all of them.
