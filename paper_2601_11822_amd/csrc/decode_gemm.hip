@@ -513,11 +513,6 @@ void launch_dgemm_epilogue(hipStream_t st, const DEpiArgs &a) {
     else hipLaunchKernelGGL(dgemm_epilogue_kernel<8>, grid, dim3(256), 0, st, a);
 }
 
-// A launch of 128 rows or more (row_grid rounds it up to whole groups of 128) gives an XCD 16 consecutive rows of each group:
-// the pieces of a line that belong to neighbouring rows (a V block's tokens, a fragment-packed operand's rows) meet in one L2.
-__device__ __forceinline__ int row_of(int x, int grid) { return grid < 128 ? x : (x & ~127) + (x & 7) * 16 + ((x >> 3) & 15); }
-static int row_grid(int M) { return M < 128 ? M : (M + 127) / 128 * 128; }
-
 // QKV epilogue: sums the K slices, applies the first RMSNorm's row scale, rotates q and k at the row's position
 // (rotate-half pairs (i, i + hd/2), angles from the host-built table), stores q | k | v as bf16 rows for the
 // attention kernels, and writes k and v to the paged cache through the block table (rows [0, T) are prompt rows,

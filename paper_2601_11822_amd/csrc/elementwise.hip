@@ -159,7 +159,8 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(RopeKvArgs a, int v_b
         v_block_write(a, blockIdx.x);
         return;
     }
-    const int row = (int)blockIdx.x - v_blocks;
+    const int row = row_of((int)blockIdx.x - v_blocks, (int)gridDim.x - v_blocks);
+    if (row >= a.M) return;
     const int tid = threadIdx.x;
     int req, pos;
     if (a.ctx_lens) {
@@ -229,7 +230,7 @@ void launch_rope_kvwrite(hipStream_t st, const RopeKvArgs &a) {
     if (!a.ctx_lens)
         for (int r = 0; r < a.seq.n_req; ++r)
             v_blocks += (a.seq.cu[r + 1] - a.seq.cu[r] + RS_BLOCK_TOKENS - 1) / RS_BLOCK_TOKENS;
-    hipLaunchKernelGGL(rope_kvwrite_kernel, dim3(a.M + v_blocks), dim3(256), 0, st, a, v_blocks);
+    hipLaunchKernelGGL(rope_kvwrite_kernel, dim3(row_grid(a.M) + v_blocks), dim3(256), 0, st, a, v_blocks);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -9,6 +9,11 @@
 // x is row-major [M][d]; `out` is written fragment-packed (packed_offset with packed_mt(M) row tiles).
 void launch_rmsnorm(hipStream_t st, const bf16_t *x, const bf16_t *g, bf16_t *out, int M, int d, float eps);
 
+// A launch of 128 rows or more (row_grid rounds it up to whole groups of 128) gives an XCD 16 consecutive rows of each group:
+// the pieces of a line that belong to neighbouring rows (a K or V block's tokens, a fragment-packed operand's rows) meet in one L2.
+__device__ __forceinline__ int row_of(int x, int grid) { return grid < 128 ? x : (x & ~127) + (x & 7) * 16 + ((x >> 3) & 15); }
+static int row_grid(int M) { return M < 128 ? M : (M + 127) / 128 * 128; }
+
 struct RopeKvArgs {
     bf16_t *qkv;            // [M][nqkv]; q part rotated in place
     const CosSin *table;    // [max_pos][hd/2]
