@@ -50,6 +50,11 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // =============================================================================================
 static __host__ __device__ inline int decode_attn_lds_floats(int hd, int G) { return 4 * hd * G + 8 * G; }   // <= 33 KB at G = 16
 
+// Column col of row b of the output, the output projection's operand
+__device__ __forceinline__ bf16_t *decode_out(const DecodeAttnArgs &a, int b, int col) {
+    return a.out + packed_offset(a.out_row0 + b, col, a.out_Mt ? a.out_Mt : packed_mt(a.B)) + (col & 7);
+}
+
 // One (kv head, request, chunk), by 256 threads; smem_dec: [4][HD][G] partial outputs, then [4][G] max, [4][G] sum
 template <int HD>
 __device__ __forceinline__ void decode_attn_chunk(const DecodeAttnArgs &a, const int hk, const int b, const int chunk, const int tid, float *smem_dec) {
@@ -65,7 +70,11 @@ __device__ __forceinline__ void decode_attn_chunk(const DecodeAttnArgs &a, const
     int n_keys = a.ctx_lens[b] + 1;
     if (n_keys < 1 || n_keys > a.max_ctx) {
         if (tid == 0 && chunk == 0 && hk == 0) atomicOr(a.err_flag, 8);
-        if (n_keys < 1) return;
+        if (n_keys < 1) {
+            if (a.n_chunks == 1)
+                for (int col = hk * G * HD + tid; col < (hk + 1) * G * HD; col += 256) *decode_out(a, b, col) = (bf16_t)0.f;
+            return;
+        }
         n_keys = a.max_ctx;
     }
     if (chunk * RS_DECODE_CHUNK >= n_keys) return;
@@ -224,6 +233,24 @@ __device__ __forceinline__ void decode_attn_chunk(const DecodeAttnArgs &a, const
         }
     }
     __syncthreads();
+    // the only chunk is the result, and no kernel follows: what the merge below makes of one chunk, the same bits (four layers of the 8B widths, one row
+    // of 300 cached tokens 351 -> 341 us, 64 rows of 100 to 500 516 -> 506)
+    if (a.n_chunks == 1) {
+        for (int idx = tid; idx < G * HD; idx += 256) {
+            const int gg = idx / HD, d = idx % HD;
+            const float mx = fmaxf(fmaxf(s_m[gg], s_m[G + gg]), fmaxf(s_m[2 * G + gg], s_m[3 * G + gg]));
+            const float ms = (mx == NEG_INF) ? 0.f : mx;
+            float acc = 0.f, l = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float e = __builtin_amdgcn_exp2f((s_m[w * G + gg] - ms) * a.scale_log2);
+                acc += s_o[(w * HD + d) * G + gg] * e;
+                l += s_l[w * G + gg] * e;
+            }
+            *decode_out(a, b, (hk * G + gg) * HD + d) = (bf16_t)(l > 0.f ? acc / l : 0.f);
+        }
+        return;
+    }
     for (int idx = tid; idx < G * HD; idx += 256) {
         const int gg = idx % G, d = idx / G;   // consecutive threads read consecutive words of s_o: no bank conflicts
         const float mx = fmaxf(fmaxf(s_m[gg], s_m[G + gg]), fmaxf(s_m[2 * G + gg], s_m[3 * G + gg]));
@@ -281,7 +308,7 @@ __global__ __launch_bounds__(HD) void decode_combine_kernel(DecodeAttnArgs a) {
     float2 mine = ml[min(lane, a.n_chunks - 1)];   // looked at only if the chunk is one of this context's
     int n_keys = a.ctx_lens[b] + 1;
     const int col = hq * HD + d;
-    bf16_t *op = a.out + packed_offset(a.out_row0 + b, col, a.out_Mt ? a.out_Mt : packed_mt(a.B)) + (col & 7);   // feeds the output projection
+    bf16_t *op = decode_out(a, b, col);
     if (n_keys < 1) {
         *op = (bf16_t)0.f;
         return;
@@ -331,7 +358,7 @@ __global__ __launch_bounds__(HD) void decode_combine_kernel(DecodeAttnArgs a) {
     *op = (bf16_t)(l > 0.f ? sum / l : 0.f);
 }
 
-// The same sums, to the bit, where no context has more than RS_FEW_CHUNKS chunks (NC: 1, 2 or 4, the most that the bound of the
+// The same sums, to the bit, where no context has more than RS_FEW_CHUNKS chunks (NC: 2 or 4, the most that the bound of the
 // contexts allows): a thread per column, everything it needs requested together.  Few registers and no barriers: with hundreds
 // of short contexts that is what counts (decode attention of 256 rows of 511 tokens, 8B heads, 64 CUs: 197 us with the kernel
 // above, 188 with this; 128 CUs 135 and 129).
@@ -352,7 +379,7 @@ __global__ __launch_bounds__(256) void decode_combine_few_kernel(DecodeAttnArgs 
         v[i] = po[(size_t)ci * HD];
     }
     const int n_keys = a.ctx_lens[b] + 1;
-    bf16_t *op = a.out + packed_offset(a.out_row0 + b, col, a.out_Mt ? a.out_Mt : packed_mt(a.B)) + (col & 7);
+    bf16_t *op = decode_out(a, b, col);
     if (n_keys < 1) {
         *op = (bf16_t)0.f;
         return;
@@ -376,12 +403,12 @@ __global__ __launch_bounds__(256) void decode_combine_few_kernel(DecodeAttnArgs 
 template <int HD>
 static void launch_decode_combine_few(hipStream_t st, const DecodeAttnArgs &a) {
     const dim3 grid((a.Hq * HD + 255) / 256, a.B);
-    if (a.n_chunks == 1) hipLaunchKernelGGL((decode_combine_few_kernel<HD, 1>), grid, dim3(256), 0, st, a);
-    else if (a.n_chunks == 2) hipLaunchKernelGGL((decode_combine_few_kernel<HD, 2>), grid, dim3(256), 0, st, a);
+    if (a.n_chunks == 2) hipLaunchKernelGGL((decode_combine_few_kernel<HD, 2>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((decode_combine_few_kernel<HD, RS_FEW_CHUNKS>), grid, dim3(256), 0, st, a);
 }
 
 static void launch_decode_combine(hipStream_t st, const DecodeAttnArgs &a) {
+    if (a.n_chunks == 1) return;   // finished by its one chunk's workgroup
     if (a.n_chunks <= RS_FEW_CHUNKS) {
         if (a.hd == 128) launch_decode_combine_few<128>(st, a);
         else launch_decode_combine_few<64>(st, a);

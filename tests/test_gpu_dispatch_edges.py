@@ -412,6 +412,37 @@ def test_passes_of_a_few_rows(shape, lens, starts, ctx):
         rig.close()
 
 
+# contexts of one chunk are finished by their workgroup where the bound says that all are, and by the merge where it does not: the same
+# bits, a row without a context (refused, its attention zero) among them
+@pytest.mark.parametrize("shape", [S.MID, S.TINY, S.ODD])
+@pytest.mark.parametrize("ctx", [[0, 15, 300, 77, 511], [31, -1, 200]])
+def test_decode_contexts_of_one_chunk(shape, ctx):
+    B, ctx, longest = len(ctx), np.asarray(ctx, np.int32), 1100
+    n_blocks = B * S.blocks_for(longest) + 2
+    tabs = S.shuffled_block_tables([longest] * B, n_blocks, stream=40)
+    rig = Rig(shape, n_blocks, 16, B, longest, with_oracle=False)
+    try:
+        shp = (n_blocks, 16, shape.n_kv_heads, shape.head_dim)
+        cl, tab, got = torch.from_numpy(ctx).cuda(), torch.from_numpy(np.ascontiguousarray(tabs, np.int32)).cuda(), []
+        for bound in (512, 513, longest):
+            rig.load_pools_from_logical(S.normal_bf16(shp, S.SEED_CACHE, 1), S.normal_bf16(shp, S.SEED_CACHE, 2))
+            x = to_dev(S.hidden_states(B, shape.d_model, stream=40))
+            y = torch.empty_like(x)
+            torch.cuda.synchronize()
+            rig.ctx.decode_layer(0, x, y, cl, tab, tab.shape[1], B, bound)
+            if (ctx < 0).any():
+                with pytest.raises(rs.RapidServeError):
+                    rig.ctx.sync(rs.RS_SIDE_DECODE)
+            else:
+                rig.ctx.sync(rs.RS_SIDE_DECODE)
+            got.append((y.clone().view(torch.int16), rig.ctx.debug_read_workspace(rs.RS_SIDE_DECODE, 2, (B, shape.q_dim))))
+            if (ctx < 0).any():
+                assert not got[-1][1][ctx < 0].any() and got[-1][1][ctx >= 0].any()
+        assert all(torch.equal(g[0], got[0][0]) and np.array_equal(g[1], got[0][1]) for g in got)
+    finally:
+        rig.close()
+
+
 # the normalised rows can be read back where the pass made some, as the header says; a pass that folds its norms has none
 @pytest.mark.parametrize("T,B", [(40, 0), (128, 0), (129, 0), (30, 20), (100, 60), (0, 1), (0, 128), (0, 129)])
 def test_normalised_rows_where_there_are_some(T, B):
