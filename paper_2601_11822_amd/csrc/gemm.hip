@@ -190,9 +190,9 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
 // chunk l: the slab of a K tile is BM/32 + BN/32 contiguous kilobytes per k block, which spreads
 // over the memory channels (a row-major operand would give one 64-byte piece per 2K-byte-strided
 // row, crowding a few channels: the DMA fill rate of this tile walk measured 13 TB/s row-major
-// and 22 TB/s packed).  In LDS a block keeps the lane order, so a fragment read is 64 consecutive
-// 16-byte chunks: conflict free without a swizzle.  Row tiles past M or N are clamped to the last
-// tile (their results are never stored); K tiles past the end re-fetch the last tile into a stage
+// and 22 TB/s packed).  In LDS a block keeps the lane order, so a fragment read is four runs of 16
+// consecutive 16-byte chunks: conflict free without a swizzle.  Row tiles past M or N are not fetched
+// (their results are never stored); K tiles past the end re-fetch the last tile into a stage
 // nobody reads, which keeps the loop body branch free.
 //
 // Per K tile (one MFMA step of K = 32, one barrier): the loads of tile kt+NS-1 and the reads of tile kt+1's
@@ -586,6 +586,8 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // back, where power sets the clock (gate/up of 224 rows or of 256 with a last round of halves: 70B 5482 rows 7887 and 7783 us a layer,
 // 8B 7050 rows 2898 and 2876, 6460 rows on 192 CUs 3072 and 3032).
 // A slice adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.
+// (All of these are timings of the loop with 32x32x16 products.  With the present one every form was forced in turn at ten row counts
+// of the 8B widths from 200 to 8000, on 256 and 128 CUs, and four of the 70B widths: the choice is still within 1 % of the fastest.)
 // Against the rule before it (128-row tiles for slices, their count a power of two up to half the chip; no 192-row tiles), product and
 // epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
 // 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
