@@ -73,6 +73,7 @@ __device__ __forceinline__ void sum_slices(const float *p, int off, size_t strid
 }
 
 #define DS_INLINE_PIECES 12
+#define FEW_PARTS (RS_FEW_COLS / 1024)   // parts of a row's sum of squares, where a pass of few rows forms it
 #define DS_CH 16   // k-blocks per activation chunk: two slabs of MT x 16 KB in LDS
 
 // ACT 0: activations fragment-packed (packed_mt(M) row tiles per k-block), as their producers write them.
@@ -180,11 +181,19 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs 
         }
     };
     RowSsq rs[MT];   // FUSED: what this lane's rows' RMSNorm scales are made of
-    __shared__ float self_ssq[SELF ? RS_FEW_ROWS : 1][4];
+    __shared__ f32x4 self_ssq[SELF ? RS_FEW_ROWS : 1][FEW_PARTS];   // SELF: by row, part of 1024 and wave
     if (FUSED && !SELF) {
 #pragma unroll
         for (int tm = 0; tm < MT; ++tm) rs[tm].request(fz.ssq_part, fz.S_ssq, 32 * tm + c32);
     }
+    bf16x4 self[SELF ? RS_FEW_ROWS : 1][FEW_PARTS];   // requested in front of the weights, whose ring must not be waited for
+    if (SELF)
+#pragma unroll
+        for (int r = 0; r < RS_FEW_ROWS; ++r) {
+            if (r >= M) break;
+#pragma unroll
+            for (int i = 0; i < FEW_PARTS; ++i) self[r][i] = *(const bf16x4 *)(fz.rows + (size_t)r * K + min(1024 * i + 4 * tid, K - 4));
+        }
     float gf[8];
     auto gains = [&](bf16x8 g) {
 #pragma unroll
@@ -204,26 +213,33 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs 
 #pragma unroll
         for (int t = 0; t < RT; ++t) rw[p][t] = ld_bf16x8_stream(w[t] + kb * wstride);
     };
+    // (SELF: in this order, which the loop's wait counts go by; left to the scheduler, gate/up of one row on 128 CUs takes 49.7 us
+    // instead of 47.3)
+    if (SELF) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int p = 0; p < PD; ++p) load_w(p, p);
-    if (SELF) {   // a few rows: the sums of squares are formed here, from the rows themselves, four at a time
-        for (int r0 = 0; r0 < M; r0 += 4) {
-            float s[4] = {};
-            for (int c = tid; c < K / 8; c += 256) {
-                bf16x8 v[4];
+    for (int p = 0; p < PD; ++p) {
+        load_w(p, p);
+        if (SELF) __builtin_amdgcn_sched_barrier(0);
+    }
+    if (SELF) {   // a few rows: the sums of squares are formed here, from the rows themselves, as dgemm_epilogue_kernel forms them
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = ld_bf16x8(fz.rows + (size_t)min(r0 + r, M - 1) * K + c * 8);
+        for (int r = 0; r < RS_FEW_ROWS; ++r) {
+            if (r >= M) break;
+            float s[FEW_PARTS] = {};
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+            for (int i = 0; i < FEW_PARTS; ++i)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) s[r] += (float)v[r][e] * (float)v[r][e];
-            }
+                for (int e = 0; e < 4; ++e) {
+                    const float f = 1024 * i + 4 * tid < K ? (float)self[r][i][e] : 0.f;
+                    s[i] += f * f;
+                }
+            // wave_sum of all four, each with the other half's or quarter's: lanes 16 i .. 16 i + 15 end with part i
+            const bool up = lane & 32, odd = lane & 16;
+            const float s0 = (up ? s[2] : s[0]) + __shfl_xor(up ? s[0] : s[2], 32, 64), s1 = (up ? s[3] : s[1]) + __shfl_xor(up ? s[1] : s[3], 32, 64);
+            float t = (odd ? s1 : s0) + __shfl_xor(odd ? s0 : s1, 16, 64);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (r0 + r >= M) break;
-                s[r] = wave_sum(s[r]);
-                if (lane == 0) self_ssq[r0 + r][wave] = s[r];
-            }
+            for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+            if ((lane & 15) == 0) self_ssq[r][lane >> 4][wave] = t;
         }
     }
     float sc[MT];
@@ -233,8 +249,13 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs 
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (SELF) {
-        const float *s = self_ssq[min(c32, M - 1)];
-        sc[0] = 1.0f / sqrtf(((s[0] + s[1]) + (s[2] + s[3])) / (float)K + fz.eps);
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < FEW_PARTS; ++i) {
+            const f32x4 s = self_ssq[min(c32, M - 1)][i];
+            if (1024 * i < K) t += (s[0] + s[1]) + (s[2] + s[3]);
+        }
+        sc[0] = 1.0f / sqrtf(t / (float)K + fz.eps);
     }
 
     for (int c = 0; c < nchunks; ++c) {
@@ -615,31 +636,48 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// A pass of at most RS_FEW_ROWS rows: the projections that a stream cuts in K for enough workgroups, whole.  A workgroup's four waves take a
-// quarter of K each of the same R x 16 weight rows (QKV: R x 16 dims and those that they are rotated with), are summed in wave order
-// through LDS, and the workgroup finishes its columns: no partial sums in memory and no epilogue kernel that reads them.  What bounds
-// a layer of one row, beside its weights, is some 4 us of every kernel in it (launch, first bytes, last ones), and so it is six
-// of them instead of nine.  The activation fragments come with the weights from memory (the L2); of QKV every workgroup forms
-// x . gain of all rows in LDS, and the sums of squares with it.  A layer of the 8B widths on 256 CUs, streams / this: 1 row
-// of 900 cached tokens 97.9 / 89.3 us, 2 rows 95.6 / 88.0, 4 rows 98.7 / 91.7, 8 rows 100.9 / 97.5 with a rule that took them too, but
-// on 128 CUs 114.5 / 116.6: the lines that the rows' fragments touch grow with the rows.  More bytes in flight are slower (eight waves
-// of eight steps each 1.066 of the streams' rate where four of four have 1.084).
+// A pass of at most RS_FEW_ROWS rows: the projections that a stream cuts in K for enough workgroups, whole.  A workgroup's four to seven waves
+// take the plan's K slices between them, of the same R x 16 weight rows (QKV: R x 16 dims and those that they are rotated with), the slices' sums
+// are added in their order through LDS, and the workgroup finishes its columns: no partial sums in memory and no epilogue kernel that reads
+// them, and the bits are the stream's.  What bounds a layer of one row, beside its weights, is some 4 us of every kernel in it (launch, first
+// bytes, last ones), and so it is six of them instead of nine.  The activation fragments come with the weights from memory (the L2); of QKV
+// every wave forms x . gain of its slices' columns in LDS, and their sums of squares.  Four layers of the 8B widths on 256 CUs behind 900
+// cached tokens, streams / this: 1 row 389 / 355 us, 4 rows 395 / 365.  More rows are slower on partitions (8 rows on 128 CUs, a layer
+// 114.5 / 116.6): the lines that the rows' fragments touch grow with the rows.  More bytes in flight are slower (eight waves of eight
+// steps each 1.066 of the streams' rate where four of four have 1.084).
 // ---------------------------------------------------------------------------------------------
-#define FEW_WAVES 4
 #define FEW_PD 4   // 16x32 weight fragments in flight per wave and tile
-bool few_applies(int M, int N, int K) { return M <= RS_FEW_ROWS && K % (32 * FEW_WAVES * FEW_PD) == 0 && N % 32 == 0; }
+#define FEW_LEAST 4     // fewest and
+#define FEW_SLICES 16   // most slices that a workgroup's waves share
+#define FEW_WAVES 7     // most waves
+#define FEW_PAIRS 2     // QKV: most pairs of activation chunks of a wave, of rows of RS_FEW_COLS columns
+bool few_applies(int M, int N, const DGemmPlan &p) { return M <= RS_FEW_ROWS && N % 32 == 0 && p.S >= FEW_LEAST && p.S <= FEW_SLICES; }
+// Slices of a wave: the fewest waves, from four on, among those that leave the last one the least idle.
+static int few_slices_of_wave(int S) {
+    int best = FEW_LEAST;
+    for (int w = FEW_LEAST; w <= FEW_WAVES; ++w)
+        if ((S + w - 1) / w * w < (S + best - 1) / best * best) best = w;
+    return (S + best - 1) / best;
+}
+bool few_qkv_applies(int M, int N, int K, const DGemmPlan &p) {
+    if (K > RS_FEW_COLS || !dgemm_gains_inline(M, p) || !few_applies(M, N, p)) return false;
+    return few_slices_of_wave(p.S) * ((p.kb_per_wg / DS_CH + 1) / 2) <= FEW_PAIRS;
+}
+static_assert(DS_CH % (2 * FEW_PD) == 0, "a slice is whole rounds of the ring");
 
 // HD: head_dim of the QKV projection, 0: a residual projection.  R: 16-row tiles of a workgroup (QKV: of either half of a head).
 template <int HD, int R>
 __global__ __launch_bounds__(64 * FEW_WAVES) void few_kernel(FewArgs a, QkvEpiArgs q) {
     constexpr bool QKV = HD > 0;
     constexpr int NT = QKV ? 2 * R : R, PD = FEW_PD;
-    extern __shared__ __attribute__((aligned(16))) bf16_t xs[];   // QKV: [M][K + 8]
-    __shared__ f32x4 red[FEW_WAVES][NT][64];
-    __shared__ float ssq[RS_FEW_ROWS][FEW_WAVES];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
-    const int M = a.M, N = a.N, K = a.K, m = min(c16, M - 1);
-    const int n = K / (32 * FEW_WAVES), k0 = wave * n;            // this wave's steps of 32
+    extern __shared__ __attribute__((aligned(16))) f32x4 few_lds[];
+    __shared__ float ssq[RS_FEW_ROWS][FEW_SLICES];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, c16 = lane & 15, g = lane >> 4;
+    const int M = a.M, N = a.N, K = a.K, S = a.S, m = min(c16, M - 1);
+    f32x4 *red = few_lds;                                   // [S][NT][4 column groups][RS_FEW_ROWS]
+    bf16_t *xs = (bf16_t *)(red + S * NT * 4 * RS_FEW_ROWS);   // QKV: [M][K + 8], every wave the columns of its slices
+    const int sl0 = wave * a.wave_slices, sl1 = min(sl0 + a.wave_slices, S);   // this wave's slices
+    const int ns = K / (32 * S), n = (sl1 - sl0) * ns, k0 = sl0 * ns;          // steps of 32 of one and of all, and the first
     const int Nt = ((N + 63) / 64) * 2;
     const size_t wstride = (size_t)Nt * 512, xstride = (size_t)packed_mt(M) * 512;   // per k block
     // columns n0 (and n0 + HD / 2) .. + 16 R - 1; wave j finishes the j-th 16 of them
@@ -660,15 +698,27 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void few_kernel(FewArgs a, QkvEpiAr
         for (int t = 0; t < NT; ++t) rw[p][t] = ld_bf16x8_stream(w[t] + s * 2 * wstride);
         if (!QKV) rx[p] = ld_bf16x8(x + s * 2 * xstride);
     };
-    // the first part of four rows is requested in front of the weights, and waited for alone
-    bf16x8 xv[4], gv = zero_bf16x8();
-    auto request = [&](int r0, int c) {
-        c = min(c, K / 8 - 1);
-        gv = ld_bf16x8(a.gain + c * 8);
+    // QKV: a wave brings the columns of its own slices, two chunks of 16 k-blocks at a time (a half-wave each), requested in front of the
+    // weights and waited for alone
+    const int nch = K / (16 * DS_CH * S), pairs = (nch + 1) >> 1, k8 = lane & 31, half = lane >> 5;   // chunks of a slice, and pairs of them
+    bf16x8 xv[FEW_PAIRS][RS_FEW_ROWS], gv[FEW_PAIRS];
+    auto column = [&](int i) { return ((sl0 + i / pairs) * nch + min(2 * (i % pairs) + half, nch - 1)) * 32 + k8; };   // of 8 elements
+    const int items = (sl1 - sl0) * pairs;
+    // a residual projection: what the finished columns are added to and multiplied by
+    const int col = min(n0 + 16 * wave, N - 16) + 4 * g;
+    bf16x4 resid{}, gain{};
+    if (!QKV) {
+        resid = *(const bf16x4 *)(a.resid + (size_t)m * N + col);
+        gain = *(const bf16x4 *)((a.gain ? a.gain : a.resid) + col);
+    }
+    if (QKV)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) xv[r] = ld_bf16x8(a.X_rows + (size_t)min(r0 + r, M - 1) * K + c * 8);
-    };
-    if (QKV) request(0, tid);
+        for (int i = 0; i < FEW_PAIRS; ++i) {
+            const int c = column(min(i, items - 1));
+            gv[i] = ld_bf16x8(a.gain + c * 8);
+#pragma unroll
+            for (int r = 0; r < RS_FEW_ROWS; ++r) xv[i][r] = ld_bf16x8(a.X_rows + (size_t)min(r, M - 1) * K + c * 8);
+        }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < PD; ++p) load(p, p);
@@ -676,76 +726,94 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void few_kernel(FewArgs a, QkvEpiAr
     QkvPlace place{};
     const int ld = K + 8;
     if (QKV) {
-        for (int r0 = 0; r0 < M; r0 += 4) {
-            float s[4] = {};
-            for (int c = tid; c < K / 8 + tid; c += 64 * FEW_WAVES) {   // (as often for every thread)
-                if (r0 > 0 || c != tid) request(r0, c);
-                if (c >= K / 8) continue;
+        // x . gain to LDS, and a slice's sums of squares in the stream's order: over the chunks for each 16-byte column of a chunk, then
+        // eight columns as a tree, then the four eights one after the other
+        float t[RS_FEW_ROWS];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    bf16x8 h;
+        for (int i = 0; i < FEW_PAIRS; ++i) {
+            if (i >= items) break;
+            const int j = i % pairs, c = column(i);
+            const bool two = 2 * j + 1 < nch;   // else the upper half-wave has the lower one's chunk
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        s[r] += (float)xv[r][e] * (float)xv[r][e];
-                        h[e] = (bf16_t)((float)xv[r][e] * (float)gv[e]);
-                    }
-                    if (r0 + r < M) *(bf16x8 *)&xs[(r0 + r) * ld + c * 8] = h;
+            for (int r = 0; r < RS_FEW_ROWS; ++r) {
+                if (r >= M) break;
+                bf16x8 h;
+                float s = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    s += (float)xv[i][r][e] * (float)xv[i][r][e];
+                    h[e] = (bf16_t)((float)xv[i][r][e] * (float)gv[i][e]);
                 }
+                *(bf16x8 *)&xs[r * ld + c * 8] = h;
+                const float other = __shfl_xor(s, 32, 64);
+                t[r] = (j ? t[r] : 0.f) + (half ? other : s);
+                if (two) t[r] += half ? s : other;
             }
+            if (j + 1 < pairs) continue;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (r0 + r >= M) break;
-                s[r] = wave_sum(s[r]);
-                if (lane == 0) ssq[r0 + r][wave] = s[r];
+            for (int r = 0; r < RS_FEW_ROWS; ++r) {
+                if (r >= M) break;
+#pragma unroll
+                for (int o = 1; o < 8; o *= 2) t[r] += __shfl_xor(t[r], o, 64);
+                const float q = ((__shfl(t[r], 0, 64) + __shfl(t[r], 8, 64)) + __shfl(t[r], 16, 64)) + __shfl(t[r], 24, 64);
+                if (lane == 0) ssq[r][sl0 + i / pairs] = q;
             }
         }
         if (wave < R) place = qkv_place<QKV ? HD : 64>(q, m, head, i0);
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the weight loads stay in flight
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows are read by other lanes of the wave; the weight loads stay in flight
     }
-    f32x4 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const bf16_t *xr = xs + m * ld + k0 * 32 + 8 * g;
-    for (int s0 = 0; s0 < n; s0 += PD) {
+    for (int sl = sl0; sl < sl1; ++sl) {
+        f32x4 acc[NT];
 #pragma unroll
-        for (int p = 0; p < PD; ++p) {
-            const bf16x8 xf = QKV ? *(const bf16x8 *)&xr[(s0 + p) * 32] : rx[p];
+        for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = (sl - sl0) * ns; s0 < (sl - sl0 + 1) * ns; s0 += PD) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rw[p][t], xf, acc[t], 0, 0, 0);
-            load(p, s0 + p + PD);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int p = 0; p < PD; ++p) {
+                const bf16x8 xf = QKV ? *(const bf16x8 *)&xr[(s0 + p) * 32] : rx[p];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rw[p][t], xf, acc[t], 0, 0, 0);
+                load(p, s0 + p + PD);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-    }
-    // lane: columns n0 + 4g .. + 3 of row c16
+        // lane: columns n0 + 4g .. + 3 of row c16
+        if (c16 < RS_FEW_ROWS)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) red[wave][t][lane] = acc[t];
+            for (int t = 0; t < NT; ++t) red[((sl * NT + t) * 4 + g) * RS_FEW_ROWS + c16] = acc[t];
+    }
     __syncthreads();
     if (wave >= R || c16 >= M) return;
-    f32x4 sum[2];
+    f32x4 sum[NT / R];
 #pragma unroll
-    for (int t = 0; t < NT / R; ++t) {
-        sum[t] = red[0][t * R + wave][lane];
+    for (int t = 0; t < NT / R; ++t) sum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma clang loop unroll(disable)
+    for (int s0 = 0; s0 < S; s0 += 8) {
+        f32x4 v[8][NT / R];
 #pragma unroll
-        for (int v = 1; v < FEW_WAVES; ++v) sum[t] += red[v][t * R + wave][lane];
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int t = 0; t < NT / R; ++t) v[s][t] = red[((min(s0 + s, S - 1) * NT + t * R + wave) * 4 + g) * RS_FEW_ROWS + c16];
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int t = 0; t < NT / R; ++t)
+                if (s0 + s < S) sum[t] += v[s][t];
     }
     if constexpr (QKV) {
         float t = 0.f;
-#pragma unroll
-        for (int v = 0; v < FEW_WAVES; ++v) t += ssq[m][v];
+        for (int s = 0; s < S; ++s) t += ssq[m][s];
         const float sc = 1.0f / sqrtf(t / (float)K + a.eps);
         qkv_finish<HD>(q, place, m, head, i0, sum[0] * sc, sum[1] * sc, blockIdx.x == 0 && wave == 0 && g == 0, i0 == 0);
     } else {
-        const int col = n0 + 16 * wave + 4 * g;
-        const bf16x4 r = *(const bf16x4 *)(a.resid + (size_t)m * N + col);
         bf16x4 v;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(sum[0][i] + (float)r[i]);
+        for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(sum[0][i] + (float)resid[i]);
         *(bf16x4 *)(a.out + (size_t)m * N + col) = v;
         if (a.gain) {
-            const bf16x4 gv = *(const bf16x4 *)(a.gain + col);
             bf16x4 h;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) h[i] = (bf16_t)((float)v[i] * (float)gv[i]);
+            for (int i = 0; i < 4; ++i) h[i] = (bf16_t)((float)v[i] * (float)gain[i]);
             *(bf16x4 *)(a.out_gain + packed_offset(m, col, packed_mt(M)) + (col & 7)) = h;
         }
     }
@@ -763,15 +831,21 @@ static int few_tiles(int tiles, int cus, double act, int most) {
     }
     return best;
 }
-void launch_few_residual(hipStream_t st, const FewArgs &a, int cus) {
-    const int R = few_tiles(a.N / 16, cus, 0.6, a.N % 64 ? 2 : 4);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.N / (16 * R)), dim3(64 * FEW_WAVES), 0, st, a, QkvEpiArgs{}); };
+// (At most 50 KB, which needs no leave: rows of RS_FEW_COLS columns, 32 KB, have up to eight slices, 16 KB of sums.)
+static size_t few_lds_bytes(int S, int tiles) { return (size_t)S * tiles * 4 * RS_FEW_ROWS * sizeof(f32x4); }
+static int few_threads(FewArgs &a) {
+    a.wave_slices = few_slices_of_wave(a.S);
+    return 64 * ((a.S + a.wave_slices - 1) / a.wave_slices);
+}
+void launch_few_residual(hipStream_t st, FewArgs a, int cus) {
+    const int R = few_tiles(a.N / 16, cus, 0.6, a.N % 64 ? 2 : 4), threads = few_threads(a);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.N / (16 * R)), dim3(threads), few_lds_bytes(a.S, R), st, a, QkvEpiArgs{}); };
     R == 4 ? go(few_kernel<0, 4>) : R == 2 ? go(few_kernel<0, 2>) : go(few_kernel<0, 1>);
 }
-void launch_few_qkv(hipStream_t st, const FewArgs &a, const QkvEpiArgs &q, int cus) {
+void launch_few_qkv(hipStream_t st, FewArgs a, const QkvEpiArgs &q, int cus) {
     const int R = few_tiles(a.N / 32, cus, 0.1, q.hd == 64 ? 2 : 4);
-    const dim3 grid(a.N / (32 * R)), block(64 * FEW_WAVES);
-    const size_t lds = (size_t)a.M * (a.K + 8) * sizeof(bf16_t);
+    const dim3 grid(a.N / (32 * R)), block(few_threads(a));
+    const size_t lds = few_lds_bytes(a.S, 2 * R) + (size_t)a.M * (a.K + 8) * sizeof(bf16_t);
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a, q); };
     if (q.hd == 128) R == 4 ? go(few_kernel<128, 4>) : R == 2 ? go(few_kernel<128, 2>) : go(few_kernel<128, 1>);
     else R == 2 ? go(few_kernel<64, 2>) : go(few_kernel<64, 1>);
@@ -854,11 +928,6 @@ void decode_gemm_kernels_init() {
     auto set = [](const void *f, int lds) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
     set((const void *)dstream_kernel<0, 1, false, true, 1, true>, ds_lds(1));
     set((const void *)dstream_kernel<0, 2, true, false, 1, true>, ds_lds(1));
-    set((const void *)few_kernel<128, 1>, RS_FEW_LDS);
-    set((const void *)few_kernel<128, 2>, RS_FEW_LDS);
-    set((const void *)few_kernel<128, 4>, RS_FEW_LDS);
-    set((const void *)few_kernel<64, 1>, RS_FEW_LDS);
-    set((const void *)few_kernel<64, 2>, RS_FEW_LDS);
     dstream_init<1>();
     dstream_init<2>();
     dstream_init<3>();

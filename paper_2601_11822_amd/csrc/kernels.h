@@ -137,7 +137,7 @@ struct DFuseArgs {            // a gate/up pair: out = silu(s g) * (s u) with th
     int S_ssq = 0;
     float eps = 0.f;
     bf16_t *out = nullptr;              // fragment-packed [M][N]
-    const bf16_t *rows = nullptr;       // instead of ssq_part, up to RS_FEW_ROWS rows: the rows [M][K] themselves
+    const bf16_t *rows = nullptr;       // instead of ssq_part, up to RS_FEW_ROWS rows of RS_FEW_COLS: the rows [M][K] themselves
 };
 struct DGemmPlan {
     bool pair;
@@ -185,22 +185,24 @@ struct QkvEpiArgs {
     SeqInfo seq{};
 };
 void launch_qkv_rope_epilogue(hipStream_t st, const QkvEpiArgs &a);
-// The projections of at most RS_FEW_ROWS rows, finished in one kernel.
+// The projections of at most RS_FEW_ROWS rows, finished in one kernel: the bits of the stream and its epilogue.
 #define RS_FEW_ROWS 4
+#define RS_FEW_COLS 4096   // most columns of such rows
 struct FewArgs {
     const bf16_t *A;          // fragment-packed activations, or (QKV)
     const bf16_t *X_rows;     // the rows [M][K], normalised with
     const bf16_t *gain;       //   this gain [K]; of a residual projection: the next RMSNorm's gain [N] or nullptr
     const bf16_t *Wp;
-    int M, N, K;
+    int M, N, K, S;           // S: the plan's K slices
     float eps;
     const bf16_t *resid;      // row-major [M][N]
     bf16_t *out, *out_gain;   // resid + product, row-major; times the gain, fragment-packed
+    int wave_slices = 0;      // of each wave; set by the launch
 };
-#define RS_FEW_LDS 98304   // most bytes of LDS for the rows; up to 33 KB more for the waves' sums
-bool few_applies(int M, int N, int K);   // K a multiple of 512, N of 32; the QKV projection's rows must fit RS_FEW_LDS too: M * (K + 8) * 2
-void launch_few_residual(hipStream_t st, const FewArgs &a, int cus);
-void launch_few_qkv(hipStream_t st, const FewArgs &a, const QkvEpiArgs &q, int cus);   // rotated q | k | v and the cache write, as launch_qkv_rope_epilogue
+bool few_applies(int M, int N, const DGemmPlan &p);   // 4 to 16 slices, N a multiple of 32
+bool few_qkv_applies(int M, int N, int K, const DGemmPlan &p);
+void launch_few_residual(hipStream_t st, FewArgs a, int cus);
+void launch_few_qkv(hipStream_t st, FewArgs a, const QkvEpiArgs &q, int cus);   // rotated q | k | v and the cache write, as launch_qkv_rope_epilogue
 // x1 = resid + the slices' sum (row-major) and h = RMSNorm(x1; gain) (fragment-packed), a row a workgroup.  Needs
 // residual_norm_applies: rows of at most 8192, a multiple of 8.
 struct ResidualNormArgs {

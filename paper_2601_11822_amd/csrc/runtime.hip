@@ -644,15 +644,16 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     };
     tick(c, side, 0);
     tick(c, side, 1);
+    const DGemmPlan pq = dgemm_plan(nqkv, d, false), po = dgemm_plan(d, qd, false), pd = dgemm_plan(d, f, false);
     // (not for wider layers, whose workgroups are more than a round of the chip: 70B widths, 1 row, on 256 CUs 279 -> 271 us, on 128 348 -> 351,
-    // on 96 458 -> 487; a function of the shapes alone, so that the sums are)
-    const bool few = d <= 16 * RS_TOTAL_CUS && few_applies(M, nqkv, d) && few_applies(M, d, qd) && few_applies(M, d, f) && (size_t)M * (d + 8) * 2 <= RS_FEW_LDS;
-    const DGemmPlan pq = dgemm_plan(nqkv, d, false);
+    // on 96 458 -> 487)
+    const bool few = d <= RS_FEW_COLS, few_q = few_qkv_applies(M, nqkv, d, pq), few_o = few && few_applies(M, d, po),
+               few_d = few && dgemm_applies(d, f) && few_applies(M, d, pd);
     int S_ssq = pq.S;
     QkvEpiArgs qe{w.partials, ssq1, pq.S, S_ssq, pq.Nv, d, m.rms_eps, w.qkv, c->rope, kp, vp, dtables, ctx_lens, err, M,
                   m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq};
-    if (few) {
-        launch_few_qkv(st, FewArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, pl.wqkv, M, nqkv, d, m.rms_eps, nullptr, nullptr, nullptr}, qe, cus);
+    if (few_q) {
+        launch_few_qkv(st, FewArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, pl.wqkv, M, nqkv, d, pq.S, m.rms_eps, nullptr, nullptr, nullptr}, qe, cus);
     } else if (dgemm_gains_inline(M, pq)) {
         stream(DGemmArgs{nullptr, (const bf16_t *)x_in, (const bf16_t *)lw.g1, ssq1, pl.wqkv, nullptr, w.partials, M, nqkv, d}, pq);
     } else {
@@ -662,7 +663,7 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
         stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wqkv, nullptr, w.partials, M, nqkv, d}, pq);
     }
     qe.S_ssq = S_ssq;
-    if (!few) launch_qkv_rope_epilogue(st, qe);
+    if (!few_q) launch_qkv_rope_epilogue(st, qe);
     tick(c, side, 2);
     tick(c, side, 3);
     PrefillAttnArgs pa{w.qkv, nqkv, w.attn, kp, vp, ptables, err, m.n_q_heads, m.n_kv_heads, hd, max_blk_p, c->pool.n_blocks, sl2, seq};
@@ -677,30 +678,24 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     else if (T > 0) launch_prefill_attention(st, pa);
     else launch_decode_attention(st, da);
     tick(c, side, 4);
-    const DGemmPlan po = dgemm_plan(d, qd, false);
-    if (few) {
-        launch_few_residual(st, FewArgs{w.attn, nullptr, (const bf16_t *)lw.g2, pl.wo, M, d, qd, m.rms_eps, (const bf16_t *)x_in, w.x1, w.h}, cus);
-        tick(c, side, 5);
-        tick(c, side, 6);
-        stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wg, pl.wu, nullptr, M, f, d}, dgemm_plan(f, d, true),
-               DFuseArgs{nullptr, 0, m.rms_eps, w.act, w.x1});
-        tick(c, side, 7);
-        launch_few_residual(st, FewArgs{w.act, nullptr, nullptr, pl.wd, M, d, f, m.rms_eps, w.x1, (bf16_t *)x_out, nullptr}, cus);
-        tick(c, side, 8);
-        HIP_TRY(hipGetLastError());
-        return RS_OK;
+    // x1 = x + attn Wo, and with it the gate/up projection's operand: x1 . g2 (packed) and the rows' sums of squares (of a few rows
+    // gate/up forms them)
+    DFuseArgs fz{ssq2, (d + 1023) / 1024, m.rms_eps, w.act};
+    if (few_o) {
+        launch_few_residual(st, FewArgs{w.attn, nullptr, (const bf16_t *)lw.g2, pl.wo, M, d, qd, po.S, m.rms_eps, (const bf16_t *)x_in, w.x1, w.h}, cus);
+        fz.rows = w.x1;
+    } else {
+        stream(DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, M, d, qd}, po);
+        launch_dgemm_epilogue(st, DEpiArgs{w.partials, po.S, po.Nv, (const bf16_t *)x_in, w.x1, M, d, (const bf16_t *)lw.g2, w.h, ssq2});
     }
-    stream(DGemmArgs{w.attn, nullptr, nullptr, nullptr, pl.wo, nullptr, w.partials, M, d, qd}, po);
-    // x1 = x + attn Wo, and with it the gate/up projection's operand: x1 . g2 (packed) and the rows' sums of squares
-    launch_dgemm_epilogue(st, DEpiArgs{w.partials, po.S, po.Nv, (const bf16_t *)x_in, w.x1, M, d, (const bf16_t *)lw.g2, w.h, ssq2});
     tick(c, side, 5);
     tick(c, side, 6);
-    stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wg, pl.wu, nullptr, M, f, d}, dgemm_plan(f, d, true),
-           DFuseArgs{ssq2, (d + 1023) / 1024, m.rms_eps, w.act});
+    stream(DGemmArgs{w.h, nullptr, nullptr, nullptr, pl.wg, pl.wu, nullptr, M, f, d}, dgemm_plan(f, d, true), fz);
     tick(c, side, 7);
     bool ok = true;
-    if (dgemm_applies(d, f)) {
-        const DGemmPlan pd = dgemm_plan(d, f, false);
+    if (few_d) {
+        launch_few_residual(st, FewArgs{w.act, nullptr, nullptr, pl.wd, M, d, f, pd.S, m.rms_eps, w.x1, (bf16_t *)x_out, nullptr}, cus);
+    } else if (dgemm_applies(d, f)) {
         stream(DGemmArgs{w.act, nullptr, nullptr, nullptr, pl.wd, nullptr, w.partials, M, d, f}, pd);
         launch_dgemm_epilogue(st, DEpiArgs{w.partials, pd.S, pd.Nv, w.x1, (bf16_t *)x_out, M, d});
     } else {

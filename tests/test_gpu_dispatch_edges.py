@@ -161,6 +161,34 @@ def test_decode_rows_do_not_depend_on_their_batch(shape):
         rig.close()
 
 
+# the same of a dense layer: one to four rows take kernels of their own, whose sums are the streams' (K slices in order, sums of squares
+# by their parts), so a row's hidden state and its cache entries are the same bits alone and in a batch
+@pytest.mark.parametrize("shape", [S.LLAMA8B, S.LayerShape("rows-2048", 2048, 32, 8, 64, 4608), S.WIDE])
+def test_dense_decode_rows_do_not_depend_on_their_batch(shape):
+    B = 40
+    ctx = np.array([(37 * i) % 300 for i in range(B)], np.int32)
+    held = [int(c) + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=41)
+    rig = Rig(shape, n_blocks, 16, B, 300, with_oracle=False)
+    try:
+        kb, vb = S.kv_cache_bits(n_blocks, shape.n_kv_heads, shape.head_dim)
+        xb = S.hidden_states(B, shape.d_model, stream=41)
+        own = lambda bits, n: [bits[tabs[i, ctx[i] // 16], ctx[i] % 16] for i in range(n)]   # the rows' own tokens
+        for split in ((256, 256), (128, 128), (96, 160), (64, 192)):
+            rig.ctx.set_cu_split(*split)
+            rig.load_pools_from_logical(kb, vb)
+            whole = rig.decode(xb, ctx, tabs, max_ctx=300)
+            kv = own(rig.k_bits_logical(), B), own(rig.v_bits_logical(), B)
+            for n in (1, 2, 3, 4, 5, 33):
+                print(shape.name, split, n, flush=True)
+                rig.load_pools_from_logical(kb, vb)
+                assert np.array_equal(rig.decode(xb[:n], ctx[:n], tabs[:n], max_ctx=300), whole[:n]), f"a batch of {n}"
+                assert np.array_equal(own(rig.k_bits_logical(), n), kv[0][:n]) and np.array_equal(own(rig.v_bits_logical(), n), kv[1][:n]), f"a batch of {n}"
+    finally:
+        rig.close()
+
+
 # prompt attention: single 128-query tiles and pairs of them, one and two teams over the key tiles, at odd and even numbers
 # of 64-key tiles; own operands (the kernel's q and cache, the oracle's attention).  A gain of 8 makes the scores large
 # (tens of powers of two): the maximum moves far from tile to tile.
@@ -381,8 +409,9 @@ def test_large_tile_products_repeat(T, split):
 
 
 # passes of one to four rows, whose projections are finished in one kernel (five rows and the next kernels beside them): prompt rows,
-# decode rows and both, head_dim 128 and 64, workgroups of one, two and four 16-column tiles.  The same bits on every partition.
-@pytest.mark.parametrize("shape", [S.LLAMA8B, S.LayerShape("few-64", 1024, 16, 4, 64, 2560, 1e-5, 10000.0)])
+# decode rows and both, head_dim 128 and 64, workgroups of one, two and four 16-column tiles; widths whose streams have too few K slices for
+# that kernel.  The same bits on every partition.
+@pytest.mark.parametrize("shape", [S.LLAMA8B, S.LayerShape("few-64", 1024, 16, 4, 64, 2560, 1e-5, 10000.0), S.LayerShape("few-64-2048", 2048, 32, 8, 64, 4608, 1e-5, 10000.0)])
 @pytest.mark.parametrize("lens,starts,ctx", [([], [], [0]), ([], [], [15, 16]), ([], [], [700, 3, 31, 512]), ([], [], [5, 6, 7, 8, 300]), ([1], [32], []), ([3], [0], []),
                                              ([1, 2], [16, 0], [40])])
 def test_passes_of_a_few_rows(shape, lens, starts, ctx):
