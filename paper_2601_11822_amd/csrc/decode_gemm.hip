@@ -636,7 +636,7 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// A pass of at most RS_FEW_ROWS rows: the projections that a stream cuts in K for enough workgroups, whole.  A workgroup's four to seven waves
+// A pass of at most RS_FEW_ROWS rows: the projections that a stream cuts in K for enough workgroups, whole.  A workgroup's two to seven waves
 // take the plan's K slices between them, of the same R x 16 weight rows (QKV: R x 16 dims and those that they are rotated with), the slices' sums
 // are added in their order through LDS, and the workgroup finishes its columns: no partial sums in memory and no epilogue kernel that reads
 // them, and the bits are the stream's.  What bounds a layer of one row, beside its weights, is some 4 us of every kernel in it (launch, first
@@ -647,21 +647,16 @@ __global__ __launch_bounds__(256) void qkv_rope_epilogue_kernel(QkvEpiArgs a) {
 // steps each 1.066 of the streams' rate where four of four have 1.084).
 // ---------------------------------------------------------------------------------------------
 #define FEW_PD 4   // 16x32 weight fragments in flight per wave and tile
-#define FEW_LEAST 4     // fewest and
+#define FEW_LEAST 2     // fewest and
 #define FEW_SLICES 16   // most slices that a workgroup's waves share
 #define FEW_WAVES 7     // most waves
 #define FEW_PAIRS 2     // QKV: most pairs of activation chunks of a wave, of rows of RS_FEW_COLS columns
-bool few_applies(int M, int N, const DGemmPlan &p) { return M <= RS_FEW_ROWS && N % 32 == 0 && p.S >= FEW_LEAST && p.S <= FEW_SLICES; }
 // Slices of a wave: the fewest waves, from four on, among those that leave the last one the least idle.
 static int few_slices_of_wave(int S) {
-    int best = FEW_LEAST;
-    for (int w = FEW_LEAST; w <= FEW_WAVES; ++w)
+    int best = std::min(S, 4);
+    for (int w = best; w <= FEW_WAVES; ++w)
         if ((S + w - 1) / w * w < (S + best - 1) / best * best) best = w;
     return (S + best - 1) / best;
-}
-bool few_qkv_applies(int M, int N, int K, const DGemmPlan &p) {
-    if (K > RS_FEW_COLS || !dgemm_gains_inline(M, p) || !few_applies(M, N, p)) return false;
-    return few_slices_of_wave(p.S) * ((p.kb_per_wg / DS_CH + 1) / 2) <= FEW_PAIRS;
 }
 static_assert(DS_CH % (2 * FEW_PD) == 0, "a slice is whole rounds of the ring");
 
@@ -821,15 +816,48 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void few_kernel(FewArgs a, QkvEpiAr
 
 // Tiles of a workgroup: rounds of workgroups (one per CU) times what a workgroup moves, its tiles of weights and `act` of one for the rows.
 // The same sums whatever the number.  One row of the 8B widths, streams / one tile throughout / this, four layers: on 128 CUs 446 / 469 / 438 us,
-// on 64 698 / 767 / 680 (four rows), on 192 437 / 459 / 428, on 96, where no number of tiles fills the CUs, 586 / 629 / 603.
+// on 64 698 / 767 / 680 (four rows), on 192 437 / 459 / 428.
+static int few_rounds(int tiles, int R, int cus) { return (tiles / R + cus - 1) / cus; }
 static int few_tiles(int tiles, int cus, double act, int most) {
     int best = 1;
     double least = 1e30;
     for (int R = 1; R <= most; R *= 2) {
-        const double cost = (double)((tiles / R + cus - 1) / cus) * (R + act);
+        const double cost = few_rounds(tiles, R, cus) * (R + act);
         if (cost < least) { least = cost; best = R; }
     }
     return best;
+}
+// (A tile is finished by a wave of its own.)
+static int few_residual_tiles(int N, int S, int cus) { return few_tiles(N / 16, cus, 0.6, S < 4 ? 1 : N % 64 ? 2 : 4); }
+static int few_qkv_tiles(int N, int S, int hd, int cus) { return few_tiles(N / 32, cus, 0.1, S < 4 ? 1 : hd == 64 ? 2 : 4); }
+
+// Whether a projection of a few rows is finished in one kernel or streamed, with the same bits.  It saves the partial sums and a kernel of some
+// 4 us; what can cost more is a CU's load, in 16-row tiles of K: the most of them that any CU has, here and in the stream's chosen form.
+// Measured for each projection by itself, one row, four layers, against the streams on 256 / 224 / 192 / 160 / 128 / 96 / 64 / 32 CUs:
+//   8B widths, QKV -12 -11 -11 -10 -11 -11 0 -7 us, output -13 -4 -1 -2 -3 0 -8 -13, down (K = 14336) -10 +3 +4 +5 +5 +27 -3 -4
+//   3072 columns, QKV -10 -14 -15 -15 -3 -14 +2 -1, output -6 -5 -6 +4 -6 -5 -2 -10, down (K = 8192) -1 -1 -2 +1 0 +1 +16 +13
+//   2560 columns, QKV -8 -8 -8 -8 -16 -6 -17 -18, output -8 -8 -8 -8 +1 -10 +6 -1, down (K = 10240) +4 +4 -8 -8 +19 -3 +36 +15
+// (and five other widths, four rows).  So a residual projection where a CU's load does not grow; QKV, whose rows cost a workgroup less than
+// the stream's, where it grows by no more than what a CU moves in 2 us (57 KB each).  Long K with several tiles a workgroup loses even at
+// equal loads: the rows' fragments come with every step.  Two or three slices are two or three waves, too few to load a CU at its rate:
+// where a workgroup a tile is one round (down projection of 3584 columns, K = 18944: -35 us on 256 CUs; on 96, three rounds, +12).
+static double stream_load(const DGemmPlan &p, int cus) {
+    const int wgs = p.cols * p.S;
+    return dgemm_prefers_half_height(p, cus) ? (2 * wgs + cus - 1) / cus * (8.0 / p.S) : (wgs + cus - 1) / cus * (16.0 / p.S);
+}
+static bool few_applies(int M, int N, const DGemmPlan &p) { return M <= RS_FEW_ROWS && N % 32 == 0 && p.S >= FEW_LEAST && p.S <= FEW_SLICES; }
+bool few_takes_residual(int M, int N, int K, int cus) {
+    const DGemmPlan p = dgemm_plan(N, K, false);
+    if (N > RS_FEW_COLS || !dgemm_applies(N, K) || !few_applies(M, N, p)) return false;
+    const int R = few_residual_tiles(N, p.S, cus);
+    return few_rounds(N / 16, R, cus) * R <= stream_load(p, cus) && (R == 1 || K <= 8192) && (p.S >= 4 || N / 16 <= cus);
+}
+bool few_takes_qkv(int M, int N, int K, int hd, int cus) {
+    const DGemmPlan p = dgemm_plan(N, K, false);
+    if (K > RS_FEW_COLS || !dgemm_gains_inline(M, p) || !few_applies(M, N, p)) return false;
+    if (few_slices_of_wave(p.S) * ((p.kb_per_wg / DS_CH + 1) / 2) > FEW_PAIRS) return false;
+    const int R = few_qkv_tiles(N, p.S, hd, cus);
+    return (p.S >= 4 || N / 32 <= cus) && (few_rounds(N / 32, R, cus) * 2 * R - stream_load(p, cus)) * (32.0 * K) <= 2 * 57e3;
 }
 // (At most 50 KB, which needs no leave: rows of RS_FEW_COLS columns, 32 KB, have up to eight slices, 16 KB of sums.)
 static size_t few_lds_bytes(int S, int tiles) { return (size_t)S * tiles * 4 * RS_FEW_ROWS * sizeof(f32x4); }
@@ -838,12 +866,12 @@ static int few_threads(FewArgs &a) {
     return 64 * ((a.S + a.wave_slices - 1) / a.wave_slices);
 }
 void launch_few_residual(hipStream_t st, FewArgs a, int cus) {
-    const int R = few_tiles(a.N / 16, cus, 0.6, a.N % 64 ? 2 : 4), threads = few_threads(a);
+    const int R = few_residual_tiles(a.N, a.S, cus), threads = few_threads(a);
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.N / (16 * R)), dim3(threads), few_lds_bytes(a.S, R), st, a, QkvEpiArgs{}); };
     R == 4 ? go(few_kernel<0, 4>) : R == 2 ? go(few_kernel<0, 2>) : go(few_kernel<0, 1>);
 }
 void launch_few_qkv(hipStream_t st, FewArgs a, const QkvEpiArgs &q, int cus) {
-    const int R = few_tiles(a.N / 32, cus, 0.1, q.hd == 64 ? 2 : 4);
+    const int R = few_qkv_tiles(a.N, a.S, q.hd, cus);
     const dim3 grid(a.N / (32 * R)), block(few_threads(a));
     const size_t lds = few_lds_bytes(a.S, 2 * R) + (size_t)a.M * (a.K + 8) * sizeof(bf16_t);
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, st, a, q); };

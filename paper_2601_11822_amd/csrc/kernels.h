@@ -199,8 +199,9 @@ struct FewArgs {
     bf16_t *out, *out_gain;   // resid + product, row-major; times the gain, fragment-packed
     int wave_slices = 0;      // of each wave; set by the launch
 };
-bool few_applies(int M, int N, const DGemmPlan &p);   // 4 to 16 slices, N a multiple of 32
-bool few_qkv_applies(int M, int N, int K, const DGemmPlan &p);
+// Whether they are the faster (and take the projection: 2 to 16 K slices, N a multiple of 32, rows of at most RS_FEW_COLS columns).
+bool few_takes_residual(int M, int N, int K, int cus);
+bool few_takes_qkv(int M, int N, int K, int hd, int cus);
 void launch_few_residual(hipStream_t st, FewArgs a, int cus);
 void launch_few_qkv(hipStream_t st, FewArgs a, const QkvEpiArgs &q, int cus);   // rotated q | k | v and the cache write, as launch_qkv_rope_epilogue
 // x1 = resid + the slices' sum (row-major) and h = RMSNorm(x1; gain) (fragment-packed), a row a workgroup.  Needs

@@ -647,8 +647,8 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
     const DGemmPlan pq = dgemm_plan(nqkv, d, false), po = dgemm_plan(d, qd, false), pd = dgemm_plan(d, f, false);
     // (not for wider layers, whose workgroups are more than a round of the chip: 70B widths, 1 row, on 256 CUs 279 -> 271 us, on 128 348 -> 351,
     // on 96 458 -> 487)
-    const bool few = d <= RS_FEW_COLS, few_q = few_qkv_applies(M, nqkv, d, pq), few_o = few && few_applies(M, d, po),
-               few_d = few && dgemm_applies(d, f) && few_applies(M, d, pd);
+    const bool few = d <= RS_FEW_COLS, few_q = few && few_takes_qkv(M, nqkv, d, hd, cus), few_o = few && few_takes_residual(M, d, qd, cus),
+               few_d = few && few_takes_residual(M, d, f, cus);
     int S_ssq = pq.S;
     QkvEpiArgs qe{w.partials, ssq1, pq.S, S_ssq, pq.Nv, d, m.rms_eps, w.qkv, c->rope, kp, vp, dtables, ctx_lens, err, M,
                   m.n_q_heads, m.n_kv_heads, hd, max_blk_d, c->pool.n_blocks, m.max_pos, T, ptables, max_blk_p, seq};

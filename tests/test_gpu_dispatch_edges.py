@@ -163,7 +163,8 @@ def test_decode_rows_do_not_depend_on_their_batch(shape):
 
 # the same of a dense layer: one to four rows take kernels of their own, whose sums are the streams' (K slices in order, sums of squares
 # by their parts), so a row's hidden state and its cache entries are the same bits alone and in a batch
-@pytest.mark.parametrize("shape", [S.LLAMA8B, S.LayerShape("rows-2048", 2048, 32, 8, 64, 4608), S.WIDE])
+@pytest.mark.parametrize("shape", [S.LLAMA8B, S.LayerShape("rows-2048", 2048, 32, 8, 64, 4608), S.LayerShape("rows-2560", 2560, 20, 4, 128, 10240),
+                                   S.LayerShape("rows-3584", 3584, 28, 4, 128, 18944), S.WIDE])
 def test_dense_decode_rows_do_not_depend_on_their_batch(shape):
     B = 40
     ctx = np.array([(37 * i) % 300 for i in range(B)], np.int32)

@@ -219,6 +219,21 @@ def test_operand_layouts_shared_by_host_and_kernels(tmp_path):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
+def test_kernels_are_chosen_as_measured(tmp_path):
+    """The dispatch rules, at sizes where both kernels were timed and where GPU tests compare them."""
+    import shutil
+    import subprocess
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "host_dispatch_check.hip")
+    exe = str(tmp_path / "host_dispatch_check")
+    rs.load()
+    subprocess.run([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", src, "-L" + os.path.dirname(rs.LIB_PATH), "-l:" + os.path.basename(rs.LIB_PATH),
+                    "-Wl,-rpath," + os.path.dirname(rs.LIB_PATH), "-o", exe], check=True,
+                   stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 def test_release_source_weights_only_where_the_packed_copies_suffice():
     c = host_ctx(shape=S.LLAMA8B)
     with pytest.raises(rs.RapidServeError) as e:
