@@ -223,7 +223,8 @@ int32_t rs_decode_layer_graph(rs_ctx *ctx, int32_t layer, const void *x_in, void
  *                the chunk's rows up to itself; start_pos[r] is a multiple of 16 (host array, like cu_seqlens);
  *   rows [T, T+B) are decode rows exactly as in rs_decode_layer (ctx_lens, decode_tables device arrays).
  * All rows go through every projection together (the weights are read once for the whole batch); each kind
- * takes its own attention kernel.  Enqueued on the PREFILL side's stream with that side's workspace: T + B <=
+ * takes its own attention kernel (which form of it is judged by max_ctx too: a bound near the longest context serves
+ * best).  Enqueued on the PREFILL side's stream with that side's workspace: T + B <=
  * max_prefill_tokens, B <= max_decode_batch (B may be 0: a chunk alone).  Errors as for the two passes. */
 int32_t rs_hybrid_layer(rs_ctx *ctx, int32_t layer, const void *x_in, void *x_out, const int32_t *cu_seqlens,
                         const int32_t *start_pos, int32_t n_req, const int32_t *prefill_tables,

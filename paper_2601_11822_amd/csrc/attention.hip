@@ -936,13 +936,17 @@ void launch_prefill_attention(hipStream_t st, const PrefillAttnArgs &args) {
 }
 
 // Which of the two: a prompt tile takes a team of its own longer than two teams (some 2.3 us a 64-key tile), so the small workgroups
-// where the decode rows, at half of the longest context on average, are read for longer than that.  The same bits in both.  Layers of the
-// 8B widths, 512 rows behind 1024 tokens beside 64 decode rows of 512 to 4096 and beside 128, large / small workgroups: 404 / 395 and 540 /
-// 525 us; where the rule takes the large ones, 512 rows behind 3072 beside 16 of up to 600 tokens 337 / 356, behind 2416 beside 11 324 / 344.
+// where the decode rows are read for longer than that: the contexts' own tokens where the host has counted them, else half of their
+// bound for each, which the caller sets near the longest (64 rows of 100 to 500 tokens under a bound of 4097 take the small ones, 328 us,
+// where the large ones take 316).  The same bits in both.  Layers of the 8B widths, 512 rows behind 1024 tokens beside 64 decode rows of 512 to
+// 4096 and beside 128, large / small workgroups: 404 / 395 and 541 / 523 us; where the rule takes the large ones, 512 rows behind 3072 beside 16
+// of up to 600 tokens 337 / 356, behind 1024 beside 32 of 1000 to 2000 323 / 328.  head_dim 64 (32 heads over 8, the 512 rows behind 1024):
+// beside 64 of 512 to 4096, where the rule changes over, 196 / 196, beside 128 265 / 245, beside 32 of 1000 to 2000 159 / 176.
 static bool hybrid_small(const PrefillAttnArgs &p, const DecodeAttnArgs &d, const PrefillForm &f) {
     int keys = 0;
     for (int r = 0; r < p.seq.n_req; ++r) keys = std::max(keys, p.seq.start[r] + p.seq.cu[r + 1] - p.seq.cu[r]);
-    const double bytes = 0.5 * d.B * d.max_ctx * (4.0 * d.Hkv * d.hd), rate = std::min(6.0e6, 0.034e6 * prefill_cus(p));   // bytes a us
+    const double tokens = d.n_keys > 0 ? (double)d.n_keys : 0.5 * d.B * d.max_ctx;
+    const double bytes = tokens * (4.0 * d.Hkv * d.hd), rate = std::min(6.0e6, 0.034e6 * prefill_cus(p));   // bytes a us
     return p.park && (size_t)f.tiles * 128 * p.hd <= p.park_cap && 2.3 * keys / 64 < bytes / rate;
 }
 
@@ -950,30 +954,36 @@ static bool hybrid_small(const PrefillAttnArgs &p, const DecodeAttnArgs &d, cons
 // 32 heads behind 1024 cached tokens beside 64 decode rows: 131 us, 141 in two launches; 2048 rows 132 and 121), a quarter of a
 // partition, where decode rows need every unit for themselves (the 512 rows on 128 CUs 215 and 173 us; 100 rows beside 28: 48 and
 // 59).  Or beside so few decode workgroups that it is the launch that counts (200 and 300 rows beside one: 29 and 35 us).
-void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &pargs, const DecodeAttnArgs &d) {
-    PrefillAttnArgs p = pargs;
+struct HybridPlan { HybridForm form; int n_prefill, n_decode; bool pairs; };
+static HybridPlan hybrid_plan(const PrefillAttnArgs &p, const DecodeAttnArgs &d) {
     const PrefillForm f = prefill_form(p);
     const int pairs = prefill_unit_count(p, true) * p.Hq, n_decode = (d.Hkv + 1) / 2 * d.n_chunks * d.B;
     const int cus = prefill_cus(p), most = cus >= 256 ? cus / 2 : cus / 4;
     const bool light = f.teams && (8 * n_decode <= cus || f.tiles + n_decode <= cus);
-    if (!f.split || !(light || pairs <= most)) {
+    if (!f.split || !(light || pairs <= most)) return {HYBRID_APART, 0, 0, false};
+    if (hybrid_small(p, d, f)) return {HYBRID_SMALL, f.tiles, d.Hkv * d.n_chunks * d.B, false};
+    const bool in_pairs = light ? f.pairs : f.tiles > most;
+    return {HYBRID_TEAMS, in_pairs ? pairs : f.tiles, n_decode, in_pairs};
+}
+HybridForm hybrid_form(const PrefillAttnArgs &p, const DecodeAttnArgs &d) { return hybrid_plan(p, d).form; }
+
+void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &pargs, const DecodeAttnArgs &d) {
+    const HybridPlan h = hybrid_plan(pargs, d);
+    if (h.form == HYBRID_APART) {
         launch_prefill_attention(st, pargs);
         launch_decode_attention(st, d);
         return;
     }
-    p.pairs = light ? f.pairs : f.tiles > most;
-    const int n_prefill = p.pairs ? pairs : f.tiles;
-    if (hybrid_small(p, d, f)) {
-        p.pairs = false;
-        const dim3 g1(f.tiles + d.Hkv * d.n_chunks * d.B);
-        if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_small_kernel<128>, g1, dim3(256), prefill_lds(128, 1), st, p, d, f.tiles);
-        else hipLaunchKernelGGL(hybrid_attn_small_kernel<64>, g1, dim3(256), prefill_lds(64, 1), st, p, d, f.tiles);
-        launch_decode_combine(st, d);
-        return;
+    PrefillAttnArgs p = pargs;
+    p.pairs = h.pairs;
+    const dim3 grid(h.n_prefill + h.n_decode);
+    if (h.form == HYBRID_SMALL) {
+        if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_small_kernel<128>, grid, dim3(256), prefill_lds(128, 1), st, p, d, h.n_prefill);
+        else hipLaunchKernelGGL(hybrid_attn_small_kernel<64>, grid, dim3(256), prefill_lds(64, 1), st, p, d, h.n_prefill);
+    } else {
+        if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_kernel<128>, grid, dim3(512), prefill_lds(128, 2), st, p, d, h.n_prefill);
+        else hipLaunchKernelGGL(hybrid_attn_kernel<64>, grid, dim3(512), prefill_lds(64, 2), st, p, d, h.n_prefill);
     }
-    const dim3 grid(n_prefill + n_decode);
-    if (d.hd == 128) hipLaunchKernelGGL(hybrid_attn_kernel<128>, grid, dim3(512), prefill_lds(128, 2), st, p, d, n_prefill);
-    else hipLaunchKernelGGL(hybrid_attn_kernel<64>, grid, dim3(512), prefill_lds(64, 2), st, p, d, n_prefill);
     launch_decode_combine(st, d);
 }
 

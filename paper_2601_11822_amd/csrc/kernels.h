@@ -59,11 +59,15 @@ struct DecodeAttnArgs {
     float scale_log2;
     int chunk_major;   // order of the workgroups only (results do not depend on it): chunks slowest, else requests slowest
     int out_row0 = 0, out_Mt = 0;   // the packed output matrix holds other rows first / more row tiles (0: packed_mt(B))
+    int64_t n_keys = 0;             // tokens of all contexts, where the host knows them (0: it knows max_ctx alone); scheduling only
 };
 #define RS_SKINNY_TARGET_WGS 384  // the skinny GEMM splits K until it has about this many workgroups
 #define RS_DECODE_CHUNK 512  // tokens per workgroup of the decode attention
 void launch_decode_attention(hipStream_t st, const DecodeAttnArgs &a);
-void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &p, const DecodeAttnArgs &d);   // both, in one launch
+// Both.  HYBRID_APART: a launch each; else one launch, in workgroups of 512 threads (HYBRID_TEAMS) or of 256 (HYBRID_SMALL).
+enum HybridForm { HYBRID_APART, HYBRID_TEAMS, HYBRID_SMALL };
+HybridForm hybrid_form(const PrefillAttnArgs &p, const DecodeAttnArgs &d);
+void launch_hybrid_attention(hipStream_t st, const PrefillAttnArgs &p, const DecodeAttnArgs &d);
 
 enum GemmEpilogue { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2 };
 

@@ -625,7 +625,7 @@ bool streams(const rs_ctx *c, int layer, int rows) { return rows <= RS_STREAM_RO
 
 int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const void *x_in, void *x_out, int T, const SeqInfo &seq,
                      const int32_t *ptables, int32_t max_blk_p, int B, const int32_t *ctx_lens, const int32_t *dtables,
-                     int32_t max_blk_d, int32_t max_ctx) {
+                     int32_t max_blk_d, int32_t max_ctx, int64_t n_keys = 0) {
     const rs_model_desc &m = c->m;
     const rs_layer_weights &lw = c->weights[layer];
     const rs_ctx::PackedLayer &pl = c->packed[layer];
@@ -674,6 +674,7 @@ int32_t stream_layer(rs_ctx *c, int side, Workspace &w, int32_t layer, const voi
                       (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, sl2, cus < RS_TOTAL_CUS};
     da.out_row0 = T;
     da.out_Mt = packed_mt(M);
+    da.n_keys = n_keys;
     if (T > 0 && B > 0) launch_hybrid_attention(st, pa, da);
     else if (T > 0) launch_prefill_attention(st, pa);
     else launch_decode_attention(st, da);
@@ -795,10 +796,11 @@ int32_t prefill_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, c
 // One layer over a hybrid batch (section 3.1: chunked prefill co-batched with decode, the baseline the paper
 // compares with): rows [0, T) are one chunk of each of n_req prompts (prompt r's chunk starts at position
 // start[r]), rows [T, T+B) are decode rows.  Both kinds share every projection (one pass over the weights for
-// all rows) and take their own attention kernel.  Runs on the prefill side's stream and workspace.
+// all rows) and take their own attention kernel.  Runs on the prefill side's stream and workspace.  n_keys: tokens of all decode
+// rows' contexts where the caller has them on the host, else 0.
 int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, const int32_t *cu, const int32_t *start,
                      int32_t n_req, const int32_t *ptables, int32_t max_blk_p, const int32_t *ctx_lens,
-                     const int32_t *dtables, int32_t max_blk_d, int32_t B, int32_t max_ctx) {
+                     const int32_t *dtables, int32_t max_blk_d, int32_t B, int32_t max_ctx, int64_t n_keys) {
     const rs_model_desc &m = c->m;
     if (!cu || !start || n_req < 1 || n_req > RS_MAX_PREFILL_REQS) return fail(RS_ERR_BAD_ARG, "n_req %d out of range", n_req);
     if (cu[0] != 0) return fail(RS_ERR_BAD_ARG, "cu_seqlens must start at 0");
@@ -837,7 +839,7 @@ int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, co
     const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
 
     if (streams(c, layer, M))
-        return stream_layer(c, RS_SIDE_PREFILL, w, layer, x_in, x_out, T, seq, ptables, max_blk_p, B, ctx_lens, dtables, max_blk_d, max_ctx);
+        return stream_layer(c, RS_SIDE_PREFILL, w, layer, x_in, x_out, T, seq, ptables, max_blk_p, B, ctx_lens, dtables, max_blk_d, max_ctx, n_keys);
     tick(c, RS_SIDE_PREFILL, 0);
     c->last_rows[RS_SIDE_PREFILL] = M;
     c->streamed[RS_SIDE_PREFILL] = false;
@@ -855,6 +857,7 @@ int32_t hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, co
                           (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, sl2, c->side[RS_SIDE_PREFILL].cus < RS_TOTAL_CUS};
         da.out_row0 = T;
         da.out_Mt = packed_mt(M);
+        da.n_keys = n_keys;
         launch_hybrid_attention(st, pa, da);
     } else {
         launch_prefill_attention(st, pa);
@@ -1410,7 +1413,7 @@ int32_t rs_hybrid_layer(rs_ctx *c, int32_t layer, const void *x_in, void *x_out,
     int32_t rc = check_layer_call(c, RS_SIDE_PREFILL, layer, x_in, x_out, prefill_tables);
     if (rc) return rc;
     return hybrid_layer(c, layer, x_in, x_out, cu_seqlens, start_pos, n_req, prefill_tables, max_blk_prefill, ctx_lens,
-                        decode_tables, max_blk_decode, B, max_ctx);
+                        decode_tables, max_blk_decode, B, max_ctx, 0);
 }
 
 int32_t rs_decode_layer_noalloc(rs_ctx *c, int32_t layer, const void *x_in, void *x_out, const int32_t *ctx_lens,
@@ -2117,7 +2120,8 @@ int32_t serve_step(rs_ctx *c, const rs_step_in *in, rs_step_out *out, bool token
     c->last_batch.assign(c->running.begin(), c->running.end());
     if (B > 0 || n_chunk > 0) {
         int max_ctx = 1;
-        for (int64_t id : c->running) max_ctx = std::max(max_ctx, c->reqs[id].ctx_len + 1);
+        int64_t n_keys = 0;   // tokens of the running contexts
+        for (int64_t id : c->running) max_ctx = std::max(max_ctx, c->reqs[id].ctx_len + 1), n_keys += c->reqs[id].ctx_len + 1;
         const int nS = B + F;   // rows whose next token this step chooses
         const int flip = nS > 0 ? (c->stage_flip ^= 1) : c->stage_flip;
         if (nS > 0 && token_mode && c->pending[flip]) {   // the staging buffers are about to be rewritten
@@ -2194,7 +2198,7 @@ int32_t serve_step(rs_ctx *c, const rs_step_in *in, rs_step_out *out, bool token
                                                c->err_flag + sd, B, dm, c->head.vocab});
                     for (int l = 0; l < c->m.n_layers; ++l) {
                         if (!c->have_weights[l]) return fail(RS_ERR_STATE, "weights of layer %d not set", l);
-                        int32_t rc = hybrid_layer(c, l, w.xbuf, w.xbuf, pcu, pstart, np, c->d_ptab, mb, c->d_ctx, c->d_tab, mb, B, ctx_bound);
+                        int32_t rc = hybrid_layer(c, l, w.xbuf, w.xbuf, pcu, pstart, np, c->d_ptab, mb, c->d_ctx, c->d_tab, mb, B, ctx_bound, n_keys);
                         if (rc) return rc;
                     }
                     if (B > 0) {

@@ -1,6 +1,7 @@
 // Host-side check of the rules by which passes take their kernels (no GPU call), at sizes where both sides were measured
 // and at those where tests compare the two.  Built against the library and run by tests/test_host_abi.py.
 #include <cstdio>
+#include <vector>
 
 #include "../paper_2601_11822_amd/csrc/kernels.h"
 
@@ -34,8 +35,43 @@ static void few_rows() {
     CHECK(few_takes_qkv(1, 3072, 2048, 64, 256) && few_takes_residual(1, 2048, 2048, 256) && few_takes_residual(1, 2048, 4608, 64), "2048 columns");
 }
 
+// The form of hybrid attention: prompts of `lens` rows behind `starts` tokens, B decode rows of at most max_ctx tokens (all of them n_keys)
+struct Heads { int Hq, Hkv, hd; };
+static HybridForm form_of(Heads h, std::vector<int> lens, std::vector<int> starts, int B, int max_ctx, int64_t n_keys, int cus) {
+    static float park;
+    PrefillAttnArgs p{};
+    p.Hq = h.Hq, p.Hkv = h.Hkv, p.hd = h.hd, p.cus = cus, p.park = &park, p.park_cap = (size_t)1 << 40;
+    p.seq.n_req = (int)lens.size();
+    for (size_t r = 0; r < lens.size(); ++r) p.seq.cu[r + 1] = p.seq.cu[r] + lens[r], p.seq.start[r] = starts[r];
+    DecodeAttnArgs d{};
+    d.B = B, d.Hq = h.Hq, d.Hkv = h.Hkv, d.hd = h.hd, d.max_ctx = max_ctx, d.n_chunks = (max_ctx + RS_DECODE_CHUNK - 1) / RS_DECODE_CHUNK, d.n_keys = n_keys;
+    return hybrid_form(p, d);
+}
+
+static void hybrid_forms() {
+    const Heads of8b{32, 8, 128}, mid{8, 2, 128}, odd{9, 3, 128}, tiny{4, 4, 64};
+    // 512 rows of the 8B heads: small workgroups where the decode rows are read for longer than the longest prompt tile takes
+    CHECK(form_of(of8b, {512}, {1024}, 64, 4097, 0, 256) == HYBRID_SMALL, "64 rows of up to 4096");
+    CHECK(form_of(of8b, {512}, {3072}, 16, 601, 0, 256) == HYBRID_TEAMS, "16 rows of up to 600");
+    CHECK(form_of(of8b, {512}, {1024}, 32, 2001, 0, 256) == HYBRID_TEAMS, "32 rows of up to 2000");
+    CHECK(form_of(of8b, {512}, {1024}, 64, 4097, 0, 128) == HYBRID_APART, "a partition");
+    // by the tokens themselves where they are known: one long context among short ones is not 64 long ones, and many long ones are more than half
+    CHECK(form_of(of8b, {512}, {1024}, 64, 4097, 4097 + 63 * 300, 256) == HYBRID_TEAMS, "63 rows of 300 beside one of 4096");
+    CHECK(form_of(of8b, {512}, {1024}, 64, 3001, 64 * 3001, 256) == HYBRID_SMALL, "64 rows of 3000");
+    CHECK(form_of(of8b, {512}, {1536}, 64, 4097, 0, 256) == HYBRID_SMALL && form_of(of8b, {512}, {1536}, 64, 4097, 64 * 1000, 256) == HYBRID_TEAMS, "bound and tokens");
+    // the sizes at which a GPU test compares the forms
+    struct { Heads h; std::vector<int> lens, starts; int B; } tests[] = {{mid, {90}, {16}, 40}, {odd, {200, 31}, {0, 48}, 50}, {tiny, {140, 1}, {32, 0}, 50}};
+    for (auto &t : tests) {
+        CHECK(form_of(t.h, t.lens, t.starts, t.B, 301, 0, 256) == HYBRID_TEAMS, "%d rows of up to 300", t.B);
+        CHECK(form_of(t.h, t.lens, t.starts, t.B, 2600, 0, 256) == HYBRID_SMALL, "%d rows of up to 2600", t.B);
+    }
+    for (int cus : {256, 128, 64}) CHECK(form_of(mid, {16}, {0}, 60, 301, 0, cus) == HYBRID_SMALL, "one chunk on %d", cus);
+    CHECK(form_of(mid, {16}, {0}, 2, 301, 0, 256) == HYBRID_TEAMS, "2 rows of one chunk");
+}
+
 int main() {
     few_rows();
+    hybrid_forms();
     if (fails) { std::printf("%d checks failed\n", fails); return 1; }
     std::printf("dispatch ok\n");
     return 0;

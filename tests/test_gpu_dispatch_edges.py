@@ -246,6 +246,32 @@ def test_hybrid_attention_in_small_workgroups(shape, lens, starts, B):
         rig.close()
 
 
+# the same where the decode rows have one chunk each, which their workgroups finish, on the whole chip and on partitions (their
+# time is judged by the units): the same bits on every one, and as a batch of two decode rows, which take the large workgroups
+def test_small_workgroups_finish_contexts_of_one_chunk():
+    shape, B, T = S.MID, 60, 16
+    ctx = np.array([(37 * i) % 300 for i in range(B)], np.int32)
+    held = [T] + [int(c) + 1 for c in ctx]
+    n_blocks = sum(S.blocks_for(n) for n in held) + 2
+    tabs = S.shuffled_block_tables(held, n_blocks, stream=42)
+    rig = Rig(shape, n_blocks, T + B, B, 301)
+    try:
+        kb, vb = S.kv_cache_bits(n_blocks, shape.n_kv_heads, shape.head_dim)
+        xb, cu, got = S.hidden_states(T + B, shape.d_model, stream=42), np.array([0, T], np.int32), []
+        for n, split in ((B, (256, 256)), (B, (128, 128)), (B, (64, 192)), (2, (256, 256))):
+            rig.ctx.set_cu_split(*split)
+            rig.load_pools_from_logical(kb, vb)
+            rig.hybrid(xb[:T + n], cu, [0], tabs[:1], ctx[:n], tabs[1:1 + n], max_ctx=301)
+            got.append(rig.ctx.debug_read_workspace(rs.RS_SIDE_PREFILL, 2, (T + n, shape.q_dim)))
+        assert all(np.array_equal(g, got[0][:len(g)]) for g in got)
+        rig.load_pools_from_logical(kb, vb)
+        y, x, Kc, Vc = rig.hybrid(xb, cu, [0], tabs[:1], ctx, tabs[1:], max_ctx=301), f32(xb), f32(kb), f32(vb)
+        check_tensor("prompt rows", f32(y)[:T], rig.olayers[0].prefill_chunk(x[:T], cu, [0], tabs[:1], Kc, Vc), x[:T], 2, elem_mult=END_TO_END)
+        check_tensor("decode rows", f32(y)[T:], rig.olayers[0].decode(x[T:], ctx, tabs[1:], Kc, Vc), x[T:], 2, elem_mult=END_TO_END)
+    finally:
+        rig.close()
+
+
 # the forms that prompt attention takes as the side's compute units become few: two teams of waves, one that does both
 # teams' work one after the other, tiles and pairs of tiles, decode rows in the same launch and in one of their own; with
 # one key tile a row, and with chunks that have earlier keys.  The same bits in all of them.
