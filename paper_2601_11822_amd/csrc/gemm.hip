@@ -592,8 +592,6 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
 // 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
 // ---------------------------------------------------------------------------------------------
-enum DirectForm { FORM_128x256, FORM_160x256, FORM_192x256, FORM_224x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192 };
-
 static double direct_round_us(DirectForm f, int nk, long w) {
     constexpr double A[] = {0.30, 0.365, 0.38, 0.44, 0.44, 0.36, 0.225}, B[] = {0.10, 0.105, 0.145, 0.175, 0.25, 0.165, 0.09};
     return 4.8 + nk * (A[f] + B[f] * (double)w / 256.0);
@@ -633,12 +631,18 @@ static double direct_best_form(int M, int N, int K, int epi, int S, int cus, Dir
     return best;
 }
 
+DirectForm direct_form(int M, int N, int K, int epi, int S, int cus) {
+    DirectForm f;
+    direct_best_form(M, N, K, epi, S, cus, f);
+    return f;
+}
+
 // K slices: from (M, N, K) alone, so that results do not depend on the CU share; the whole chip's time counts four times what half
 // of it takes.  At least 16 K tiles a slice, one round of workgroups, and no more partial sums than RS_DIRECT_PARTIAL_ELEMS.
 // (With the whole chip alone 576 to 1150 rows lost up to 15 % of a product on 128 CUs.  What is left: two slices of 1150x4096x14336 gain 33 us
 // of the layer on 256 CUs and cost 18 on 128.)  Heights of an odd number of row blocks take no part in the choice: counted in, they
 // raised the slices of 680 to 770 rows of a 4096-wide down projection from two to three, 2 % of the layer on 256 CUs for 8 % on 128.
-static int direct_splits(int M, int N, int K) {
+int direct_splits(int M, int N, int K) {
     DirectForm f;
     auto us = [&](int epi, int S) { return direct_best_form(M, N, K, epi, S, 256, f, false) + 0.25 * direct_best_form(M, N, K, epi, S, 128, f, false); };
     int S = 1;
@@ -671,8 +675,7 @@ static void launch_direct_splitk_tiles(hipStream_t st, const GemmArgs &a, int S)
                        m_tiles, n_tiles, S, nk_per, a.partials);
 }
 static void launch_direct_splitk_main(hipStream_t st, const GemmArgs &a, int S) {
-    DirectForm f;
-    direct_best_form(a.M, a.N, a.K, EPI_STORE, S, a.cus > 0 ? a.cus : 256, f);
+    const DirectForm f = direct_form(a.M, a.N, a.K, EPI_STORE, S, a.cus > 0 ? a.cus : 256);
     if (f == FORM_256x256) launch_direct_splitk_tiles<256, RS_NS_FULL>(st, a, S);
     else if (f == FORM_224x256) launch_direct_splitk_tiles<224, 4>(st, a, S);
     else if (f == FORM_192x256) launch_direct_splitk_tiles<192, 4>(st, a, S);
@@ -826,9 +829,7 @@ bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
             return true;
         }
         const int cus = a.cus > 0 ? a.cus : 256;
-        DirectForm f;
-        direct_best_form(a.M, a.N, a.K, a.epi, 1, cus, f);
-        switch (f) {
+        switch (direct_form(a.M, a.N, a.K, a.epi, 1, cus)) {
             case FORM_256x256: launch_direct<256, 256, RS_NS_FULL>(st, a); break;   // RS_NS_FULL x 32 KB of LDS
             case FORM_224x256: launch_direct<224, 256, 4>(st, a); break;            // 4 x 30 KB
             case FORM_192x256: launch_direct<192, 256, 4>(st, a); break;            // 4 x 28 KB

@@ -69,9 +69,35 @@ static void hybrid_forms() {
     CHECK(form_of(mid, {16}, {0}, 2, 301, 0, 256) == HYBRID_TEAMS, "2 rows of one chunk");
 }
 
+// Large tiles of an odd number of 32-row blocks: each of the passes that a GPU test repeats for their sake has a product in them
+static void odd_heights() {
+    const struct { int M, cus; } passes[] = {{576, 256}, {300, 256}, {1120, 128}, {650, 96}};
+    const int N[] = {6144, 4096, 4096}, K[] = {4096, 4096, 14336};   // QKV, output, down of the 8B widths; gate/up below
+    auto odd = [](DirectForm f) { return f == FORM_160x256 || f == FORM_224x256; };
+    for (auto &p : passes) {
+        bool any = odd(direct_form(p.M, 14336, 4096, EPI_SWIGLU, 1, p.cus));
+        for (int j = 0; j < 3; ++j) {
+            const int S = direct_splits(p.M, N[j], K[j]);
+            any = any || odd(direct_form(p.M, N[j], K[j], S > 1 || j == 0 ? EPI_STORE : EPI_RESIDUAL, S, p.cus));
+        }
+        CHECK(any, "%d rows on %d compute units have no tile of 160 or 224 rows", p.M, p.cus);
+    }
+}
+
+// The experts' down projection: of up to 8 units 4 (1024 columns) tiles each, narrow on the whole chip, not on 32 units
+static void expert_tiles() {
+    for (int nu = 1; nu <= 64; ++nu)
+        for (int cus : {32, 64, 128, 256}) {
+            CHECK(grouped_narrow(true, nu, 4, cus) == (8 * nu <= cus), "%d units on %d", nu, cus);
+            CHECK(!grouped_narrow(false, nu, 4, cus), "gate/up");
+        }
+}
+
 int main() {
     few_rows();
     hybrid_forms();
+    odd_heights();
+    expert_tiles();
     if (fails) { std::printf("%d checks failed\n", fails); return 1; }
     std::printf("dispatch ok\n");
     return 0;
