@@ -359,7 +359,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
         const bool more = !second || TA % 2 == 0;
         constexpr int TBH = TB / 2;   // SwiGLU: a k block's first half is gate rows, its second half the matching up rows
         // Its part of K tile 0: from there to the last block that there is (of a tile past the edge, or of an expert's last unit) is the
-        // buffer of its loads; what lies behind is not fetched, and the results it would give are never looked at.
+        // buffer of its loads; what lies behind is not fetched, and the results it gives are of no row that anybody reads.
         const int t0a = (bm >> 5) + second * LA, t0b = EPI == EPI_SWIGLU ? nb * TBH : nb * TB + second * TBH;
         const int bytes_a = max(min(Mt - t0a, blocks - second * LA), 0) * 1024, bytes_b = max(Nt - t0b, 0) * 1024;
         const char *ga = (const char *)(a.A + (size_t)kt0 * ksa + (size_t)(kb * Mt + t0a) * 512);
@@ -586,8 +586,11 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // back, where power sets the clock (gate/up of 224 rows or of 256 with a last round of halves: 70B 5482 rows 7887 and 7783 us a layer,
 // 8B 7050 rows 2898 and 2876, 6460 rows on 192 CUs 3072 and 3032).
 // A slice adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.
-// (All of these are timings of the loop with 32x32x16 products.  With the present one every form was forced in turn at ten row counts
-// of the 8B widths from 200 to 8000, on 256 and 128 CUs, and four of the 70B widths: the choice is still within 1 % of the fastest.)
+// (All of these are timings of the loop with 32x32x16 products; the present one takes 0.89 to 0.95 of the times of long products, so a slice's
+// cost, which stands beside them in microseconds, counts for that much less than it should.  With the present loop every form and every count of
+// slices was forced in turn, 12 row counts of the 8B widths from 200 to 8000 on 256 and 128 CUs and four of the 70B widths
+// (profiles/large_tile_forms_forced.md): the forms are within 1 % of the fastest layer; the slices, which may not follow the CUs, within 2 %
+// on the whole chip and 6 % on half of it.)
 // Against the rule before it (128-row tiles for slices, their count a power of two up to half the chip; no 192-row tiles), product and
 // epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
 // 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
@@ -744,7 +747,8 @@ static void launch_direct(hipStream_t st, const GemmArgs &a) {
 
 // Grouped GEMM: rows laid out expert by expert, every unit of the work list (moe_plan_kernel) a tile of 128 to 256
 // rows, in steps of 32, of one expert by 256 columns.  The arithmetic of an output element does not depend on the tile that holds it.
-// Blocks of 32 rows that are padding are neither fetched nor looked at (64 rows of 8 experts in tiles of 128 rows: gate/up 337 -> 333 us).
+// Blocks of 32 rows that are padding are not fetched (64 rows of 8 experts in tiles of 128 rows: gate/up 337 -> 333 us).  What they are multiplied
+// with is whatever their stage holds, and the sums are stored with the others, to rows that nobody reads.
 // An expert's rows are cut into units of one height (two from four units on), so that the units that share its weights run
 // through K at one pace and fetch them together.  A 256-row tile beside a shorter one that runs ahead of it had every weight leave the L2 in
 // between (8 experts of 275 rows of the 8B widths, 256 + 128 rows each against 192 + 192: gate/up 801 -> 649 us, down 395 -> 324 us).
@@ -1257,7 +1261,7 @@ void launch_gemm_skinny_partials(hipStream_t st, const GemmArgs &a, float *parti
 // 192: 130 rows 429 -> 400 us, 150 rows 464 -> 408, 192 rows 484 -> 451).
 // The product used to leave its float32 sums in a scratch matrix that one workgroup per row read back, chose from and
 // copied to the caller's logits: at 256 rows of a 128256-wide head 106 us of argmax behind 323 us of product (131 MB
-// written, read and written again, and 1002 tiles of 128x256 where 501 of 256x256 are two rounds); now 280 + 5 us.
+// written, read and written again, and 1002 tiles of 128x256 where 501 of 256x256 are two rounds); now 251 + 4 us.
 int head_candidates(int M, int N, int K) {
     if (M < 1 || N % 4) return 0;
     if (M <= 64 && head_streams(N, K)) return shared_splits(N, K, EPI_STORE) == 1 ? shared_virtual_n(N, EPI_STORE) / 64 : 0;
