@@ -295,9 +295,9 @@ void launch_fill_zero(hipStream_t st, void *dst, size_t bytes) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Matrix-core probe: what the chip sustains when nothing but MFMAs is issued.  Every wave keeps 8
-// independent 32x32x16 bf16 accumulator tiles in registers and issues MFMAs back to back, operands
-// never leave registers; 2 workgroups of 4 waves per compute unit.  2 * 32 * 32 * 16 flop per MFMA.
+// Matrix-core probe: what the chip sustains when nothing but MFMAs is issued.  Every wave keeps 16
+// independent 16x16x32 bf16 accumulator tiles (the form of the large-tile products) in registers and issues MFMAs back to back,
+// operands never leave registers; 2 workgroups of 4 waves per compute unit.  2 * 16 * 16 * 32 flop per MFMA.
 // The operands are pseudo-random values in +-[0.5, 1) with random mantissas, a different pair per
 // accumulator: the clock the chip holds under matrix load depends on how many bits toggle, and constant
 // or few-valued operands let it clock far higher than any real GEMM's data does.
@@ -321,26 +321,24 @@ __global__ __launch_bounds__(256, 2) void mfma_probe_kernel(float *sink, int ite
         a[j] = __builtin_bit_cast(bf16x8, wa);
         b[j] = __builtin_bit_cast(bf16x8, wb);
     }
-    f32x16 acc[8];
+    f32x4 acc[16];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+    for (int j = 0; j < 16; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], b[j], acc[j], 0, 0, 0);
+        for (int j = 0; j < 16; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j & 7], b[(j + (j >> 3)) & 7], acc[j], 0, 0, 0);
     }
     float t = 0.f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < 16; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) t += acc[j][e];
+        for (int e = 0; e < 4; ++e) t += acc[j][e];
     if (t == -1.0f) sink[0] = t;   // keeps the loop alive; sink is a valid float whether or not this ever fires
 }
 
 double launch_mfma_probe(hipStream_t st, float *sink, int n_workgroups, int iters) {
     hipLaunchKernelGGL(mfma_probe_kernel, dim3(n_workgroups), dim3(256), 0, st, sink, iters);
-    return (double)n_workgroups * 4 * (double)iters * 8 * 32768.0;
+    return (double)n_workgroups * 4 * (double)iters * 16 * 16384.0;
 }
 
 // An empty kernel: used once per new pair of masked streams to make the runtime set up whatever two
