@@ -87,7 +87,7 @@ __device__ __forceinline__ void sum_slices(const float *p, int off, size_t strid
 // output are the epilogue of this kernel and no partial products are written.
 // Llama-3-8B gate/up on 256 CUs: at 64 rows 51.6 + 5.7 us with the gain and the squares formed in this stream (about 50
 // vector instructions per staged kilobyte, more cycles than its matrix instructions) and SwiGLU in a kernel of its own,
-// 47 us now; at one row 37.4 + 4.8 -> 38.3 us (6.2 TB/s).  A second row tile that holds no row is not staged or
+// 47 us now; at one row 37.4 + 4.8 -> 36.8 us (6.4 TB/s).  A second row tile that holds no row is not staged or
 // multiplied (QKV at one row 13.0 -> 10.9 us).
 template <int ACT, int RT, bool PAIR, bool PSPLIT, int MT, bool SELF = false>
 __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void dstream_kernel(DGemmArgs a, int kb_per_wg, int Nv, DFuseArgs fz) {
@@ -815,7 +815,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void few_kernel(FewArgs a, QkvEpiAr
 }
 
 // Tiles of a workgroup: rounds of workgroups (one per CU) times what a workgroup moves, its tiles of weights and `act` of one for the rows.
-// The same sums whatever the number.  One row of the 8B widths, streams / one tile throughout / this, four layers: on 128 CUs 446 / 469 / 438 us,
+// The same sums whatever the number.  One row of the 8B widths, streams / one tile throughout / this in all three projections, four layers: on 128 CUs 446 / 469 / 438 us,
 // on 64 698 / 767 / 680 (four rows), on 192 437 / 459 / 428.
 static int few_rounds(int tiles, int R, int cus) { return (tiles / R + cus - 1) / cus; }
 static int few_tiles(int tiles, int cus, double act, int most) {
