@@ -491,6 +491,158 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
     else rows(std::true_type{});
 }
 
+// One output tile by eight waves, two per SIMD, each with XF x 4 accumulators of 16 x 16 (WGM waves along the rows, the others along the
+// columns): tiles of up to 320 x 256 or 640 x 128, where four waves end at 256 x 256.  Every element's sum is in gemm_direct_tile's order.
+// What it is for: a CU has some 32 KB of loads in flight however many it has asked for (57 to 61 GB/s from HBM, 131 from L2), and a product of
+// a few rounds of tiles is bound by that, not by its matrix instructions; a taller tile asks for its weights once where two lower ones ask for them twice.
+// The registers: 160 accumulators, the activations' fragments (40) once and the weights' (32) twice: a wave's products go through the activation
+// fragments one after the other, and the one that is done with is read again for the next K tile.  No more than 256 in all, all of them vector
+// registers (a function that uses accumulation registers gets half of each, which spills).
+// What bounds it: the LDS.  A K tile of 320 x 256 is 112 KB of fragment reads and 36 KB of DMA writes beside 1280 cycles of products, 1156 at 128 bytes
+// a cycle; the place of the barrier, the reads and the loads among the products changes nothing.
+// rows_end: rows from here on are not stored; blocks: 32-row blocks from here on are not fetched.
+#define RS_TALL_LDS 163840   // all of a compute unit's: at most NS stages of BM + BN rows of 64 bytes
+template <int XF, int WGM, int EPI, int NS, bool NT>
+__device__ __forceinline__ void gemm_tall_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem, const int blocks, const int rows_end) {
+    constexpr int BK = 32, WGN = 8 / WGM, BM = 16 * XF * WGM, BN = 64 * WGN;
+    static_assert(WGM == 2 || WGM == 4, "the wave's 16-row units lie WGM apart, which puts them at one LDS stride");
+    static_assert(NS * (BM + BN) * 64 <= RS_TALL_LDS, "the ring");
+    constexpr int TA = BM / 32, TB = BN / 32, LA = (TA + 3) / 4, LB = TB / 4, LT = LA + LB, LEAST = TA / 4 + LB;
+    constexpr int STAGE = (BM + BN) * BK, SL = 4 * XF, NF = 4 + XF;
+    constexpr int BAR = SL / 4 < 4 ? 4 : SL / 4;                          // the slot that the barrier is in front of
+    constexpr int RSTEP = (SL - 1 - BAR) / (NF - 1) < 1 ? 1 : (SL - 1 - BAR) / (NF - 1), LSTEP = (SL - 2 - BAR) / LT < 1 ? 1 : (SL - 2 - BAR) / LT;
+
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wm = wave / WGN, wn = wave % WGN;
+    const int c16 = lane & 15, g16 = lane >> 4;
+    const int M = a.M, N = a.N, K = a.K;
+    const int Mt = packed_mt(M), Nt = ((N + 63) / 64) * 2;
+    const size_t ksa = (size_t)Mt * 1024, ksb = (size_t)Nt * 1024;
+    const int nk = K / BK;
+
+    f32x4 acc[4][XF];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < XF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    {
+        constexpr int TBH = TB / 2;
+        const int W = __builtin_amdgcn_readfirstlane(wave), kb = W >> 2, q = W & 3;
+        const int na = TA / 4 + (q < TA % 4 ? 1 : 0), sa = q * (TA / 4) + min(q, TA % 4);
+        const int t0a = (bm >> 5) + sa, t0b = EPI == EPI_SWIGLU ? nb * TBH + (q & 1) * LB : nb * TB + q * LB;
+        const int bytes_a = __builtin_amdgcn_readfirstlane(max(min(min(Mt - t0a, blocks - sa), na), 0) * 1024), bytes_b = __builtin_amdgcn_readfirstlane(max(min(Nt - t0b, LB), 0) * 1024);
+        const char *ga = (const char *)(a.A + (size_t)(kb * Mt + t0a) * 512);
+        const char *gb = (const char *)((EPI == EPI_SWIGLU && q >= 2 ? a.Wp2 : a.Wp) + (size_t)(kb * Nt + t0b) * 512);
+        int fetch_kt = 0;
+        auto advance = [&]() RS_INLINE {
+            const size_t in = fetch_kt + 1 < nk ? 1 : 0;
+            ga += in * ksa * 2;
+            gb += in * ksb * 2;
+            ++fetch_kt;
+        };
+        auto issue = [&](int so, auto jtag) RS_INLINE {
+            constexpr int j = decltype(jtag)::value;
+            if constexpr (j < LA) {
+                if (j >= TA / 4 && j >= na) return;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)ga, 0, bytes_a, 0x00020000),
+                                                         (__attribute__((address_space(3))) void *)(smem + so + (kb * TA + sa) * 512), 16, lane * 16, 0, j * 1024, 0);
+            } else {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)gb, 0, bytes_b, 0x00020000),
+                                                         (__attribute__((address_space(3))) void *)(smem + so + BM * BK + (kb * TB + q * LB) * 512), 16, lane * 16, 0,
+                                                         (j - LA) * 1024, NT ? 2 : 0);
+            }
+        };
+        bf16x8 wf[2][4], xf[XF];
+        const int la = (g16 >> 1) * TA * 512 + ((g16 & 1) * 32 + c16) * 8 + (WGM == 2 ? wm * 128 : (wm >> 1) * 512 + (wm & 1) * 128);
+        const int lb = BM * BK + ((g16 >> 1) * TB + (EPI == EPI_SWIGLU ? wn : 2 * wn)) * 512 + ((g16 & 1) * 32 + c16) * 8;
+        auto read_frag = [&](auto stag, int so, auto ftag) RS_INLINE {
+            constexpr int set = decltype(stag)::value, f = decltype(ftag)::value;
+            if constexpr (f >= 4) xf[f - 4] = *(const bf16x8 *)&smem[so + la + (f - 4) * (WGM == 2 ? 512 : 1024)];
+            else wf[set][f] = *(const bf16x8 *)&smem[so + lb + (f >> 1) * (EPI == EPI_SWIGLU ? TBH : 1) * 512 + (f & 1) * 128];
+        };
+        static_for<NS>([&](auto i) RS_INLINE {
+            static_for<LT>([&](auto j) RS_INLINE { issue(decltype(i)::value * STAGE, j); });
+            advance();
+        });
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 1) * LEAST) : "memory");
+        static_for<NF>([&](auto f) RS_INLINE { read_frag(std::integral_constant<int, 0>{}, 0, f); });
+
+        int so_cur = 0;
+        auto k_tile = [&](auto stag) RS_INLINE {
+            constexpr int SET = decltype(stag)::value;
+            const int so_nxt = so_cur == (NS - 1) * STAGE ? 0 : so_cur + STAGE;
+            static_for<SL>([&](auto sltag) RS_INLINE {
+                constexpr int sl = decltype(sltag)::value, t = sl >> 2, c = sl & 3;
+                if constexpr (sl == BAR) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * LEAST) : "memory");
+                acc[c][t] = mfma16(wf[SET][c], xf[t], acc[c][t]);
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<NF>([&](auto ftag) RS_INLINE {
+                    constexpr int f = decltype(ftag)::value, due = BAR + f * RSTEP > SL - 1 ? SL - 1 : BAR + f * RSTEP, last = 4 * (f - 4) + 3;
+                    if constexpr ((f >= 4 && last > due ? last : due) == sl) read_frag(std::integral_constant<int, 1 - SET>{}, so_nxt, ftag);
+                });
+                static_for<LT>([&](auto jtag) RS_INLINE {
+                    constexpr int j = decltype(jtag)::value, due = BAR + 1 + j * LSTEP > SL - 1 ? SL - 1 : BAR + 1 + j * LSTEP;
+                    if constexpr (due == sl) issue(so_cur, jtag);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            advance();
+            so_cur = so_nxt;
+        };
+#pragma clang loop unroll(disable)
+        for (int kt = 0; kt < nk >> 1; ++kt) {
+            k_tile(std::integral_constant<int, 0>{});
+            k_tile(std::integral_constant<int, 1>{});
+        }
+        if (nk & 1) k_tile(std::integral_constant<int, 0>{});
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    const int m_end = min(M, rows_end);
+    if constexpr (EPI == EPI_SWIGLU) {
+        const size_t S16 = (size_t)Mt * 512;
+        const int c0 = nb * (BN / 2) + wn * 32;
+        const size_t col_term = (size_t)(c0 >> 4) * S16 + (g16 >> 1) * 256 + (g16 & 1) * 4;
+#pragma unroll
+        for (int t = 0; t < XF; ++t) {
+            const int m = bm + (t * WGM + wm) * 16 + c16;
+            if (m >= m_end) continue;
+            bf16_t *dst = a.out + (size_t)(m >> 5) * 512 + (size_t)(m & 31) * 8 + col_term;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (c0 + 16 * q + 4 * g16 >= N) continue;
+                const f32x4 &gate = acc[q][t], &up = acc[2 + q][t];
+                bf16x4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = (bf16_t)(silu_f(gate[i]) * up[i]);
+                *(bf16x4 *)(dst + (size_t)q * S16) = v;
+            }
+        }
+    } else {
+        constexpr int LD = 68;
+        float *buf = (float *)smem + wave * (16 * LD);
+        const int n0 = nb * BN + wn * 64;
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < XF; ++t) {
+            const int m0 = bm + (t * WGM + wm) * 16;
+            if (m0 >= m_end) break;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) *(f32x4 *)&buf[c16 * LD + 16 * c + 4 * g16] = acc[c][t];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const int row = it * 8 + (lane >> 3), col = (lane & 7) * 8, m = m0 + row, n = n0 + col;
+                const f32x4 lo = *(const f32x4 *)&buf[row * LD + col], hi = *(const f32x4 *)&buf[row * LD + col + 4];
+                bf16x8 v;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = (bf16_t)(i < 4 ? lo[i & 3] : hi[i & 3]);
+                if (m < m_end && n < N) st_bf16x8(a.out + (size_t)m * N + n, v);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+    }
+}
+
 // Order of the output tiles: super columns of four column tiles, inside one the row tiles four at a time, a
 // 4 x 4 block column by column.  Tiles that run at the same time on an XCD (16 on half the chip, 32 on the whole
 // chip) then share four weight slabs and four or eight activation slabs, whatever the number of row tiles: with
@@ -755,7 +907,7 @@ static void launch_direct(hipStream_t st, const GemmArgs &a) {
 template <int EPI, bool NT>
 __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_tiles, int cus) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
-    const int nu = __builtin_amdgcn_readfirstlane(a.units[0]);
+    const int nu = __builtin_amdgcn_readfirstlane(a.units[0]) & 0xffff;
     if (nu <= 0) return;
     const bool narrow = grouped_narrow(EPI == EPI_STORE, nu, n_tiles, cus);
     if (narrow) n_tiles = (a.N + 127) / 128;
@@ -788,13 +940,64 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_til
 #undef RS_T
 }
 
+// The same with tiles of up to 320 rows, by eight waves (grouped_cut says when): an XCD's tall units (more than 256 rows) first, then the others, so that
+// those that share weights still run side by side and the last tiles to start are the short ones (1300 rows of 8 experts, half of them cut in two: 1153 -> 1100 us);
+// a last round of few tiles is cut into halves of 128 columns (grouped_piece: 1100 rows 926 -> 894 us).
+template <int EPI, bool NT>
+__global__ __launch_bounds__(512) void gemm_grouped_tall_kernel(GemmArgs a, int n_tiles, int cus) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    const int nus = __builtin_amdgcn_readfirstlane(a.units[0]), nu = nus & 0xffff, nu_tall = nus >> 16;
+    if (nu <= 0) return;
+    const bool narrow = grouped_narrow(EPI == EPI_STORE, nu, n_tiles, cus);
+    if (narrow) n_tiles = (a.N + 127) / 128;
+    const int x = blockIdx.x & 7;
+    const GroupPiece p = grouped_piece(x, blockIdx.x >> 3, nu_tall, nu - nu_tall, n_tiles, cus);
+    GroupTile t = grouped_tile(x, p.i, p.tall ? nu_tall : nu - nu_tall, n_tiles);
+    if (t.u < 0) return;
+    if (!p.tall) t.u += nu_tall;
+    const int code = __builtin_amdgcn_readfirstlane(a.units[2 + t.u]);
+    const int row0 = (code >> 13) * 32, height = (code >> 5) & 15, blocks = (code >> 9) & 15;
+    GemmArgs g = a;
+    g.Wp += (size_t)(code & 31) * a.expert_stride;
+    if (EPI == EPI_SWIGLU) g.Wp2 += (size_t)(code & 31) * a.expert_stride;
+    const bool half = p.half >= 0 || narrow;
+    const int nb = p.half >= 0 ? 2 * t.nb + p.half : t.nb;
+    auto tile = [&](auto xf, auto wgm, auto ns) {
+        gemm_tall_tile<decltype(xf)::value, decltype(wgm)::value, EPI, decltype(ns)::value, NT>(g, row0, nb, smem, blocks, row0 + 32 * height);
+    };
+#define RS_T(xf, wgm, ns) tile(std::integral_constant<int, xf>{}, std::integral_constant<int, wgm>{}, std::integral_constant<int, ns>{})
+    if (half) {
+        if (height > 8) RS_T(5, 4, 5);
+        else if (height > 6) RS_T(4, 4, 6);
+        else if (height > 4) RS_T(3, 4, 8);
+        else RS_T(2, 4, 8);
+        return;
+    }
+    if (height == 10) RS_T(10, 2, 4);
+    else if (height == 9) RS_T(9, 2, 4);
+    else if (height == 8) RS_T(8, 2, 5);
+    else if (height == 7) RS_T(7, 2, 5);
+    else if (height == 6) RS_T(6, 2, 5);
+    else if (height == 5) RS_T(5, 2, 6);
+    else RS_T(4, 2, 6);
+#undef RS_T
+}
+
+template <int EPI, bool NT>
+static void launch_grouped_nt(hipStream_t st, const GemmArgs &a) {
+    const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + 127) / 128 : (a.N + 255) / 256;
+    const int cus = a.cus > 0 ? a.cus : 256, most = (a.M >> 7) * n_tiles;   // of as many units as there can be
+    if (a.tall) {   // and the second halves
+        const int grid = (std::max(most + cus / 2, cus) + 7) / 8 * 8 + 8;
+        hipLaunchKernelGGL((gemm_grouped_tall_kernel<EPI, NT>), dim3(grid), dim3(512), RS_TALL_LDS, st, a, n_tiles, cus);
+    } else {        // of narrow tiles no more than CUs
+        const int grid = (std::max(most, EPI == EPI_STORE ? cus : 0) + 7) / 8 * 8;
+        hipLaunchKernelGGL((gemm_grouped_kernel<EPI, NT>), dim3(grid), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles, cus);
+    }
+}
 template <int EPI>
 static void launch_grouped_epi(hipStream_t st, const GemmArgs &a) {
-    const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + 127) / 128 : (a.N + 255) / 256;
-    const int cus = a.cus > 0 ? a.cus : 256;
-    const int grid = (std::max((a.M >> 7) * n_tiles, EPI == EPI_STORE ? cus : 0) + 7) / 8 * 8;   // of as many units as there can be; of narrow tiles no more than CUs
-    if (a.stream_weights) hipLaunchKernelGGL((gemm_grouped_kernel<EPI, true>), dim3(grid), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles, cus);
-    else hipLaunchKernelGGL((gemm_grouped_kernel<EPI, false>), dim3(grid), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles, cus);
+    a.stream_weights ? launch_grouped_nt<EPI, true>(st, a) : launch_grouped_nt<EPI, false>(st, a);
 }
 
 bool launch_gemm_grouped(hipStream_t st, const GemmArgs &a) {
@@ -1324,6 +1527,10 @@ void gemm_kernels_init() {
     set((const void *)gemm_direct_splitk_kernel<192, 4>, 114688);
     set((const void *)gemm_direct_splitk_kernel<224, 4>, 122880);
     set((const void *)gemm_direct_splitk_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
+    set((const void *)gemm_grouped_tall_kernel<EPI_STORE, true>, RS_TALL_LDS);
+    set((const void *)gemm_grouped_tall_kernel<EPI_SWIGLU, true>, RS_TALL_LDS);
+    set((const void *)gemm_grouped_tall_kernel<EPI_STORE, false>, RS_TALL_LDS);
+    set((const void *)gemm_grouped_tall_kernel<EPI_SWIGLU, false>, RS_TALL_LDS);
     set((const void *)gemm_grouped_kernel<EPI_STORE, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_STORE, false>, RS_NS_FULL * 32768);

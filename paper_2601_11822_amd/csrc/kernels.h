@@ -93,6 +93,7 @@ struct GemmArgs {
     const int32_t *units = nullptr;
     size_t expert_stride = 0;
     bool stream_weights = false;   // grouped_streams_weights
+    bool tall = false;             // grouped_cut
 };
 // Upper bound of what the K-sliced path of launch_gemm_tiled needs, for any M: S * M * N <= this.
 #define RS_DIRECT_PARTIAL_ELEMS ((size_t)10 << 20)
@@ -257,6 +258,25 @@ __host__ __device__ inline GroupTile grouped_tile(int x, int i, int nu, int n_ti
     return {g * RS_GROUP_UNITS + v % units, c0 + v / units};
 }
 
+// The i-th workgroup of XCD x: first the XCD's tiles of the tall units, then those of the others; where its last round is of tiles for no more than
+// half of its compute units, those are cut in two (half 0, 1; -1: a whole tile).
+struct GroupPiece { int i, half; bool tall; };
+__host__ __device__ inline int grouped_share(int x, int total) {
+    const int per = (total + 7) >> 3, first = x * per;
+    return first >= total ? 0 : (first + per < total ? per : total - first);
+}
+__host__ __device__ inline GroupPiece grouped_piece(int x, int i, int nu_tall, int nu_low, int n_tiles, int cus) {
+    const int n0 = grouped_share(x, nu_tall * n_tiles), n = n0 + grouped_share(x, nu_low * n_tiles);
+    const int units = cus >> 3, rest = n % units, whole = 2 * rest <= units && n > rest ? n - rest : n;
+    int half = -1;
+    if (i >= whole) {
+        if (whole == n) return {n, -1, false};
+        half = (i - whole) & 1;
+        i = whole + ((i - whole) >> 1);
+    }
+    return i < n0 ? GroupPiece{i, half, true} : GroupPiece{i - n0, half, false};
+}
+
 // Whether the down projection's tiles are 128 columns wide instead of 256: where all of them then run at once, on twice as many CUs.
 // What bounds them is what a CU loads, 57 GB/s however deep the ring (from HBM and L2 alike: the times of the two add up); 8
 // experts of one unit each leave half of 256 CUs idle with 256 columns.  Down of the 8B widths through 8 experts on 256 CUs,
@@ -271,6 +291,20 @@ static __host__ __device__ inline bool grouped_narrow(bool store, int nu, int n_
 // 1178 / 1180; through 8 of 900, 1100, 1500, 2048 rows 971 / 952, 1018 / 1011, 1224 / 1212, 1707 / 1710, of 3000 2322 / 2359; through 16
 // of 600, 1500, 2500, 3000 rows 1191 / 1121, 1461 / 1424, 2124 / 2104, 2474 / 2457.
 static inline bool grouped_streams_weights(int rows, int E) { return rows <= 256 * E; }
+// How the experts' rows are cut into units: `limit` rows at most, and whether by the kernel of eight waves, which alone takes more than 256.
+// An expert has `rows` rows in E to two of them; its share and a deviation above it is what the fullest are taken to have.  On more than 128 CUs taller tiles are worth it
+// where fewer of them hold that; where their number stays the same the four-wave tiles are 2 % faster (LDS traffic), and four of 224 rows 1 % than three of 288.
+// On 128 and fewer, where the loads of a CU count for more, eight waves are the faster from 256 rows on.  Prefill of the 8B widths through 8 experts, four waves / this, on 256 CUs:
+// 950 rows 818 / 812 us (not taken), 1000 918 / 841, 1100 1022 / 898, 1200 990 / 973, 1250 1016 / 1038 (not taken), 1500 1121 / 1122 (not), 1900 1290 / 1309 (not), 2048 1550 / 1393, 2400 1812 / 1641,
+// 3300 2255 / 2295 (not), 4000 2775 / 2590; on 128 CUs: 1000 1356 / 1082, 1100 1515 / 1127, 1300 1546 / 1537, 2048 2311 / 1951, 3300 3378 / 3119.
+struct GroupCut { int limit; bool tall; };
+static inline GroupCut grouped_cut(int rows, int E, int cus) {
+    const double mean = 2.0 * rows / E, most = mean + __builtin_sqrt(mean);
+    const int of320 = (int)__builtin_ceil(most / 320), of256 = (int)__builtin_ceil(most / 256);
+    const bool fewer = of320 < of256;
+    if (cus > 0 && cus <= 128) return {fewer ? 320 : 256, of256 > 1};
+    return fewer && of320 != 3 ? GroupCut{320, true} : GroupCut{256, false};
+}
 // Rows of the grouped (expert-major) layout that M rows with two experts each can need: an expert's segment is less than
 // 256 rows longer than its rows.
 static inline int moe_row_cap(int M, int E) { return ((2 * M + 255 * E + 127) / 128) * 128; }
@@ -281,12 +315,13 @@ struct MoeArgs {
     float *wt;              // [M][2] their weights
     int32_t *pos;           // [M][2] grouped row of each assignment
     int32_t *src;           // [Mg_cap] source row of each grouped row, -1 for padding
-    int32_t *units;         // [2 + Mg_cap / 128]: units, rows in use, first row / 32 << 13 | 32-row blocks with rows << 9 | height / 32 << 5 | expert of each
+    int32_t *units;         // [2 + Mg_cap / 128]: units of more than 256 rows << 16 | units, rows in use, first row / 32 << 13 | 32-row blocks with rows << 9 | height / 32 << 5 | expert of each
     bf16_t *a_g;            // gathered rows, fragment-packed with Mg_cap / 32 row tiles
     const bf16_t *out_g;    // [Mg_cap][d] expert outputs, row-major
     const bf16_t *x1;       // [M][d]
     bf16_t *y;              // [M][d]
     int M, d, E, Mg_cap;
+    int limit;              // rows of a unit at most: 256 or 320 (grouped_cut)
 };
 void launch_moe_route_and_gather(hipStream_t st, const MoeArgs &a);
 void launch_moe_combine(hipStream_t st, const MoeArgs &a);

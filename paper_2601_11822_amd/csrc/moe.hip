@@ -66,7 +66,7 @@ __global__ __launch_bounds__(1024) void moe_router_kernel(MoeArgs a) {
 
 // ---------------------------------------------------------------------------------------------
 // Plan (one workgroup): per-expert counts, each expert's segment in whole tiles (of one height per expert: as few tiles of
-// at most 256 rows as hold it, each no higher than needed, in steps of 32 rows and at least 128; of four or more the last ones
+// at most a.limit rows as hold it, each no higher than needed, in steps of 32 rows and at least 128; of four or more the last ones
 // a step lower where that still holds it: four tiles hide that one of them runs ahead, which two do not; 4000 rows through 8 experts
 // of the 8B widths 3247 -> 3130 us, on 64 CUs 8057 -> 7888, in steps of 64; steps of 32 against 64, the whole layer: 600 rows 764 -> 758 us,
 // 1100 1160 -> 1130, 1500 1273 -> 1226, 2500 2086 -> 1957, 4000 2959 -> 2922), the grouped GEMM's work
@@ -83,19 +83,23 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoeArgs a) {
     for (int i = tid; i < a.Mg_cap; i += 1024) a.src[i] = -1;
     __syncthreads();
     if (tid == 0) {
-        int row = 0, nu = 0;
-        for (int e = 0; e < a.E; ++e) {
-            const int k = (cnt[e] + 255) >> 8, h32 = k ? max(4, (cnt[e] + 32 * k - 1) / (32 * k)) : 0;
-            const int lower = k >= 4 ? k * h32 - ((cnt[e] + 31) >> 5) : 0;   // this many of the last ones
-            off[e] = row;
-            for (int j = 0, left = cnt[e]; j < k; ++j) {
-                const int h = j < k - lower ? h32 : h32 - 1;
-                a.units[2 + nu++] = (row >> 5) << 13 | min((left + 31) >> 5, h) << 9 | h << 5 | e;
-                row += 32 * h;
-                left -= 32 * h;
+        int row = 0, nu = 0, nu_tall = 0;
+        for (int tall = 1; tall >= 0; --tall) {   // experts whose units are of more than 256 rows first
+            for (int e = 0; e < a.E; ++e) {
+                const int k = (cnt[e] + a.limit - 1) / a.limit, h32 = k ? max(4, (cnt[e] + 32 * k - 1) / (32 * k)) : 0;
+                if ((h32 > 8) != tall) continue;
+                const int lower = k >= 4 ? k * h32 - ((cnt[e] + 31) >> 5) : 0;   // this many of the last ones
+                off[e] = row;
+                for (int j = 0, left = cnt[e]; j < k; ++j) {
+                    const int h = j < k - lower ? h32 : h32 - 1;
+                    a.units[2 + nu++] = (row >> 5) << 13 | min((left + 31) >> 5, h) << 9 | h << 5 | e;
+                    row += 32 * h;
+                    left -= 32 * h;
+                }
             }
+            if (tall) nu_tall = nu;
         }
-        a.units[0] = nu;
+        a.units[0] = nu_tall << 16 | nu;
         a.units[1] = row;
     }
     __syncthreads();

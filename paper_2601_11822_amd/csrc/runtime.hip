@@ -584,18 +584,21 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     if (ml.E > 0) {
         // sparse block: route, gather expert by expert, two grouped GEMMs over all tiles, weighted sum
         const int cap = std::min(w.m_cap, moe_row_cap(M, ml.E));
-        MoeArgs ma{w.h, ml.router, w.m_sel, w.m_wt, w.m_pos, w.m_src, w.m_units, w.m_a, w.m_out, w.x1, y, M, d, ml.E, cap};
+        const GroupCut cut = grouped_cut(M, ml.E, c->side[side].cus);
+        MoeArgs ma{w.h, ml.router, w.m_sel, w.m_wt, w.m_pos, w.m_src, w.m_units, w.m_a, w.m_out, w.x1, y, M, d, ml.E, cap, cut.limit};
         launch_moe_route_and_gather(st, ma);
         GemmArgs gu{w.m_a, nullptr, nullptr, ml.wg, ml.wu, nullptr, w.m_act, cap, f, d, EPI_SWIGLU, c->side[side].cus};
         gu.units = w.m_units;
         gu.expert_stride = ml.stride_gu;
         gu.stream_weights = grouped_streams_weights(M, ml.E);
+        gu.tall = cut.tall;
         bool ok = launch_gemm_grouped(st, gu);
         tick(c, side, 7);
         GemmArgs gd{w.m_act, nullptr, nullptr, ml.wd, nullptr, nullptr, w.m_out, cap, d, f, EPI_STORE, c->side[side].cus};
         gd.units = w.m_units;
         gd.expert_stride = ml.stride_d;
         gd.stream_weights = grouped_streams_weights(M, ml.E);
+        gd.tall = cut.tall;
         ok = launch_gemm_grouped(st, gd) && ok;
         launch_moe_combine(st, ma);
         tick(c, side, 8);

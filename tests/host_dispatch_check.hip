@@ -1,5 +1,6 @@
 // Host-side check of the rules by which passes take their kernels (no GPU call), at sizes where both sides were measured
 // and at those where tests compare the two.  Built against the library and run by tests/test_host_abi.py.
+#include <algorithm>
 #include <cstdio>
 #include <vector>
 
@@ -93,7 +94,37 @@ static void expert_tiles() {
         }
 }
 
+// Eight-wave expert tiles: every XCD's workgroups are each of its tiles once, the last round of no more than half its units in two halves each
+static void expert_pieces() {
+    for (int tall : {0, 1, 3, 8})
+        for (int low : {0, 1, 2, 5, 16})
+            for (int n_tiles : {4, 11, 16, 112})
+                for (int cus : {32, 96, 128, 256}) {
+                    std::vector<int> seen((tall + low) * n_tiles);
+                    int most = 0;
+                    for (int x = 0; x < 8; ++x)
+                        for (int i = 0; i < (tall + low) * n_tiles + cus; ++i) {
+                            const GroupPiece p = grouped_piece(x, i, tall, low, n_tiles, cus);
+                            const GroupTile t = grouped_tile(x, p.i, p.tall ? tall : low, n_tiles);
+                            if (t.u < 0) continue;
+                            seen[((p.tall ? 0 : tall) + t.u) * n_tiles + t.nb] += p.half < 0 ? 3 : 1 + p.half;
+                            most = std::max(most, i + 1);
+                        }
+                    for (int v : seen) CHECK(v == 3, "%d + %d units, %d tiles on %d: %d", tall, low, n_tiles, cus, v);
+                    CHECK(8 * most <= (std::max((tall + low) * n_tiles + cus / 2, cus) + 7) / 8 * 8 + 8, "%d + %d units, %d tiles on %d: %d workgroups", tall, low, n_tiles, cus, most);
+                }
+    // the kernel and the limit, where both were measured: 8 experts
+    struct { int rows, cus, limit; bool tall; } of8[] = {{64, 256, 256, false}, {950, 256, 256, false}, {1000, 256, 320, true}, {1100, 256, 320, true}, {1250, 256, 256, false},
+                                                         {1900, 256, 256, false}, {2048, 256, 320, true}, {3300, 256, 256, false}, {4000, 256, 320, true},
+                                                         {900, 128, 256, false}, {1000, 128, 320, true}, {1300, 128, 256, true}, {3300, 128, 320, true}};
+    for (auto &w : of8) {
+        const GroupCut c = grouped_cut(w.rows, 8, w.cus);
+        CHECK(c.limit == w.limit && c.tall == w.tall, "%d rows on %d: %d %d", w.rows, w.cus, c.limit, c.tall);
+    }
+}
+
 int main() {
+    expert_pieces();
     few_rows();
     hybrid_forms();
     odd_heights();

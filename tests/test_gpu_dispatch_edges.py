@@ -414,6 +414,13 @@ def test_expert_tiles_of_either_width(T, E):
         rig.close()
 
 
+# units of up to 320 rows by eight waves: experts of 257 to 320 rows in one, of 513 to 640 in two, fuller ones beside them in two lower ones, a last round
+# in halves; experts that have as many units either way (256 CUs: four waves, 32 and 64: eight).  The same bits on every partition, checked as above.
+@pytest.mark.parametrize("T,E", [(450, 3), (420, 3), (900, 3), (1000, 7), (470, 3), (500, 3)])
+def test_tall_expert_tiles(T, E):
+    test_expert_tiles_of_either_width(T, E)
+
+
 # tiles of an odd number of 32-row blocks, whose waves do not all bring as many loads of a K tile: what a wave waits for is counted by the
 # waves with fewer.  Every pass gives the same bits (with one load too few waited for, one in some ten of these passes did not)
 @pytest.mark.parametrize("T,split", [(576, (256, 256)), (300, (256, 256)), (1120, (128, 128)), (650, (96, 160))])
