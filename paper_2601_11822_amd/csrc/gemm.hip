@@ -306,8 +306,7 @@ __device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x4 (&acc)
 // HEAD: the epilogue is head_row above.  PARTIAL: the tile covers K tiles [kt0, kt0 + nk_part) only and stores its raw float32 sums to
 // part[z][m][n] (row stride N), for an epilogue pass that adds the slices in order.
 // NT: the weights are fetched as a stream (non-temporal: first out of the L2).  Right where few row tiles share a slab and all of
-// them run at once: K slices, the head, expert tiles (grouped_streams_weights).  Whole products gain 1 % at some sizes and lose 2 to 5 at others (1300 rows of
-// the 8B layer 634 -> 663 us): their later rounds read the slabs again.
+// them run at once: K slices, the head, expert tiles (grouped_streams_weights), whole products of few row tiles (direct_streams).
 // LDS stages of the 256x256 tile's ring (32 KB each): a K tile is requested three tiles ahead.  A fifth stage (the
 // whole 160 KB of a compute unit) measured the same, alone and beside a bandwidth-bound kernel on the other
 // partition: what that neighbour costs is not memory latency the ring could cover.
@@ -502,8 +501,9 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
 // a cycle; the place of the barrier, the reads and the loads among the products changes nothing.
 // rows_end: rows from here on are not stored; blocks: 32-row blocks from here on are not fetched.
 #define RS_TALL_LDS 163840   // all of a compute unit's: at most NS stages of BM + BN rows of 64 bytes
-template <int XF, int WGM, int EPI, int NS, bool NT>
-__device__ __forceinline__ void gemm_tall_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem, const int blocks, const int rows_end) {
+template <int XF, int WGM, int EPI, int NS, bool NT, bool PARTIAL = false>
+__device__ __forceinline__ void gemm_tall_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem, const int blocks, const int rows_end,
+                                               const int kt0 = 0, const int nk_part = 0, float *part = nullptr) {
     constexpr int BK = 32, WGN = 8 / WGM, BM = 16 * XF * WGM, BN = 64 * WGN;
     static_assert(WGM == 2 || WGM == 4, "the wave's 16-row units lie WGM apart, which puts them at one LDS stride");
     static_assert(NS * (BM + BN) * 64 <= RS_TALL_LDS, "the ring");
@@ -518,7 +518,7 @@ __device__ __forceinline__ void gemm_tall_tile(const GemmArgs &a, const int bm, 
     const int M = a.M, N = a.N, K = a.K;
     const int Mt = packed_mt(M), Nt = ((N + 63) / 64) * 2;
     const size_t ksa = (size_t)Mt * 1024, ksb = (size_t)Nt * 1024;
-    const int nk = K / BK;
+    const int nk = PARTIAL ? nk_part : K / BK;
 
     f32x4 acc[4][XF];
 #pragma unroll
@@ -531,8 +531,8 @@ __device__ __forceinline__ void gemm_tall_tile(const GemmArgs &a, const int bm, 
         const int na = TA / 4 + (q < TA % 4 ? 1 : 0), sa = q * (TA / 4) + min(q, TA % 4);
         const int t0a = (bm >> 5) + sa, t0b = EPI == EPI_SWIGLU ? nb * TBH + (q & 1) * LB : nb * TB + q * LB;
         const int bytes_a = __builtin_amdgcn_readfirstlane(max(min(min(Mt - t0a, blocks - sa), na), 0) * 1024), bytes_b = __builtin_amdgcn_readfirstlane(max(min(Nt - t0b, LB), 0) * 1024);
-        const char *ga = (const char *)(a.A + (size_t)(kb * Mt + t0a) * 512);
-        const char *gb = (const char *)((EPI == EPI_SWIGLU && q >= 2 ? a.Wp2 : a.Wp) + (size_t)(kb * Nt + t0b) * 512);
+        const char *ga = (const char *)(a.A + (size_t)kt0 * ksa + (size_t)(kb * Mt + t0a) * 512);
+        const char *gb = (const char *)((EPI == EPI_SWIGLU && q >= 2 ? a.Wp2 : a.Wp) + (size_t)kt0 * ksb + (size_t)(kb * Nt + t0b) * 512);
         int fetch_kt = 0;
         auto advance = [&]() RS_INLINE {
             const size_t in = fetch_kt + 1 < nk ? 1 : 0;
@@ -618,7 +618,8 @@ __device__ __forceinline__ void gemm_tall_tile(const GemmArgs &a, const int bm, 
             }
         }
     } else {
-        constexpr int LD = 68;
+        // rows of the wave's 64 columns, 16 at a time through LDS (store_rows)
+        constexpr int LD = 68, EPC = PARTIAL ? 4 : 8, CPR = 64 / EPC, IT = 16 * CPR / 64;
         float *buf = (float *)smem + wave * (16 * LD);
         const int n0 = nb * BN + wn * 64;
         __syncthreads();
@@ -626,19 +627,35 @@ __device__ __forceinline__ void gemm_tall_tile(const GemmArgs &a, const int bm, 
         for (int t = 0; t < XF; ++t) {
             const int m0 = bm + (t * WGM + wm) * 16;
             if (m0 >= m_end) break;
+            bf16x8 r[IT];
+            if (EPI == EPI_RESIDUAL && !PARTIAL) {
+#pragma unroll
+                for (int it = 0; it < IT; ++it) {
+                    const int q = it * 64 + lane;
+                    r[it] = ld_bf16x8(a.resid + (size_t)min(m0 + q / CPR, m_end - 1) * N + min(n0 + (q % CPR) * EPC, N - 8));
+                }
+            }
 #pragma unroll
             for (int c = 0; c < 4; ++c) *(f32x4 *)&buf[c16 * LD + 16 * c + 4 * g16] = acc[c][t];
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the strip is read by other lanes than wrote it
 #pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                const int row = it * 8 + (lane >> 3), col = (lane & 7) * 8, m = m0 + row, n = n0 + col;
-                const f32x4 lo = *(const f32x4 *)&buf[row * LD + col], hi = *(const f32x4 *)&buf[row * LD + col + 4];
-                bf16x8 v;
+            for (int it = 0; it < IT; ++it) {
+                const int q = it * 64 + lane, row = q / CPR, col = (q % CPR) * EPC, m = m0 + row, n = n0 + col;
+                const f32x4 lo = *(const f32x4 *)&buf[row * LD + col];
+                if constexpr (PARTIAL) {
+                    if (m < m_end && n < N) *(f32x4 *)(part + (size_t)m * N + n) = lo;
+                } else {
+                    const f32x4 hi = *(const f32x4 *)&buf[row * LD + col + 4];
+                    bf16x8 v;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = (bf16_t)(i < 4 ? lo[i & 3] : hi[i & 3]);
-                if (m < m_end && n < N) st_bf16x8(a.out + (size_t)m * N + n, v);
+                    for (int i = 0; i < 8; ++i) {
+                        const float x = i < 4 ? lo[i & 3] : hi[i & 3];
+                        v[i] = (bf16_t)(EPI == EPI_RESIDUAL ? x + (float)r[it][i] : x);
+                    }
+                    if (m < m_end && n < N) st_bf16x8(a.out + (size_t)m * N + n, v);
+                }
             }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next rows overwrite it
         }
     }
 }
@@ -663,7 +680,7 @@ __device__ __forceinline__ void tile_rc(int t, int m_tiles, int n_tiles, int &r,
 
 // The flat workgroup id is remapped so that the workgroups resident on one XCD (ids congruent
 // mod 8) own a contiguous run of tiles in that order, served by that XCD's L2.
-template <int BM, int BN, int EPI, int NS>
+template <int BM, int BN, int EPI, int NS, bool NT>
 __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmArgs a, int m_tiles, int n_tiles) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     const int total = m_tiles * n_tiles;
@@ -672,7 +689,20 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmArgs a, int m_tile
     if (t >= total) return;
     int r, c;
     tile_rc(t, m_tiles, n_tiles, r, c);
-    gemm_direct_tile<BM, BN, EPI, NS>(a, r * BM, c, smem);
+    gemm_direct_tile<BM, BN, EPI, NS, false, false, NT>(a, r * BM, c, smem);
+}
+
+// The same with tiles of eight waves.
+template <int XF, int EPI, int NS, bool NT>
+__global__ __launch_bounds__(512) void gemm_tall_kernel(GemmArgs a, int m_tiles, int n_tiles) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    const int total = m_tiles * n_tiles;
+    const int per_xcd = (total + 7) >> 3;
+    const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (t >= total) return;
+    int r, c;
+    tile_rc(t, m_tiles, n_tiles, r, c);
+    gemm_tall_tile<XF, 2, EPI, NS, NT>(a, r * 32 * XF, c, smem, XF, a.M);
 }
 
 // Whole rounds of large tiles, then a last half round: when the tiles do not divide by the number of compute units, the first
@@ -680,7 +710,7 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmArgs a, int m_tile
 // which are dispatched last: 256x256 into two of 128x256, 192x256 (TALL false) into two of 192x128.
 // The arithmetic of an output element does not depend on the tile
 // that holds it, so the schedule may follow the size of the partition.
-template <int EPI, bool TALL>
+template <int EPI, bool TALL, bool NT>
 __global__ __launch_bounds__(256) void gemm_direct_mixed_kernel(GemmArgs a, int m_tiles, int n_full, int n_half) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     constexpr int BM = TALL ? 256 : 192;
@@ -690,7 +720,7 @@ __global__ __launch_bounds__(256) void gemm_direct_mixed_kernel(GemmArgs a, int 
     if (id < n_full) {
         const int t = (id & 7) * (n_full >> 3) + (id >> 3);          // n_full is a multiple of 8
         tile_rc(t, m_tiles, n_tiles, r, c);
-        gemm_direct_tile<BM, 256, EPI, RS_NS_FULL>(a, r * BM, c, smem);
+        gemm_direct_tile<BM, 256, EPI, RS_NS_FULL, false, false, NT>(a, r * BM, c, smem);
     } else {
         const int j = id - n_full;
         const int u = (j & 7) * ((n_half + 7) >> 3) + (j >> 3);
@@ -699,10 +729,10 @@ __global__ __launch_bounds__(256) void gemm_direct_mixed_kernel(GemmArgs a, int 
         tile_rc(t, m_tiles, n_tiles, r, c);
         if (TALL) {
             const int bm = r * 256 + (u & 1) * 128;
-            if (bm < a.M) gemm_direct_tile<128, 256, EPI, 5>(a, bm, c, smem);
+            if (bm < a.M) gemm_direct_tile<128, 256, EPI, 5, false, false, NT>(a, bm, c, smem);
         } else {
             const int nb = 2 * c + (u & 1);
-            if (nb * (EPI == EPI_SWIGLU ? 64 : 128) < a.N) gemm_direct_tile<192, 128, EPI, 5>(a, r * 192, nb, smem);
+            if (nb * (EPI == EPI_SWIGLU ? 64 : 128) < a.N) gemm_direct_tile<192, 128, EPI, 5, false, false, NT>(a, r * 192, nb, smem);
         }
     }
 }
@@ -724,6 +754,18 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
     gemm_direct_tile<BM, 256, EPI_STORE, NS, true>(a, r * BM, c, smem, kt0, min(nk_per, a.K / 32 - kt0), part, z);
 }
 
+template <int XF, int NS>
+__global__ __launch_bounds__(512) void gemm_tall_splitk_kernel(GemmArgs a, int m_tiles, int n_tiles, int S, int nk_per, float *part) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    const int tiles = m_tiles * n_tiles, total = tiles * S, per_xcd = (total + 7) >> 3;
+    const int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (id >= total) return;
+    const int z = id / tiles, t = id % tiles, kt0 = z * nk_per;
+    int r, c;
+    tile_rc(t, m_tiles, n_tiles, r, c);
+    gemm_tall_tile<XF, 2, EPI_STORE, NS, true, true>(a, r * 32 * XF, c, smem, XF, a.M, kt0, min(nk_per, a.K / 32 - kt0), part + (size_t)z * a.M * a.N);
+}
+
 // ---------------------------------------------------------------------------------------------
 // The schedule of a large-tile product: tile shape and K slices by what they are expected to cost.
 // A round of w workgroups of one tile shape takes 4.8 + nk * (a + b * w / 256) us for nk K tiles: 4.8 are the first loads and the
@@ -734,6 +776,9 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // on average, 10 % at most.  With constants found on 256 CUs (0.415 + 0.055 and 0.495 + 0.12) it was 1.4 % and 21 %, nearly all on half of
 // the chip and less; layers at those and these: 8B 1150 rows on 128 CUs 773 -> 750 us, 576 rows 483 -> 466, 800 rows on 96 CUs 762 -> 715,
 // 70B 1153 rows on 128 CUs 2723 -> 2555, 620 rows on 96 1869 -> 1785.
+// 288 and 320 rows (eight waves) stand where layers with them and without them crossed: 8B widths on 256 CUs, without / with: 576 rows 293 / 273 us, 640 318 / 300,
+// 1152 487 / 471, 1280 521 / 505 (their gate/up; forced at 512 rows 250 / 250, at 700 353 / 380, at 1400 602 / 639, at 2048 742 / 816); on 128 CUs 288 rows 293 / 232, 576 458 / 369,
+// 1088 716 / 641, 1400 827 / 781 (slices too); 70B widths on 256 CUs 288 rows 540 / 490.  What they save is what a CU loads: 34 KB a K tile for 288 x 256 where two of 160 x 256 take 52.
 // Their b is 0.005 dearer than those timings gave: among forms that cost the same to 1 %, the larger tile is the faster one in passes back to
 // back, where power sets the clock (gate/up of 224 rows or of 256 with a last round of halves: 70B 5482 rows 7887 and 7783 us a layer,
 // 8B 7050 rows 2898 and 2876, 6460 rows on 192 CUs 3072 and 3032).
@@ -748,11 +793,11 @@ __global__ __launch_bounds__(256) void gemm_direct_splitk_kernel(GemmArgs a, int
 // 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
 // ---------------------------------------------------------------------------------------------
 static double direct_round_us(DirectForm f, int nk, long w) {
-    constexpr double A[] = {0.30, 0.365, 0.38, 0.44, 0.44, 0.36, 0.225}, B[] = {0.10, 0.105, 0.145, 0.175, 0.25, 0.165, 0.09};
+    constexpr double A[] = {0.30, 0.365, 0.38, 0.44, 0.44, 0.36, 0.225, 0, 0, 0.50, 0.56}, B[] = {0.10, 0.105, 0.145, 0.175, 0.25, 0.165, 0.09, 0, 0, 0.28, 0.31};
     return 4.8 + nk * (A[f] + B[f] * (double)w / 256.0);
 }
 static long direct_tiles(DirectForm f, int M, int nv) {
-    constexpr int BM[] = {128, 160, 192, 224, 256, 256, 192}, BN[] = {256, 256, 256, 256, 256, 192, 128};
+    constexpr int BM[] = {128, 160, 192, 224, 256, 256, 192, 0, 0, 288, 320}, BN[] = {256, 256, 256, 256, 256, 192, 128, 0, 0, 256, 256};
     return (long)((M + BM[f] - 1) / BM[f]) * ((nv + BN[f] - 1) / BN[f]);
 }
 static double direct_rounds_us(DirectForm f, int nk, long wgs, int cus) {
@@ -766,14 +811,14 @@ static double direct_mixed_us(DirectForm full, DirectForm half, int nk, long til
     return (double)(n_full / cus) * direct_round_us(full, nk, cus) + direct_round_us(half, nk, 2 * rest);
 }
 
-// The fastest form for S slices (1: the finished product) on `cus` compute units, and its cost.  odd: with the heights of an odd
-// number of row blocks.
-static double direct_best_form(int M, int N, int K, int epi, int S, int cus, DirectForm &form, bool odd = true) {
+// The fastest form for S slices (1: the finished product) on `cus` compute units, and its cost.  all: with the heights of an odd
+// number of row blocks and those of eight waves.
+static double direct_best_form(int M, int N, int K, int epi, int S, int cus, DirectForm &form, bool all = true) {
     const int nv = epi == EPI_SWIGLU ? (N + 127) / 128 * 256 : N, nk = (K / 32 + S - 1) / S;
     double best = 1e30;
     auto consider = [&](DirectForm f, double us) { if (us < best) { best = us; form = f; } };
-    for (DirectForm f : {FORM_256x256, FORM_224x256, FORM_192x256, FORM_160x256, FORM_128x256})
-        if (odd || (f != FORM_160x256 && f != FORM_224x256)) consider(f, direct_rounds_us(f, nk, S * direct_tiles(f, M, nv), cus));
+    for (DirectForm f : {FORM_320x256, FORM_288x256, FORM_256x256, FORM_224x256, FORM_192x256, FORM_160x256, FORM_128x256})
+        if (all || (f != FORM_160x256 && f != FORM_224x256 && f != FORM_288x256 && f != FORM_320x256)) consider(f, direct_rounds_us(f, nk, S * direct_tiles(f, M, nv), cus));
     if (S > 1) return best;
     int n_full;
     if (epi == EPI_SWIGLU) {
@@ -826,12 +871,15 @@ __global__ __launch_bounds__(256) void skinny_epilogue_kernel(GemmArgs a, const 
 template <int BM, int NS>
 static void launch_direct_splitk_tiles(hipStream_t st, const GemmArgs &a, int S) {
     const int m_tiles = (a.M + BM - 1) / BM, n_tiles = (a.N + 255) / 256, nk_per = (a.K / 32 + S - 1) / S;
-    hipLaunchKernelGGL((gemm_direct_splitk_kernel<BM, NS>), dim3((m_tiles * n_tiles * S + 7) / 8 * 8), dim3(256), NS * (BM + 256) * 64, st, a,
-                       m_tiles, n_tiles, S, nk_per, a.partials);
+    const dim3 grid((m_tiles * n_tiles * S + 7) / 8 * 8);
+    if constexpr (BM > 256) hipLaunchKernelGGL((gemm_tall_splitk_kernel<BM / 32, NS>), grid, dim3(512), NS * (BM + 256) * 64, st, a, m_tiles, n_tiles, S, nk_per, a.partials);
+    else hipLaunchKernelGGL((gemm_direct_splitk_kernel<BM, NS>), grid, dim3(256), NS * (BM + 256) * 64, st, a, m_tiles, n_tiles, S, nk_per, a.partials);
 }
 static void launch_direct_splitk_main(hipStream_t st, const GemmArgs &a, int S) {
     const DirectForm f = direct_form(a.M, a.N, a.K, EPI_STORE, S, a.cus > 0 ? a.cus : 256);
     if (f == FORM_256x256) launch_direct_splitk_tiles<256, RS_NS_FULL>(st, a, S);
+    else if (f == FORM_320x256) launch_direct_splitk_tiles<320, 4>(st, a, S);
+    else if (f == FORM_288x256) launch_direct_splitk_tiles<288, 4>(st, a, S);
     else if (f == FORM_224x256) launch_direct_splitk_tiles<224, 4>(st, a, S);
     else if (f == FORM_192x256) launch_direct_splitk_tiles<192, 4>(st, a, S);
     else if (f == FORM_160x256) launch_direct_splitk_tiles<160, 4>(st, a, S);
@@ -869,13 +917,20 @@ __global__ __launch_bounds__(256) void gemm_head_kernel(GemmArgs a, HeadOut o, i
     gemm_direct_tile<BM, 256, EPI_STORE, NS, false, true>(a, (t % m_tiles) * BM, t / m_tiles, smem, 0, 0, nullptr, 0, &o);
 }
 
+// Whether a whole product's weights are a stream (non-temporal).  tile_rc runs up to four row tiles of a column side by side: with no more than those nobody
+// reads the weights again.  Layers of the 8B widths on 256 CUs, not streamed / streamed: 160 rows 165.9 / 162.5 us, 512 249.6 / 247.4, 768 369.6 / 360.8,
+// 1024 429 / 418; of the 70B widths 160 rows 376 / 360; streamed throughout 1300 rows of the 8B widths 579 / 602, 4000 of the 70B widths 5140 / 5269.
+static bool direct_streams(int m_tiles) { return m_tiles <= 4; }
+
 template <int EPI, bool TALL>
 static void launch_direct_mixed(hipStream_t st, const GemmArgs &a, int cus) {
     constexpr int BM = TALL ? 256 : 192;
     const int m_tiles = (a.M + BM - 1) / BM, n_tiles = EPI == EPI_SWIGLU ? (a.N + 127) / 128 : (a.N + 255) / 256;
     const int n_full = m_tiles * n_tiles / cus * cus, n_half = 2 * (m_tiles * n_tiles - n_full);
-    hipLaunchKernelGGL((gemm_direct_mixed_kernel<EPI, TALL>), dim3(n_full + (n_half + 7) / 8 * 8), dim3(256), RS_NS_FULL * (BM + 256) * 64, st, a,
-                       m_tiles, n_full, n_half);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(n_full + (n_half + 7) / 8 * 8), dim3(256), RS_NS_FULL * (BM + 256) * 64, st, a, m_tiles, n_full, n_half);
+    };
+    direct_streams(m_tiles) ? go(gemm_direct_mixed_kernel<EPI, TALL, true>) : go(gemm_direct_mixed_kernel<EPI, TALL, false>);
 }
 
 template <int BM, int BN, int EPI, int NS>
@@ -885,7 +940,9 @@ static void launch_direct_epi(hipStream_t st, const GemmArgs &a) {
     const int total = m_tiles * n_tiles;
     const int grid = ((total + 7) / 8) * 8;
     constexpr int lds = NS * (BM + BN) * 32 * 2;
-    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, EPI, NS>), dim3(grid), dim3(256), lds, st, a, m_tiles, n_tiles);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(BM > 256 ? 512 : 256), lds, st, a, m_tiles, n_tiles); };
+    if constexpr (BM > 256) direct_streams(m_tiles) ? go(gemm_tall_kernel<BM / 32, EPI, NS, true>) : go(gemm_tall_kernel<BM / 32, EPI, NS, false>);
+    else direct_streams(m_tiles) ? go(gemm_direct_kernel<BM, BN, EPI, NS, true>) : go(gemm_direct_kernel<BM, BN, EPI, NS, false>);
 }
 
 template <int BM, int BN, int NS>
@@ -1038,6 +1095,8 @@ bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
         const int cus = a.cus > 0 ? a.cus : 256;
         switch (direct_form(a.M, a.N, a.K, a.epi, 1, cus)) {
             case FORM_256x256: launch_direct<256, 256, RS_NS_FULL>(st, a); break;   // RS_NS_FULL x 32 KB of LDS
+            case FORM_320x256: launch_direct<320, 256, 4>(st, a); break;            // 4 x 36 KB
+            case FORM_288x256: launch_direct<288, 256, 4>(st, a); break;            // 4 x 34 KB
             case FORM_224x256: launch_direct<224, 256, 4>(st, a); break;            // 4 x 30 KB
             case FORM_192x256: launch_direct<192, 256, 4>(st, a); break;            // 4 x 28 KB
             case FORM_160x256: launch_direct<160, 256, 4>(st, a); break;            // 4 x 26 KB
@@ -1511,6 +1570,7 @@ void launch_gemm_skinny(hipStream_t st, const GemmArgs &a, float *partials) {
 // creation: nothing but launches is then left for a call that may run under stream capture.
 void gemm_kernels_init() {
     auto set = [](const void *f, int lds) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+    auto set_nt = [&](const void *f, const void *nt, int lds) { set(f, lds), set(nt, lds); };
     constexpr int RT = RS_SKINNY_RT, PD = 10;
     set((const void *)gemm_skinny_kernel<EPI_STORE, RT, PD>, RT * 32768);
     set((const void *)gemm_skinny_kernel<EPI_RESIDUAL, RT, PD>, RT * 32768);
@@ -1524,6 +1584,14 @@ void gemm_kernels_init() {
     set((const void *)gemm_skinny_shared_kernel<EPI_RESIDUAL, RS_SHARED_CH>, 2 * RS_SHARED_CH * 2048);
     set((const void *)gemm_direct_splitk_kernel<128, 5>, 122880);
     set((const void *)gemm_direct_splitk_kernel<160, 4>, 106496);
+    set((const void *)gemm_tall_splitk_kernel<9, 4>, 139264);
+    set((const void *)gemm_tall_splitk_kernel<10, 4>, 147456);
+    set_nt((const void *)gemm_tall_kernel<9, EPI_STORE, 4, false>, (const void *)gemm_tall_kernel<9, EPI_STORE, 4, true>, 139264);
+    set_nt((const void *)gemm_tall_kernel<9, EPI_RESIDUAL, 4, false>, (const void *)gemm_tall_kernel<9, EPI_RESIDUAL, 4, true>, 139264);
+    set_nt((const void *)gemm_tall_kernel<9, EPI_SWIGLU, 4, false>, (const void *)gemm_tall_kernel<9, EPI_SWIGLU, 4, true>, 139264);
+    set_nt((const void *)gemm_tall_kernel<10, EPI_STORE, 4, false>, (const void *)gemm_tall_kernel<10, EPI_STORE, 4, true>, 147456);
+    set_nt((const void *)gemm_tall_kernel<10, EPI_RESIDUAL, 4, false>, (const void *)gemm_tall_kernel<10, EPI_RESIDUAL, 4, true>, 147456);
+    set_nt((const void *)gemm_tall_kernel<10, EPI_SWIGLU, 4, false>, (const void *)gemm_tall_kernel<10, EPI_SWIGLU, 4, true>, 147456);
     set((const void *)gemm_direct_splitk_kernel<192, 4>, 114688);
     set((const void *)gemm_direct_splitk_kernel<224, 4>, 122880);
     set((const void *)gemm_direct_splitk_kernel<256, RS_NS_FULL>, RS_NS_FULL * 32768);
@@ -1535,27 +1603,27 @@ void gemm_kernels_init() {
     set((const void *)gemm_grouped_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_STORE, false>, RS_NS_FULL * 32768);
     set((const void *)gemm_grouped_kernel<EPI_SWIGLU, false>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_mixed_kernel<EPI_STORE, true>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_mixed_kernel<EPI_RESIDUAL, true>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, true>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL>, RS_NS_FULL * 32768);
-    set((const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5>, 122880);
-    set((const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4>, 106496);
-    set((const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4>, 114688);
-    set((const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4>, 122880);
-    set((const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5>, 122880);
-    set((const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4>, 106496);
-    set((const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4>, 114688);
-    set((const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4>, 122880);
-    set((const void *)gemm_direct_kernel<128, 256, EPI_SWIGLU, 5>, 122880);
-    set((const void *)gemm_direct_kernel<160, 256, EPI_SWIGLU, 4>, 106496);
-    set((const void *)gemm_direct_kernel<192, 256, EPI_SWIGLU, 4>, 114688);
-    set((const void *)gemm_direct_kernel<224, 256, EPI_SWIGLU, 4>, 122880);
-    set((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, false>, RS_NS_FULL * 28672);
-    set((const void *)gemm_direct_kernel<192, 128, EPI_SWIGLU, 5>, 102400);
-    set((const void *)gemm_direct_kernel<256, 192, EPI_STORE, 4>, 114688);
-    set((const void *)gemm_direct_kernel<256, 192, EPI_RESIDUAL, 4>, 114688);
+    set_nt((const void *)gemm_direct_mixed_kernel<EPI_STORE, true, false>, (const void *)gemm_direct_mixed_kernel<EPI_STORE, true, true>, RS_NS_FULL * 32768);
+    set_nt((const void *)gemm_direct_mixed_kernel<EPI_RESIDUAL, true, false>, (const void *)gemm_direct_mixed_kernel<EPI_RESIDUAL, true, true>, RS_NS_FULL * 32768);
+    set_nt((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, true, false>, (const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, true, true>, RS_NS_FULL * 32768);
+    set_nt((const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL, false>, (const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL, true>, RS_NS_FULL * 32768);
+    set_nt((const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL, false>, (const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL, true>, RS_NS_FULL * 32768);
+    set_nt((const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL, false>, (const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL, true>, RS_NS_FULL * 32768);
+    set_nt((const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5, false>, (const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5, true>, 122880);
+    set_nt((const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4, false>, (const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4, true>, 106496);
+    set_nt((const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4, false>, (const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4, true>, 114688);
+    set_nt((const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4, false>, (const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4, true>, 122880);
+    set_nt((const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5, false>, (const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5, true>, 122880);
+    set_nt((const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4, false>, (const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4, true>, 106496);
+    set_nt((const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4, false>, (const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4, true>, 114688);
+    set_nt((const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4, false>, (const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4, true>, 122880);
+    set_nt((const void *)gemm_direct_kernel<128, 256, EPI_SWIGLU, 5, false>, (const void *)gemm_direct_kernel<128, 256, EPI_SWIGLU, 5, true>, 122880);
+    set_nt((const void *)gemm_direct_kernel<160, 256, EPI_SWIGLU, 4, false>, (const void *)gemm_direct_kernel<160, 256, EPI_SWIGLU, 4, true>, 106496);
+    set_nt((const void *)gemm_direct_kernel<192, 256, EPI_SWIGLU, 4, false>, (const void *)gemm_direct_kernel<192, 256, EPI_SWIGLU, 4, true>, 114688);
+    set_nt((const void *)gemm_direct_kernel<224, 256, EPI_SWIGLU, 4, false>, (const void *)gemm_direct_kernel<224, 256, EPI_SWIGLU, 4, true>, 122880);
+    set_nt((const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, false, false>, (const void *)gemm_direct_mixed_kernel<EPI_SWIGLU, false, true>, RS_NS_FULL * 28672);
+    set_nt((const void *)gemm_direct_kernel<192, 128, EPI_SWIGLU, 5, false>, (const void *)gemm_direct_kernel<192, 128, EPI_SWIGLU, 5, true>, 102400);
+    set_nt((const void *)gemm_direct_kernel<256, 192, EPI_STORE, 4, false>, (const void *)gemm_direct_kernel<256, 192, EPI_STORE, 4, true>, 114688);
+    set_nt((const void *)gemm_direct_kernel<256, 192, EPI_RESIDUAL, 4, false>, (const void *)gemm_direct_kernel<256, 192, EPI_RESIDUAL, 4, true>, 114688);
 }
 

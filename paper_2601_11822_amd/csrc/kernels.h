@@ -105,7 +105,7 @@ int launch_gemm_tiled_partials(hipStream_t st, const GemmArgs &a);
 
 // How launch_gemm_tiled cuts a large-tile product: K slices (1: none) and, for S of them, tile rows x columns (MIXED: whole rounds of the
 // tile of these rows, then a round of half tiles).
-enum DirectForm { FORM_128x256, FORM_160x256, FORM_192x256, FORM_224x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192 };
+enum DirectForm { FORM_128x256, FORM_160x256, FORM_192x256, FORM_224x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192, FORM_288x256, FORM_320x256 };
 int direct_splits(int M, int N, int K);
 DirectForm direct_form(int M, int N, int K, int epi, int S, int cus);
 

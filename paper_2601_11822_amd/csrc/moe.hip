@@ -82,26 +82,37 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoeArgs a) {
     for (int i = tid; i < 2 * a.M; i += 1024) atomicAdd(&cnt[a.sel[i]], 1);
     for (int i = tid; i < a.Mg_cap; i += 1024) a.src[i] = -1;
     __syncthreads();
+    __shared__ int units[RS_MOE_MAX_EXPERTS], h32[RS_MOE_MAX_EXPERTS], lower[RS_MOE_MAX_EXPERTS], first[RS_MOE_MAX_EXPERTS];
+    if (tid < a.E) {
+        const int c = cnt[tid], k = (c + a.limit - 1) / a.limit, h = k ? max(4, (c + 32 * k - 1) / (32 * k)) : 0;
+        units[tid] = k;
+        h32[tid] = h;
+        lower[tid] = k >= 4 ? k * h - ((c + 31) >> 5) : 0;   // this many of the last ones
+    }
+    __syncthreads();
     if (tid == 0) {
         int row = 0, nu = 0, nu_tall = 0;
         for (int tall = 1; tall >= 0; --tall) {   // experts whose units are of more than 256 rows first
             for (int e = 0; e < a.E; ++e) {
-                const int k = (cnt[e] + a.limit - 1) / a.limit, h32 = k ? max(4, (cnt[e] + 32 * k - 1) / (32 * k)) : 0;
-                if ((h32 > 8) != tall) continue;
-                const int lower = k >= 4 ? k * h32 - ((cnt[e] + 31) >> 5) : 0;   // this many of the last ones
+                if ((h32[e] > 8) != tall) continue;
                 off[e] = row;
-                for (int j = 0, left = cnt[e]; j < k; ++j) {
-                    const int h = j < k - lower ? h32 : h32 - 1;
-                    a.units[2 + nu++] = (row >> 5) << 13 | min((left + 31) >> 5, h) << 9 | h << 5 | e;
-                    row += 32 * h;
-                    left -= 32 * h;
-                }
+                first[e] = nu;
+                nu += units[e];
+                row += 32 * (units[e] * h32[e] - lower[e]);
             }
             if (tall) nu_tall = nu;
         }
         a.units[0] = nu_tall << 16 | nu;
         a.units[1] = row;
     }
+    __syncthreads();
+    if (tid < a.E)
+        for (int j = 0, left = cnt[tid], row = off[tid]; j < units[tid]; ++j) {
+            const int h = j < units[tid] - lower[tid] ? h32[tid] : h32[tid] - 1;
+            a.units[2 + first[tid] + j] = (row >> 5) << 13 | min((left + 31) >> 5, h) << 9 | h << 5 | tid;
+            row += 32 * h;
+            left -= 32 * h;
+        }
     __syncthreads();
     for (int i = tid; i < 2 * a.M; i += 1024) {
         const int e = a.sel[i];

@@ -668,3 +668,10 @@ def test_large_tile_products(shape, rows):
                 assert worst <= 1.0, name
     finally:
         rig.close()
+
+
+# tiles of 288 and 320 rows by eight waves, on some partition each: full and one row over a full one, as gate/up, in K slices, stored
+# and with the residual, weights streamed and not
+@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [288, 320, 640, 832, 1800]), (S.LLAMA70B, [290, 1100]), (S.ODD, [310, 640])])
+def test_tall_products(shape, rows):
+    test_large_tile_products(shape, rows)
