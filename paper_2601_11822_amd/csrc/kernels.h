@@ -379,5 +379,6 @@ void launch_fill_zero(hipStream_t st, void *dst, size_t bytes);
 
 // Called once per context creation (see gemm.hip).
 void gemm_kernels_init();
+void grouped_kernels_init();
 void attention_kernels_init();
 
