@@ -164,6 +164,22 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(GemmArgs a, int m_tile
     gemm_direct_tile<BM, BN, EPI, NS, false, false, NT>(a, r * BM, c, smem);
 }
 
+// Tiles of 128 x 256 with the residual, or stored as they are: the loads by four more waves (FED).  These products are long rounds of a CU's loads (2048x4096x14336: 192 us,
+// its loads alone 160, its products 131), and a wave that multiplies no longer stands at a load that the full queue does not take.  Layers of the 8B widths on 256 CUs: 1536 rows
+// 628 -> 612 us, 2048 748 -> 733; of the 70B widths 768 1154 -> 1124.  Not the short ones, whose first bytes come later so: gate/up and K slices of 160 rows +4 % of the layer, of 512 +1.5.
+#define RS_FED_LDS 147456   // 6 x 24 KB
+template <int EPI, bool NT>
+__global__ __launch_bounds__(512) void gemm_fed_kernel(GemmArgs a, int m_tiles, int n_tiles) {
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    const int total = m_tiles * n_tiles;
+    const int per_xcd = (total + 7) >> 3;
+    const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (t >= total) return;
+    int r, c;
+    tile_rc(t, m_tiles, n_tiles, r, c);
+    gemm_direct_tile<128, 256, EPI, 6, false, false, NT, true>(a, r * 128, c, smem);
+}
+
 // The same with tiles of eight waves.
 template <int XF, int EPI, int NS, bool NT>
 __global__ __launch_bounds__(512) void gemm_tall_kernel(GemmArgs a, int m_tiles, int n_tiles) {
@@ -412,8 +428,12 @@ static void launch_direct_epi(hipStream_t st, const GemmArgs &a) {
     const int total = m_tiles * n_tiles;
     const int grid = ((total + 7) / 8) * 8;
     constexpr int lds = NS * (BM + BN) * 32 * 2;
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(BM > 256 ? 512 : 256), lds, st, a, m_tiles, n_tiles); };
-    if constexpr (BM > 256) direct_streams(m_tiles) ? go(gemm_tall_kernel<BM / 32, EPI, NS, true>) : go(gemm_tall_kernel<BM / 32, EPI, NS, false>);
+    constexpr bool fed = BM == 128 && BN == 256 && EPI != EPI_SWIGLU;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(BM > 256 || fed ? 512 : 256), fed ? RS_FED_LDS : lds, st, a, m_tiles, n_tiles);
+    };
+    if constexpr (fed) direct_streams(m_tiles) ? go(gemm_fed_kernel<EPI, true>) : go(gemm_fed_kernel<EPI, false>);
+    else if constexpr (BM > 256) direct_streams(m_tiles) ? go(gemm_tall_kernel<BM / 32, EPI, NS, true>) : go(gemm_tall_kernel<BM / 32, EPI, NS, false>);
     else direct_streams(m_tiles) ? go(gemm_direct_kernel<BM, BN, EPI, NS, true>) : go(gemm_direct_kernel<BM, BN, EPI, NS, false>);
 }
 
@@ -461,7 +481,7 @@ bool launch_gemm_tiled(hipStream_t st, const GemmArgs &a) {
             case FORM_224x256: launch_direct<224, 256, 4>(st, a); break;            // 4 x 30 KB
             case FORM_192x256: launch_direct<192, 256, 4>(st, a); break;            // 4 x 28 KB
             case FORM_160x256: launch_direct<160, 256, 4>(st, a); break;            // 4 x 26 KB
-            case FORM_128x256: launch_direct<128, 256, 5>(st, a); break;            // 5 x 24 KB
+            case FORM_128x256: launch_direct<128, 256, 5>(st, a); break;            // 5 x 24 KB, fed 6
             case FORM_256x192:                                                         // 4 x 28 KB
                 if (a.epi == EPI_STORE) launch_direct_epi<256, 192, EPI_STORE, 4>(st, a);
                 else launch_direct_epi<256, 192, EPI_RESIDUAL, 4>(st, a);
@@ -963,11 +983,11 @@ void gemm_kernels_init() {
     set_nt((const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL, false>, (const void *)gemm_direct_kernel<256, 256, EPI_STORE, RS_NS_FULL, true>, RS_NS_FULL * 32768);
     set_nt((const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL, false>, (const void *)gemm_direct_kernel<256, 256, EPI_RESIDUAL, RS_NS_FULL, true>, RS_NS_FULL * 32768);
     set_nt((const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL, false>, (const void *)gemm_direct_kernel<256, 256, EPI_SWIGLU, RS_NS_FULL, true>, RS_NS_FULL * 32768);
-    set_nt((const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5, false>, (const void *)gemm_direct_kernel<128, 256, EPI_STORE, 5, true>, 122880);
+    set_nt((const void *)gemm_fed_kernel<EPI_STORE, false>, (const void *)gemm_fed_kernel<EPI_STORE, true>, RS_FED_LDS);
     set_nt((const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4, false>, (const void *)gemm_direct_kernel<160, 256, EPI_STORE, 4, true>, 106496);
     set_nt((const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4, false>, (const void *)gemm_direct_kernel<192, 256, EPI_STORE, 4, true>, 114688);
     set_nt((const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4, false>, (const void *)gemm_direct_kernel<224, 256, EPI_STORE, 4, true>, 122880);
-    set_nt((const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5, false>, (const void *)gemm_direct_kernel<128, 256, EPI_RESIDUAL, 5, true>, 122880);
+    set_nt((const void *)gemm_fed_kernel<EPI_RESIDUAL, false>, (const void *)gemm_fed_kernel<EPI_RESIDUAL, true>, RS_FED_LDS);
     set_nt((const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4, false>, (const void *)gemm_direct_kernel<160, 256, EPI_RESIDUAL, 4, true>, 106496);
     set_nt((const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4, false>, (const void *)gemm_direct_kernel<192, 256, EPI_RESIDUAL, 4, true>, 114688);
     set_nt((const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4, false>, (const void *)gemm_direct_kernel<224, 256, EPI_RESIDUAL, 4, true>, 122880);

@@ -164,8 +164,9 @@ __device__ __forceinline__ void store_rows(const GemmArgs &a, const f32x4 (&acc)
 // LDS stages of the 256x256 tile's ring (32 KB each): a K tile is requested three tiles ahead.  A fifth stage (the
 // whole 160 KB of a compute unit) measured the same, alone and beside a bandwidth-bound kernel on the other
 // partition: what that neighbour costs is not memory latency the ring could cover.
+// FED: eight waves, of which the last four only load.
 #define RS_NS_FULL 4
-template <int BM, int BN, int EPI, int NS, bool PARTIAL = false, bool HEAD = false, bool NT = PARTIAL || HEAD>
+template <int BM, int BN, int EPI, int NS, bool PARTIAL = false, bool HEAD = false, bool NT = PARTIAL || HEAD, bool FED = false>
 __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm, const int nb, bf16_t *smem,
                                                  const int kt0 = 0, const int nk_part = 0, float *part = nullptr, const int z = 0,
                                                  const HeadOut *ho = nullptr, const int blocks = BM / 32) {
@@ -181,9 +182,10 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
     // the slots of a K tile that the barrier is in front of (the fragment reads follow it), and that its first load is behind
     constexpr int BAR = 2 * TN * TM < 4 * TN * TM - 1 - 2 * (TN + TM) ? 2 * TN * TM : 4 * TN * TM - 1 - 2 * (TN + TM), LSLOT = 2;
     static_assert(!HEAD || WGN == 2, "two candidates per row and column tile");
+    static_assert(!FED || (EPI != EPI_SWIGLU && !HEAD), "the barrier of store_rows");
     static_assert(BAR > 0, "a K tile must have a slot per fragment read");
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = (tid >> 6) & 3, lane = tid & 63;
     const int wm = wave / WGN, wn = wave % WGN;
     const int c16 = lane & 15, g16 = lane >> 4;
     const int M = a.M, N = a.N, K = a.K;
@@ -253,12 +255,37 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
                 wf[set][t] = *(const bf16x8 *)&smem[so + lb + blk * 512 + (t & 1) * 128];
             }
         };
+        if constexpr (FED) {
+            // four more waves bring the operands, a whole ring ahead: the ones that multiply never wait to issue a load
+            if (__builtin_amdgcn_readfirstlane(tid >> 8)) {
+                static_for<NS>([&](auto i) RS_INLINE {
+                    static_for<LT>([&](auto j) RS_INLINE { issue(decltype(i)::value * STAGE, j); });
+                    advance();
+                });
+                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 1) * LEAST) : "memory");
+                int so = 0;
+#pragma clang loop unroll(disable)
+                for (int kt = 0; kt < nk; ++kt) {   // a barrier a K tile: the next one has landed, and this one's stage is free
+                    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 2) * LEAST) : "memory");
+                    static_for<LT>([&](auto j) RS_INLINE { issue(so, j); });
+                    advance();
+                    so = so == (NS - 1) * STAGE ? 0 : so + STAGE;
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();   // store_rows' own
+                return;
+            }
+        }
         // prologue: K tiles 0 .. D-1 into stages 0 .. D-1
-        static_for<D>([&](auto i) RS_INLINE {
-            static_for<LT>([&](auto j) RS_INLINE { issue(decltype(i)::value * STAGE, j); });
-            advance();
-        });
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((D - 1) * LEAST) : "memory");
+        if constexpr (FED) {
+            asm volatile("s_barrier" ::: "memory");
+        } else {
+            static_for<D>([&](auto i) RS_INLINE {
+                static_for<LT>([&](auto j) RS_INLINE { issue(decltype(i)::value * STAGE, j); });
+                advance();
+            });
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((D - 1) * LEAST) : "memory");
+        }
         static_for<NF>([&](auto f) RS_INLINE { read_frag(std::integral_constant<int, 0>{}, 0, f); });
 
         // One K tile = SL MFMA slots; its loads fill the stage before its own (tile kt + D), and it reads the fragments of the
@@ -270,7 +297,8 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
             const int so_nxt = so_cur == (NS - 1) * STAGE ? 0 : so_cur + STAGE;
             static_for<SL>([&](auto sltag) RS_INLINE {
                 constexpr int sl = decltype(sltag)::value, tn = sl / (2 * TM), tm = sl % (2 * TM);
-                if constexpr (sl == BAR)
+                if constexpr (FED && sl == BAR) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                if constexpr (!FED && sl == BAR)
                     // tile kt+1 has landed once only the younger loads are outstanding; this wave's
                     // LDS reads are complete before it tells the others so at the barrier
                     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((D - 2) * LEAST + EARLY) : "memory");
@@ -280,10 +308,10 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
                 constexpr int f = ((sl - BAR) * NF + SL - BAR - 2) / (SL - BAR - 1);
                 if constexpr (sl >= BAR && f < NF && BAR + f * (SL - BAR - 1) / NF == sl)
                     read_frag(std::integral_constant<int, 1 - SET>{}, so_nxt, std::integral_constant<int, f>{});
-                if constexpr (sl >= LSLOT && (sl - LSLOT) % SP == 0 && (sl - LSLOT) / SP < LT) issue(so_ld, std::integral_constant<int, (sl - LSLOT) / SP>{});
+                if constexpr (!FED && sl >= LSLOT && (sl - LSLOT) % SP == 0 && (sl - LSLOT) / SP < LT) issue(so_ld, std::integral_constant<int, (sl - LSLOT) / SP>{});
                 __builtin_amdgcn_sched_barrier(0);
             });
-            advance();
+            if constexpr (!FED) advance();
             so_cur = so_nxt;
         };
 #pragma clang loop unroll(disable)
