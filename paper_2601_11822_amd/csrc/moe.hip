@@ -123,13 +123,12 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoeArgs a) {
 }
 
 // Gathered, fragment-packed GEMM input: grouped row g takes the chunks of its source row (zeros for padding).
-__global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a) {
-    const int chunks = a.d >> 3;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)a.Mg_cap * chunks) return;
+// A workgroup has 256 rows of one 16-byte column; all workgroups of a column run on one XCD, since the lines that they read, eight rows' chunks each, are the same ones
+// in another order (dealt out in turn every XCD fetched all of the rows: 1100 rows of 4096 and 8 experts 12.3 -> 9.0 us, 4000 24.6 -> 20.6; 64 rows 5.5 -> 6.0).
+__global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a, int row_groups) {
+    const int i = blockIdx.x >> 3, c = (i / row_groups) * 8 + (blockIdx.x & 7), g = (i % row_groups) * 256 + threadIdx.x;
     // consecutive threads take consecutive rows of one k chunk: whole 128-byte lines on the writing side
-    const int g = (int)(idx % a.Mg_cap), c = (int)(idx / a.Mg_cap);
-    if (g >= a.units[1]) return;   // past the last tile in use
+    if (c >= a.d >> 3 || g >= a.units[1]) return;   // past the last tile in use
     const int s = a.src[g];
     const bf16x8 v = s >= 0 ? ld_bf16x8(a.h + packed_offset(s, c * 8, packed_mt(a.M))) : zero_bf16x8();
     st_bf16x8(a.a_g + packed_offset(g, c * 8, a.Mg_cap >> 5), v);
@@ -155,8 +154,8 @@ void launch_moe_route_and_gather(hipStream_t st, const MoeArgs &a) {
     if (a.M <= 0) return;
     hipLaunchKernelGGL(moe_router_kernel, dim3((a.M + 31) / 32), dim3(1024), 0, st, a);
     hipLaunchKernelGGL(moe_plan_kernel, dim3(1), dim3(1024), 0, st, a);
-    const long n = (long)a.Mg_cap * (a.d >> 3);
-    hipLaunchKernelGGL(moe_gather_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
+    const int row_groups = (a.Mg_cap + 255) / 256, columns = (a.d / 8 + 7) / 8 * 8;
+    hipLaunchKernelGGL(moe_gather_kernel, dim3(row_groups * columns), dim3(256), 0, st, a, row_groups);
 }
 
 void launch_moe_combine(hipStream_t st, const MoeArgs &a) {
