@@ -50,29 +50,22 @@ __global__ __launch_bounds__(256) void gemm_grouped_kernel(GemmArgs a, int n_til
 // those that share weights still run side by side and the last tiles to start are the short ones (1300 rows of 8 experts, half of them cut in two: 1153 -> 1100 us);
 // a last round of few tiles is cut into halves of 128 columns (grouped_piece: 1100 rows 926 -> 894 us).
 template <int EPI, bool NT>
-__global__ __launch_bounds__(512) void gemm_grouped_tall_kernel(GemmArgs a, int n_tiles, int cus) {
+__global__ __launch_bounds__(512) void gemm_grouped_tall_kernel(GemmArgs a, int cus) {
     extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
     const int nus = __builtin_amdgcn_readfirstlane(a.units[0]), nu = nus & 0xffff, nu_tall = nus >> 16;
     if (nu <= 0) return;
-    const bool narrow = grouped_narrow(EPI == EPI_STORE, nu, n_tiles, cus);
-    if (narrow) n_tiles = (a.N + 127) / 128;
-    const int x = blockIdx.x & 7;
-    const GroupPiece p = grouped_piece(x, blockIdx.x >> 3, nu_tall, nu - nu_tall, n_tiles, cus);
-    GroupTile t = grouped_tile(x, p.i, p.tall ? nu_tall : nu - nu_tall, n_tiles);
+    const GroupTallTile t = grouped_tall_tile(blockIdx.x & 7, blockIdx.x >> 3, nu_tall, nu, a.N, EPI == EPI_STORE, cus);
     if (t.u < 0) return;
-    if (!p.tall) t.u += nu_tall;
     const int code = __builtin_amdgcn_readfirstlane(a.units[2 + t.u]);
     const int row0 = (code >> 13) * 32, height = (code >> 5) & 15, blocks = (code >> 9) & 15;
     GemmArgs g = a;
     g.Wp += (size_t)(code & 31) * a.expert_stride;
     if (EPI == EPI_SWIGLU) g.Wp2 += (size_t)(code & 31) * a.expert_stride;
-    const bool half = p.half >= 0 || narrow;
-    const int nb = p.half >= 0 ? 2 * t.nb + p.half : t.nb;
     auto tile = [&](auto xf, auto wgm, auto ns) {
-        gemm_tall_tile<decltype(xf)::value, decltype(wgm)::value, EPI, decltype(ns)::value, NT>(g, row0, nb, smem, blocks, row0 + 32 * height);
+        gemm_tall_tile<decltype(xf)::value, decltype(wgm)::value, EPI, decltype(ns)::value, NT>(g, row0, t.nb, smem, blocks, row0 + 32 * height);
     };
 #define RS_T(xf, wgm, ns) tile(std::integral_constant<int, xf>{}, std::integral_constant<int, wgm>{}, std::integral_constant<int, ns>{})
-    if (half) {
+    if (t.half) {
         if (height > 8) RS_T(5, 4, 5);
         else if (height > 6) RS_T(4, 4, 6);
         else if (height > 4) RS_T(3, 4, 8);
@@ -92,12 +85,11 @@ __global__ __launch_bounds__(512) void gemm_grouped_tall_kernel(GemmArgs a, int 
 template <int EPI, bool NT>
 static void launch_grouped_nt(hipStream_t st, const GemmArgs &a) {
     const int n_tiles = (EPI == EPI_SWIGLU) ? (a.N + 127) / 128 : (a.N + 255) / 256;
-    const int cus = a.cus > 0 ? a.cus : 256, most = (a.M >> 7) * n_tiles;   // of as many units as there can be
-    if (a.tall) {   // and the second halves
-        const int grid = (std::max(most + cus / 2, cus) + 7) / 8 * 8 + 8;
-        hipLaunchKernelGGL((gemm_grouped_tall_kernel<EPI, NT>), dim3(grid), dim3(512), RS_TALL_LDS, st, a, n_tiles, cus);
-    } else {        // of narrow tiles no more than CUs
-        const int grid = (std::max(most, EPI == EPI_STORE ? cus : 0) + 7) / 8 * 8;
+    const int cus = a.cus > 0 ? a.cus : 256, units = a.M >> 7;   // as many as there can be
+    if (a.tall) {
+        hipLaunchKernelGGL((gemm_grouped_tall_kernel<EPI, NT>), dim3(grouped_tall_grid(units, n_tiles, cus)), dim3(512), RS_TALL_LDS, st, a, cus);
+    } else {   // of narrow tiles no more than CUs
+        const int grid = (std::max(units * n_tiles, EPI == EPI_STORE ? cus : 0) + 7) / 8 * 8;
         hipLaunchKernelGGL((gemm_grouped_kernel<EPI, NT>), dim3(grid), dim3(256), RS_NS_FULL * 32768, st, a, n_tiles, cus);
     }
 }

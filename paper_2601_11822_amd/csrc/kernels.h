@@ -258,6 +258,12 @@ __host__ __device__ inline GroupTile grouped_tile(int x, int i, int nu, int n_ti
     return {g * RS_GROUP_UNITS + v % units, c0 + v / units};
 }
 
+// Whether the down projection's tiles are 128 columns wide instead of 256: where all of them then run at once, on twice as many CUs.
+// What bounds them is what a CU loads, 57 GB/s however deep the ring (from HBM and L2 alike: the times of the two add up); 8
+// experts of one unit each leave half of 256 CUs idle with 256 columns.  Down of the 8B widths through 8 experts on 256 CUs,
+// 256 / 128 columns: 64 rows 223 / 154 us, 256 rows 222 / 171, 600 rows 252 / 201, 900 rows 343 / 237.
+static __host__ __device__ inline bool grouped_narrow(bool store, int nu, int n_tiles, int cus) { return store && 2 * nu * n_tiles <= cus; }
+
 // The i-th workgroup of XCD x: first the XCD's tiles of the tall units, then those of the others; where its last round is of tiles for no more than
 // half of its compute units, those are cut in two (half 0, 1; -1: a whole tile).
 struct GroupPiece { int i, half; bool tall; };
@@ -276,12 +282,27 @@ __host__ __device__ inline GroupPiece grouped_piece(int x, int i, int nu_tall, i
     }
     return i < n0 ? GroupPiece{i, half, true} : GroupPiece{i - n0, half, false};
 }
-
-// Whether the down projection's tiles are 128 columns wide instead of 256: where all of them then run at once, on twice as many CUs.
-// What bounds them is what a CU loads, 57 GB/s however deep the ring (from HBM and L2 alike: the times of the two add up); 8
-// experts of one unit each leave half of 256 CUs idle with 256 columns.  Down of the 8B widths through 8 experts on 256 CUs,
-// 256 / 128 columns: 64 rows 223 / 154 us, 256 rows 222 / 171, 600 rows 252 / 201, 900 rows 343 / 237.
-static __host__ __device__ inline bool grouped_narrow(bool store, int nu, int n_tiles, int cus) { return store && 2 * nu * n_tiles <= cus; }
+// What the i-th workgroup of XCD x computes in the eight-wave kernel: column tile nb of unit u (-1: nothing), nb counted in whole tiles (256
+// columns of the down projection, 128 of gate and up) or, if half, in tiles of half as many.
+struct GroupTallTile { int u, nb; bool half; };
+__host__ __device__ inline GroupTallTile grouped_tall_tile(int x, int i, int nu_tall, int nu, int N, bool store, int cus) {
+    const int n_tiles = store ? (N + 255) / 256 : (N + 127) / 128;
+    if (grouped_narrow(store, nu, n_tiles, cus)) {
+        // all run at once, so the tall units need not come first, and there is no last round to cut: dealt apart, their share of an
+        // XCD and the others', each rounded up, can be one tile more than it has compute units
+        const GroupTile t = grouped_tile(x, i, nu, (N + 127) / 128);
+        return {t.u, t.nb, true};
+    }
+    const GroupPiece p = grouped_piece(x, i, nu_tall, nu - nu_tall, n_tiles, cus);
+    const GroupTile t = grouped_tile(x, p.i, p.tall ? nu_tall : nu - nu_tall, n_tiles);
+    if (t.u < 0) return {-1, 0, false};
+    return {p.tall ? t.u : t.u + nu_tall, p.half >= 0 ? 2 * t.nb + p.half : t.nb, p.half >= 0};
+}
+// Its workgroups, where there can be `units` units: their tiles and the second halves of a last round; narrow tiles are no more than CUs.
+static inline int grouped_tall_grid(int units, int n_tiles, int cus) {
+    const int most = units * n_tiles + cus / 2;
+    return ((most > cus ? most : cus) + 7) / 8 * 8 + 8;
+}
 
 #define RS_MOE_MAX_EXPERTS 16
 // Whether the grouped GEMM fetches the weights as a stream (non-temporal): `rows` rows go to two of E experts each, and where an expert

@@ -94,25 +94,29 @@ static void expert_tiles() {
         }
 }
 
-// Eight-wave expert tiles: every XCD's workgroups are each of its tiles once, the last round of no more than half its units in two halves each
+// Eight-wave expert tiles: the launched workgroups have each column of each unit once, whatever the units, the width and the partition.
+// `cells` are as many columns as half a tile has.
 static void expert_pieces() {
-    for (int tall : {0, 1, 3, 8})
-        for (int low : {0, 1, 2, 5, 16})
-            for (int n_tiles : {4, 11, 16, 112})
-                for (int cus : {32, 96, 128, 256}) {
-                    std::vector<int> seen((tall + low) * n_tiles);
-                    int most = 0;
-                    for (int x = 0; x < 8; ++x)
-                        for (int i = 0; i < (tall + low) * n_tiles + cus; ++i) {
-                            const GroupPiece p = grouped_piece(x, i, tall, low, n_tiles, cus);
-                            const GroupTile t = grouped_tile(x, p.i, p.tall ? tall : low, n_tiles);
+    std::vector<unsigned char> seen;
+    for (bool store : {true, false})
+        for (int N = 1024; N <= 8192; N += store ? 128 : 640)
+            for (int cus = 32; cus <= 256; cus += 32)
+                for (int nu = 1; nu <= 24; ++nu)
+                    for (int tall = 0; tall <= nu; ++tall) {
+                        const int n_tiles = store ? (N + 255) / 256 : (N + 127) / 128, cells = store ? (N + 127) / 128 : (N + 63) / 64;
+                        const int grid = grouped_tall_grid(nu, n_tiles, cus);   // no unit is lower than 128 rows
+                        seen.assign((size_t)nu * cells, 0);
+                        bool inside = true;
+                        for (int id = 0; id < grid; ++id) {
+                            const GroupTallTile t = grouped_tall_tile(id & 7, id >> 3, tall, nu, N, store, cus);
                             if (t.u < 0) continue;
-                            seen[((p.tall ? 0 : tall) + t.u) * n_tiles + t.nb] += p.half < 0 ? 3 : 1 + p.half;
-                            most = std::max(most, i + 1);
+                            inside = inside && t.u < nu && t.nb >= 0 && t.nb < (t.half ? 2 : 1) * n_tiles;
+                            for (int c = t.half ? t.nb : 2 * t.nb; inside && c < (t.half ? t.nb + 1 : 2 * t.nb + 2); ++c)
+                                if (c < cells) ++seen[(size_t)t.u * cells + c];
                         }
-                    for (int v : seen) CHECK(v == 3, "%d + %d units, %d tiles on %d: %d", tall, low, n_tiles, cus, v);
-                    CHECK(8 * most <= (std::max((tall + low) * n_tiles + cus / 2, cus) + 7) / 8 * 8 + 8, "%d + %d units, %d tiles on %d: %d workgroups", tall, low, n_tiles, cus, most);
-                }
+                        const bool once = std::all_of(seen.begin(), seen.end(), [](unsigned char v) { return v == 1; });
+                        CHECK(inside && once, "%s: %d tall of %d units, %d columns on %d", store ? "down" : "gate/up", tall, nu, N, cus);
+                    }
     // the kernel and the limit, where both were measured: 8 experts
     struct { int rows, cus, limit; bool tall; } of8[] = {{64, 256, 256, false}, {950, 256, 256, false}, {1000, 256, 320, true}, {1100, 256, 320, true}, {1250, 256, 256, false},
                                                          {1900, 256, 256, false}, {2048, 256, 320, true}, {3300, 256, 256, false}, {4000, 256, 320, true},

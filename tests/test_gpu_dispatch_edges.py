@@ -421,6 +421,35 @@ def test_tall_expert_tiles(T, E):
     test_expert_tiles_of_either_width(T, E)
 
 
+# the experts' down projection by eight waves in tiles of 128 columns: experts of more than 256 rows beside others, at widths and on partitions where
+# the tiles of either kind, shared out by themselves, would be one more on an XCD than it has compute units.  Another prompt goes before each
+# pass, so that a tile that is not computed holds something else.  The first pass against the oracle's sparse block on the library's own operands: x1, and the
+# routing with its weights, which the check of the routing allows 2e-2 of (where two experts' columns of four sigma each cancel, 0.4 % of a weight is more than
+# the 2e-2 of a row's rms that an element is allowed).  On the same operands that is the bound, where a whole layer is allowed three times as much for its softmax.
+@pytest.mark.parametrize("d,heads,T,E,cus", [(1280, (10, 2), 380, 3, 32), (1280, (10, 2), 400, 3, 32), (1536, (12, 4), 1000, 8, 96), (1536, (12, 4), 1060, 8, 96),
+                                             (3584, (28, 4), 1040, 8, 224)])
+def test_tall_expert_tiles_of_128_columns(d, heads, T, E, cus):
+    shape, n_blocks, ref = S.LayerShape(f"experts-{d}", d, *heads, 128, 1024), S.blocks_for(T) + 2, None
+    tabs, xb, other = S.shuffled_block_tables([T], n_blocks, stream=36), S.hidden_states(T, d, stream=36), S.hidden_states(T, d, stream=39)
+    rig, mw, L = _moe_rig(shape, E, n_blocks, T, 1, T + 1)
+    try:
+        for split in ((cus, 256 - cus), (256, 256), (128, 128)):
+            print(d, T, E, split, flush=True)
+            rig.ctx.set_cu_split(*split)
+            rig.prefill(other, [0, T], tabs)
+            y = rig.prefill(xb, [0, T], tabs)
+            if ref is None:
+                ref, x1 = y, f32(rig.ctx.debug_read_workspace(rs.RS_SIDE_PREFILL, 3, (T, d)))
+                _check_routing(rs.RS_SIDE_PREFILL, rig, L, mw, x1, T)
+                sel, wt = rig.ctx.debug_read_moe_routing(rs.RS_SIDE_PREFILL, T)
+                rows = np.bincount(sel.ravel(), minlength=E)
+                assert 0 < (rows > 256).sum() < E and rows.max() <= 320, "experts of both kinds, in one unit each"
+                check_tensor("y", f32(y), L._ffn(x1, sel, wt)[0], x1, 1)
+            assert np.array_equal(y, ref), f"differs at split {split}"
+    finally:
+        rig.close()
+
+
 # tiles of an odd number of 32-row blocks, whose waves do not all bring as many loads of a K tile: what a wave waits for is counted by the
 # waves with fewer.  Every pass gives the same bits (with one load too few waited for, one in some ten of these passes did not)
 @pytest.mark.parametrize("T,split", [(576, (256, 256)), (300, (256, 256)), (1120, (128, 128)), (650, (96, 160))])
