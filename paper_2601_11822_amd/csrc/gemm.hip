@@ -408,7 +408,10 @@ __global__ __launch_bounds__(256) void gemm_head_kernel(GemmArgs a, HeadOut o, i
 // Whether a whole product's weights are a stream (non-temporal).  tile_rc runs up to four row tiles of a column side by side: with no more than those nobody
 // reads the weights again.  Layers of the 8B widths on 256 CUs, not streamed / streamed: 160 rows 165.9 / 162.5 us, 512 249.6 / 247.4, 768 369.6 / 360.8,
 // 1024 429 / 418; of the 70B widths 160 rows 376 / 360; streamed throughout 1300 rows of the 8B widths 579 / 602, 4000 of the 70B widths 5140 / 5269.
-static bool direct_streams(int m_tiles) { return m_tiles <= 4; }
+// Not three row tiles on 32 or 64 CUs: an XCD runs four or eight tiles at a time there, so that one column in three has its last tile in the next round, which
+// reads the weights again.  70B widths, 660 to 768 rows: on 64 CUs 2727 - 2869 / 2853 - 2967 us, on 32 4994 - 5320 / 5215 - 5534; 8B widths on 32 1521 - 1573 /
+// 1554 - 1605, on 64 level.  On 128 CUs, one column in five: 8B widths 0.7 to 1.4 % for streams, 70B widths 1.4 % against to 0.4 % for; 96 and 192 split none.
+bool direct_streams(int m_tiles, int cus) { return m_tiles <= 4 && (m_tiles != 3 || cus > 64); }
 
 template <int EPI, bool TALL>
 static void launch_direct_mixed(hipStream_t st, const GemmArgs &a, int cus) {
@@ -418,7 +421,7 @@ static void launch_direct_mixed(hipStream_t st, const GemmArgs &a, int cus) {
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(n_full + (n_half + 7) / 8 * 8), dim3(256), RS_NS_FULL * (BM + 256) * 64, st, a, m_tiles, n_full, n_half);
     };
-    direct_streams(m_tiles) ? go(gemm_direct_mixed_kernel<EPI, TALL, true>) : go(gemm_direct_mixed_kernel<EPI, TALL, false>);
+    direct_streams(m_tiles, cus) ? go(gemm_direct_mixed_kernel<EPI, TALL, true>) : go(gemm_direct_mixed_kernel<EPI, TALL, false>);
 }
 
 template <int BM, int BN, int EPI, int NS>
@@ -432,9 +435,10 @@ static void launch_direct_epi(hipStream_t st, const GemmArgs &a) {
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(BM > 256 || fed ? 512 : 256), fed ? RS_FED_LDS : lds, st, a, m_tiles, n_tiles);
     };
-    if constexpr (fed) direct_streams(m_tiles) ? go(gemm_fed_kernel<EPI, true>) : go(gemm_fed_kernel<EPI, false>);
-    else if constexpr (BM > 256) direct_streams(m_tiles) ? go(gemm_tall_kernel<BM / 32, EPI, NS, true>) : go(gemm_tall_kernel<BM / 32, EPI, NS, false>);
-    else direct_streams(m_tiles) ? go(gemm_direct_kernel<BM, BN, EPI, NS, true>) : go(gemm_direct_kernel<BM, BN, EPI, NS, false>);
+    const bool nt = direct_streams(m_tiles, a.cus > 0 ? a.cus : 256);
+    if constexpr (fed) nt ? go(gemm_fed_kernel<EPI, true>) : go(gemm_fed_kernel<EPI, false>);
+    else if constexpr (BM > 256) nt ? go(gemm_tall_kernel<BM / 32, EPI, NS, true>) : go(gemm_tall_kernel<BM / 32, EPI, NS, false>);
+    else nt ? go(gemm_direct_kernel<BM, BN, EPI, NS, true>) : go(gemm_direct_kernel<BM, BN, EPI, NS, false>);
 }
 
 template <int BM, int BN, int NS>

@@ -108,6 +108,7 @@ int launch_gemm_tiled_partials(hipStream_t st, const GemmArgs &a);
 enum DirectForm { FORM_128x256, FORM_160x256, FORM_192x256, FORM_224x256, FORM_256x256, FORM_256x192, FORM_192x128, FORM_MIXED_256, FORM_MIXED_192, FORM_288x256, FORM_320x256 };
 int direct_splits(int M, int N, int K);
 DirectForm direct_form(int M, int N, int K, int epi, int S, int cus);
+bool direct_streams(int m_tiles, int cus);   // whether a whole product of so many row tiles reads its weights as a stream
 
 // Skinny variant for M <= 64 (decode): weight-streaming, deterministic split-K through
 // `partials` (fp32, at least skinny_partial_elems(...) elements).  Reads A, Wp and Wp2.

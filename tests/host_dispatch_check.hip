@@ -85,6 +85,13 @@ static void odd_heights() {
     }
 }
 
+// Weights as a stream: only where a column's row tiles run side by side (three of them do not on 32 or 64 units, where an XCD runs four or eight tiles at a time)
+static void streamed_weights() {
+    for (int cus = 32; cus <= 256; cus += 32)
+        for (int m_tiles = 1; m_tiles <= 8; ++m_tiles)
+            CHECK(direct_streams(m_tiles, cus) == (m_tiles <= 4 && !(m_tiles == 3 && cus <= 64)), "%d row tiles on %d", m_tiles, cus);
+}
+
 // The experts' down projection: of up to 8 units 4 (1024 columns) tiles each, narrow on the whole chip, not on 32 units
 static void expert_tiles() {
     for (int nu = 1; nu <= 64; ++nu)
@@ -132,6 +139,7 @@ int main() {
     few_rows();
     hybrid_forms();
     odd_heights();
+    streamed_weights();
     expert_tiles();
     if (fails) { std::printf("%d checks failed\n", fails); return 1; }
     std::printf("dispatch ok\n");
