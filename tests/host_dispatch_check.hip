@@ -2,6 +2,7 @@
 // and at those where tests compare the two.  Built against the library and run by tests/test_host_abi.py.
 #include <algorithm>
 #include <cstdio>
+#include <utility>
 #include <vector>
 
 #include "../paper_2601_11822_amd/csrc/kernels.h"
@@ -85,6 +86,48 @@ static void odd_heights() {
     }
 }
 
+// Every kind of product in tiles of 288 and 320 rows and, of 128, in the fed form, that GPU tests are about: on one of the partitions that they run, is it chosen?
+struct Widths { int d, qkv, q, f; };
+enum Kind { GATE_UP, STORED, RESIDUAL, SLICED };
+struct Wanted { Kind kind; DirectForm form; int rows_over; bool streamed; int nk; };   // rows_over: in the last tile (0: full); streamed: of whole products; nk: K tiles (0: any)
+static void forms_of(const char *what, std::vector<std::pair<Widths, std::vector<int>>> passes, std::vector<Wanted> wanted) {
+    for (auto &w : wanted) {
+        const int bm = w.form == FORM_320x256 ? 320 : w.form == FORM_288x256 ? 288 : 128;
+        bool any = false;
+        for (auto &p : passes)
+            for (int M : p.second)
+                for (int cus : {256, 128, 64, 96}) {
+                    const Widths &s = p.first;
+                    const struct { Kind kind; int N, K; } products[] = {{GATE_UP, s.f, s.d}, {STORED, s.qkv, s.d}, {RESIDUAL, s.d, s.q}, {RESIDUAL, s.d, s.f}};
+                    for (auto &q : products) {
+                        if (q.N < 1024) continue;
+                        const int S = q.kind == GATE_UP ? 1 : direct_splits(M, q.N, q.K), tiles = (M + bm - 1) / bm;
+                        const DirectForm f = direct_form(M, q.N, q.K, S > 1 || q.kind == STORED ? EPI_STORE : q.kind == GATE_UP ? EPI_SWIGLU : EPI_RESIDUAL, S, cus);
+                        any = any || (f == w.form && (S > 1 ? SLICED : q.kind) == w.kind && M % bm == w.rows_over && (!w.nk || q.K / 32 == w.nk) &&
+                                      (S > 1 || direct_streams(tiles, cus) == w.streamed));
+                    }
+                }
+        CHECK(any, "%s: kind %d, form %d, %d rows over, streamed %d, %d K tiles", what, w.kind, w.form, w.rows_over, w.streamed, w.nk);
+    }
+}
+static void tall_and_fed_forms() {
+    const Widths of8b{4096, 6144, 4096, 14336}, of70b{8192, 10240, 8192, 28672}, odd{1152, 1920, 1152, 3104};
+    forms_of("tall", {{of8b, {288, 320, 640, 832, 1280, 1600, 1800}}, {of70b, {290, 1100}}, {odd, {310, 640, 2593, 2881, 3169, 3521}}},
+             {{GATE_UP, FORM_288x256, 0, true, 0}, {GATE_UP, FORM_320x256, 0, true, 0}, {GATE_UP, FORM_288x256, 1, false, 0}, {GATE_UP, FORM_320x256, 1, false, 0},
+              {SLICED, FORM_288x256, 0, true, 0}, {SLICED, FORM_320x256, 0, true, 0}, {SLICED, FORM_320x256, 290, true, 0}, {SLICED, FORM_288x256, 256, true, 0},
+              {STORED, FORM_320x256, 0, true, 0}, {STORED, FORM_320x256, 0, false, 0}, {STORED, FORM_288x256, 1, false, 36}, {STORED, FORM_320x256, 1, false, 36},
+              {RESIDUAL, FORM_288x256, 236, true, 0}, {RESIDUAL, FORM_320x256, 0, true, 0}, {RESIDUAL, FORM_288x256, 1, false, 97}, {RESIDUAL, FORM_320x256, 1, false, 97}});
+    // fed: fewer K tiles than the ring has stages, an odd number of them, one row tile and many
+    const Widths one_head{1024, 384, 128, 1056}, odd_k{1056, 1280, 1024, 1120}, narrow{160, 1280, 1024, 1024};
+    forms_of("fed", {{one_head, {128, 129, 500, 641, 897}}, {odd_k, {897, 1300, 1500}}, {narrow, {128, 129, 400, 641}}, {of8b, {1537}}},
+             {{RESIDUAL, FORM_128x256, 0, true, 4}, {RESIDUAL, FORM_128x256, 1, true, 4}, {RESIDUAL, FORM_128x256, 1, false, 4}, {RESIDUAL, FORM_128x256, 1, false, 33},
+              {RESIDUAL, FORM_128x256, 20, false, 35}, {STORED, FORM_128x256, 1, false, 33}, {STORED, FORM_128x256, 0, true, 5}, {STORED, FORM_128x256, 1, true, 5},
+              {STORED, FORM_128x256, 1, false, 5}, {RESIDUAL, FORM_128x256, 1, false, 448}});
+    // the passes that are repeated: fed on the whole chip, through 7 experts in tall units whose down projection is 128 columns wide there and 256 on 32 units
+    for (int cus : {256, 32}) CHECK(grouped_cut(1000, 7, cus).tall && grouped_narrow(true, 7, 4, cus) == (cus == 256), "1000 rows through 7 experts on %d", cus);
+    for (int K : {4096, 14336}) CHECK(direct_splits(1536, 4096, K) == 1 && direct_form(1536, 4096, K, EPI_RESIDUAL, 1, 256) == FORM_128x256, "1536 rows, K %d", K);
+}
+
 // Weights as a stream: only where a column's row tiles run side by side (three of them do not on 32 or 64 units, where an XCD runs four or eight tiles at a time)
 static void streamed_weights() {
     for (int cus = 32; cus <= 256; cus += 32)
@@ -139,6 +182,7 @@ int main() {
     few_rows();
     hybrid_forms();
     odd_heights();
+    tall_and_fed_forms();
     streamed_weights();
     expert_tiles();
     if (fails) { std::printf("%d checks failed\n", fails); return 1; }

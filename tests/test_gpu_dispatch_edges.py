@@ -451,8 +451,9 @@ def test_tall_expert_tiles_of_128_columns(d, heads, T, E, cus):
 
 
 # tiles of an odd number of 32-row blocks, whose waves do not all bring as many loads of a K tile: what a wave waits for is counted by the
-# waves with fewer.  Every pass gives the same bits (with one load too few waited for, one in some ten of these passes did not)
-@pytest.mark.parametrize("T,split", [(576, (256, 256)), (300, (256, 256)), (1120, (128, 128)), (650, (96, 160))])
+# waves with fewer; 1536 rows: output and down projection with waves that only load.  Every pass gives the same bits (with one load too few waited
+# for, one in some ten of these passes did not)
+@pytest.mark.parametrize("T,split", [(576, (256, 256)), (300, (256, 256)), (1120, (128, 128)), (650, (96, 160)), (1536, (256, 256))])
 def test_large_tile_products_repeat(T, split):
     n_blocks = S.blocks_for(T) + 2
     rig = Rig(S.LLAMA8B, n_blocks, T, 1, T + 1, with_oracle=False)
@@ -467,6 +468,29 @@ def test_large_tile_products_repeat(T, split):
             rig.ctx.sync(rs.RS_SIDE_PREFILL)
             first = y.clone() if first is None else first
             assert torch.equal(y.view(torch.int16), first.view(torch.int16)), f"pass {i} differs"
+    finally:
+        rig.close()
+
+
+# the same of the experts' eight-wave tiles, of 288 and of 320 rows: in the down projection 256 columns wide (32 CUs) and 128 (256 CUs)
+@pytest.mark.parametrize("split", [(256, 256), (32, 224)])
+def test_tall_expert_tiles_repeat(split):
+    shape, T, E = S.WIDE, 1000, 7
+    n_blocks = S.blocks_for(T) + 2
+    rig, _, _ = _moe_rig(shape, E, n_blocks, T, 1, T + 1)
+    try:
+        rig.ctx.set_cu_split(*split)
+        cu, tabs = np.array([0, T], np.int32), S.shuffled_block_tables([T], n_blocks, stream=36)
+        x, tab = to_dev(S.hidden_states(T, shape.d_model, stream=36)), torch.from_numpy(np.ascontiguousarray(tabs, np.int32)).cuda()
+        y, first = torch.empty_like(x), None
+        for i in range(60):
+            torch.cuda.synchronize()
+            rig.ctx.prefill_layer(0, x, y, cu, tab, tab.shape[1])
+            rig.ctx.sync(rs.RS_SIDE_PREFILL)
+            first = y.clone() if first is None else first
+            assert torch.equal(y.view(torch.int16), first.view(torch.int16)), f"pass {i} differs"
+        rows = np.bincount(rig.ctx.debug_read_moe_routing(rs.RS_SIDE_PREFILL, T)[0].ravel(), minlength=E)
+        assert ((rows > 256) & (rows <= 288)).any() and ((rows > 288) & (rows <= 320)).any(), rows
     finally:
         rig.close()
 
@@ -699,8 +723,16 @@ def test_large_tile_products(shape, rows):
         rig.close()
 
 
-# tiles of 288 and 320 rows by eight waves, on some partition each: full and one row over a full one, as gate/up, in K slices, stored
-# and with the residual, weights streamed and not
-@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [288, 320, 640, 832, 1800]), (S.LLAMA70B, [290, 1100]), (S.ODD, [310, 640])])
+# tiles of 288 and 320 rows by eight waves, on some partition each: the last tile full, partly empty and of one row; as gate/up, in K slices, stored
+# and with the residual; weights streamed and not; an odd number of K tiles.  (The host check of the dispatch rules holds the forms.)
+@pytest.mark.parametrize("shape,rows", [(S.LLAMA8B, [288, 320, 640, 832, 1280, 1600, 1800]), (S.LLAMA70B, [290, 1100]), (S.ODD, [310, 640, 2593, 2881, 3169, 3521])])
 def test_tall_products(shape, rows):
+    test_large_tile_products(shape, rows)
+
+
+# whole products in tiles of 128 x 256 whose loads four more waves issue: fewer K tiles (4, 5) than the ring has stages, an odd number of them (5, 33, 35)
+# and many (448); stored and with the residual; weights streamed and not; the last row tile full and of one row
+@pytest.mark.parametrize("shape,rows", [(S.LayerShape("one-head", 1024, 1, 1, 128, 1056), [128, 129, 500, 641, 897]), (S.LayerShape("odd-k", 1056, 8, 1, 128, 1120), [897, 1300, 1500]),
+                                        (S.LayerShape("narrow", 160, 8, 1, 128, 1024), [128, 129, 400, 641]), (S.LLAMA8B, [1537])])
+def test_fed_products(shape, rows):
     test_large_tile_products(shape, rows)
