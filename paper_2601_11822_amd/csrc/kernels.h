@@ -315,16 +315,24 @@ static inline int grouped_tall_grid(int units, int n_tiles, int cus) {
 static inline bool grouped_streams_weights(int rows, int E) { return rows <= 256 * E; }
 // How the experts' rows are cut into units: `limit` rows at most, and whether by the kernel of eight waves, which alone takes more than 256.
 // An expert has `rows` rows in E to two of them; its share and a deviation above it is what the fullest are taken to have.  On more than 128 CUs taller tiles are worth it
-// where fewer of them hold that; where their number stays the same the four-wave tiles are 2 % faster (LDS traffic), and four of 224 rows 1 % than three of 288.
+// where fewer of them hold that; where their number stays the same the four-wave tiles are 2 % faster on 256 CUs (LDS traffic), and four of 224 rows 1 % than three of 288.
 // On 128 and fewer, where the loads of a CU count for more, eight waves are the faster from 256 rows on.  Prefill of the 8B widths through 8 experts, four waves / this, on 256 CUs:
-// 950 rows 818 / 812 us (not taken), 1000 918 / 841, 1100 1022 / 898, 1200 990 / 973, 1250 1016 / 1038 (not taken), 1500 1121 / 1122 (not), 1900 1290 / 1309 (not), 2048 1550 / 1393, 2400 1812 / 1641,
-// 3300 2255 / 2295 (not), 4000 2775 / 2590; on 128 CUs: 1000 1356 / 1082, 1100 1515 / 1127, 1300 1546 / 1537, 2048 2311 / 1951, 3300 3378 / 3119.
+// 950 rows 818 / 812 us (not taken), 1000 890 / 843, 1100 1022 / 906, 1200 992 / 951, 1250 1012 / 1030 (not taken), 1500 1142 / 1147 (not), 1900 1332 / 1365 (not), 2048 1590 / 1437, 2400 1850 / 1644,
+// 3300 2291 / 2330 (not), 4000 2837 / 2702; on 192: 1100 1247 / 1017, 1200 1242 / 1077, 2048 1778 / 1662; on 128 CUs: 1000 1324 / 1075, 1100 1507 / 1130, 1300 1529 / 1519, 2048 2322 / 1960, 3300 3369 / 3153.
+// (The line of 256 CUs is not that of 160 to 224, where eight waves are 2 to 5 % the faster at the same number of tiles, too, nor is a deviation above the share always the
+// fullest: 1250 rows 1247 / 1103 on 192, 1494 / 1328 on 128, not taken.  Half of the rows on one of 8 experts, which no rule on the host sees: 2400 rows on 192 CUs 1840 / 1894.)
+// Not where the lower tiles of the down projection, 128 columns wide, leave CUs idle as it is: fewer and taller ones leave half of what works.  With all but an eighth of the
+// CUs at work they do that for what a taller tile saves if the projection is long (f) and nearly every expert fills its lower tiles.  Four waves / 320 rows by eight, on
+// 256 CUs: 8 experts of 290 rows, d 1024, f 14336, 367 / 428 us; 4 of d 2816, f 4096, 196 / 231; 4 of d 2048, f 8192, 237 / 271; 4 of d 4096, f 14336, 275 rows 539 / 558, 300 553 / 582 (266 568 / 542:
+// taken); 16 of d 1024, f 3584, 277 / 256 (taken).  On 128 CUs 4 of d 2048 293 / 306, of d 1024 147 / 158.
 struct GroupCut { int limit; bool tall; };
-static inline GroupCut grouped_cut(int rows, int E, int cus) {
-    const double mean = 2.0 * rows / E, most = mean + __builtin_sqrt(mean);
-    const int of320 = (int)__builtin_ceil(most / 320), of256 = (int)__builtin_ceil(most / 256);
-    const bool fewer = of320 < of256;
-    if (cus > 0 && cus <= 128) return {fewer ? 320 : 256, of256 > 1};
+static inline GroupCut grouped_cut(int rows, int E, int d, int f, int cus) {
+    if (cus <= 0) cus = 256;
+    const double mean = 2.0 * rows / E, dev = __builtin_sqrt(mean);
+    const int of320 = (int)__builtin_ceil((mean + dev) / 320), of256 = (int)__builtin_ceil((mean + dev) / 256), low = E * of256 * ((d + 127) / 128);
+    const bool idle = 8 * low <= 7 * cus || (low <= cus && f >= 8192 && mean - dev > 256 * (of256 - 1));
+    const bool fewer = of320 < of256 && !idle;
+    if (cus <= 128) return {fewer ? 320 : 256, of256 > 1};
     return fewer && of320 != 3 ? GroupCut{320, true} : GroupCut{256, false};
 }
 // Rows of the grouped (expert-major) layout that M rows with two experts each can need: an expert's segment is less than

@@ -584,7 +584,7 @@ bool run_post_attention(rs_ctx *c, int side, hipStream_t st, Workspace &w, const
     if (ml.E > 0) {
         // sparse block: route, gather expert by expert, two grouped GEMMs over all tiles, weighted sum
         const int cap = std::min(w.m_cap, moe_row_cap(M, ml.E));
-        const GroupCut cut = grouped_cut(M, ml.E, c->side[side].cus);
+        const GroupCut cut = grouped_cut(M, ml.E, d, f, c->side[side].cus);
         MoeArgs ma{w.h, ml.router, w.m_sel, w.m_wt, w.m_pos, w.m_src, w.m_units, w.m_a, w.m_out, w.x1, y, M, d, ml.E, cap, cut.limit};
         launch_moe_route_and_gather(st, ma);
         GemmArgs gu{w.m_a, nullptr, nullptr, ml.wg, ml.wu, nullptr, w.m_act, cap, f, d, EPI_SWIGLU, c->side[side].cus};

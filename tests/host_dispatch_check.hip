@@ -123,8 +123,7 @@ static void tall_and_fed_forms() {
              {{RESIDUAL, FORM_128x256, 0, true, 4}, {RESIDUAL, FORM_128x256, 1, true, 4}, {RESIDUAL, FORM_128x256, 1, false, 4}, {RESIDUAL, FORM_128x256, 1, false, 33},
               {RESIDUAL, FORM_128x256, 20, false, 35}, {STORED, FORM_128x256, 1, false, 33}, {STORED, FORM_128x256, 0, true, 5}, {STORED, FORM_128x256, 1, true, 5},
               {STORED, FORM_128x256, 1, false, 5}, {RESIDUAL, FORM_128x256, 1, false, 448}});
-    // the passes that are repeated: fed on the whole chip, through 7 experts in tall units whose down projection is 128 columns wide there and 256 on 32 units
-    for (int cus : {256, 32}) CHECK(grouped_cut(1000, 7, cus).tall && grouped_narrow(true, 7, 4, cus) == (cus == 256), "1000 rows through 7 experts on %d", cus);
+    // the passes that are repeated: fed on the whole chip
     for (int K : {4096, 14336}) CHECK(direct_splits(1536, 4096, K) == 1 && direct_form(1536, 4096, K, EPI_RESIDUAL, 1, 256) == FORM_128x256, "1536 rows, K %d", K);
 }
 
@@ -172,9 +171,24 @@ static void expert_pieces() {
                                                          {1900, 256, 256, false}, {2048, 256, 320, true}, {3300, 256, 256, false}, {4000, 256, 320, true},
                                                          {900, 128, 256, false}, {1000, 128, 320, true}, {1300, 128, 256, true}, {3300, 128, 320, true}};
     for (auto &w : of8) {
-        const GroupCut c = grouped_cut(w.rows, 8, w.cus);
+        const GroupCut c = grouped_cut(w.rows, 8, 4096, 14336, w.cus);
         CHECK(c.limit == w.limit && c.tall == w.tall, "%d rows on %d: %d %d", w.rows, w.cus, c.limit, c.tall);
     }
+    // where a lower down projection leaves compute units idle, and where it nearly does: experts of `mean` rows, of other widths
+    struct { int mean, E, d, f, cus, limit; bool tall; } others[] = {
+        {290, 8, 1024, 14336, 256, 256, false}, {270, 8, 1024, 14336, 224, 256, false}, {290, 4, 1024, 3584, 160, 256, false}, {600, 4, 2048, 8192, 256, 256, false}, {290, 4, 2816, 4096, 256, 256, false},
+        {290, 4, 2048, 8192, 192, 256, false}, {290, 2, 4096, 14336, 192, 256, false}, {250, 4, 4096, 14336, 256, 320, true}, {266, 4, 4096, 14336, 256, 320, true}, {276, 4, 4096, 14336, 256, 256, false}, {300, 4, 4096, 14336, 256, 256, false},
+        {300, 4, 4096, 14336, 224, 320, true}, {600, 4, 4096, 14336, 256, 320, true}, {290, 16, 1024, 3584, 256, 320, true}, {270, 8, 2048, 8192, 256, 320, true}, {290, 8, 2048, 8192, 256, 256, false}, {290, 8, 2048, 8192, 192, 320, true},
+        {290, 8, 2816, 4096, 256, 320, true}, {290, 4, 2048, 8192, 128, 256, true}, {290, 4, 1024, 3584, 128, 256, true}, {290, 4, 2048, 8192, 96, 320, true}, {290, 4, 1024, 3584, 64, 320, true}, {600, 4, 2048, 8192, 128, 320, true}};
+    for (auto &w : others) {
+        const GroupCut c = grouped_cut(w.mean * w.E / 2, w.E, w.d, w.f, w.cus);
+        CHECK(c.limit == w.limit && c.tall == w.tall, "%d experts of %d rows, %d x %d, on %d: %d %d", w.E, w.mean, w.d, w.f, w.cus, c.limit, c.tall);
+    }
+    // the GPU tests of units of up to 320 rows, down projection 128 columns wide or 256
+    for (int E : {3, 7}) CHECK(grouped_cut(E == 3 ? 450 : 1000, E, 1024, 2816, 32).limit == 320 && !grouped_narrow(true, E, 4, 32) == (E == 7), "%d experts on 32", E);
+    CHECK(grouped_cut(1000, 7, 1024, 2816, 64).limit == 320 && grouped_narrow(true, 7, 4, 64), "7 experts on 64");
+    struct { int d, T, E, cus; } of128[] = {{1280, 380, 3, 32}, {1280, 400, 3, 32}, {1536, 1000, 8, 96}, {1536, 1060, 8, 96}, {3584, 1040, 8, 224}};
+    for (auto &w : of128) CHECK(grouped_cut(w.T, w.E, w.d, 1024, w.cus).limit == 320, "%d rows, width %d on %d", w.T, w.d, w.cus);
 }
 
 int main() {

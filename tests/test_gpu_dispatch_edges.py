@@ -415,7 +415,7 @@ def test_expert_tiles_of_either_width(T, E):
 
 
 # units of up to 320 rows by eight waves: experts of 257 to 320 rows in one, of 513 to 640 in two, fuller ones beside them in two lower ones, a last round
-# in halves; experts that have as many units either way (256 CUs: four waves, 32 and 64: eight).  The same bits on every partition, checked as above.
+# in halves; experts that have as many units either way (256 CUs, which these widths do not fill: four waves, 32 and 64: eight).  The same bits on every partition, checked as above.
 @pytest.mark.parametrize("T,E", [(450, 3), (420, 3), (900, 3), (1000, 7), (470, 3), (500, 3)])
 def test_tall_expert_tiles(T, E):
     test_expert_tiles_of_either_width(T, E)
@@ -472,8 +472,8 @@ def test_large_tile_products_repeat(T, split):
         rig.close()
 
 
-# the same of the experts' eight-wave tiles, of 288 and of 320 rows: in the down projection 256 columns wide (32 CUs) and 128 (256 CUs)
-@pytest.mark.parametrize("split", [(256, 256), (32, 224)])
+# the same of the experts' eight-wave tiles, of 288 and of 320 rows: in the down projection 256 columns wide (32 CUs) and 128 (64 CUs)
+@pytest.mark.parametrize("split", [(64, 192), (32, 224)])
 def test_tall_expert_tiles_repeat(split):
     shape, T, E = S.WIDE, 1000, 7
     n_blocks = S.blocks_for(T) + 2
