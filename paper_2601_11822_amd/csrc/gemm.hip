@@ -273,9 +273,10 @@ __global__ __launch_bounds__(512) void gemm_tall_splitk_kernel(GemmArgs a, int m
 // A slice adds its partial sums, written and read back, 0.3 us, and once 2 us for the epilogue kernel.
 // (All of these are timings of the loop with 32x32x16 products; the present one takes 0.89 to 0.95 of the times of long products, so a slice's
 // cost, which stands beside them in microseconds, counts for that much less than it should.  With the present loop every form and every count of
-// slices was forced in turn, 12 row counts of the 8B widths from 200 to 8000 on 256 and 128 CUs and four of the 70B widths
-// (profiles/large_tile_forms_forced.md): the forms are within 1 % of the fastest layer; the slices, which may not follow the CUs, within 2 %
-// on the whole chip and 6 % on half of it.)
+// slices was forced in turn, those of eight waves and the fed one among them, 12 row counts of the 8B widths from 200 to 8000 on 256 and 128 CUs, five on 192 and seven
+// passes of the 70B widths (profiles/large_tile_forms_forced.md): the forms are within 1 % of the fastest layer; the slices, which may not follow the CUs, within 1 %
+// on the whole chip, 2 % on 192 CUs and 4 % on half of it.  With every tile of 288 and 320 rows of whole products left out, 1400 to 12000 rows take 0.99 to 1.14 times as long;
+// 70B widths, 7000 rows on 192 CUs 0.98.)
 // Against the rule before it (128-row tiles for slices, their count a power of two up to half the chip; no 192-row tiles), product and
 // epilogue, on 256 CUs: 576x4096x14336 94 -> 74 us, 1152x4096x14336 172 -> 127, 576x8192x28672 330 -> 252, gate/up 576x14336x4096
 // 157 -> 133, 384x14336x4096 107 -> 75, 192x28672x8192 231 -> 175; over the products timed 4 % on 256 CUs and 10 % on 128.
@@ -411,6 +412,7 @@ __global__ __launch_bounds__(256) void gemm_head_kernel(GemmArgs a, HeadOut o, i
 // Not three row tiles on 32 or 64 CUs: an XCD runs four or eight tiles at a time there, so that one column in three has its last tile in the next round, which
 // reads the weights again.  70B widths, 660 to 768 rows: on 64 CUs 2727 - 2869 / 2853 - 2967 us, on 32 4994 - 5320 / 5215 - 5534; 8B widths on 32 1521 - 1573 /
 // 1554 - 1605, on 64 level.  On 128 CUs, one column in five: 8B widths 0.7 to 1.4 % for streams, 70B widths 1.4 % against to 0.4 % for; 96 and 192 split none.
+// Weights few enough to stay in the memory-side cache from pass to pass lose by it: four layers of d 1024, f 3584 at 512 rows 85.4 / 87.5 us; twenty of them level.
 bool direct_streams(int m_tiles, int cus) { return m_tiles <= 4 && (m_tiles != 3 || cus > 64); }
 
 template <int EPI, bool TALL>

@@ -375,13 +375,13 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &a, const int bm
 }
 
 // One output tile by eight waves, two per SIMD, each with XF x 4 accumulators of 16 x 16 (WGM waves along the rows, the others along the
-// columns): tiles of up to 320 x 256 or 640 x 128, where four waves end at 256 x 256.  Every element's sum is in gemm_direct_tile's order.
+// columns): tiles of up to 320 x 256, and of 320 x 128, where four waves end at 256 x 256.  Every element's sum is in gemm_direct_tile's order.
 // What it is for: a CU has some 32 KB of loads in flight however many it has asked for (57 to 61 GB/s from HBM, 131 from L2), and a product of
 // a few rounds of tiles is bound by that, not by its matrix instructions; a taller tile asks for its weights once where two lower ones ask for them twice.
 // The registers: 160 accumulators, the activations' fragments (40) once and the weights' (32) twice: a wave's products go through the activation
 // fragments one after the other, and the one that is done with is read again for the next K tile.  No more than 256 in all, all of them vector
 // registers (a function that uses accumulation registers gets half of each, which spills).
-// What bounds it: the LDS.  A K tile of 320 x 256 is 112 KB of fragment reads and 36 KB of DMA writes beside 1280 cycles of products, 1156 at 128 bytes
+// What bounds it: the LDS.  A K tile of 320 x 256 is 112 KB of fragment reads and 36 KB of DMA writes beside 1280 cycles of products, 1184 at 128 bytes
 // a cycle; the place of the barrier, the reads and the loads among the products changes nothing.
 // rows_end: rows from here on are not stored; blocks: 32-row blocks from here on are not fetched.
 #define RS_TALL_LDS 163840   // all of a compute unit's: at most NS stages of BM + BN rows of 64 bytes

@@ -314,17 +314,22 @@ static inline int grouped_tall_grid(int units, int n_tiles, int cus) {
 // of 600, 1500, 2500, 3000 rows 1191 / 1121, 1461 / 1424, 2124 / 2104, 2474 / 2457.
 static inline bool grouped_streams_weights(int rows, int E) { return rows <= 256 * E; }
 // How the experts' rows are cut into units: `limit` rows at most, and whether by the kernel of eight waves, which alone takes more than 256.
-// An expert has `rows` rows in E to two of them; its share and a deviation above it is what the fullest are taken to have.  On more than 128 CUs taller tiles are worth it
-// where fewer of them hold that; where their number stays the same the four-wave tiles are 2 % faster on 256 CUs (LDS traffic), and four of 224 rows 1 % than three of 288.
-// On 128 and fewer, where the loads of a CU count for more, eight waves are the faster from 256 rows on.  Prefill of the 8B widths through 8 experts, four waves / this, on 256 CUs:
-// 950 rows 818 / 812 us (not taken), 1000 890 / 843, 1100 1022 / 906, 1200 992 / 951, 1250 1012 / 1030 (not taken), 1500 1142 / 1147 (not), 1900 1332 / 1365 (not), 2048 1590 / 1437, 2400 1850 / 1644,
-// 3300 2291 / 2330 (not), 4000 2837 / 2702; on 192: 1100 1247 / 1017, 1200 1242 / 1077, 2048 1778 / 1662; on 128 CUs: 1000 1324 / 1075, 1100 1507 / 1130, 1300 1529 / 1519, 2048 2322 / 1960, 3300 3369 / 3153.
-// (The line of 256 CUs is not that of 160 to 224, where eight waves are 2 to 5 % the faster at the same number of tiles, too, nor is a deviation above the share always the
-// fullest: 1250 rows 1247 / 1103 on 192, 1494 / 1328 on 128, not taken.  Half of the rows on one of 8 experts, which no rule on the host sees: 2400 rows on 192 CUs 1840 / 1894.)
-// Not where the lower tiles of the down projection, 128 columns wide, leave CUs idle as it is: fewer and taller ones leave half of what works.  With all but an eighth of the
-// CUs at work they do that for what a taller tile saves if the projection is long (f) and nearly every expert fills its lower tiles.  Four waves / 320 rows by eight, on
-// 256 CUs: 8 experts of 290 rows, d 1024, f 14336, 367 / 428 us; 4 of d 2816, f 4096, 196 / 231; 4 of d 2048, f 8192, 237 / 271; 4 of d 4096, f 14336, 275 rows 539 / 558, 300 553 / 582 (266 568 / 542:
-// taken); 16 of d 1024, f 3584, 277 / 256 (taken).  On 128 CUs 4 of d 2048 293 / 306, of d 1024 147 / 158.
+// An expert has `rows` rows in E to two of them; its share and a deviation above it is what the fullest are taken to have.  On more than 128 CUs
+// taller tiles are worth it where fewer of them hold that, but three of 288 are 1 % slower than four of 224 rows; where their number stays the
+// same the four-wave tiles are 2 % faster on 256 CUs (LDS traffic).  On 128 and fewer, where the loads of a CU count for more, eight waves are the
+// faster from 256 rows on.  Prefill through 8 experts of the 8B widths, us, units of 256 rows by four waves / of 320 by eight ("-": not taken):
+//            950 rows      1000        1100       1250         1500         2048         2400         3300         4000
+//   256 CUs  827 / 818 -   890 / 843   1022 / 906 1012 / 1030 - 1142 / 1147 - 1590 / 1437 1850 / 1644 2291 / 2330 - 2837 / 2702
+//   192 CUs  925 / 927 -   995 / 951   1247 / 1017 1247 / 1103 - 1381 / 1322 - 1778 / 1662 1985 / 1914 2670 / 2579 - 3156 / 3124
+//   128 CUs  1058 / 1052 - 1324 / 1079 1507 / 1134 1494 / 1328 - 1643 / 1621  2322 / 1960 2586 / 2235 3369 / 3168   4074 / 3793
+// (So the line of 256 CUs is not that of 160 to 224, nor is a deviation above the share always the fullest.  Half of the rows on one of the experts,
+// which no rule on the host sees: 2400 rows on 192 CUs 1840 / 1894, 1000 to 4000 rows otherwise 0.91 to 1.01.)
+// Not where the lower tiles of the down projection, 128 columns wide, leave CUs idle as it is: fewer and taller ones leave half of what works.
+// With all but an eighth of the CUs at work they do that for what a taller tile saves only if the projection is long (f) and nearly every expert
+// fills its lower tiles.  The same pair, of E experts of `mean` rows:
+//   256 CUs: E 8, 290 rows, d 1024, f 14336 367 / 428;  E 4, 290, d 2816, f 4096 196 / 231;  E 4, 290, d 2048, f 8192 237 / 271
+//            E 4, d 4096, f 14336: 266 rows 568 / 542 (taken), 275 539 / 558, 300 553 / 582;  E 16, 290, d 1024, f 3584 277 / 256 (taken)
+//   128 CUs: E 4, 290 rows, d 2048, f 8192 293 / 306;  E 4, 290, d 1024, f 3584 147 / 158
 struct GroupCut { int limit; bool tall; };
 static inline GroupCut grouped_cut(int rows, int E, int d, int f, int cus) {
     if (cus <= 0) cus = 256;

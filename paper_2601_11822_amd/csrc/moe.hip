@@ -124,7 +124,7 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoeArgs a) {
 
 // Gathered, fragment-packed GEMM input: grouped row g takes the chunks of its source row (zeros for padding).
 // A workgroup has 256 rows of one 16-byte column; all workgroups of a column run on one XCD, since the lines that they read, eight rows' chunks each, are the same ones
-// in another order (dealt out in turn every XCD fetched all of the rows: 1100 rows of 4096 and 8 experts 12.3 -> 9.0 us, 4000 24.6 -> 20.6; 64 rows 5.5 -> 6.0).
+// in another order (dealt out in turn every XCD fetched all of the rows: 1100 rows of 4096 and 8 experts 12.3 -> 9.0 us, 4000 24.6 -> 20.6; 64 to 450 rows 5.4 to 5.6 either way).
 __global__ __launch_bounds__(256) void moe_gather_kernel(MoeArgs a, int row_groups) {
     const int i = blockIdx.x >> 3, c = (i / row_groups) * 8 + (blockIdx.x & 7), g = (i % row_groups) * 256 + threadIdx.x;
     // consecutive threads take consecutive rows of one k chunk: whole 128-byte lines on the writing side
