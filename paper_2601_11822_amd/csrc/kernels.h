@@ -317,11 +317,12 @@ static inline bool grouped_streams_weights(int rows, int E) { return rows <= 256
 // An expert has `rows` rows in E to two of them; its share and a deviation above it is what the fullest are taken to have.  On more than 128 CUs
 // taller tiles are worth it where fewer of them hold that, but three of 288 are 1 % slower than four of 224 rows; where their number stays the
 // same the four-wave tiles are 2 % faster on 256 CUs (LDS traffic).  On 128 and fewer, where the loads of a CU count for more, eight waves are the
-// faster from 256 rows on.  Prefill through 8 experts of the 8B widths, us, units of 256 rows by four waves / of 320 by eight ("-": not taken):
+// faster from 256 rows on.  Prefill through 8 experts of the 8B widths, us, units of 256 rows by four waves / of 320 by eight ("-": not taken; on 128 CUs
+// those go by eight waves in units of 256):
 //            950 rows      1000        1100       1250         1500         2048         2400         3300         4000
 //   256 CUs  827 / 818 -   890 / 843   1022 / 906 1012 / 1030 - 1142 / 1147 - 1590 / 1437 1850 / 1644 2291 / 2330 - 2837 / 2702
 //   192 CUs  925 / 927 -   995 / 951   1247 / 1017 1247 / 1103 - 1381 / 1322 - 1778 / 1662 1985 / 1914 2670 / 2579 - 3156 / 3124
-//   128 CUs  1058 / 1052 - 1324 / 1079 1507 / 1134 1494 / 1328 - 1643 / 1621  2322 / 1960 2586 / 2235 3369 / 3168   4074 / 3793
+//   128 CUs  1058 / 1052 - 1324 / 1079 1507 / 1134 1494 / 1328 - 1643 / 1621 - 2322 / 1960 2586 / 2235 3369 / 3168   4074 / 3793
 // (So the line of 256 CUs is not that of 160 to 224, nor is a deviation above the share always the fullest.  Half of the rows on one of the experts,
 // which no rule on the host sees: 2400 rows on 192 CUs 1840 / 1894, 1000 to 4000 rows otherwise 0.91 to 1.01.)
 // Not where the lower tiles of the down projection, 128 columns wide, leave CUs idle as it is: fewer and taller ones leave half of what works.
